@@ -107,8 +107,8 @@ typedef struct llc_stats {
  * Inputs.  draft is [B,K,V] addressed as draft[b*draft_stride_b + k*draft_stride_k + i]
  * (strides in elements, last dimension contiguous); draft_stride_k == 0 means the K
  * drafts of a row are i.i.d. from one proposal p_X (Section 4.1: a single draft model),
- * otherwise draft k has its own p^(k) (Appendix A.3).  target is [B,V].  Rows should
- * start on 16-byte boundaries for full-width loads; other layouts are read element-wise.
+ * otherwise draft k has its own p^(k) (Appendix A.3).  target is [B,V].  Rows may
+ * start on any element boundary (the loads are full-width either way).
  *
  * Outputs.  X[b,k] = argmin_i S_i^(k) / p_i^(k);  Y[b] = argmin_i min_k S_i^(k) / q_i;
  * accept[b] = 1 iff Y[b] is one of X[b,0..K) (Section 3, Algorithm 1).

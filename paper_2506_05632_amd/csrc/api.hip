@@ -129,7 +129,6 @@ struct ScanJob {
   long long bins_stride_b = 0;
   const int32_t *bin_of = nullptr;
   const long long *draft_row_off = nullptr;  // per-row extra offset of the draft row (see ScanParams)
-  long long draft_row_off_unit = 0;  // every entry of draft_row_off is a multiple of this many elements
   size_t lse_in_extra = (size_t)-1;  // keep the normalisers at this offset of the caller's region
   size_t extra_at = (size_t)-1;      // where the caller's region starts (default: right behind the partials)
   int32_t *tau_ready = nullptr;      // the rows' shared running bests, already reset, if not in the workspace
@@ -146,7 +145,7 @@ struct ScanJob {
 struct ScanPlan {
   Plan pl;
   Layout lay;
-  bool shared, vec;
+  bool shared;
   long long blocks;
 };
 
@@ -181,15 +180,6 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   if (out->blocks > kMaxBlocks) return LLC_E_SHAPE;
   out->lay = layout_for(j.B, j.K, pl.n_kgroups, pl.n_chunks);
   out->shared = shared;
-
-  // vector loads need every row to start on a 4-element boundary of a 16-byte (fp32) or
-  // 8-byte (bf16) aligned base (per-row offsets of the draft rows included)
-  const size_t vbytes = 4 * esize;
-  const RowMap &m = j.map;
-  out->vec = ((uintptr_t)j.draft % vbytes) == 0 && ((uintptr_t)j.target % vbytes) == 0 &&
-             (m.draft_outer % 4) == 0 && (m.draft_inner % 4) == 0 && (j.draft_stride_k % 4) == 0 &&
-             (m.target_outer % 4) == 0 && (m.target_inner % 4) == 0 &&
-             (j.draft_row_off == nullptr || (j.draft_row_off_unit % 4) == 0);
   return LLC_OK;
 }
 
@@ -209,7 +199,7 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
                     bool *finished = nullptr) {
   const Plan &pl = plan.pl;
   const Layout &lay = plan.lay;
-  const bool shared = plan.shared, vec = plan.vec;
+  const bool shared = plan.shared;
   const long long blocks = plan.blocks;
   const bool logits = j.kind == LLC_LOGITS;
   const float *temp_draft = logits ? j.temp_draft : nullptr;
@@ -248,7 +238,6 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
     lp.per_k = shared ? 0 : 1;
     lp.with_target = j.no_pool ? 0 : 1;
     lp.with_drafts = fused_lse ? 0 : 1;
-    lp.vector_loads = vec ? 1 : 0;
     lp.bins = j.bins; lp.bins_stride_b = j.bins_stride_b; lp.bin_of = j.bin_of;
     lp.draft_row_off = j.draft_row_off;
     lp.lse = part.lse;
@@ -289,7 +278,6 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
   sp.temp_target = logits ? j.temp_target : 1.0f;
   sp.temp_draft_all = logits ? j.temp_draft_all : 1.0f;
   sp.temp_draft = temp_draft;
-  sp.vector_loads = vec ? 1 : 0;
   sp.force_exact = (j.flags & LLC_FLAG_EXACT_SCAN) ? 1 : 0;
   sp.no_pool = j.no_pool ? 1 : 0;
   sp.no_draft = j.no_draft ? 1 : 0;
@@ -693,18 +681,14 @@ int llc_verify(const llc_verify_args *a) {
     q.map.row_outer = a->row_stride_s;
     q.draft_stride_k = 0;
     q.force_perk = false;
-    q.draft_row_off_unit = a->stride_k;   // the offsets are (first viable draft) * stride_k
     q.need_lse = false;                   // the rows' normalisers are known from the one-shot scan
     q.lse_in_extra = (size_t)-1;
     q.stats = nullptr; q.ev_begin = nullptr; q.ev_end = nullptr;
     q.extra_bytes = 0;
     q.draft = (const char *)a->target + (size_t)a->stride_j * esize;  // position 1 stands for all
     q.target = q.draft;
-    // (positions differ by a multiple of stride_j: the alignment that position 1 shows must hold
-    // for all of them, so the vector path also needs stride_j to be a multiple of 4)
     rc = plan_scan(q, &plan_one);
     if (rc != LLC_OK) return rc;
-    if ((a->stride_j % 4) != 0) plan_one.vec = false;
     if (plan_one.lay.total > plan_all.lay.total) j.extra_at = plan_one.lay.total;
   }
   if (!workspace_ok(j, plan_all)) return LLC_E_WORKSPACE;

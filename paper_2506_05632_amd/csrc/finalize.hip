@@ -18,11 +18,11 @@ __global__ void __launch_bounds__(64) finalize_kernel(const FinalizeParams p) {
 // running maximum and the sum of exp relative to it (fp32 terms, four at a time, into an fp64
 // running sum that is rescaled when the maximum moves).  NaN and +inf entries carry no mass.
 template <typename E>
-__device__ __forceinline__ void load_group(const E *row, int i0, int V, bool vec, float (&v)[4]);
+__device__ __forceinline__ void load_group(const E *row, int i0, int V, float (&v)[4]);
 template <>
-__device__ __forceinline__ void load_group<float>(const float *row, int i0, int V, bool vec, float (&v)[4]) {
-  if (vec && i0 + 3 < V) {
-    const float4 t = *reinterpret_cast<const float4 *>(row + i0);
+__device__ __forceinline__ void load_group<float>(const float *row, int i0, int V, float (&v)[4]) {
+  if (i0 + 3 < V) {
+    const float4 t = load_four(row + i0);
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
   } else {
 #pragma unroll
@@ -30,9 +30,9 @@ __device__ __forceinline__ void load_group<float>(const float *row, int i0, int 
   }
 }
 template <>
-__device__ __forceinline__ void load_group<uint16_t>(const uint16_t *row, int i0, int V, bool vec, float (&v)[4]) {
-  if (vec && i0 + 3 < V) {
-    const uint2 t = *reinterpret_cast<const uint2 *>(row + i0);
+__device__ __forceinline__ void load_group<uint16_t>(const uint16_t *row, int i0, int V, float (&v)[4]) {
+  if (i0 + 3 < V) {
+    const uint2 t = load_four(row + i0);
     v[0] = __uint_as_float(t.x << 16);
     v[1] = __uint_as_float(t.x & 0xFFFF0000u);
     v[2] = __uint_as_float(t.y << 16);
@@ -71,7 +71,6 @@ __global__ void __launch_bounds__(256) lse_kernel(const LseParams p) {
   }
   if (!p.is_logits) T = 1.0f;
   const float inf = __builtin_huge_valf();
-  const bool vec = p.vector_loads != 0;
   // log2(e)/T as a two-float sum, so that the exponent carries no systematic rounding of 1/T
   const double c64 = 1.4426950408889634 / (double)T;
   const float c_hi = (float)c64;
@@ -90,7 +89,7 @@ __global__ void __launch_bounds__(256) lse_kernel(const LseParams p) {
   }
   for (int g = tid; g < G; g += 256) {
     float v[4];
-    load_group<E>(row, g * 4, p.V, vec, v);
+    load_group<E>(row, g * 4, p.V, v);
     if (binned) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)

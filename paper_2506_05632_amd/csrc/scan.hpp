@@ -175,14 +175,14 @@ __device__ __forceinline__ uint32_t cvt_u32_saturating(float f) {
 }
 
 template <typename T>
-__device__ __forceinline__ void load4(const typename T::elem *row, int i0, int V, bool vec,
-                                      float fill, float (&v)[4]);
+__device__ __forceinline__ void load4(const typename T::elem *row, int i0, int V, float fill,
+                                      float (&v)[4]);
 
 template <>
-__device__ __forceinline__ void load4<F32In>(const float *row, int i0, int V, bool vec, float fill,
+__device__ __forceinline__ void load4<F32In>(const float *row, int i0, int V, float fill,
                                              float (&v)[4]) {
-  if (vec && i0 + 3 < V) {
-    const float4 t = *reinterpret_cast<const float4 *>(row + i0);
+  if (i0 + 3 < V) {
+    const float4 t = load_four(row + i0);
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
   } else {
 #pragma unroll
@@ -191,10 +191,10 @@ __device__ __forceinline__ void load4<F32In>(const float *row, int i0, int V, bo
 }
 
 template <>
-__device__ __forceinline__ void load4<BF16In>(const uint16_t *row, int i0, int V, bool vec,
-                                              float fill, float (&v)[4]) {
-  if (vec && i0 + 3 < V) {
-    const uint2 t = *reinterpret_cast<const uint2 *>(row + i0);
+__device__ __forceinline__ void load4<BF16In>(const uint16_t *row, int i0, int V, float fill,
+                                              float (&v)[4]) {
+  if (i0 + 3 < V) {
+    const uint2 t = load_four(row + i0);
     v[0] = __uint_as_float(t.x << 16);
     v[1] = __uint_as_float(t.x & 0xFFFF0000u);
     v[2] = __uint_as_float(t.y << 16);
@@ -206,18 +206,17 @@ __device__ __forceinline__ void load4<BF16In>(const uint16_t *row, int i0, int V
   }
 }
 
-// Four in-range elements of an aligned row, kept as loaded; unpack() widens them to fp32.
+// Four in-range elements of a row, kept as loaded; unpack() widens them to fp32.
 template <typename T>
 __device__ __forceinline__ typename T::raw load_raw(const typename T::elem *row, int i0) {
-  return *reinterpret_cast<const typename T::raw *>(row + i0);
+  return load_four(row + i0);
 }
-// The same four elements with bounds checks (ragged tails, unaligned rows); `fill` stands for
-// elements past the end.
+// The same four elements with bounds checks (ragged tails); `fill` stands for elements past the end.
 template <typename T>
-__device__ __forceinline__ typename T::raw load_raw_checked(const typename T::elem *row, int i0, int V, bool vec, float fill);
+__device__ __forceinline__ typename T::raw load_raw_checked(const typename T::elem *row, int i0, int V, float fill);
 template <>
-__device__ __forceinline__ float4 load_raw_checked<F32In>(const float *row, int i0, int V, bool vec, float fill) {
-  if (vec && i0 + 3 < V) return *reinterpret_cast<const float4 *>(row + i0);
+__device__ __forceinline__ float4 load_raw_checked<F32In>(const float *row, int i0, int V, float fill) {
+  if (i0 + 3 < V) return load_four(row + i0);
   float4 r;
   r.x = (i0 + 0 < V) ? row[i0 + 0] : fill;
   r.y = (i0 + 1 < V) ? row[i0 + 1] : fill;
@@ -226,8 +225,8 @@ __device__ __forceinline__ float4 load_raw_checked<F32In>(const float *row, int 
   return r;
 }
 template <>
-__device__ __forceinline__ uint2 load_raw_checked<BF16In>(const uint16_t *row, int i0, int V, bool vec, float fill) {
-  if (vec && i0 + 3 < V) return *reinterpret_cast<const uint2 *>(row + i0);
+__device__ __forceinline__ uint2 load_raw_checked<BF16In>(const uint16_t *row, int i0, int V, float fill) {
+  if (i0 + 3 < V) return load_four(row + i0);
   const uint32_t f = __float_as_uint(fill) >> 16;  // 0 and -inf are exact in bf16
   const uint32_t e0 = (i0 + 0 < V) ? row[i0 + 0] : f, e1 = (i0 + 1 < V) ? row[i0 + 1] : f;
   const uint32_t e2 = (i0 + 2 < V) ? row[i0 + 2] : f, e3 = (i0 + 3 < V) ? row[i0 + 3] : f;
@@ -243,11 +242,18 @@ __device__ __forceinline__ void unpack(const uint2 &r, float (&v)[4]) {
   v[3] = __uint_as_float(r.y & 0xFFFF0000u);
 }
 
+// A value that is the same in all lanes, held in a scalar register (the compiler leaves one that a
+// vector instruction computed in a vector register, of which the variants with normalisers have none
+// to spare).
+__device__ __forceinline__ float in_scalar(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
 // Bins of four consecutive candidates (one byte each) and the mask they imply: a candidate whose
 // bin differs from the announced one carries no mass on the draft (decoder) side (paper Section
 // 5.1: the decoder's target distribution holds the indicator 1{l_i = l_j}).
-__device__ __forceinline__ uint32_t load_bins4(const uint8_t *row, int i0, int V, bool aligned) {
-  if (aligned && i0 + 3 < V) return *reinterpret_cast<const uint32_t *>(row + i0);
+__device__ __forceinline__ uint32_t load_bins4(const uint8_t *row, int i0, int V) {
+  if (i0 + 3 < V) return *reinterpret_cast<const uint_any *>(row + i0);
   uint32_t w = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
@@ -491,7 +497,7 @@ __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int 
   float m = -inf;
   for (int g = g_begin + tid; g < g_end; g += kBlock) {
     float v[4];
-    load4<T>(row, g * 4, V, false, -inf, v);
+    load4<T>(row, g * 4, V, -inf, v);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (v[j] < inf) m = fmaxf(m, v[j]);
@@ -506,7 +512,7 @@ __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int 
   if (m > -inf) {
     for (int g = g_begin + tid; g < g_end; g += kBlock) {
       float v[4];
-      load4<T>(row, g * 4, V, false, -inf, v);
+      load4<T>(row, g * 4, V, -inf, v);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         if (v[j] < inf && v[j] > -inf) sum += exp(((double)v[j] - (double)m) / temp);
@@ -572,7 +578,6 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
   const int g_begin = chunk * p.groups_per_chunk;
   const int g_end = min(g_begin + p.groups_per_chunk, G);
   const int iters = (g_end - g_begin + kBlock - 1) / kBlock;
-  const bool vec = p.vector_loads != 0;
   const bool with_pool = p.no_pool == 0;  // false: draft-side reductions only, the target is not read
   const float fill = PROBS ? 0.0f : -__builtin_huge_valf();
 
@@ -613,7 +618,6 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
     const int y = p.bin_of[b];
     if (y >= 0 && y < V) announced = (int)brow[y];
   }
-  const bool bins_aligned = binned && (((uintptr_t)p.bins | (uintptr_t)p.bins_stride_b) & 3u) == 0;
   // pool only (the encoder's pass of the binned selection): the draft rows are not read and no
   // candidate counts on the draft side, as if every bin differed from the announced one
   const bool no_draft = MASKED && p.no_draft != 0;
@@ -629,14 +633,14 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
     float t = p.temp_draft_all;
     if (p.temp_draft != nullptr && k < p.K) t = p.temp_draft[k];
     kok[kk] = (k < p.K) && (t > 0.0f) && (t < __builtin_huge_valf());
-    cd23[kk] = PROBS ? 1.0f : (kLog2e / t) * kTwo23;
+    cd23[kk] = PROBS ? 1.0f : in_scalar((kLog2e / t) * kTwo23);
   }
   // min-first: the smallest of an index's K times is (-ln U0) / K
-  const float lgK = MINF ? log2f((float)p.K) : 0.0f;
-  const float invK = MINF ? 1.0f / (float)p.K : 1.0f;
+  const float lgK = MINF ? in_scalar(log2f((float)p.K)) : 0.0f;
+  const float invK = MINF ? in_scalar(1.0f / (float)p.K) : 1.0f;
   const float Tq = p.temp_target;
-  const float cq = PROBS ? 1.0f : kLog2e / Tq;
-  const float cq23 = PROBS ? 1.0f : cq * kTwo23;
+  const float cq = PROBS ? 1.0f : in_scalar(kLog2e / Tq);
+  const float cq23 = PROBS ? 1.0f : in_scalar(cq * kTwo23);
   // LSE: log2(e)/T of every slot as a two-float sum (no systematic rounding of 1/T in the exponent)
   float lse_hi[KT + 1], lse_lo[KT + 1];
   // With one shared proposal the scan also forms the target row's normaliser (two rows per
@@ -652,8 +656,8 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       // entry of -inf then gives -inf in both products, never NaN)
       float hi = (float)c64;
       if (fabs((double)hi) > fabs(c64)) hi = __uint_as_float(__float_as_uint(hi) - 1u);
-      lse_hi[kk] = hi;
-      lse_lo[kk] = fmaxf((float)(c64 - (double)hi), 1e-30f);
+      lse_hi[kk] = in_scalar(hi);
+      lse_lo[kk] = in_scalar(fmaxf((float)(c64 - (double)hi), 1e-30f));
     }
   }
   bool lse_ran = false;  // the main loop (which feeds the sums) was executed
@@ -718,7 +722,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       float a_even = __builtin_huge_valf(), a_odd = __builtin_huge_valf(), a_pool = __builtin_huge_valf();
       if (g < g_end && kbase + 2 * m < p.K) {
         float vq[4] = {fill, fill, fill, fill};
-        if (with_pool) load4<T>(trow, g * 4, V, vec, fill, vq);
+        if (with_pool) load4<T>(trow, g * 4, V, fill, vq);
         uint32_t up[4], lo[4];
         const uint32_t pair = same_race ? 0u : pair_base + m;
         philox_block(row_lo, (uint32_t)g, row_hi, pair, p.seed_lo, p.seed_hi, up);
@@ -746,8 +750,8 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
             const bool ok = (tk > 0.0f) && (tk < __builtin_huge_valf());
             const float ck = PROBS ? 1.0f : kLog2e / tk;
             float vd[4];
-            load4<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), g * 4, V, vec, fill, vd);
-            if (draft_masked) mask_bins(no_draft ? 0u : load_bins4(brow, g * 4, V, bins_aligned), announced, fill, vd);
+            load4<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), g * 4, V, fill, vd);
+            if (draft_masked) mask_bins(no_draft ? 0u : load_bins4(brow, g * 4, V), announced, fill, vd);
             float a_k = __builtin_huge_valf();
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -820,7 +824,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       // Without a pool the target-side exponent is pinned at 0 (threshold 0: never a hit).
       using raw = typename T::raw;
       auto load_tile = [&](const int g, const bool interior, raw &rq, raw (&rd)[KD], uint32_t &rb) {
-        if (binned && !no_draft) rb = load_bins4(brow, g * 4, V, bins_aligned);
+        if (binned && !no_draft) rb = load_bins4(brow, g * 4, V);
         if (interior) {
           if (with_pool) rq = load_raw<T>(trow, g * 4);
           if (!no_draft) {
@@ -828,10 +832,10 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
             for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw<T>(drow[kk], g * 4);
           }
         } else {
-          if (with_pool) rq = load_raw_checked<T>(trow, g * 4, V, vec, fill);
+          if (with_pool) rq = load_raw_checked<T>(trow, g * 4, V, fill);
           if (!no_draft) {
 #pragma unroll
-            for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw_checked<T>(drow[kk], g * 4, V, vec, fill);
+            for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw_checked<T>(drow[kk], g * 4, V, fill);
           }
         }
       };
@@ -1174,7 +1178,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       };
       // A tile is interior when every lane's group is complete and inside the chunk: all rows
       // are then read with unconditional vector loads.
-      const int interior_end = vec ? min(g_end, V >> 2) : g_begin;
+      const int interior_end = min(g_end, V >> 2);
       const int n_interior = max(0, (interior_end - g_begin) / kBlock);
       int it = 0;
       if (n_interior > 0) {
@@ -1339,14 +1343,14 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       const int g = g_begin + it * kBlock + tid;
       if (g >= g_end) continue;
       float vq[4] = {fill, fill, fill, fill};
-      if (with_pool) load4<T>(trow, g * 4, V, false, fill, vq);
+      if (with_pool) load4<T>(trow, g * 4, V, fill, vq);
 #pragma unroll 1
       for (int kk = 0; kk < KT; ++kk) {
         const int k = kbase + kk;
         if (k >= p.K) break;
         float vd[4];
-        load4<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), g * 4, V, false, fill, vd);
-        if (draft_masked) mask_bins(no_draft ? 0u : load_bins4(brow, g * 4, V, bins_aligned), announced, fill, vd);
+        load4<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), g * 4, V, fill, vd);
+        if (draft_masked) mask_bins(no_draft ? 0u : load_bins4(brow, g * 4, V), announced, fill, vd);
         uint32_t up[4], lo[4];
         const int kr = same_race ? 0 : k;
         philox_block(row_lo, (uint32_t)g, row_hi, (uint32_t)(kr >> 1), p.seed_lo, p.seed_hi, up);
