@@ -10,13 +10,12 @@ namespace {
 constexpr int kMaxChunks = 4096;
 constexpr long long kMaxBlocks = 0xFFFFFFFFLL / kBlock;  // workgroups of one launch
 constexpr int kPlannedChunkFloor = 16;  // the workspace always covers this many chunks
-constexpr long long kTargetBlocks = 1024;  // four resident workgroups on each of 256 CUs
-constexpr long long kMinTilesPerChunk = 8; // a chunk pays its own warm-up: keep it worth it
+constexpr long long kMinTilesPerChunk = 2;
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 struct Plan {
-  int kt, n_kgroups, n_chunks, groups_per_chunk;
+  int kt, n_kgroups, threads, n_chunks, groups_per_chunk;
 };
 
 // Drafts per workgroup pass.  With one shared proposal the per-index work is amortised over the
@@ -27,26 +26,37 @@ int auto_ktile(long long K, bool shared) {
   return K >= 3 ? 4 : 2;
 }
 
-// Split the G four-element groups of a row into chunks of a multiple of kBlock groups.
-void plan_chunks(long long G, int want, int *n_chunks, int *groups_per_chunk) {
-  const long long tiles = (G + kBlock - 1) / kBlock;  // 256-group tiles in a row
+// Split the G four-element groups of a row into chunks of a multiple of `threads` groups.
+void plan_chunks(long long G, int threads, int want, int *n_chunks, int *groups_per_chunk) {
+  const long long tiles = (G + threads - 1) / threads;  // tiles in a row, one group per thread
   long long nc = want < 1 ? 1 : want;
   if (nc > tiles) nc = tiles;
   if (nc > kMaxChunks) nc = kMaxChunks;
   const long long tiles_per_chunk = (tiles + nc - 1) / nc;
-  *groups_per_chunk = (int)(tiles_per_chunk * kBlock);
+  *groups_per_chunk = (int)(tiles_per_chunk * threads);
   *n_chunks = (int)((tiles + tiles_per_chunk - 1) / tiles_per_chunk);
 }
 
-int auto_chunks(long long B, long long n_kgroups, long long G) {
-  const long long rows = B * n_kgroups;
-  if (rows >= kTargetBlocks || rows <= 0) return 1;
-  long long c = (kTargetBlocks + rows - 1) / rows;
-  const long long tiles = (G + kBlock - 1) / kBlock;
-  const long long most = tiles / kMinTilesPerChunk;
+// Threads per workgroup and workgroups per row for `rows` (row, draft group) pairs.  What pays, in this
+// order: fill the chip (256 CUs hold 2^18 threads of the lean variants), a row in one workgroup (its
+// bound is found once, and the workgroup finishes the row: one launch in all), few large workgroups
+// instead of many small ones where a row has to be split.  So a workgroup takes as many threads as the
+// batch leaves room for, and chunks fill what is still free, down to two tiles each (every chunk pays
+// its own warm-up and exact step).  Measured against 256 threads with chunks to fill, and its fill and
+// finalize launches (us a call): 256 rows x 32 000, K = 4, bf16 38 -> 24; 300 x 50 257, K = 5, with
+// keys 95 -> 73; 512 x 128 256, K = 8, min-first, with keys 127 -> 114; 64 x 128 256 60 -> 37;
+// 1 x 128 256 32 -> 26; 4 x 32 000 29 -> 21.  From 513 rows on a workgroup of 256 is the better one
+// (700 rows: 163 against 185 with 512 threads; 1024: 218 against 220, 242 with 1024).
+void auto_shape(long long rows, long long G, int most_threads, bool lean, int *threads, int *chunks) {
+  // (the others run one workgroup of 512 per CU)
+  const long long room = lean ? 1LL << 18 : 1LL << 17;
+  *threads = kBlock;
+  while (*threads * 2 <= most_threads && rows * *threads * 2 <= room) *threads *= 2;
+  long long c = rows > 0 ? room / (rows * *threads) : 1;
+  const long long most = (G + *threads - 1) / *threads / kMinTilesPerChunk;
   if (c > most) c = most;
   if (c < 1) c = 1;
-  return (int)(c > kMaxChunks ? kMaxChunks : c);
+  *chunks = (int)(c > kMaxChunks ? kMaxChunks : c);
 }
 
 struct Layout {
@@ -173,8 +183,13 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   pl.kt = j.k_tile != 0 ? (j.k_tile == 1 ? 2 : j.k_tile) : auto_ktile(j.K, shared);
   pl.n_kgroups = (int)((j.K + pl.kt - 1) / pl.kt);
   const long long G = (j.V + 3) / 4;
-  plan_chunks(G, j.v_chunks != 0 ? j.v_chunks : auto_chunks(j.B, pl.n_kgroups, G), &pl.n_chunks,
-              &pl.groups_per_chunk);
+  const bool masked = j.bins != nullptr || j.no_draft || j.same_race;
+  const bool lean = lean_variant(shared, pl.kt / 2, j.need_lse && j.kind != LLC_PROBS && !masked);
+  pl.threads = kBlock;
+  int want = j.v_chunks;
+  if (want == 0)  // (min-first: a staging area and a queue per wavefront, within 64 KB of LDS)
+    auto_shape(j.B * pl.n_kgroups, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, lean, &pl.threads, &want);
+  plan_chunks(G, pl.threads, want, &pl.n_chunks, &pl.groups_per_chunk);
   out->blocks = j.B * pl.n_kgroups * pl.n_chunks;
   // (a launch takes fewer than 2^32 threads in all)
   if (out->blocks > kMaxBlocks) return LLC_E_SHAPE;
@@ -244,13 +259,12 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
     if (launch_lse(st, lp) != hipSuccess) return LLC_E_LAUNCH;
   }
 
-  // Where every row is one workgroup, a plain scan (no bins, no normalisers to merge) takes the
-  // finalize step itself: one launch less.  (For rows spread over several workgroups the same was
+  // Where every row is one workgroup, the scan takes the finalize step itself: one launch less.  (For rows spread over several workgroups the same was
   // tried with a ticket per row, the last workgroup finishing the row: publishing the partial
   // results needs either device-scope fences, which write back and invalidate an XCD's whole L2
   // and doubled the scan's time, or write-through stores and reads, whose latency at the end of
   // the launch cost more than the finalize launch they saved.)
-  const bool finish = j.fin != nullptr && !masked && !fused_lse && pl.n_chunks * pl.n_kgroups == 1;
+  const bool finish = j.fin != nullptr && pl.n_chunks * pl.n_kgroups == 1;
   if (finished != nullptr) *finished = finish;
 
   // a row spread over several workgroups shares its running bests through the workspace
@@ -266,6 +280,9 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
 
   ScanParams sp;
   sp.shared_tau = shared_tau;
+  sp.threads = pl.threads;
+  sp.finish = finish ? 1 : 0;
+  sp.form_lse = fused_lse ? 1 : 0;
   sp.lse_part = part.lse_part;
   sp.bins = j.bins; sp.bins_stride_b = j.bins_stride_b; sp.bin_of = j.bin_of;
   sp.draft_row_off = j.draft_row_off;
@@ -299,17 +316,17 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
   hipError_t e;
   if (j.min_first) {
     if (j.dtype == LLC_F32)
-      e = shared ? launch_scan_f32_shared_minf(pl.kt, probs, finish, (unsigned)blocks, st, sp)
-                 : launch_scan_f32_perk_minf(pl.kt, probs, finish, (unsigned)blocks, st, sp);
+      e = shared ? launch_scan_f32_shared_minf(pl.kt, probs, (unsigned)blocks, st, sp)
+                 : launch_scan_f32_perk_minf(pl.kt, probs, (unsigned)blocks, st, sp);
     else
-      e = shared ? launch_scan_bf16_shared_minf(pl.kt, probs, finish, (unsigned)blocks, st, sp)
-                 : launch_scan_bf16_perk_minf(pl.kt, probs, finish, (unsigned)blocks, st, sp);
+      e = shared ? launch_scan_bf16_shared_minf(pl.kt, probs, (unsigned)blocks, st, sp)
+                 : launch_scan_bf16_perk_minf(pl.kt, probs, (unsigned)blocks, st, sp);
   } else if (j.dtype == LLC_F32) {
-    e = shared ? launch_scan_f32_shared(pl.kt, probs, finish, (unsigned)blocks, st, sp)
-               : launch_scan_f32_perk(pl.kt, probs, finish, (unsigned)blocks, st, sp);
+    e = shared ? launch_scan_f32_shared(pl.kt, probs, (unsigned)blocks, st, sp)
+               : launch_scan_f32_perk(pl.kt, probs, (unsigned)blocks, st, sp);
   } else {
-    e = shared ? launch_scan_bf16_shared(pl.kt, probs, finish, (unsigned)blocks, st, sp)
-               : launch_scan_bf16_perk(pl.kt, probs, finish, (unsigned)blocks, st, sp);
+    e = shared ? launch_scan_bf16_shared(pl.kt, probs, (unsigned)blocks, st, sp)
+               : launch_scan_bf16_perk(pl.kt, probs, (unsigned)blocks, st, sp);
   }
   if (e != hipSuccess) return LLC_E_LAUNCH;
   if (j.ev_end != nullptr && hipEventRecord((hipEvent_t)j.ev_end, st) != hipSuccess)
@@ -376,6 +393,7 @@ int couple_on(const llc_couple_args *a, void *workspace, size_t workspace_bytes)
     fp.Y = nullptr; fp.accept = nullptr; fp.match_k = nullptr; fp.keyY = nullptr; fp.count_pool = 0;
   }
   fp.stats = a->stats;
+  fp.need_norm = j.need_lse && a->kind != LLC_PROBS ? 1 : 0; fp.store_norm = 0;
   j.fin = &fp;  // (where it can, the scan finishes the rows itself and no finalize launch follows)
 
   Plan pl;
@@ -417,10 +435,10 @@ size_t llc_couple_workspace_size(int64_t B, int64_t K, int64_t V) {
   if (!shape_ok(B, K, V)) return 0;
   // worst case over k_tile (one draft per group) and over v_chunks up to the planned floor
   const long long G = (V + 3) / 4;
-  int nc, gpc;
-  int want = auto_chunks(B, 1, G);
+  int nc, gpc, threads, want;
+  auto_shape(B, G, kMaxThreads / 2, true, &threads, &want);
   if (want < kPlannedChunkFloor) want = kPlannedChunkFloor;
-  plan_chunks(G, want, &nc, &gpc);
+  plan_chunks(G, kBlock, want, &nc, &gpc);
   return layout_for(B, K, K, nc).total + 256;
 }
 
@@ -470,9 +488,9 @@ int llc_compress_select(const llc_compress_select_args *a) {
   j.extra_bytes = 0;
   Plan pl;
   Partials part;
-  int rc = run_scan(j, dry, &pl, &part, nullptr);
-  if (rc != LLC_OK) return rc;
-  if (dry) {  // the decoders' pass is planned as well, nothing is launched
+  if (dry) {  // both passes are planned, nothing is launched
+    const int rc = run_scan(j, true, &pl, &part, nullptr);
+    if (rc != LLC_OK) return rc;
     j.K = a->L; j.same_race = same_race;
     j.draft = a->logw_dec; j.map = plain_rows(a->dec_stride_b, a->enc_stride_b);
     j.draft_stride_k = a->dec_stride_l; j.no_pool = true; j.no_draft = false;
@@ -483,15 +501,24 @@ int llc_compress_select(const llc_compress_select_args *a) {
   fp.cand = nullptr; fp.side = nullptr; fp.source = nullptr; fp.W = nullptr; fp.A_hat = nullptr; fp.sq_err = nullptr;
   fp.cand_stride_b = 0; fp.side_stride_b = 0; fp.var_e = 0.0; fp.var_z = 0.0;
   // (with one shared set of race times the pool runs over that set alone: K = 1 in this pass)
-  fp.B = a->B; fp.K = (int)j.K; fp.n_chunks = pl.n_chunks; fp.n_kgroups = pl.n_kgroups;
+  fp.B = a->B; fp.K = (int)j.K; fp.n_chunks = 0; fp.n_kgroups = 0;
   fp.log_kind = 1;
-  fp.in = part;
+  std::memset(&fp.in, 0, sizeof(fp.in));
+  fp.need_norm = j.need_lse ? 1 : 0; fp.store_norm = 0;
   fp.X = a->X; fp.Y = a->Y; fp.match_k = nullptr; fp.accept = a->accept;
   fp.keyX = nullptr; fp.keyY = a->keyY; fp.log_keyX = nullptr; fp.log_secX = nullptr;
   fp.y_given = 0; fp.bins = nullptr; fp.bins_stride_b = 0; fp.message = nullptr;
   fp.count_draft = 0; fp.count_pool = 1; fp.count_near = 1;  // pass 1's draft side is not part of the result
   fp.stats = a->stats;
-  if (launch_finalize(st, fp) != hipSuccess) return LLC_E_LAUNCH;
+  j.fin = &fp;
+  bool finished = false;
+  int rc = run_scan(j, false, &pl, &part, nullptr, &finished);
+  if (rc != LLC_OK) return rc;
+  if (!finished) {
+    fp.n_chunks = pl.n_chunks; fp.n_kgroups = pl.n_kgroups;
+    fp.in = part;
+    if (launch_finalize(st, fp) != hipSuccess) return LLC_E_LAUNCH;
+  }
 
   // pass 2, the decoders: X^(l) = argmin under lambda_p^(l) over the candidates of Y's bin
   j.K = a->L; j.same_race = same_race;
@@ -503,10 +530,8 @@ int llc_compress_select(const llc_compress_select_args *a) {
   j.need_lse = a->keyX != nullptr;
   j.bins = a->bins; j.bins_stride_b = a->bins_stride_b; j.bin_of = a->Y;
   j.ev_begin = a->ev_scan_begin; j.ev_end = a->ev_scan_end;
-  rc = run_scan(j, false, &pl, &part, nullptr);
-  if (rc != LLC_OK) return rc;
-  fp.K = (int)a->L; fp.n_chunks = pl.n_chunks; fp.n_kgroups = pl.n_kgroups;
-  fp.in = part;
+  fp.K = (int)a->L;
+  fp.need_norm = j.need_lse ? 1 : 0;
   if (decode) {
     fp.cand = a->cand; fp.cand_stride_b = a->cand_stride_b;
     fp.side = a->side; fp.side_stride_b = a->side_stride_b;
@@ -518,7 +543,10 @@ int llc_compress_select(const llc_compress_select_args *a) {
   fp.keyX = a->keyX; fp.keyY = nullptr;
   fp.y_given = 1; fp.bins = a->bins; fp.bins_stride_b = a->bins_stride_b; fp.message = a->message;
   fp.count_draft = 1; fp.count_pool = 0; fp.count_near = 1;
-  fp.stats = a->stats;
+  rc = run_scan(j, false, &pl, &part, nullptr, &finished);
+  if (rc != LLC_OK || finished) return rc;
+  fp.n_chunks = pl.n_chunks; fp.n_kgroups = pl.n_kgroups;
+  fp.in = part;
   if (launch_finalize(st, fp) != hipSuccess) return LLC_E_LAUNCH;
   return LLC_OK;
 }
@@ -694,11 +722,8 @@ int llc_verify(const llc_verify_args *a) {
   if (!workspace_ok(j, plan_all)) return LLC_E_WORKSPACE;
   if (dry) return LLC_OK;
 
-  Plan pl = plan_all.pl;
-  Partials part;
-  char *extra = nullptr;
-  rc = launch_scan_job(j, plan_all, &part, &extra);
-  if (rc != LLC_OK) return rc;
+  const Plan pl = plan_all.pl;
+  char *extra = (char *)a->workspace + extra_offset(j, plan_all);
   double *cand_key = (double *)(extra + ex.cand_key);
   double *cand_sec = (double *)(extra + ex.cand_sec);
   int32_t *cand = a->Yk != nullptr ? a->Yk : (int32_t *)(extra + ex.cand);
@@ -709,13 +734,20 @@ int llc_verify(const llc_verify_args *a) {
   fp.cand_stride_b = 0; fp.side_stride_b = 0; fp.var_e = 0.0; fp.var_z = 0.0;
   fp.B = B; fp.K = (int)a->K; fp.n_chunks = pl.n_chunks; fp.n_kgroups = pl.n_kgroups;
   fp.log_kind = 1;
-  fp.in = part;
+  std::memset(&fp.in, 0, sizeof(fp.in));
+  fp.need_norm = 1; fp.store_norm = strong ? 1 : 0;
   fp.X = cand; fp.Y = nullptr; fp.match_k = nullptr; fp.accept = nullptr;
-  fp.keyX = a->keyYk; fp.keyY = nullptr; fp.log_keyX = cand_key; fp.log_secX = cand_sec;
+  fp.keyX = a->keyYk; fp.keyY = nullptr; fp.log_keyX = cand_key; fp.log_secX = a->stats != nullptr ? cand_sec : nullptr;
   fp.y_given = 0; fp.bins = nullptr; fp.bins_stride_b = 0; fp.message = nullptr;
   fp.count_draft = 1; fp.count_pool = 0; fp.count_near = 0;  // (near-ties: those of the loop's pools, counted there)
   fp.stats = a->stats;
-  if (launch_finalize(st, fp) != hipSuccess) return LLC_E_LAUNCH;
+  j.fin = &fp;
+  Partials part;
+  bool finished = false;
+  rc = launch_scan_job(j, plan_all, &part, nullptr, &finished);
+  if (rc != LLC_OK) return rc;
+  fp.in = part;
+  if (!finished && launch_finalize(st, fp) != hipSuccess) return LLC_E_LAUNCH;
 
   if (strong) {
     // Appendix B: position by position, because which drafts are dropped (and whose row prices

@@ -8,7 +8,12 @@
 
 namespace llc {
 
-constexpr int kBlock = 256;        // threads per workgroup: four 64-wide wavefronts
+constexpr int kBlock = 256;        // threads of a workgroup: four 64-wide wavefronts, or two or four times that
+constexpr int kMaxThreads = 1024;  // of a scan's workgroup
+
+// Variants of the scan kernel held to 128 registers (four wavefronts per SIMD, up to 1024 threads);
+// the others get 256 (two wavefronts per SIMD, up to 512 threads).
+constexpr bool lean_variant(bool shared, int pairs, bool lse) { return (shared || pairs <= 2) && !(lse && !shared); }
 constexpr int kListCap = 1024;     // candidate records a workgroup can hold in LDS
 
 // Four consecutive elements of a row wherever the row starts: the alignment stated is the element's,
@@ -66,6 +71,8 @@ struct FinalizeParams {
   int K, n_chunks, n_kgroups;
   int log_kind;        // keys are in the log domain and need the normaliser
   Partials in;
+  int need_norm;       // the keys' normalisers are wanted ...
+  int store_norm;      // ... and, of the drafts, also kept in in.lse
   int32_t *X, *Y, *match_k;  // Y, accept may be null (draft side only)
   int y_given;               // Y holds the pool's index already: only the accept test is taken
   const uint8_t *bins;       // optional: message[b] = bin of candidate Y[b]
@@ -98,8 +105,11 @@ struct ScanParams {
   long long draft_stride_k;  // elements
   long long B;
   int K, V;
+  int threads;           // of a workgroup
+  int finish;            // a row is one workgroup, which also takes the finalize step (fin)
+  int form_lse;          // the scan also forms the rows' normalisers (into lse_part unless it finishes them)
   int n_chunks;          // workgroups a row's V is split over
-  int groups_per_chunk;  // 4-element groups per chunk (a multiple of kBlock)
+  int groups_per_chunk;  // 4-element groups per chunk (a multiple of the threads)
   int n_kgroups;         // ceil(K / KT)
   unsigned seed_lo, seed_hi;
   unsigned long long row_offset;
@@ -120,9 +130,7 @@ struct ScanParams {
                             // the ordered image of +inf; nullptr when a row is one workgroup
   Partials out;
   llc_stats *stats;
-  // The variant for rows that are one workgroup each also takes the finalize step, so that no
-  // finalize launch follows.
-  FinalizeParams fin;       // used by that variant only
+  FinalizeParams fin;       // used if finish is set
 };
 
 
@@ -239,17 +247,16 @@ struct LmlParams {
 };
 
 // One launcher per (element type, draft layout); defined in scan_*.hip.
-// kt: drafts per workgroup pass (1, 2, 4, 8); probs: inputs are probabilities; finish: the
-// variant that also takes the finalize step (plain scans only: no bins, no fused normalisers).
-hipError_t launch_scan_f32_shared(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
-hipError_t launch_scan_f32_perk(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
-hipError_t launch_scan_bf16_shared(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
-hipError_t launch_scan_bf16_perk(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
+// kt: drafts per workgroup pass (2, 4, 8); probs: inputs are probabilities.
+hipError_t launch_scan_f32_shared(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_f32_perk(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_bf16_shared(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_bf16_perk(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
 // the same with the race times drawn min-first (no binned or pool-only passes)
-hipError_t launch_scan_f32_shared_minf(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
-hipError_t launch_scan_f32_perk_minf(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
-hipError_t launch_scan_bf16_shared_minf(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
-hipError_t launch_scan_bf16_perk_minf(int kt, bool probs, bool finish, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_f32_shared_minf(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_f32_perk_minf(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_bf16_shared_minf(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
+hipError_t launch_scan_bf16_perk_minf(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
 
 // llc_couple on a given workspace (api.hip).
 int couple_on(const llc_couple_args *a, void *workspace, size_t workspace_bytes);

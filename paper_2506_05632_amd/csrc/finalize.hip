@@ -9,9 +9,87 @@ namespace llc {
 
 namespace {
 
-__global__ void __launch_bounds__(64) finalize_kernel(const FinalizeParams p) {
-  __shared__ FinalizeShared sh;
-  finalize_row<64>(p, (long long)blockIdx.x, (int)threadIdx.x, sh);
+// Folds one more part of a draft's reduction into a running one (the parts hold different indices:
+// whichever winner loses is a candidate for the runner-up).
+__device__ __forceinline__ void fold_part(Merged &v, double key, int idx, double sec) {
+  v.sec = fmin(v.sec, sec);
+  if (beats(key, idx, 0, v.key, v.idx, 0)) {
+    if (v.idx >= 0) v.sec = fmin(v.sec, v.key);
+    v.key = key;
+    v.idx = idx;
+  } else if (idx >= 0) {
+    v.sec = fmin(v.sec, key);
+  }
+}
+
+// One wavefront per row.  Bound by the latency of its loads: a draft's chunk partials are fetched by
+// `width` lanes at once (a power of two, at least the number of chunks if that is 64 or less) and
+// merged by shuffles, 64 / width drafts at a time.  (One lane per draft walking its chunks, and one
+// lane walking the pool's parts, took 5.5 us at four chunks.)
+__global__ void __launch_bounds__(64) finalize_kernel(const FinalizeParams p, const int width) {
+  const long long b = (long long)blockIdx.x;
+  const int lane = (int)threadIdx.x, c0 = lane & (width - 1), nc = p.n_chunks;
+  const bool want_sec = p.stats != nullptr || p.log_secX != nullptr;
+  const double inf = __builtin_huge_val();
+  // ln of a normaliser, slot k of the row: ln sum_chunks exp(share), or in place already
+  auto normaliser = [&](const int k, const bool merge) {
+    if (!p.need_norm || k > p.K) return 0.0;
+    if (!merge) return p.in.lse[b * (p.K + 1) + k];
+    const double *sh = p.in.lse_part + (b * (p.K + 1) + k) * nc;
+    double m = -inf;
+    for (int c = c0; c < nc; c += width) m = fmax(m, sh[c]);
+    for (int d = width >> 1; d >= 1; d >>= 1) m = fmax(m, __shfl_xor(m, d));
+    double sum = 0.0;
+    if (m > -inf)
+      for (int c = c0; c < nc; c += width) sum += exp(sh[c] - m);
+    for (int d = width >> 1; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+    return m > -inf ? m + log(sum) : -inf;
+  };
+  Merged pool;
+  pool.key = inf; pool.idx = -1; pool.sec = inf; pool.norm = 0.0;
+  if (p.Y != nullptr && !p.y_given) {
+    // the pool over draft groups and chunks
+    const int parts = p.n_kgroups * nc;
+    const long long o = b * parts;
+    int bk = -1;
+    for (int c = lane; c < parts; c += 64) {
+      const double key = p.in.keyY[o + c];
+      const int idx = p.in.idxY[o + c], k = p.in.kY[o + c];
+      if (beats(key, idx, k, pool.key, pool.idx, bk)) { pool.key = key; pool.idx = idx; bk = k; }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      const double key = __shfl_xor(pool.key, d);
+      const int idx = __shfl_xor(pool.idx, d), k = __shfl_xor(bk, d);
+      if (beats(key, idx, k, pool.key, pool.idx, bk)) { pool.key = key; pool.idx = idx; bk = k; }
+    }
+    if (want_sec && p.count_pool) {
+      // the runner-up at another index: a part whose winner sits at the same index (another draft
+      // group met it under other race times) contributes its own runner-up instead
+      for (int c = lane; c < parts; c += 64) {
+        const int idx = p.in.idxY[o + c];
+        if (idx >= 0) pool.sec = fmin(pool.sec, idx != pool.idx ? p.in.keyY[o + c] : p.in.secY[o + c]);
+      }
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) pool.sec = fmin(pool.sec, __shfl_xor(pool.sec, d));
+    }
+    if (p.keyY != nullptr) pool.norm = normaliser(p.K, p.in.lse_part != nullptr && p.in.lse_part_target);
+  }
+  finish_row(p, b, lane, width, pool, [&](const int k) {
+    Merged m;
+    m.key = inf; m.idx = -1; m.sec = inf;
+    const bool in = k < p.K;
+    const long long o = (b * p.K + k) * nc;
+    if (in)
+      for (int c = c0; c < nc; c += width) fold_part(m, p.in.keyX[o + c], p.in.idxX[o + c], want_sec ? p.in.secX[o + c] : inf);
+    for (int d = width >> 1; d >= 1; d >>= 1) {
+      const double key = __shfl_xor(m.key, d), sec = __shfl_xor(m.sec, d);
+      const int idx = __shfl_xor(m.idx, d);
+      fold_part(m, key, idx, sec);
+    }
+    m.norm = normaliser(in ? k : p.K, p.in.lse_part != nullptr && in);
+    return m;
+  });
 }
 
 // ln sum_i exp(x_i / T) of one input row, in one pass over the row: every thread keeps a
@@ -172,7 +250,7 @@ __global__ void __launch_bounds__(64) verify_kernel(const VerifyParams p) {
       key[u] = sec[u] = __builtin_huge_val(); idx[u] = -1; tok[u] = -2;
       if (j <= L && lane < K) {
         key[u] = ckey[(long long)j * K + lane];
-        sec[u] = csec[(long long)j * K + lane];
+        if (p.stats != nullptr) sec[u] = csec[(long long)j * K + lane];
         idx[u] = cand[(long long)j * K + lane];
         if (j < L) tok[u] = p.tokens[s * p.tok_stride_s + (long long)j * p.tok_stride_j + lane];
       }
@@ -251,7 +329,7 @@ __global__ void __launch_bounds__(64) strong_step_kernel(const StrongStepParams 
   if (lane < K) {
     if (viable) {
       key = p.cand_key[(s * (L + 1) + j) * K + lane];
-      sec = p.cand_sec[(s * (L + 1) + j) * K + lane];
+      if (p.stats != nullptr) sec = p.cand_sec[(s * (L + 1) + j) * K + lane];
       idx = p.cand[(s * (L + 1) + j) * K + lane];
     } else {
       // merge the chunks of this draft's scan (as the finalize kernel does) and normalise
@@ -342,7 +420,9 @@ hipError_t launch_strong_step(hipStream_t s, const StrongStepParams &p) {
 
 hipError_t launch_finalize(hipStream_t s, const FinalizeParams &p) {
   if (p.B == 0) return hipSuccess;
-  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)p.B), dim3(64), 0, s, p);
+  int width = 1;
+  while (width < p.n_chunks && width < 64) width *= 2;
+  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)p.B), dim3(64), 0, s, p, width);
   return hipGetLastError();
 }
 

@@ -351,18 +351,19 @@ __device__ __forceinline__ double exact_key(double S, float v, double T) {
   return log(S) - (double)v / T;
 }
 
-// LSE with one shared proposal: the lanes' two running sums, kept in LDS (the other variants carry
-// an empty stand-in).
-template <bool ON, int N>
-struct LaneSums { double v[N][kBlock]; };
-template <int N>
-struct LaneSums<false, N> { double v[1][1]; };
-
 // Min-first survivors' path: words of a wavefront's staging area (eight lanes' tiles of 4 words, 4 target
 // values, the group's number (padded) and up to 32 draft values) and of its queue (up to 8 + 32
 // indices of 3 words and up to 8 draft values).
 constexpr int kStageWords = 8 * 44;
 constexpr int kQueueWords = 40 * 11;
+constexpr int kMaxWaves = kMaxThreads / 64;
+
+// Dynamic LDS of a launch, behind the static part: min-first, a staging area and a queue per wavefront;
+// fused normalisers with one shared proposal, the lanes' two running sums.
+inline unsigned dynamic_lds(bool min_first, bool lane_sums, int threads) {
+  return (min_first ? (unsigned)(threads / 64) * 4u * (kStageWords + kQueueWords) : 0u) +
+         (lane_sums ? 2u * (unsigned)threads * (unsigned)sizeof(double) : 0u);
+}
 
 struct Lds {
   int tau[9];            // ordered-int log2 keys: drafts 0..KT-1, pool at [KT]
@@ -381,14 +382,15 @@ struct Lds {
     uint32_t up[16];
     float vq[4];
     float vd[32];
-  } stage[4];
-  int qn[4];             // min-first: candidates in each wavefront's queue
+  } stage[kMaxWaves];
+  int qn[kMaxWaves];     // min-first: candidates in each wavefront's queue
   int lse_redo;          // LSE: the running sums were not formed (the main loop was skipped) or are not finite
-  float lse_wmax[4][9];  // LSE: per-wave references (whole numbers, in powers of two) ...
-  double lse_wave[4][9]; // ... and per-wave sums relative to them, merged in a fixed order
+  float lse_wmax[kMaxWaves][9];  // LSE: per-wave references (whole numbers, in powers of two) ...
+  double lse_wave[kMaxWaves][9]; // ... and per-wave sums relative to them, merged in a fixed order
+  double share[9];       // LSE: ln sum exp(x/T) of this chunk, per slot
   int *shared_tau;       // the row's running bests shared by all its workgroups (or null)
   int shared_base, shared_pool;  // where this workgroup's draft 0 and the pool sit in it
-  float rec_a[kListCap];
+  double rec_key[kListCap];  // the approximate key (an fp32 value) until level 3 puts the exact one in its place
   int rec_i[kListCap];
   int rec_tag[kListCap];
 };
@@ -456,7 +458,7 @@ __device__ __forceinline__ void level2(Lds &s, float l2S, float vd, float vq, in
     const float a = l2S - ell;
     if (a <= tau_d + kEps2) {
       const int pos = atomicAdd(&s.count, 1);
-      if (pos < kListCap) { s.rec_a[pos] = a; s.rec_i[pos] = i; s.rec_tag[pos] = kk; }
+      if (pos < kListCap) { s.rec_key[pos] = (double)a; s.rec_i[pos] = i; s.rec_tag[pos] = kk; }
       if (a < tau_d) publish<KT, SHARED, PROBS, MINF>(s, kk, a);
     }
   }
@@ -464,7 +466,7 @@ __device__ __forceinline__ void level2(Lds &s, float l2S, float vd, float vq, in
     const float a = l2S - ell;
     if (a <= tau_p + kEps2) {
       const int pos = atomicAdd(&s.count, 1);
-      if (pos < kListCap) { s.rec_a[pos] = a; s.rec_i[pos] = i; s.rec_tag[pos] = KT + kk; }
+      if (pos < kListCap) { s.rec_key[pos] = (double)a; s.rec_i[pos] = i; s.rec_tag[pos] = KT + kk; }
       if (a < tau_p) publish<KT, SHARED, PROBS, MINF>(s, KT, a);
     }
   }
@@ -492,10 +494,10 @@ __device__ __forceinline__ void offer_second(Lds &s, int slot, double key, int i
 template <typename T>
 __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int g_end, int V, double temp,
                                   float *s_max, double *s_sum) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6;
   const float inf = __builtin_huge_valf();
   float m = -inf;
-  for (int g = g_begin + tid; g < g_end; g += kBlock) {
+  for (int g = g_begin + tid; g < g_end; g += nt) {
     float v[4];
     load4<T>(row, g * 4, V, -inf, v);
 #pragma unroll
@@ -507,10 +509,11 @@ __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int 
   __syncthreads();  // the scratch arrays may still be read from a previous call
   if ((tid & 63) == 0) s_max[tid >> 6] = m;
   __syncthreads();
-  m = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+  m = s_max[0];
+  for (int w = 1; w < nw; ++w) m = fmaxf(m, s_max[w]);
   double sum = 0.0;
   if (m > -inf) {
-    for (int g = g_begin + tid; g < g_end; g += kBlock) {
+    for (int g = g_begin + tid; g < g_end; g += nt) {
       float v[4];
       load4<T>(row, g * 4, V, -inf, v);
 #pragma unroll
@@ -522,9 +525,18 @@ __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int 
   for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
   if ((tid & 63) == 0) s_sum[tid >> 6] = sum;
   __syncthreads();
-  sum = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+  sum = s_sum[0];
+  for (int w = 1; w < nw; ++w) sum += s_sum[w];
   const bool ok = m > -inf && temp > 0.0 && temp < (double)inf;
   return ok ? (double)m / temp + log(sum) : -__builtin_huge_val();
+}
+
+// The kernel's parameters, read from memory where this is called (see its use).
+__device__ __forceinline__ const ScanParams &fetch_params_again() {
+  typedef const ScanParams __attribute__((address_space(4))) *kernarg;
+  uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));
+  return *(const ScanParams *)(kernarg)at;
 }
 
 // One workgroup scans one (row, draft group, chunk).  KB = draft pairs per pass (KT = 2 KB
@@ -533,8 +545,10 @@ __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int 
 // log-weights only, which is what the compression scheme uses).
 // LSE: the variant that also accumulates the rows' normalisers ln sum exp(x/T) while it scans
 // them (logit kinds), so that no second pass over the inputs is needed.
-// FIN: the variant for rows that are one workgroup each: it also takes the finalize step (Algorithm
-// 1's accept test and the outputs), so that no finalize launch follows.
+// A workgroup is 256, 512 or 1024 threads (the host's choice, see plan_scan): larger ones let a batch
+// of a few hundred rows fill the chip with one workgroup per row.  Where a row is one workgroup
+// (p.finish) the kernel also takes the finalize step (Algorithm 1's accept test and the outputs), from
+// LDS, so that no finalize launch follows.
 // MINF: the race times are drawn min-first (see the top of the file).
 // Registers: four workgroups per CU (128 registers) where a workgroup reads one shared proposal or
 // at most four drafts' rows, except for the variants that read per-draft rows and form their
@@ -544,18 +558,21 @@ __device__ double chunk_lse_exact(const typename T::elem *row, int g_begin, int 
 // every lane needs into a stretch of code that runs with the exec mask narrowed to a few lanes.
 // The build's audit looks for that in the assembly of every kernel.)  They are allowed more
 // and take about 150: three workgroups per CU.
-template <typename T, int KB, bool SHARED, bool PROBS, bool MASKED, bool LSE, bool FIN, bool MINF>
-__global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHARED)) ? 4 : 2) scan_kernel(const ScanParams p) {
+template <typename T, int KB, bool SHARED, bool PROBS, bool MASKED, bool LSE, bool MINF>
+__global__ void __launch_bounds__(lean_variant(SHARED, KB, LSE) ? kMaxThreads : kMaxThreads / 2, lean_variant(SHARED, KB, LSE) ? 4 : 2)
+scan_kernel(const ScanParams p) {
   using elem = typename T::elem;
   constexpr int KT = 2 * KB;
   static_assert(!(MINF && MASKED), "the binned and pool-only passes draw one word per (index, draft)");
   __shared__ Lds s;
-  __shared__ __align__(16) uint32_t s_minf[MINF ? 4 * (kStageWords + kQueueWords) : 4];  // (see the main loop)
+  extern __shared__ __align__(16) char s_dyn[];  // see dynamic_lds
   // (with per-draft rows the sums stay in registers: in LDS they measured slower there)
   constexpr bool kSumsInLds = LSE && SHARED;
-  __shared__ LaneSums<kSumsInLds, 2> sums;
 
   const int tid = threadIdx.x;
+  const int nt = p.threads;  // of this workgroup
+  uint32_t *const s_minf = reinterpret_cast<uint32_t *>(s_dyn);  // (see the main loop)
+  double *const s_sums = reinterpret_cast<double *>(s_dyn + (MINF ? (nt >> 6) * 4 * (kStageWords + kQueueWords) : 0)) + tid;
   // Workgroups are handed to the 8 XCDs round-robin by index.  Renumber them so that the
   // workgroups of one row (its draft groups and chunks, which share the target row and, in the
   // shared layout, the draft row) get indices that are congruent modulo 8: they then run on one
@@ -577,7 +594,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
   const int G = (V + 3) >> 2;
   const int g_begin = chunk * p.groups_per_chunk;
   const int g_end = min(g_begin + p.groups_per_chunk, G);
-  const int iters = (g_end - g_begin + kBlock - 1) / kBlock;
+  const int iters = (g_end - g_begin + nt - 1) / nt;
   const bool with_pool = p.no_pool == 0;  // false: draft-side reductions only, the target is not read
   const float fill = PROBS ? 0.0f : -__builtin_huge_valf();
 
@@ -677,7 +694,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
   // round trip through the memory system per tile.
   if (kSumsInLds) {
 #pragma unroll
-    for (int kk = 0; kk < NL; ++kk) sums.v[kSumsInLds ? kk : 0][tid] = 0.0;
+    for (int kk = 0; kk < NL; ++kk) s_sums[kk * nt] = 0.0;
   }
 
   if (tid < 9) {
@@ -696,6 +713,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
     s.where[tid] = ~0ull;
     s.second[tid] = kOrdInf64;
   }
+  if (tid < kMaxWaves) s.qn[tid] = 0;
   if (tid == 0) {
 #pragma unroll
     for (int kk = 0; kk < KT; ++kk) { s.cd23[kk] = cd23[kk]; s.kok[kk] = kok[kk] ? 1 : 0; }
@@ -705,7 +723,6 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
     s.shared_base = kbase;
     s.shared_pool = p.K;
     s.lse_redo = 0;
-    s.qn[0] = 0; s.qn[1] = 0; s.qn[2] = 0; s.qn[3] = 0;
   }
   __syncthreads();
 
@@ -866,7 +883,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
           if (nn > lse_n[sl]) {  // (not so if only a +inf entry brought us here)
             if (lse_n[sl] > -__builtin_huge_valf()) {
               const int down = (int)fmaxf(lse_n[sl] - nn, -4000.0f);
-              if (kSumsInLds) sums.v[kSumsInLds ? sl : 0][tid] = ldexp(sums.v[kSumsInLds ? sl : 0][tid], down);
+              if (kSumsInLds) s_sums[sl * nt] = ldexp(s_sums[sl * nt], down);
               else lse_acc[sl] = ldexp(lse_acc[sl], down);
             }
             lse_n[sl] = nn;
@@ -878,7 +895,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
           // (the bare hardware exp2: a term below 2^-126 may flush to 0)
           const float part = (__builtin_amdgcn_exp2f(e[0]) + __builtin_amdgcn_exp2f(e[1])) +
                              (__builtin_amdgcn_exp2f(e[2]) + __builtin_amdgcn_exp2f(e[3]));
-          if (kSumsInLds) sums.v[kSumsInLds ? sl : 0][tid] += (double)part;
+          if (kSumsInLds) s_sums[sl * nt] += (double)part;
           else lse_acc[sl] += (double)part;
         }
       };
@@ -1179,7 +1196,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       // A tile is interior when every lane's group is complete and inside the chunk: all rows
       // are then read with unconditional vector loads.
       const int interior_end = min(g_end, V >> 2);
-      const int n_interior = max(0, (interior_end - g_begin) / kBlock);
+      const int n_interior = max(0, (interior_end - g_begin) / nt);
       int it = 0;
       if (n_interior > 0) {
         // the next tile's loads are issued one tile of arithmetic before they are used (two
@@ -1221,8 +1238,8 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
               publish<KT, SHARED, PROBS, MINF>(s, tid, unord32(seen), false);
             seen = __hip_atomic_load(row_tau + follow_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
-          load_tile(g0 + min(it + 1, n_interior - 1) * kBlock, true, bq, bd, bb);
-          process_tile(g0 + it * kBlock, aq, ad, ab);
+          load_tile(g0 + min(it + 1, n_interior - 1) * nt, true, bq, bd, bb);
+          process_tile(g0 + it * nt, aq, ad, ab);
           aq = bq; ab = bb;
 #pragma unroll
           for (int kk = 0; kk < KD; ++kk) ad[kk] = bd[kk];
@@ -1231,7 +1248,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       for (; it < iters; ++it) {
         // every lane takes part (the survivors' path works wave-wide); a group past the end of the
         // row reads as entries without mass
-        const int g = g_begin + it * kBlock + tid;
+        const int g = g_begin + it * nt + tid;
         raw rq = raw(), rd[KD];
         uint32_t rb = 0;
         load_tile(g, false, rq, rd, rb);
@@ -1254,7 +1271,7 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       // the lanes of a wave share the reference: their sums add up as they are
       const float wm = lse_n[lidx(kk)];
       double v = lse_acc[lidx(kk)];
-      if (kSumsInLds) v = sums.v[kSumsInLds ? lidx(kk) : 0][tid];
+      if (kSumsInLds) v = s_sums[lidx(kk) * nt];
       if (!(wm > -__builtin_huge_valf())) v = 0.0;
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
@@ -1262,43 +1279,42 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
     }
   }
 
+  // What follows reads the launch's parameters afresh: fetched at the top of the kernel with the others
+  // they would sit in scalar registers through the main loop, which spilled there.
+  const ScanParams &q = fetch_params_again();
   unsigned long long my_exact = 0;
   const bool exact_all = s.unsafe != 0;  // uniform: read after the barrier
 
   if (!exact_all) {
     // ---- level 3: exact keys of the records that are still within the band
+    // (there are a few dozen records: one round as a rule, and one copy of the arithmetic)
     const int n = s.count;
-    constexpr int kPer = kListCap / kBlock;
-    double key[kPer];
-    int ri[kPer], rslot[kPer], rk[kPer];
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      key[e] = __builtin_huge_val();
-      ri[e] = 0; rslot[e] = 0; rk[e] = 0;
-      const int r = e * kBlock + tid;
-      if (r < n) {
+#pragma unroll 1
+    for (int r = tid; r < n; r += nt) {
+      double key = __builtin_huge_val();
+      {
         const int tag = s.rec_tag[r];
         const bool pool = tag >= KT;
         const int kk = pool ? tag - KT : tag;
         const int slot = pool ? KT : kk;
         const float tau = unord32(s.tau[slot]);
-        if (s.rec_a[r] <= tau + kEps2) {
+        if ((float)s.rec_key[r] <= tau + kEps2) {
           const int i = s.rec_i[r];
           const int k = kbase + kk;
           uint32_t up[4], lo[4];
           const int kr = same_race ? 0 : k;  // the draft whose race times this one uses
-          philox_block(row_lo, (uint32_t)(i >> 2), row_hi, (uint32_t)(kr >> 1), p.seed_lo, p.seed_hi, up);
-          philox_block(row_lo, (uint32_t)(i >> 2), row_hi, (uint32_t)(kr >> 1) | kLowBlock, p.seed_lo, p.seed_hi, lo);
+          philox_block(row_lo, (uint32_t)(i >> 2), row_hi, (uint32_t)(kr >> 1), q.seed_lo, q.seed_hi, up);
+          philox_block(row_lo, (uint32_t)(i >> 2), row_hi, (uint32_t)(kr >> 1) | kLowBlock, q.seed_lo, q.seed_hi, lo);
           const int j = i & 3;
           const uint32_t uw = j == 0 ? up[0] : j == 1 ? up[1] : j == 2 ? up[2] : up[3];
           const uint32_t lw = j == 0 ? lo[0] : j == 1 ? lo[1] : j == 2 ? lo[2] : lo[3];
           double S = exact_race_time(element_word(uw, lw, kr & 1));
           if (MINF) {
             uint32_t mn[4], hd[4];
-            philox_block(row_lo, (uint32_t)(i >> 2), row_hi, kMinBlock, p.seed_lo, p.seed_hi, mn);
-            philox_block(row_lo, (uint32_t)(i >> 2), row_hi, kHolderBlock, p.seed_lo, p.seed_hi, hd);
-            const double M = exact_race_time(j == 0 ? mn[0] : j == 1 ? mn[1] : j == 2 ? mn[2] : mn[3]) / (double)p.K;
-            const int holder = holder_of(j == 0 ? hd[0] : j == 1 ? hd[1] : j == 2 ? hd[2] : hd[3], p.K);
+            philox_block(row_lo, (uint32_t)(i >> 2), row_hi, kMinBlock, q.seed_lo, q.seed_hi, mn);
+            philox_block(row_lo, (uint32_t)(i >> 2), row_hi, kHolderBlock, q.seed_lo, q.seed_hi, hd);
+            const double M = exact_race_time(j == 0 ? mn[0] : j == 1 ? mn[1] : j == 2 ? mn[2] : mn[3]) / (double)q.K;
+            const int holder = holder_of(j == 0 ? hd[0] : j == 1 ? hd[1] : j == 2 ? hd[2] : hd[3], q.K);
             S = (pool || holder == k) ? M : M + S;  // (a pool record is the holder's: the index's smallest time)
           }
           float temp = Tq;
@@ -1306,22 +1322,23 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
           if (pool) {
             v = load1<T>(trow, i);
           } else {
-            v = load1<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), i);
-            temp = p.temp_draft != nullptr ? p.temp_draft[k] : p.temp_draft_all;
+            v = load1<T>(drow0 + (SHARED ? 0 : (long long)k * q.draft_stride_k), i);
+            temp = q.temp_draft != nullptr ? q.temp_draft[k] : q.temp_draft_all;
           }
-          key[e] = exact_key<PROBS>(S, v, (double)temp);
-          ri[e] = i; rslot[e] = slot; rk[e] = pool ? k : 0;
+          key = exact_key<PROBS>(S, v, (double)temp);
           ++my_exact;
-          offer_key(s, slot, key[e]);
+          offer_key(s, slot, key);
         }
       }
+      s.rec_key[r] = key;  // (the thread's own record: read again by this thread only)
     }
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) offer_where(s, rslot[e], key[e], ri[e], rk[e]);
+    for (int r = tid; r < n; r += nt) {
+      const int tag = s.rec_tag[r];
+      offer_where(s, min(tag, KT), s.rec_key[r], s.rec_i[r], tag >= KT ? kbase + tag - KT : 0);
+    }
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) offer_second(s, rslot[e], key[e], ri[e]);
+    for (int r = tid; r < n; r += nt) offer_second(s, min(s.rec_tag[r], KT), s.rec_key[r], s.rec_i[r]);
   } else {
     // ---- fallback: every element of the chunk in fp64 (debug flag, out-of-range tau, list overflow)
     if (tid < 9) { s.best[tid] = kOrdInf64; s.where[tid] = ~0ull; s.second[tid] = kOrdInf64; }
@@ -1340,27 +1357,27 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
 #pragma unroll
     for (int kk = 0; kk <= KT; ++kk) { best[kk] = __builtin_huge_val(); bi[kk] = -1; }
     for (int it = 0; it < iters; ++it) {
-      const int g = g_begin + it * kBlock + tid;
+      const int g = g_begin + it * nt + tid;
       if (g >= g_end) continue;
       float vq[4] = {fill, fill, fill, fill};
       if (with_pool) load4<T>(trow, g * 4, V, fill, vq);
 #pragma unroll 1
       for (int kk = 0; kk < KT; ++kk) {
         const int k = kbase + kk;
-        if (k >= p.K) break;
+        if (k >= q.K) break;
         float vd[4];
-        load4<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), g * 4, V, fill, vd);
+        load4<T>(drow0 + (SHARED ? 0 : (long long)k * q.draft_stride_k), g * 4, V, fill, vd);
         if (draft_masked) mask_bins(no_draft ? 0u : load_bins4(brow, g * 4, V), announced, fill, vd);
         uint32_t up[4], lo[4];
         const int kr = same_race ? 0 : k;
-        philox_block(row_lo, (uint32_t)g, row_hi, (uint32_t)(kr >> 1), p.seed_lo, p.seed_hi, up);
-        philox_block(row_lo, (uint32_t)g, row_hi, (uint32_t)(kr >> 1) | kLowBlock, p.seed_lo, p.seed_hi, lo);
+        philox_block(row_lo, (uint32_t)g, row_hi, (uint32_t)(kr >> 1), q.seed_lo, q.seed_hi, up);
+        philox_block(row_lo, (uint32_t)g, row_hi, (uint32_t)(kr >> 1) | kLowBlock, q.seed_lo, q.seed_hi, lo);
         uint32_t mn[4] = {0u, 0u, 0u, 0u}, hd[4] = {0u, 0u, 0u, 0u};
         if (MINF) {  // (drawn again for every draft: this path is cold, and fewer registers stay live)
-          philox_block(row_lo, (uint32_t)g, row_hi, kMinBlock, p.seed_lo, p.seed_hi, mn);
-          philox_block(row_lo, (uint32_t)g, row_hi, kHolderBlock, p.seed_lo, p.seed_hi, hd);
+          philox_block(row_lo, (uint32_t)g, row_hi, kMinBlock, q.seed_lo, q.seed_hi, mn);
+          philox_block(row_lo, (uint32_t)g, row_hi, kHolderBlock, q.seed_lo, q.seed_hi, hd);
         }
-        const float tk = p.temp_draft != nullptr ? p.temp_draft[k] : p.temp_draft_all;
+        const float tk = q.temp_draft != nullptr ? q.temp_draft[k] : q.temp_draft_all;
         const bool ok = (tk > 0.0f) && (tk < __builtin_huge_valf());
         double bx = __builtin_huge_val();
         int bxi = -1;
@@ -1370,8 +1387,8 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
           if (i >= V) continue;
           double S = exact_race_time(element_word(up[j], lo[j], kr & 1));
           if (MINF) {
-            const double M = exact_race_time(mn[j]) / (double)p.K;
-            S = holder_of(hd[j], p.K) == k ? M : M + S;
+            const double M = exact_race_time(mn[j]) / (double)q.K;
+            S = holder_of(hd[j], q.K) == k ? M : M + S;
           }
           const double kx = ok ? exact_key<PROBS>(S, vd[j], (double)tk) : __builtin_huge_val();
           const double ky = with_pool ? exact_key<PROBS>(S, vq[j], (double)Tq) : __builtin_huge_val();
@@ -1419,13 +1436,13 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
   // ---- LSE: this chunk's share of every slot's normaliser, ln of (sum of exp(x/T) over the chunk)
   if (LSE) {
     __syncthreads();
-    const bool slot_used = tid < KT ? (kbase + tid < p.K) : (tid == KT && lse_target);
+    const bool slot_used = tid < KT ? (kbase + tid < q.K) : (tid == KT && lse_target);
     // the slot whose sums this thread reports: with one shared proposal slot 0 stands for every draft
     const int from = SHARED ? (tid < KT ? 0 : KT) : tid;
     double share = -__builtin_huge_val();
     if (tid <= KT && slot_used) {
-      float tk = tid == KT ? Tq : p.temp_draft_all;
-      if (tid < KT && p.temp_draft != nullptr) tk = p.temp_draft[kbase + tid];
+      float tk = tid == KT ? Tq : q.temp_draft_all;
+      if (tid < KT && q.temp_draft != nullptr) tk = q.temp_draft[kbase + tid];
       const bool t_ok = tk > 0.0f && tk < __builtin_huge_valf();
       if (!t_ok) {
         share = -__builtin_huge_val();
@@ -1434,9 +1451,10 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       } else {
         // the waves' sums, each relative to 2^(its reference), brought to the largest reference
         float gm = -__builtin_huge_valf();
-        for (int w = 0; w < 4; ++w) gm = fmaxf(gm, s.lse_wmax[w][from]);
+        const int nw = nt >> 6;
+        for (int w = 0; w < nw; ++w) gm = fmaxf(gm, s.lse_wmax[w][from]);
         double tot = 0.0;
-        for (int w = 0; w < 4; ++w)
+        for (int w = 0; w < nw; ++w)
           if (s.lse_wmax[w][from] > -__builtin_huge_valf())
             tot += ldexp(s.lse_wave[w][from], (int)fmaxf(s.lse_wmax[w][from] - gm, -4000.0f));
         if (!(gm > -__builtin_huge_valf())) {
@@ -1454,121 +1472,100 @@ __global__ void __launch_bounds__(kBlock, ((SHARED || KB <= 2) && !(LSE && !SHAR
       double *s_sum = &s.lse_wave[0][0];
 #pragma unroll 1
       for (int kk = 0; kk <= KT; ++kk) {
-        const bool used = kk < KT ? (SHARED ? kk == 0 : kbase + kk < p.K) : lse_target;
+        const bool used = kk < KT ? (SHARED ? kk == 0 : kbase + kk < q.K) : lse_target;
         if (!used) continue;  // uniform
-        float tk = kk == KT ? Tq : p.temp_draft_all;
-        if (kk < KT && p.temp_draft != nullptr) tk = p.temp_draft[kbase + kk];
-        const elem *rowp = kk == KT ? trow : drow0 + (SHARED ? 0 : (long long)(kbase + kk) * p.draft_stride_k);
+        float tk = kk == KT ? Tq : q.temp_draft_all;
+        if (kk < KT && q.temp_draft != nullptr) tk = q.temp_draft[kbase + kk];
+        const elem *rowp = kk == KT ? trow : drow0 + (SHARED ? 0 : (long long)(kbase + kk) * q.draft_stride_k);
         const double v = chunk_lse_exact<T>(rowp, g_begin, g_end, V, (double)tk, s_max, s_sum);
         if (from == kk) share = v;
       }
     }
     if (tid <= KT && slot_used) {
-      const long long slot = tid < KT ? kbase + tid : p.K;
-      p.lse_part[(b * (p.K + 1) + slot) * p.n_chunks + chunk] = share;
+      const long long slot = tid < KT ? kbase + tid : q.K;
+      if (q.finish) s.share[tid] = share;
+      else q.lse_part[(b * (q.K + 1) + slot) * q.n_chunks + chunk] = share;
     }
   }
 
-  // ---- partial results of this (row, draft group, chunk)
-  if (tid <= KT) {
+  // ---- the row's outputs, or this chunk's partial results
+  if (q.finish) {  // uniform: the row is this workgroup's alone, and its first wavefront finishes it
+    if (LSE) __syncthreads();  // the shares
+    if (tid < 64) {
+      auto outcome = [&](const int slot, const int k, const bool formed) {  // of slot, which is draft k's or the target's (k == K)
+        Merged m;
+        const bool has = slot <= KT && s.where[min(slot, KT)] != ~0ull;
+        m.key = has ? unord64(s.best[min(slot, KT)]) : __builtin_huge_val();
+        m.idx = has ? (int)(s.where[min(slot, KT)] >> 32) : -1;
+        m.sec = unord64(s.second[min(slot, KT)]);
+        m.norm = 0.0;
+        if (formed) m.norm = s.share[min(slot, KT)];
+        else if (q.fin.need_norm && k <= q.K) m.norm = q.out.lse[b * (q.K + 1) + k];
+        return m;
+      };
+      const Merged pool = outcome(KT, q.K, LSE && lse_target);
+      finish_row(q.fin, b, tid, 1, pool, [&](const int k) { return outcome(k < q.K ? k : KT + 1, k, LSE && k < q.K); });
+    }
+  } else if (tid <= KT) {
     const bool has = s.where[tid] != ~0ull;
     const double key = has ? unord64(s.best[tid]) : __builtin_huge_val();
     const int idx = has ? (int)(s.where[tid] >> 32) : -1;
     if (tid < KT) {
       const int k = kbase + tid;
-      if (k < p.K) {
-        const long long o = (b * p.K + k) * p.n_chunks + chunk;
-        p.out.keyX[o] = key;
-        p.out.idxX[o] = idx;
-        p.out.secX[o] = unord64(s.second[tid]);
+      if (k < q.K) {
+        const long long o = (b * q.K + k) * q.n_chunks + chunk;
+        q.out.keyX[o] = key;
+        q.out.idxX[o] = idx;
+        q.out.secX[o] = unord64(s.second[tid]);
       }
     } else {
-      const long long o = (b * p.n_kgroups + kg) * p.n_chunks + chunk;
-      p.out.keyY[o] = key;
-      p.out.idxY[o] = idx;
-      p.out.kY[o] = has ? (int)(uint32_t)s.where[tid] : -1;
-      p.out.secY[o] = unord64(s.second[tid]);
+      const long long o = (b * q.n_kgroups + kg) * q.n_chunks + chunk;
+      q.out.keyY[o] = key;
+      q.out.idxY[o] = idx;
+      q.out.kY[o] = has ? (int)(uint32_t)s.where[tid] : -1;
+      q.out.secY[o] = unord64(s.second[tid]);
     }
   }
-  if (p.stats != nullptr) {
+  if (q.stats != nullptr) {
     if (my_survivors) atomicAdd(&s.n_survivors, my_survivors);
     if (my_exact) atomicAdd(&s.n_exact, my_exact);
     __syncthreads();
     if (tid == 0) {
-      if (s.n_survivors) atomicAdd(&p.stats->survivors, s.n_survivors);
-      if (s.n_exact) atomicAdd(&p.stats->exact_evals, s.n_exact);
-      if (exact_all && !p.force_exact) atomicAdd(&p.stats->slow_blocks, 1ull);
+      if (s.n_survivors) atomicAdd(&q.stats->survivors, s.n_survivors);
+      if (s.n_exact) atomicAdd(&q.stats->exact_evals, s.n_exact);
+      if (exact_all && !q.force_exact) atomicAdd(&q.stats->slow_blocks, 1ull);
     }
-  }
-  if (FIN) {
-    // the row is this workgroup's alone (the host launches this variant only then): its partial
-    // results are complete, written by this workgroup's own threads
-    __shared__ FinalizeShared s_fin;
-    __syncthreads();
-    finalize_row<kBlock>(p.fin, b, tid, s_fin);
   }
 }
 
 // kt: drafts per workgroup pass (2, 4 or 8; 1 runs as 2: a draft pair shares its blocks).
 template <typename T, bool SHARED, bool MINF>
-hipError_t launch_scan(int kt, bool probs, bool finish, unsigned grid, hipStream_t st, const ScanParams &p) {
-#define LLC_LAUNCH(KB_, PR_, MK_, LS_, FN_)                                                                        \
-  hipLaunchKernelGGL((scan_kernel<T, KB_, SHARED, PR_, MK_, LS_, FN_, MINF>), dim3(grid), dim3(kBlock), 0, st, p); \
-  return hipGetLastError();
+hipError_t launch_scan(int kt, bool probs, unsigned grid, hipStream_t st, const ScanParams &p) {
   const bool masked = p.bins != nullptr || p.no_draft != 0 || p.same_race != 0;
-  if (p.lse_part != nullptr) {
-    // fused normalisers: logit kinds, no bins
-    if (probs || masked || finish) return hipErrorInvalidValue;
-    switch (kt) {
-      case 2: LLC_LAUNCH(1, false, false, true, false)
-      case 4: LLC_LAUNCH(2, false, false, true, false)
-      case 8: LLC_LAUNCH(4, false, false, true, false)
-    }
-    return hipErrorInvalidValue;
-  }
+  const bool lse = p.form_lse != 0;
+  if ((lse || masked) && probs) return hipErrorInvalidValue;
+  if (lse && masked) return hipErrorInvalidValue;
+  const unsigned lds = dynamic_lds(MINF, lse && SHARED, p.threads);
+#define LLC_LAUNCH(KB_, PR_, MK_, LS_)                                                                                   \
+  hipLaunchKernelGGL((scan_kernel<T, KB_, SHARED, PR_, MK_, LS_, MINF>), dim3(grid), dim3((unsigned)p.threads), lds, st, p); \
+  return hipGetLastError();
+#define LLC_LAUNCH_KT(PR_, MK_, LS_)            \
+  switch (kt) {                                 \
+    case 2: LLC_LAUNCH(1, PR_, MK_, LS_)        \
+    case 4: LLC_LAUNCH(2, PR_, MK_, LS_)        \
+    case 8: LLC_LAUNCH(4, PR_, MK_, LS_)        \
+  }                                             \
+  return hipErrorInvalidValue;
+  if (lse) { LLC_LAUNCH_KT(false, false, true) }  // fused normalisers: logit kinds, no bins
   if (masked) {
     // binned candidates / pool-only passes exist for fp32 log-weights, one word per (index, draft)
-    if constexpr (sizeof(typename T::elem) == 4 && !MINF) {
-      if (probs || finish) return hipErrorInvalidValue;
-      switch (kt) {
-        case 2: LLC_LAUNCH(1, false, true, false, false)
-        case 4: LLC_LAUNCH(2, false, true, false, false)
-        case 8: LLC_LAUNCH(4, false, true, false, false)
-      }
-    }
+    if constexpr (sizeof(typename T::elem) == 4 && !MINF) { LLC_LAUNCH_KT(false, true, false) }
     return hipErrorInvalidValue;
   }
-  if (!probs) {
-    if (finish) {
-      switch (kt) {
-        case 2: LLC_LAUNCH(1, false, false, false, true)
-        case 4: LLC_LAUNCH(2, false, false, false, true)
-        case 8: LLC_LAUNCH(4, false, false, false, true)
-      }
-    } else {
-      switch (kt) {
-        case 2: LLC_LAUNCH(1, false, false, false, false)
-        case 4: LLC_LAUNCH(2, false, false, false, false)
-        case 8: LLC_LAUNCH(4, false, false, false, false)
-      }
-    }
-  } else {
-    if (finish) {
-      switch (kt) {
-        case 2: LLC_LAUNCH(1, true, false, false, true)
-        case 4: LLC_LAUNCH(2, true, false, false, true)
-        case 8: LLC_LAUNCH(4, true, false, false, true)
-      }
-    } else {
-      switch (kt) {
-        case 2: LLC_LAUNCH(1, true, false, false, false)
-        case 4: LLC_LAUNCH(2, true, false, false, false)
-        case 8: LLC_LAUNCH(4, true, false, false, false)
-      }
-    }
-  }
+  if (probs) { LLC_LAUNCH_KT(true, false, false) }
+  LLC_LAUNCH_KT(false, false, false)
+#undef LLC_LAUNCH_KT
 #undef LLC_LAUNCH
-  return hipErrorInvalidValue;
 }
 
 }  // namespace llc
