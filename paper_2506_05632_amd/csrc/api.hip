@@ -10,7 +10,6 @@ namespace {
 constexpr int kMaxChunks = 4096;
 constexpr long long kMaxBlocks = 0xFFFFFFFFLL / kBlock;  // workgroups of one launch
 constexpr int kPlannedChunkFloor = 16;  // the workspace always covers this many chunks
-constexpr long long kMinTilesPerChunk = 2;
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
@@ -53,14 +52,17 @@ void auto_shape(long long rows, long long G, int most_threads, bool lean, int *t
   *threads = kBlock;
   while (*threads * 2 <= most_threads && rows * *threads * 2 <= room) *threads *= 2;
   long long c = rows > 0 ? room / (rows * *threads) : 1;
-  const long long most = (G + *threads - 1) / *threads / kMinTilesPerChunk;
+  // (two tiles a chunk up to eight chunks, four beyond: more chunks also make the finalize launch longer;
+  // 16 rows x 128 256, min-first with keys: 36 us with 8 to 16 chunks, 45 with 31)
+  const long long tiles = (G + *threads - 1) / *threads;
+  const long long most = tiles / 2 < 8 ? tiles / 2 : tiles / 4 < 8 ? 8 : tiles / 4;
   if (c > most) c = most;
   if (c < 1) c = 1;
   *chunks = (int)(c > kMaxChunks ? kMaxChunks : c);
 }
 
 struct Layout {
-  size_t keyX, idxX, keyY, idxY, kY, secX, secY, lse, lse_part, shared_tau, total;
+  size_t keyX, idxX, keyY, idxY, kY, secX, secY, lse, lse_part, total;
 };
 
 Layout layout_for(long long B, long long K, long long n_kgroups, long long n_chunks) {
@@ -75,7 +77,6 @@ Layout layout_for(long long B, long long K, long long n_kgroups, long long n_chu
   l.secY = off; off += align256((size_t)(B * n_kgroups * n_chunks) * sizeof(double));
   l.lse = off;  off += align256((size_t)(B * (K + 1)) * sizeof(double));
   l.lse_part = off; off += align256((size_t)(B * (K + 1) * n_chunks) * sizeof(double));
-  l.shared_tau = off; off += align256((size_t)(B * (K + 1)) * sizeof(int32_t));
   l.total = off;
   return l;
 }
@@ -98,10 +99,10 @@ RowMap plain_rows(long long draft_stride_b, long long target_stride_b) {
 
 // llc_verify keeps, beyond the scan's partials, ln(key) [B][K] fp64 and the index [B][K], and for
 // the strong form the loop's state: per sequence K viability bytes, a running flag and the next
-// position's row offset; the running bests that the scans of positions 1..L share; the
+// position's row offset; the
 // normalisers of every row and of the rows that price the position at hand.
 struct VerifyExtra {
-  size_t cand_key, cand_sec, cand, viable, running, next_off, tau_all, lse, lse_sel, total;
+  size_t cand_key, cand_sec, cand, viable, running, next_off, lse, lse_sel, total;
 };
 VerifyExtra verify_extra(long long S, long long B, long long K) {  // B = S (L + 1)
   VerifyExtra e;
@@ -112,7 +113,6 @@ VerifyExtra verify_extra(long long S, long long B, long long K) {  // B = S (L +
   e.viable = off; off += align256((size_t)(S * K));
   e.running = off; off += align256((size_t)S * sizeof(int32_t));
   e.next_off = off; off += align256((size_t)S * sizeof(long long));
-  e.tau_all = off; off += align256((size_t)((B - S) * (K + 1)) * sizeof(int32_t));  // running bests of positions 1..L
   e.lse = off; off += align256((size_t)(B * (K + 1)) * sizeof(double));      // the one-shot scan's normalisers
   e.lse_sel = off; off += align256((size_t)(S * (K + 1)) * sizeof(double));  // those of the rows that price a position
   e.total = off;
@@ -141,7 +141,6 @@ struct ScanJob {
   const long long *draft_row_off = nullptr;  // per-row extra offset of the draft row (see ScanParams)
   size_t lse_in_extra = (size_t)-1;  // keep the normalisers at this offset of the caller's region
   size_t extra_at = (size_t)-1;      // where the caller's region starts (default: right behind the partials)
-  int32_t *tau_ready = nullptr;      // the rows' shared running bests, already reset, if not in the workspace
   const FinalizeParams *fin = nullptr;  // if given, the scan may take the finalize step itself (plain
                                      // scans only); `in`, n_chunks and n_kgroups are filled in here
   int flags, v_chunks, k_tile;
@@ -267,19 +266,7 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
   const bool finish = j.fin != nullptr && pl.n_chunks * pl.n_kgroups == 1;
   if (finished != nullptr) *finished = finish;
 
-  // a row spread over several workgroups shares its running bests through the workspace
-  int32_t *shared_tau = nullptr;
-  if (pl.n_chunks * pl.n_kgroups > 1) {
-    if (j.tau_ready != nullptr) {
-      shared_tau = j.tau_ready;
-    } else {
-      shared_tau = (int32_t *)(ws + lay.shared_tau);
-      if (launch_fill(st, shared_tau, j.B * (j.K + 1), 0x7F800000) != hipSuccess) return LLC_E_LAUNCH;
-    }
-  }
-
   ScanParams sp;
-  sp.shared_tau = shared_tau;
   sp.threads = pl.threads;
   sp.finish = finish ? 1 : 0;
   sp.form_lse = fused_lse ? 1 : 0;
@@ -760,7 +747,6 @@ int llc_verify(const llc_verify_args *a) {
     ss.cand = cand; ss.cand_key = cand_key; ss.cand_sec = cand_sec;
     ss.part_key = nullptr; ss.part_idx = nullptr; ss.part_sec = nullptr; ss.n_chunks = 0;
     ss.stats = a->stats;
-    ss.tau_all = (int32_t *)(extra + ex.tau_all);
     ss.tokens = a->tokens; ss.tok_stride_s = a->tok_stride_s; ss.tok_stride_j = a->tok_stride_j;
     ss.stride_k = a->stride_k;
     ss.viable = (uint8_t *)(extra + ex.viable); ss.running = (int32_t *)(extra + ex.running);
@@ -776,7 +762,6 @@ int llc_verify(const llc_verify_args *a) {
         q.draft = (const char *)a->target + (size_t)(pos * a->stride_j) * esize;
         q.target = q.draft;
         q.row_offset = a->row_offset + (uint64_t)(pos * a->row_stride_j);
-        q.tau_ready = ss.tau_all + (pos - 1) * a->S * (a->K + 1);
         Partials part2;
         const int rc2 = launch_scan_job(q, plan_one, &part2, nullptr);
         if (rc2 != LLC_OK) return rc2;

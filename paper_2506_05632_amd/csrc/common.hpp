@@ -126,8 +126,6 @@ struct ScanParams {
                             // ln of every chunk's sum of exp(x/T) (merged by the finalize kernel)
   const long long *draft_row_off;  // optional [B]: elements added to row b's draft offset; a negative
                             // entry means the row is not wanted (its partial results come out empty)
-  int *shared_tau;          // [B][K+1] running bests shared by a row's workgroups, preset to
-                            // the ordered image of +inf; nullptr when a row is one workgroup
   Partials out;
   llc_stats *stats;
   FinalizeParams fin;       // used if finish is set
@@ -186,7 +184,6 @@ struct StrongStepParams {
   const int32_t *part_idx;   // [S][K][n_chunks]
   const double *part_sec;    // [S][K][n_chunks] runner-up keys of the same partial reductions
   int n_chunks;
-  int32_t *tau_all;          // [L][S][K+1] the later positions' shared running bests: reset at j == 0
   const int32_t *tokens;
   long long tok_stride_s, tok_stride_j;
   long long stride_k;        // of the target tensor, for the next position's row offsets
@@ -265,7 +262,6 @@ hipError_t launch_finalize(hipStream_t s, const FinalizeParams &p);
 hipError_t launch_lse(hipStream_t s, const LseParams &p);
 hipError_t launch_verify(hipStream_t s, const VerifyParams &p);
 hipError_t launch_strong_step(hipStream_t s, const StrongStepParams &p);
-hipError_t launch_fill(hipStream_t s, int32_t *dst, long long n, int32_t value);
 hipError_t launch_topm(hipStream_t s, const TopmParams &p);
 hipError_t launch_lml(hipStream_t s, const LmlParams &p);
 

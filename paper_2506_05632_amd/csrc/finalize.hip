@@ -307,11 +307,6 @@ __global__ void __launch_bounds__(64) strong_step_kernel(const StrongStepParams 
   float *keyY = p.keyY != nullptr ? p.keyY + s * (L + 1) : nullptr;
   bool viable = lane < K;
   bool running = true;
-  if (j == 0 && p.tau_all != nullptr) {
-    // the scans of the later positions find their rows' running bests reset
-    for (int t = lane; t < L * (K + 1); t += 64)
-      p.tau_all[((long long)(t / (K + 1)) * p.S + s) * (K + 1) + t % (K + 1)] = 0x7F800000;
-  }
   if (j > 0) {
     viable = lane < K && p.viable[s * K + lane] != 0;
     running = p.running[s] != 0;
@@ -393,18 +388,7 @@ __global__ void __launch_bounds__(64) strong_step_kernel(const StrongStepParams 
   if (!more && p.active != nullptr && lane < K) p.active[s * K + lane] = viable ? 1 : 0;
 }
 
-__global__ void __launch_bounds__(256) fill_kernel(int32_t *dst, long long n, int32_t value) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) dst[i] = value;
-}
-
 }  // namespace
-
-hipError_t launch_fill(hipStream_t s, int32_t *dst, long long n, int32_t value) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, n, value);
-  return hipGetLastError();
-}
 
 hipError_t launch_verify(hipStream_t s, const VerifyParams &p) {
   if (p.S == 0) return hipSuccess;

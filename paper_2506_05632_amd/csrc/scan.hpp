@@ -388,8 +388,6 @@ struct Lds {
   float lse_wmax[kMaxWaves][9];  // LSE: per-wave references (whole numbers, in powers of two) ...
   double lse_wave[kMaxWaves][9]; // ... and per-wave sums relative to them, merged in a fixed order
   double share[9];       // LSE: ln sum exp(x/T) of this chunk, per slot
-  int *shared_tau;       // the row's running bests shared by all its workgroups (or null)
-  int shared_base, shared_pool;  // where this workgroup's draft 0 and the pool sit in it
   double rec_key[kListCap];  // the approximate key (an fp32 value) until level 3 puts the exact one in its place
   int rec_i[kListCap];
   int rec_tag[kListCap];
@@ -428,14 +426,13 @@ __device__ __forceinline__ uint32_t threshold_of(float F) {
 __device__ __forceinline__ uint32_t packed_hi16(float F0, float F1) {
   return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pknorm_u16(__int_as_float((int)F0), __int_as_float((int)F1)));
 }
-// Lower tau[slot] to `a` and refresh the level-1 offset that depends on it.  When the row is
-// spread over several workgroups the new best is also posted to the row's shared array, from
-// which the others pick it up (a bound found in one chunk prunes all of them).
+// Lower tau[slot] to `a` and refresh the level-1 offset that depends on it.  A row's workgroups keep
+// their bounds to themselves: posting them to an array in memory that the others poll pruned more, but
+// cost a launch that presets the array, a round trip in every warm-up and registers in the main loop
+// (512 x 16 distinct drafts x 152 064, bf16: 494 us with it, 468 without; 300 x 8 x 50 000: 125, 112).
 template <int KT, bool SHARED, bool PROBS, bool MINF>
-__device__ __forceinline__ void publish(Lds &s, int slot, float a, bool post = true) {
+__device__ __forceinline__ void publish(Lds &s, int slot, float a) {
   atomicMin(&s.tau[slot], ord32(a));
-  if (post && s.shared_tau != nullptr)
-    atomicMin(&s.shared_tau[slot < KT ? s.shared_base + slot : s.shared_pool], ord32(a));
   if (!(fabsf(a) <= kTauLimit)) s.unsafe = 1;
   if (SHARED && slot < KT) {
     int m = s.tau[0];
@@ -719,9 +716,6 @@ scan_kernel(const ScanParams p) {
     for (int kk = 0; kk < KT; ++kk) { s.cd23[kk] = cd23[kk]; s.kok[kk] = kok[kk] ? 1 : 0; }
     s.lgK = lgK;
     s.count = 0; s.unsafe = p.force_exact ? 1 : 0; s.n_survivors = 0; s.n_exact = 0;
-    s.shared_tau = p.shared_tau != nullptr ? p.shared_tau + b * (p.K + 1) : nullptr;
-    s.shared_base = kbase;
-    s.shared_pool = p.K;
     s.lse_redo = 0;
   }
   __syncthreads();
@@ -798,14 +792,6 @@ scan_kernel(const ScanParams p) {
       __syncthreads();
       if (tid <= KT) {
         const bool used = tid == KT ? with_pool : (kbase + tid < p.K);
-        if (used && p.shared_tau != nullptr) {
-          // post this chunk's first bound and take what the row's other workgroups have posted
-          int *slot = p.shared_tau + b * (p.K + 1) + (tid < KT ? kbase + tid : p.K);
-          const int mine = s.tau[tid];
-          const int theirs = mine < 0x7F800000 ? atomicMin(slot, mine)
-                                               : __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (theirs < mine) s.tau[tid] = theirs;
-        }
         const float tau = unord32(s.tau[tid]);
         if (used && tau < __builtin_huge_valf() && !(fabsf(tau) <= kTauLimit)) s.unsafe = 1;
       }
@@ -836,7 +822,7 @@ scan_kernel(const ScanParams p) {
 #pragma unroll
       for (int kk = 0; kk < KD; ++kk)
         drow[kk] = drow0 + (SHARED ? 0 : (long long)min(kbase + kk, p.K - 1) * p.draft_stride_k);
-      // One tile (kBlock groups).  The next tile's loads are issued before this tile's Philox
+      // One tile (one group per thread).  The next tile's loads are issued before this tile's Philox
       // chains, thresholds and compares, so they have a whole tile of arithmetic to arrive.
       // Without a pool the target-side exponent is pinned at 0 (threshold 0: never a hit).
       using raw = typename T::raw;
@@ -1206,14 +1192,6 @@ scan_kernel(const ScanParams p) {
         uint32_t ab = 0, bb = 0;
         const int g0 = g_begin + tid;
         load_tile(g0, true, aq, ad, ab);
-        // lanes 0..KT of the first wave follow the row's shared bounds: read every fourth
-        // iteration, merged four iterations later (the load never has to be waited for)
-        const bool follows = p.shared_tau != nullptr && tid <= KT &&
-                             (tid == KT ? with_pool : (kbase + tid < p.K));
-        // (the slot is kept as an index: the row's base is wave-uniform)
-        const int *row_tau = p.shared_tau != nullptr ? p.shared_tau + b * (p.K + 1) : nullptr;
-        const int follow_idx = tid < KT ? kbase + tid : p.K;
-        int seen = 0x7F800000;
         int prio_step = -1;
         for (; it < n_interior; ++it) {
           // A SIMD serves its wavefronts oldest first, so the workgroups of a CU drift apart and the
@@ -1232,11 +1210,6 @@ scan_kernel(const ScanParams p) {
                 default: __builtin_amdgcn_s_setprio(0); break;
               }
             }
-          }
-          if (follows && (it & 3) == 0) {
-            if (seen < __atomic_load_n(&s.tau[tid], __ATOMIC_RELAXED))
-              publish<KT, SHARED, PROBS, MINF>(s, tid, unord32(seen), false);
-            seen = __hip_atomic_load(row_tau + follow_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
           load_tile(g0 + min(it + 1, n_interior - 1) * nt, true, bq, bd, bb);
           process_tile(g0 + it * nt, aq, ad, ab);

@@ -44,8 +44,8 @@ extern "C" int llc_couple_static(const llc_couple_args *a) {
   void *ptr = nullptr;
   rc = static_scratch(&ptr);
   if (rc != LLC_OK) return rc;
-  // every cell of the partial results that is read is written by this call's scan first, and
-  // the shared running bests are preset by a fill kernel: nothing of an earlier call is seen
+  // every cell of the partial results that is read is written by this call's scan first:
+  // nothing of an earlier call is seen
   return couple_on(a, ptr, LLC_STATIC_SCRATCH_BYTES);
 }
 
