@@ -615,7 +615,7 @@ int llc_lml_bound(const llc_lml_args *a) {
   p.temp_draft = logits ? a->temp_draft : 1.0f;
   p.temp_target = logits ? a->temp_target : 1.0f;
   p.n_k = a->n_k;
-  for (int n = 0; n < LLC_LML_MAX_K; ++n) p.k[n] = n < a->n_k ? a->k[n] : 1;
+  for (int n = 0; n < LLC_LML_MAX_K; ++n) { p.k[n] = n < a->n_k ? a->k[n] : 1; p.kd[n] = (double)p.k[n]; }
   p.bound = a->bound; p.relaxed = a->relaxed; p.tv = a->tv;
   p.work = (char *)a->workspace;
   {

@@ -235,12 +235,14 @@ struct LmlParams {
   float temp_draft, temp_target;  // 1 for log-weights and probabilities
   int n_k;
   int k[kLmlMaxK];  // list sizes
+  double kd[kLmlMaxK];
   double *bound;    // [B][n_k]
   double *relaxed;  // [B][n_k] or nullptr
   double *tv;       // [B] or nullptr
   char *work;       // workspace: per slot two buffers of V sort keys, then two of V (p-mass, q-mass) pairs
   int slots;        // rows the workspace holds at a time (= rows per launch; a call is ceil(B / slots) launches)
   long long row0;   // first row of this launch (set by the launcher)
+  int only_flagged; // the sorting kernel takes only the rows that the bucket kernel left (launcher)
 };
 
 // One launcher per (element type, draft layout); defined in scan_*.hip.

@@ -7,11 +7,21 @@
 //   sum_j K / sum_i ( max{q_i/q_j, p_i/p_j} + (K - 1) q_i/q_j ).
 // max{q_i/q_j, p_i/p_j} is q_i/q_j exactly when q_i/p_i >= q_j/p_j, so with the indices sorted by
 // r = q/p the inner sum is (the q-mass from j on)/q_j + (the p-mass before j)/p_j + (K-1) Q/q_j:
-// one sort and one running sum per row.  One workgroup does a whole row: normalisers, sort keys,
-// four passes of a stable 8-bit radix sort on the fp32 image of ln r, in which the two masses of
-// an entry (rounded to fp32) travel with its key through two buffers in the workspace, and the
-// running sums in fp64.  Indices whose r agree to fp32 precision may come out in either order,
-// which together with the rounding of the masses moves a result by a relative 2^-22 at most.
+// an order by r and running sums per row.  One workgroup does a whole row.  Two forms:
+//
+//  by buckets (rows of about 10^4 to 2 10^5 entries): no entry is moved more than once.  A sample of the row
+//  gives splitters of ln r, a first pass counts the entries of every bucket between them, a second
+//  forms the normalisers, a third writes every entry's two masses (rounded to fp32) into its bucket's
+//  part of the workspace; then groups of up to 4096 entries are ordered in LDS (a counting sort on a
+//  linear map of ln r inside every bucket, entries of one cell compared one by one) and walked with
+//  running sums in fp64.  Entries that share a quantum of 2^-22 in ln r may form a bucket of any size,
+//  which needs no order.
+//  by sorting (other rows, and a row in which a bucket came out larger than a group): four passes of a
+//  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses travel with their key
+//  through two buffers in the workspace.
+//
+// Indices whose r agree to 2^-22 may come out in either order, which together with the rounding of the
+// masses moves a result by a relative 2^-22 at most.
 // Entries without mass on one side follow the limits: p_j = 0 or q_j = 0 gives term j = 0; as a
 // summand i such an entry still counts with the mass it has on the other side.
 #include "common.hpp"
@@ -35,27 +45,27 @@ __device__ __forceinline__ float elem<uint16_t>(const uint16_t *row, int i) {
   return __uint_as_float((uint32_t)row[i] << 16);
 }
 
-// Sum / maximum over the workgroup; every thread gets the result.  `scratch` holds kWaves doubles.
+// Sum / maximum over the workgroup; every thread gets the result.  `scratch` holds a double per wavefront.
 __device__ double block_sum(double v, double *scratch) {
+  const int waves = blockDim.x >> 6;
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
   __syncthreads();  // scratch may still be read from the previous reduction
   if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = 0.0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) r += scratch[w];  // a fixed order
+  for (int w = 0; w < waves; ++w) r += scratch[w];  // a fixed order
   return r;
 }
 __device__ double block_max(double v, double *scratch) {
+  const int waves = blockDim.x >> 6;
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v = fmax(v, __shfl_xor(v, d));
   __syncthreads();
   if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = scratch[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) r = fmax(r, scratch[w]);
+  for (int w = 1; w < waves; ++w) r = fmax(r, scratch[w]);
   return r;
 }
 
@@ -100,6 +110,10 @@ __device__ Side normalise(const E *row, int V, int probs, float temp, double *sc
   return s;
 }
 
+// Where the bucket kernel tells the sorting one, launched behind it, that it left a row: behind the
+// masses in the row's part of the workspace.
+__device__ __forceinline__ int *flag_of(char *work, int V) { return reinterpret_cast<int *>(work + 16u * (size_t)V); }
+
 // order-preserving image of a float in the unsigned integers
 __device__ __forceinline__ uint32_t sort_key(float f) {
   const uint32_t u = __float_as_uint(f);
@@ -107,7 +121,7 @@ __device__ __forceinline__ uint32_t sort_key(float f) {
 }
 
 template <typename E>
-__global__ void __launch_bounds__(kThreads) lml_kernel(const LmlParams p) {
+__global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
   __shared__ double s_red[kWaves];
   __shared__ unsigned short s_cnt[kWaves][256];  // per wavefront and digit of a tile: counts, then starts
   __shared__ int s_goff[256];          // where a digit's run continues in the output
@@ -130,6 +144,7 @@ __global__ void __launch_bounds__(kThreads) lml_kernel(const LmlParams p) {
   // (p-mass, q-mass) each); the launches of one call follow each other on the stream, so the
   // workspace is as large as the workgroups that can be resident need, not as the batch.
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
+  if (p.only_flagged && *flag_of(work, V) == 0) return;  // (uniform) the other kernel has done the row
   uint32_t *key_a = reinterpret_cast<uint32_t *>(work), *key_b = key_a + V;
   float2 *mass_a = reinterpret_cast<float2 *>(work + 8u * (size_t)V), *mass_b = mass_a + V;
 
@@ -371,17 +386,671 @@ __global__ void __launch_bounds__(kThreads) lml_kernel(const LmlParams p) {
     }
 }
 
+// ---- the form by buckets
+
+// The rows it takes.  Shorter ones are quicker sorted (fewer fixed steps), from about 40 000 entries on if the
+// inputs are bf16, whose many ties cost the ordering in LDS (us a call, buckets against sorting: fp32 8 192
+// entries, 1 row 114 : 102, 16 384: 171 : 184, 32 000: 281 : 346; bf16 32 000, 64 rows 401 : 386, 128 256: 1252 :
+// 1556; 1024 rows x 128 256: fp32 3245 : 7517, bf16 3700 : 5750).  Beyond the upper end a bucket's share of the
+// row nears a group's size.
+constexpr int kBucketMinV = 12288, kBucketMinVNarrow = 40960, kBucketMaxV = 1 << 18;
+constexpr int kSamples = 2048;
+constexpr int kGroup = 4096;          // entries of a tile, and of a group that is ordered in LDS
+constexpr int kR = kGroup / kThreads; // what a thread holds of it
+constexpr int kMaxBuckets = 255;
+constexpr int kNoBucket = 255;        // of an entry that lacks mass on a side
+constexpr double kQuantum = 0x1p-22;  // a step of the places in ln r
+constexpr int kFar = 2147480000;      // places end here: 511 in ln r from the row's centre
+
+__device__ __forceinline__ float4 widen(const float4 &r) { return r; }
+__device__ __forceinline__ float4 widen(const uint2 &r) {
+  return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y << 16),
+                     __uint_as_float(r.y & 0xFFFF0000u));
+}
+// Entries i..i+3 of a row; `fill` (which carries no mass) stands for those past the end.
+template <typename E>
+__device__ __forceinline__ float4 four(const E *row, int i, int V, float fill) {
+  if (i + 3 < V) return widen(load_four(row + i));
+  return make_float4(i < V ? elem<E>(row, i) : fill, i + 1 < V ? elem<E>(row, i + 1) : fill,
+                     i + 2 < V ? elem<E>(row, i + 2) : fill, fill);
+}
+__device__ __forceinline__ float at(const float4 &v, int j) { return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w; }
+
+// Exclusive prefix sum over the workgroup; *total gets the sum.  `scratch` holds an element per wavefront.
+template <typename N>
+__device__ __forceinline__ N block_prefix(N v, N *scratch, N *total) {
+  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  N incl = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const N up = __shfl_up(incl, d);
+    if (lane >= d) incl += up;
+  }
+  __syncthreads();  // scratch may still be read from the previous call
+  if (lane == 63) scratch[threadIdx.x >> 6] = incl;
+  __syncthreads();
+  N before = N(0), sum = N(0);
+  for (int w = 0; w < waves; ++w) {
+    if (w == (int)(threadIdx.x >> 6)) before = sum;
+    sum += scratch[w];
+  }
+  *total = sum;
+  return before + incl - v;
+}
+
+// The same for two sums at once, in place.
+__device__ __forceinline__ void block_prefix2(double &a, double &b, double *scratch_a, double *scratch_b, double *total_a,
+                                              double *total_b) {
+  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  double ia = a, ib = b;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double ua = __shfl_up(ia, d), ub = __shfl_up(ib, d);
+    if (lane >= d) { ia += ua; ib += ub; }
+  }
+  __syncthreads();
+  if (lane == 63) { scratch_a[threadIdx.x >> 6] = ia; scratch_b[threadIdx.x >> 6] = ib; }
+  __syncthreads();
+  double before_a = 0.0, before_b = 0.0, sum_a = 0.0, sum_b = 0.0;
+  for (int w = 0; w < waves; ++w) {
+    if (w == (int)(threadIdx.x >> 6)) { before_a = sum_a; before_b = sum_b; }
+    sum_a += scratch_a[w];
+    sum_b += scratch_b[w];
+  }
+  *total_a = sum_a;
+  *total_b = sum_b;
+  a = before_a + ia - a;
+  b = before_b + ib - b;
+}
+
+// The place of an entry in the order, as a whole number of quanta of ln r = ln(q/p) relative to a
+// value of the row (the normalisers move all entries alike and are left out, so that the places are
+// known before they are).  Evaluated twice per entry, by the same instructions.
+template <bool PROBS>
+struct Placer {
+  double itp, itq, center;
+  __device__ __forceinline__ bool mass(float x) const {
+    return x < __builtin_huge_valf() && (PROBS ? x > 0.0f : x > -__builtin_huge_valf());
+  }
+  __device__ __forceinline__ double log_ratio(float xp, float xq) const {
+    if (PROBS) return 0.6931471805599453 * ((double)log2f(xq) - (double)log2f(xp));
+    return __builtin_fma((double)xq, itq, -((double)xp * itp));
+  }
+  __device__ __forceinline__ int quanta(double lr) const {
+    return (int)__builtin_rint(fmin(fmax((lr - center) * (1.0 / kQuantum), (double)-kFar), (double)kFar));
+  }
+};
+
+// The last bucket whose splitter is not above `place` (split[0] stands for minus infinity).
+__device__ __forceinline__ int bucket_of(const int *split, int nb, int place) {
+  int b = 0;
+#pragma unroll
+  for (int step = 128; step >= 1; step >>= 1)
+    if (b + step < nb && split[b + step] <= place) b += step;
+  return b;
+}
+
+// 1 / x to about an ulp, for normal x: the hardware's estimate and two Newton steps (the general fp64
+// division's scaling and fix-up instructions are what an entry's time went to).
+__device__ __forceinline__ double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// e^x for x <= 0 or so (what is below -800 comes out as 0) to about an ulp: x = n ln 2 + f, the Taylor
+// series of e^f to its 13th term (|f| <= ln(2) / 2: the next one is below 2^-57), times 2^n.  No branch,
+// so that an entry's two exponentials run side by side.
+__device__ __forceinline__ double exp_of_negative(double x) {
+  x = fmax(x, -800.0);
+  const double n = __builtin_rint(x * 1.4426950408889634);
+  double f = fma(n, -0x1.62e42fefa39efp-1, x);  // ln 2 to 53 bits ...
+  f = fma(n, -0x1.abc9e3b39803fp-56, f);        // ... and the next 53
+  double s = 1.0 / 6227020800.0;
+  s = fma(s, f, 1.0 / 479001600.0);
+  s = fma(s, f, 1.0 / 39916800.0);
+  s = fma(s, f, 1.0 / 3628800.0);
+  s = fma(s, f, 1.0 / 362880.0);
+  s = fma(s, f, 1.0 / 40320.0);
+  s = fma(s, f, 1.0 / 5040.0);
+  s = fma(s, f, 1.0 / 720.0);
+  s = fma(s, f, 1.0 / 120.0);
+  s = fma(s, f, 1.0 / 24.0);
+  s = fma(s, f, 1.0 / 6.0);
+  s = fma(s, f, 0.5);
+  s = fma(s, f, 1.0);
+  s = fma(s, f, 1.0);
+  return __builtin_amdgcn_ldexp(s, (int)n);
+}
+
+// acc[n] += k[n] pq / (base + (k[n] - off) slope): two quotients per reciprocal (the denominators are
+// not so small that their product would vanish).  List sizes beyond n_k are 1.
+template <int PAIRS>
+__device__ __forceinline__ void add_quotients(double (&acc)[2 * PAIRS], const LmlParams &p, double pq, double base,
+                                              double off, double slope) {
+#pragma unroll
+  for (int n = 0; n < 2 * PAIRS; n += 2) {
+    const double k0 = p.kd[n], d0 = fma(k0 - off, slope, base);
+    const double k1 = p.kd[n + 1], d1 = fma(k1 - off, slope, base);
+    const double t = pq * reciprocal(d0 * d1);
+    acc[n] = fma(k0 * t, d1, acc[n]);
+    acc[n + 1] = fma(k1 * t, d0, acc[n + 1]);
+  }
+}
+
+// Place and number of a group's entry as one key.
+__device__ __forceinline__ unsigned long long key_of(int place, int number) {
+  return ((unsigned long long)((uint32_t)place ^ 0x80000000u) << 32) | (uint32_t)number;
+}
+
+// LDS index of entry j where threads read kR neighbouring entries each (spreads them over the banks).
+__device__ __forceinline__ int padded(int j) { return j + j / kR; }
+
+// One workgroup per row, two per CU.  What bounds it: instruction issue and the latency of LDS between
+// barriers, not memory: the row is read three times and a place byte and the masses are written and read
+// once (42 bytes an entry of 8 input bytes, where the sorting form moves 160).  Of the 1.6 ms that two rows of
+// 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
+// third pass 0.4 (positions 0.22, masses 0.16), the groups 0.8 (cells and their starts 0.45, the order inside
+// cells 0.17, running sums 0.15, terms 0.05).  An order by the exact ratio, general divisions and a branch
+// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.25.
+// All sums run in an order that does not depend on how the wavefronts interleave: entries keep the row's
+// order within a bucket, and within a group they are ordered by their places, then as they lie in the bucket.
+// PAIRS: room for that many pairs of list sizes.
+template <typename E, bool PROBS, int PAIRS>
+__global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams p) {
+  __shared__ double s_red[kWaves], s_red2[kWaves];
+  __shared__ int s_redi[kWaves];
+  __shared__ int s_split[kMaxBuckets + 1];  // bucket b holds the places from s_split[b] up to s_split[b + 1]
+  __shared__ int s_off[kMaxBuckets + 2];    // where bucket b starts in the workspace
+  __shared__ int s_next[kMaxBuckets + 1];   // how far it has been written; before that its count
+  __shared__ int s_start[kMaxBuckets + 1];  // where a bucket's entries start inside the tile at hand
+  __shared__ float s_scale[kMaxBuckets];    // cells per quantum of a bucket
+  __shared__ float2 s_mass[kGroup + kThreads];
+  __shared__ int s_cell[kGroup + kThreads + 1];  // groups: entries of a cell, then where the cell starts
+  __shared__ int s_info[2];
+  // the cells' room also serves the sample, and the third pass: an entry's bucket in the tile's order, and
+  // per wavefront and bucket the entries of the tile
+  int *s_sample = s_cell;
+  unsigned long long *s_key = reinterpret_cast<unsigned long long *>(s_mass);  // groups: the entries' keys
+  unsigned char *s_tag = reinterpret_cast<unsigned char *>(s_cell);
+  unsigned short(*s_cnt)[kMaxBuckets + 1] = reinterpret_cast<unsigned short(*)[kMaxBuckets + 1]>(s_cell + kGroup / 4);
+  static_assert(kSamples <= kGroup && kGroup + kWaves * (kMaxBuckets + 1) * 2 <= (int)sizeof(s_cell), "sizes");
+
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const long long b_row = p.row0 + blockIdx.x;
+  const int V = p.V;
+  const E *prow = reinterpret_cast<const E *>(p.draft) + b_row * p.draft_stride_b;
+  const E *qrow = reinterpret_cast<const E *>(p.target) + b_row * p.target_stride_b;
+  char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
+  float2 *bucketed = reinterpret_cast<float2 *>(work);
+  unsigned char *ids = reinterpret_cast<unsigned char *>(work + 8u * (size_t)V);
+  const float none = PROBS ? 0.0f : -__builtin_huge_valf();
+  const float ninf = -__builtin_huge_valf();
+
+  Placer<PROBS> pl;
+  pl.itp = 1.0 / (double)p.temp_draft;
+  pl.itq = 1.0 / (double)p.temp_target;
+
+  // ---- splitters: every bucket gets about V / 126 entries, at least 1024, by the sample's quantiles, and
+  // places that the sample holds several times get a bucket of their own quantum (inputs of few bits have
+  // many ties)
+  // (a row that is a single group needs none)
+  int nb = 1, n_valid;
+  {
+    auto sample = [&](const int j, float &xp, float &xq) {
+      const unsigned jitter = (unsigned)j * 0x9E3779B9u;
+      const int i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kSamples);
+      xp = elem<E>(prow, i);
+      xq = elem<E>(qrow, i);
+      return pl.mass(xp) && pl.mass(xq);
+    };
+    // the centre: a median of 64 of them (every wavefront finds the same one)
+    float xp, xq;
+    {
+      const bool ok = sample(lane * (kSamples / 64), xp, xq);
+      const double lr = ok ? pl.log_ratio(xp, xq) : __builtin_huge_val();
+      int rank = 0;
+      for (int l = 0; l < 64; ++l) {
+        const double o = __shfl(lr, l);
+        rank += (o < lr || (o == lr && l < lane)) ? 1 : 0;
+      }
+      const int n_ok = __popcll(__ballot(ok));
+      const unsigned long long at_rank = __ballot(rank == n_ok / 2);
+      pl.center = n_ok > 0 ? __shfl(lr, __ffsll((long long)at_rank) - 1) : 0.0;
+      if (!(fabs(pl.center) < __builtin_huge_val())) pl.center = 0.0;
+    }
+    if (V > kGroup) {  // uniform
+    int valid = 0;
+    for (int j = tid; j < kSamples; j += kThreads) {
+      const bool ok = sample(j, xp, xq);
+      s_sample[j] = ok ? pl.quanta(pl.log_ratio(xp, xq)) : 0x7FFFFFFF;
+      valid += ok ? 1 : 0;
+    }
+    block_prefix(valid, s_redi, &n_valid);
+    for (int size = 2; size <= kSamples; size <<= 1)
+      for (int stride = size >> 1; stride >= 1; stride >>= 1) {
+        __syncthreads();
+        for (int t = tid; t < kSamples / 2; t += kThreads) {
+          const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;
+          const int x = s_sample[lo], y = s_sample[hi];
+          if ((x > y) == ((lo & size) == 0)) { s_sample[lo] = y; s_sample[hi] = x; }
+        }
+      }
+    __syncthreads();
+    if (n_valid > 0) {  // uniform
+      const int entries = (int)((long long)V * n_valid / kSamples);
+      const int want = max(1, min(kMaxBuckets / 2, (entries + 1023) / 1024));
+      // a run of `many` equal places or more in the sample is two splitters (its quantum is a bucket), any
+      // other place one, if a quantile falls on it; `many` is the least that keeps to the buckets there are
+      // (with 32 there are at most want of either kind)
+      constexpr int kPer = kSamples / kThreads;
+      int emit[kPer], total, before = 0;
+#pragma unroll 1
+      for (int many = 4; many <= 32; many *= 2) {
+        int mine = 0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+          const int j = tid * kPer + e, v = s_sample[j];
+          emit[e] = 0;
+          if (j < n_valid && (j == 0 || s_sample[j - 1] != v)) {
+            if (j + many - 1 < n_valid && s_sample[j + many - 1] == v) emit[e] = 2;
+            else if (j > 0 && (long long)j * want / n_valid != (long long)(j - 1) * want / n_valid) emit[e] = 1;
+          }
+          mine += emit[e];
+        }
+        before = block_prefix(mine, s_redi, &total);
+        if (total < kMaxBuckets) break;  // uniform
+      }
+      nb = 1 + min(total, kMaxBuckets - 1);
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int v = s_sample[tid * kPer + e];
+        for (int c = 0; c < emit[e]; ++c, ++before)
+          if (1 + before < nb) s_split[1 + before] = v + c;
+      }
+    }
+    }
+  }
+  for (int j = tid; j <= kMaxBuckets; j += kThreads) s_next[j] = 0;
+  if (tid == 0) { s_split[0] = (int)0x80000000; s_info[0] = 0; }
+  __syncthreads();
+  // (not so at the ends of the places, where everything farther away gathers)
+  auto of_one_quantum = [&](const int b) {
+    return b >= 1 && b + 1 < nb && s_split[b + 1] - s_split[b] <= 1 && abs(s_split[b]) < kFar - 1;
+  };
+
+  // ---- first pass: the rows' largest entries, and every entry's bucket and the buckets' counts
+  float mp = ninf, mq = ninf;
+  int left_most = kFar, right_most = -kFar;
+  for (int i = tid * 4; i < V; i += kThreads * 4) {
+    const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+    uint32_t packed = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float xp = at(xp4, j), xq = at(xq4, j);
+      const bool hp = pl.mass(xp), hq = pl.mass(xq);
+      if (hp) mp = fmaxf(mp, xp);
+      if (hq) mq = fmaxf(mq, xq);
+      int b = kNoBucket;
+      if (hp && hq) {
+        const int place = pl.quanta(pl.log_ratio(xp, xq));
+        left_most = min(left_most, place);
+        right_most = max(right_most, place);
+        b = nb > 1 ? bucket_of(s_split, nb, place) : 0;
+        atomicAdd(&s_next[b], 1);
+      }
+      packed |= (uint32_t)b << (8 * j);
+    }
+    if (i + 3 < V) {
+      *reinterpret_cast<uint32_t *>(ids + i) = packed;
+    } else {
+      for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned char)(packed >> (8 * j));
+    }
+  }
+  Side sp, sq;
+  sp.probs = sq.probs = PROBS ? 1 : 0;
+  sp.inv_t = pl.itp;
+  sq.inv_t = pl.itq;
+  // the outer buckets' outer ends: those of the row, or two e-folds from the nearest splitter (an outlier
+  // must not stretch a bucket so far that its other entries share a cell)
+  int left_edge = -(int)block_max(-(double)left_most, s_red), right_edge = (int)block_max((double)right_most, s_red);
+  if (nb > 1) {
+    left_edge = max(left_edge, max(s_split[1], (1 << 24) - kFar) - (1 << 23));
+    right_edge = min(right_edge, min(s_split[nb - 1], kFar - (1 << 24)) + (1 << 23));
+  }
+  sp.m = PROBS ? 0.0 : block_max((double)mp, s_red);
+  sq.m = PROBS ? 0.0 : block_max((double)mq, s_red);
+  __syncthreads();
+  {
+    const int mine = tid < nb ? s_next[tid] : 0;
+    int total;
+    const int off = block_prefix(mine, s_redi, &total);
+    if (tid < nb) {
+      s_off[tid] = off;
+      s_next[tid] = off;
+      if (mine > kGroup && !of_one_quantum(tid)) s_info[0] = 1;
+      // (the outer buckets have no outer splitter: the sample's end stands for it)
+      const double left = (double)(tid > 0 ? s_split[tid] : left_edge);
+      const double right = (double)(tid + 1 < nb ? s_split[tid + 1] : right_edge);
+      s_scale[tid] = right > left ? (float)((double)mine / (right - left)) : 0.0f;
+    }
+    if (tid == 0) s_off[nb] = total;
+  }
+  __syncthreads();
+  const bool leave = s_info[0] != 0;
+  if (tid == 0) *flag_of(work, V) = leave ? 1 : 0;
+  if (leave) return;  // (uniform) a bucket larger than a group: the row is the sorting kernel's
+
+  // ---- second pass: the normalisers
+  {
+    double zp = 0.0, zq = 0.0;
+    for (int i = tid * 4; i < V; i += kThreads * 4) {
+      const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float xp = at(xp4, j), xq = at(xq4, j);
+        if (PROBS) {
+          zp += pl.mass(xp) ? (double)xp : 0.0;
+          zq += pl.mass(xq) ? (double)xq : 0.0;
+        } else {
+          zp += exp_of_negative(pl.mass(xp) ? ((double)xp - sp.m) * sp.inv_t : -__builtin_huge_val());
+          zq += exp_of_negative(pl.mass(xq) ? ((double)xq - sq.m) * sq.inv_t : -__builtin_huge_val());
+        }
+      }
+    }
+    sp.ln_z = log(block_sum(zp, s_red));
+    sq.ln_z = log(block_sum(zq, s_red));
+  }
+
+  // ---- third pass: every tile is laid out by bucket in LDS (its entries' positions follow from the bucket
+  // bytes alone), and taken from there: masses, the sums that need no order, and the masses to their
+  // bucket, neighbouring threads to neighbouring addresses
+  double tv = 0.0, p_first = 0.0, q_total = 0.0, sums[2 * PAIRS];
+#pragma unroll
+  for (int n = 0; n < 2 * PAIRS; ++n) sums[n] = 0.0;
+#pragma unroll 1
+  for (int t0 = 0; t0 < V; t0 += kGroup) {
+    const int n_tile = min(kGroup, V - t0);
+    const int base = t0 + wv * (64 * kR) + lane;  // wavefront w holds the w-th part of the tile
+    float2 x[kR];
+    int id[kR], where[kR];
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      const int i = base + e * 64;
+      id[e] = i < V ? (int)ids[i] : -1;
+      x[e] = i < V ? make_float2(elem<E>(prow, i), elem<E>(qrow, i)) : make_float2(0.0f, 0.0f);
+    }
+    __syncthreads();  // the tile before is done with
+    for (int j = tid; j < kWaves * (kMaxBuckets + 1) / 2; j += kThreads) reinterpret_cast<int *>(&s_cnt[0][0])[j] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      // lanes of this round with the same bucket: bit by bit, keep those whose bit is like mine
+      const unsigned long long live = __ballot(id[e] >= 0);
+      uint32_t peers_lo = (uint32_t)live, peers_hi = (uint32_t)(live >> 32);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe(id[e], bit, 1);  // all ones if the bit is set
+        const unsigned long long have = __ballot(mine != 0u);
+        peers_lo &= ~((uint32_t)have ^ mine);
+        peers_hi &= ~((uint32_t)(have >> 32) ^ mine);
+      }
+      where[e] = 0;
+      if (id[e] >= 0) {
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
+        const int seen = s_cnt[wv][id[e]];
+        if (rank == 0) s_cnt[wv][id[e]] = (unsigned short)(seen + __popc(peers_lo) + __popc(peers_hi));
+        where[e] = seen + rank;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    {
+      int mine = 0, all;
+      if (tid <= kMaxBuckets) {
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+          const int c = s_cnt[w][tid];
+          s_cnt[w][tid] = (unsigned short)mine;
+          mine += c;
+        }
+      }
+      const int start = block_prefix(mine, s_redi, &all);
+      if (tid <= kMaxBuckets) s_start[tid] = start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kR; ++e)
+      if (id[e] >= 0) {
+        const int pos = s_start[id[e]] + s_cnt[wv][id[e]] + where[e];
+        s_mass[pos] = x[e];
+        s_tag[pos] = (unsigned char)id[e];
+      }
+    __syncthreads();
+#pragma unroll 1
+    for (int pos = tid; pos < n_tile; pos += kThreads) {
+      const float2 in = s_mass[pos];
+      const int b = s_tag[pos];
+      const double lp = sp.log_mass(in.x), lq = sq.log_mass(in.y);
+      const bool hp = lp > -__builtin_huge_val(), hq = lq > -__builtin_huge_val();
+      double pm = exp_of_negative(lp), qm = exp_of_negative(lq);  // (-inf: no mass)
+      const float2 m = make_float2((float)pm, (float)qm);
+      tv += fabs(pm - qm);
+      q_total += (double)m.y;
+      if (hp && !hq) p_first += (double)m.x;  // ratio 0: before all others
+      if (b != kNoBucket) {
+        const int g = s_next[b] + (pos - s_start[b]);
+        if (g < s_off[b + 1]) bucketed[g] = m;  // (always; a bucket is never written past its end)
+        if (p.relaxed != nullptr) {             // q / (1 + q / (K p)) = K p q / (K p + q)
+          const bool tiny = pm * qm < 0x1p-900;  // (out of the way of products that vanish)
+          if (tiny) { pm *= 0x1p300; qm *= 0x1p300; }
+          const double pq = pm * qm;
+          if (pq > 0.0) add_quotients<PAIRS>(sums, p, tiny ? pq * 0x1p-300 : pq, qm, 0.0, pm);
+        }
+      }
+    }
+    __syncthreads();
+    if (tid < nb) {
+      int here = (tid < kMaxBuckets ? s_start[tid + 1] : n_tile) - s_start[tid];
+      s_next[tid] += here;
+    }
+  }
+  tv = block_sum(tv, s_red);
+  if (tid == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * tv;
+#pragma unroll
+  for (int n = 0; n < 2 * PAIRS; ++n)
+    if (n < p.n_k) {  // uniform
+      if (p.relaxed != nullptr) {
+        const double r = block_sum(sums[n], s_red);
+        if (tid == 0) p.relaxed[b_row * p.n_k + n] = r;
+      }
+      sums[n] = 0.0;
+    }
+  q_total = block_sum(q_total, s_red);
+
+  // ---- the groups in order, with the masses of what came before
+  double p_before = block_sum(p_first, s_red), q_before = 0.0;
+  // K q / (D(r) + (K - 1) Q) of one entry, D(r) the sum of max(q_i, r p_i) over the row: the q-mass from
+  // the entry on plus r times the p-mass before it (numerator and denominator times p)
+  auto add_term = [&](const float2 m, const double pb, const double qb) {
+    if (!(m.x > 0.0f && m.y > 0.0f)) return;
+    const double pm = (double)m.x, qm = (double)m.y;
+    add_quotients<PAIRS>(sums, p, pm * qm, fma(q_total - qb, pm, pb * qm), 1.0, q_total * pm);
+  };
+  // Placer's log_ratio of an entry from its masses: the normalisers and maxima taken off again
+  const double shift = (PROBS ? 0.0 : sq.m * sq.inv_t - sp.m * sp.inv_t) + (sq.ln_z - sp.ln_z);
+  for (int b0 = 0, b1 = 0; b0 < nb; b0 = b1) {
+    b1 = b0 + 1;
+    const int first = s_off[b0];
+    int n = s_off[b1] - first;
+    const bool tied = n > kGroup;  // (only a bucket of one quantum can be)
+    if (!tied) {
+      while (b1 < nb && s_off[b1 + 1] - first <= kGroup) ++b1;
+      n = s_off[b1] - first;
+    }
+    if (n == 0) continue;  // uniform
+    double pg = 0.0, qg = 0.0;  // the group's masses
+    if (tied) {
+      // one quantum: any order will do, so every entry counts as the first of them
+#pragma unroll 1
+      for (int i = tid; i < n; i += kThreads) {
+        const float2 m = bucketed[first + i];
+        pg += (double)m.x;
+        qg += (double)m.y;
+        add_term(m, p_before, q_before);
+      }
+      p_before += block_sum(pg, s_red);
+      q_before += block_sum(qg, s_red);
+      continue;
+    }
+    // cells: bucket b's entries spread over as many cells as there are, linearly in ln r between its
+    // splitters (so the map is monotone, which is all the order needs; one entry per cell on average)
+    float2 mass[kR];
+    int cell[kR], rank[kR], place[kR], top = 1;
+    while (top * 2 < b1 - b0) top *= 2;
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      const int i = e * kThreads + tid;
+      if (i < n) mass[e] = bucketed[first + i];
+    }
+    __syncthreads();  // the group before is done with
+    for (int c = tid; c < padded(n) + 1; c += kThreads) s_cell[c] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      const int i = e * kThreads + tid;
+      cell[e] = -1;
+      rank[e] = 0;
+      if (i < n) {
+        int b = b0;  // the bucket it lies in
+        for (int step = top; step >= 1; step >>= 1)
+          if (b + step < b1 && s_off[b + step] - first <= i) b += step;
+        const float r = mass[e].y * __builtin_amdgcn_rcpf(mass[e].x);
+        const int low = s_split[b], high = b + 1 < nb ? s_split[b + 1] - 1 : 0x7FFFFFFE;
+        // (from fp32 masses: within its bucket whatever the rounding)
+        place[e] = max(low, min(high, pl.quanta((double)(__log2f(r) * 0.69314718f) + shift)));
+        cell[e] = i;  // in a bucket of one quantum the entries stay as they lie
+        if (high > low || b == 0) {
+          const int lo = s_off[b] - first, cnt = s_off[b + 1] - s_off[b];
+          const float f = (float)((double)place[e] - (double)(b > 0 ? low : left_edge)) * s_scale[b];
+          cell[e] = lo + max(0, min(cnt - 1, (int)f));
+        }
+        rank[e] = atomicAdd(&s_cell[padded(cell[e])], 1);
+      }
+    }
+    __syncthreads();
+    {
+      // where every cell starts; thread t takes cells t kR .. t kR + kR - 1
+      int c[kR], sum = 0, total;
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        const int j = tid * kR + e;
+        c[e] = j < n ? s_cell[padded(j)] : 0;
+        sum += c[e];
+      }
+      int start = block_prefix(sum, s_redi, &total);
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        const int j = tid * kR + e;
+        if (j < n) s_cell[padded(j)] = start;
+        start += c[e];
+      }
+      if (tid == 0) s_cell[padded(n)] = n;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kR; ++e)
+      if (cell[e] >= 0) {
+        rank[e] += s_cell[padded(cell[e])];
+        s_key[rank[e]] = key_of(place[e], e * kThreads + tid);
+      }
+    if (tid < 4) s_key[n + tid] = ~0ull;
+    __syncthreads();
+    // entries of one cell among themselves: by place, then as they lie in the bucket
+    // (the thread's entries side by side, four steps at a time: what lies behind a cell has larger keys and
+    // counts for nothing, so only the longest cell of the wavefront ends the loop)
+    {
+      int longest = 0;
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        const int from = cell[e] >= 0 ? s_cell[padded(cell[e])] : n;
+        const int len = cell[e] >= 0 ? s_cell[padded(cell[e] + 1)] - from : 0;
+        longest = max(longest, len > 1 ? len : 0);
+        cell[e] = from;
+        rank[e] = from;
+      }
+      for (int t = 0; __any(t < longest); t += 4) {
+#pragma unroll
+        for (int e = 0; e < kR; ++e) {
+          const unsigned long long mine = key_of(place[e], e * kThreads + tid);
+          const unsigned long long *there = s_key + min(cell[e] + t, n);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) rank[e] += there[u] < mine ? 1 : 0;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kR; ++e)
+      if (e * kThreads + tid < n) s_mass[padded(rank[e])] = mass[e];
+    __syncthreads();
+    {
+      // running sums over the entries in order; thread t takes entries t kR .. t kR + kR - 1
+      const int mine = tid * kR;
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        mass[e] = mine + e < n ? s_mass[padded(mine + e)] : make_float2(0.0f, 0.0f);
+        pg += (double)mass[e].x;
+        qg += (double)mass[e].y;
+      }
+      double p_sum, q_sum, pb = pg, qb = qg;
+      block_prefix2(pb, qb, s_red, s_red2, &p_sum, &q_sum);
+      pb += p_before;
+      qb += q_before;
+#pragma unroll
+      for (int e = 0; e < kR; ++e) {
+        add_term(mass[e], pb, qb);
+        pb += (double)mass[e].x;
+        qb += (double)mass[e].y;
+        if (e % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (all at once does not fit the registers)
+      }
+      p_before += p_sum;
+      q_before += q_sum;
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 2 * PAIRS; ++n)
+    if (n < p.n_k) {  // uniform
+      const double r = block_sum(sums[n], s_red);
+      if (tid == 0) p.bound[b_row * p.n_k + n] = r;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
   LmlParams p = params;
+  const bool buckets = p.V >= (p.dtype == LLC_F32 ? kBucketMinV : kBucketMinVNarrow) && p.V <= kBucketMaxV;
+  p.only_flagged = buckets ? 1 : 0;
   for (p.row0 = 0; p.row0 < p.B; p.row0 += p.slots) {
     const long long left = p.B - p.row0;
     const unsigned grid = (unsigned)(left < (long long)p.slots ? left : (long long)p.slots);
-    if (p.dtype == LLC_F32)
-      hipLaunchKernelGGL(lml_kernel<float>, dim3(grid), dim3(kThreads), 0, s, p);
-    else
-      hipLaunchKernelGGL(lml_kernel<uint16_t>, dim3(grid), dim3(kThreads), 0, s, p);
+    const bool f32 = p.dtype == LLC_F32;
+    if (buckets) {
+#define LLC_LML(E, PROBS)                                                                                  \
+  if (p.n_k <= 4) hipLaunchKernelGGL((lml_bucket_kernel<E, PROBS, 2>), dim3(grid), dim3(kThreads), 0, s, p); \
+  else hipLaunchKernelGGL((lml_bucket_kernel<E, PROBS, 4>), dim3(grid), dim3(kThreads), 0, s, p);
+      if (f32 && p.probs) { LLC_LML(float, true) }
+      else if (f32) { LLC_LML(float, false) }
+      else if (p.probs) { LLC_LML(uint16_t, true) }
+      else { LLC_LML(uint16_t, false) }
+#undef LLC_LML
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    // (behind the bucket kernel: the rows that it left, as a rule none)
+    if (f32) hipLaunchKernelGGL(lml_sort_kernel<float>, dim3(grid), dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL(lml_sort_kernel<uint16_t>, dim3(grid), dim3(kThreads), 0, s, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -1,0 +1,70 @@
+"""GPU parity of llc_lml_bound on rows long enough for its bucketed form (needs an MI355X).
+
+Same oracle and same bound on the error as in test_gpu_lml.py: indices whose ratios agree to 2^-22 may
+be swapped and the masses are rounded to fp32, everything else is fp64 on both sides; rtol 1e-6."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_05632_amd as llc
+from test_gpu_lml import KS, check
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# (the ends of the range of either type, a tile of 4096 entries and one more, ragged tails)
+@pytest.mark.parametrize("V", [12287, 12288, 12289, 16384, 16385, 40959, 40961, 70003])
+@pytest.mark.parametrize("kind", ["logits", "logw", "probs"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_lengths_kinds_and_types(V, kind, dtype):
+    g = torch.Generator(device=DEV).manual_seed(V)
+    B = 5
+    tq = 2.0 * torch.randn(B, V + 1, generator=g, device=DEV)[:, 1:] + 30.0   # (odd strides, far from zero)
+    td = tq + torch.randn(B, V, generator=g, device=DEV)
+    td[1, V // 2:] = tq[1, V // 2:]          # half a row of equal logits
+    td[2] = tq[2]                            # equal distributions up to the temperatures
+    td[3, : V // 3] = float("-inf")          # no mass on one side, and on both
+    tq[3, V // 4: V // 2] = float("-inf")
+    td[4] = 8.0 * td[4]                      # widely spread ratios
+    if kind == "probs":
+        td, tq = (torch.exp(t.double() - t.double().amax(dim=1, keepdim=True)).float() for t in (td, tq))
+    td, tq = td.to(dtype), tq.to(dtype)
+    temp = 1.0 if V % 2 else 0.9
+    check(td, tq, KS if V % 3 else KS[:2], kind=kind, temp_draft=temp, temp_target=1.0)
+
+
+def _sampled(V):
+    """The positions of the kernel's sample of a row."""
+    j = np.arange(2048, dtype=np.uint64)
+    jitter = (j * np.uint64(0x9E3779B9)) & np.uint64(0xFFFFFFFF)
+    return ((j * np.uint64(V) + ((jitter * np.uint64(V)) >> np.uint64(32))) >> np.uint64(11)).astype(np.int64)
+
+
+def test_a_row_whose_sample_misleads_is_sorted():
+    # everywhere but at the sample's positions the ratios crowd into a few quanta of 2^-22, so one bucket
+    # takes most of the row; the rows beside it are ordinary
+    g = torch.Generator(device=DEV).manual_seed(1)
+    B, V = 4, 20011
+    tq = torch.randn(B, V, generator=g, device=DEV)
+    td = tq + torch.randn(B, V, generator=g, device=DEV)
+    crowd = torch.full((V,), 0.1, device=DEV) + 2e-6 * torch.rand(V, generator=g, device=DEV)
+    at = torch.from_numpy(_sampled(V)).to(DEV)
+    crowd[at] = 3.0 * torch.randn(at.numel(), generator=g, device=DEV)
+    tq[2] = 0.0
+    td[2] = crowd
+    check(td, tq, [1, 4])
+
+
+def test_results_do_not_depend_on_the_workspace_or_the_run():
+    g = torch.Generator(device=DEV).manual_seed(2)
+    B, V = 9, 33001
+    tq = (2.0 * torch.randn(B, V, generator=g, device=DEV)).bfloat16().float()   # many ties
+    td = (tq + torch.randn(B, V, generator=g, device=DEV)).bfloat16().float()
+    first = llc.llc_lml_bound(td, tq, KS)
+    for rows in (1, 4, 9, 9):
+        ws = torch.randint(0, 255, (24 * V * rows + 256,), dtype=torch.uint8, device=DEV)
+        other = llc.llc_lml_bound(td, tq, KS, workspace=ws)
+        torch.cuda.synchronize()
+        for name in ("bound", "relaxed", "tv"):
+            assert torch.equal(other[name], first[name]), (rows, name)
