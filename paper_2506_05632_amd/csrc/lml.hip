@@ -438,6 +438,14 @@ __device__ __forceinline__ N block_prefix(N v, N *scratch, N *total) {
   return before + incl - v;
 }
 
+// A value that is the same in all lanes, held in scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ double uniform(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)uniform((int)(uint32_t)b), hi = (uint32_t)uniform((int)(uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // The same for two sums at once, in place.
 __device__ __forceinline__ void block_prefix2(double &a, double &b, double *scratch_a, double *scratch_b, double *total_a,
                                               double *total_b) {
@@ -552,12 +560,13 @@ __device__ __forceinline__ int padded(int j) { return j + j / kR; }
 // 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
 // third pass 0.4 (positions 0.22, masses 0.16), the groups 0.8 (cells and their starts 0.45, the order inside
 // cells 0.17, running sums 0.15, terms 0.05).  An order by the exact ratio, general divisions and a branch
-// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.25.
+// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.05.
 // All sums run in an order that does not depend on how the wavefronts interleave: entries keep the row's
 // order within a bucket, and within a group they are ordered by their places, then as they lie in the bucket.
-// PAIRS: room for that many pairs of list sizes.
+// PAIRS: room for that many pairs of list sizes (more than four sizes do not fit 128 registers with the
+// rest, so that variant runs one workgroup per CU).
 template <typename E, bool PROBS, int PAIRS>
-__global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams p) {
+__global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel(const LmlParams p) {
   __shared__ double s_red[kWaves], s_red2[kWaves];
   __shared__ int s_redi[kWaves];
   __shared__ int s_split[kMaxBuckets + 1];  // bucket b holds the places from s_split[b] up to s_split[b + 1]
@@ -866,10 +875,10 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
       }
       sums[n] = 0.0;
     }
-  q_total = block_sum(q_total, s_red);
+  q_total = uniform(block_sum(q_total, s_red));
 
   // ---- the groups in order, with the masses of what came before
-  double p_before = block_sum(p_first, s_red), q_before = 0.0;
+  double p_before = uniform(block_sum(p_first, s_red)), q_before = 0.0;
   // K q / (D(r) + (K - 1) Q) of one entry, D(r) the sum of max(q_i, r p_i) over the row: the q-mass from
   // the entry on plus r times the p-mass before it (numerator and denominator times p)
   auto add_term = [&](const float2 m, const double pb, const double qb) {
@@ -878,29 +887,31 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
     add_quotients<PAIRS>(sums, p, pm * qm, fma(q_total - qb, pm, pb * qm), 1.0, q_total * pm);
   };
   // Placer's log_ratio of an entry from its masses: the normalisers and maxima taken off again
-  const double shift = (PROBS ? 0.0 : sq.m * sq.inv_t - sp.m * sp.inv_t) + (sq.ln_z - sp.ln_z);
+  const double shift = uniform((PROBS ? 0.0 : sq.m * sq.inv_t - sp.m * sp.inv_t) + (sq.ln_z - sp.ln_z));
   for (int b0 = 0, b1 = 0; b0 < nb; b0 = b1) {
     b1 = b0 + 1;
-    const int first = s_off[b0];
-    int n = s_off[b1] - first;
+    const int first = uniform(s_off[b0]);
+    int n = uniform(s_off[b1]) - first;
     const bool tied = n > kGroup;  // (only a bucket of one quantum can be)
     if (!tied) {
-      while (b1 < nb && s_off[b1 + 1] - first <= kGroup) ++b1;
-      n = s_off[b1] - first;
+      while (b1 < nb && uniform(s_off[b1 + 1]) - first <= kGroup) ++b1;
+      n = uniform(s_off[b1]) - first;
     }
     if (n == 0) continue;  // uniform
     double pg = 0.0, qg = 0.0;  // the group's masses
+    int me = tid;
+    asm volatile("" : "+v"(me));  // (or two dozen addresses formed from it live, and spill, across the whole loop)
     if (tied) {
       // one quantum: any order will do, so every entry counts as the first of them
 #pragma unroll 1
-      for (int i = tid; i < n; i += kThreads) {
+      for (int i = me; i < n; i += kThreads) {
         const float2 m = bucketed[first + i];
         pg += (double)m.x;
         qg += (double)m.y;
         add_term(m, p_before, q_before);
       }
-      p_before += block_sum(pg, s_red);
-      q_before += block_sum(qg, s_red);
+      p_before = uniform(p_before + block_sum(pg, s_red));
+      q_before = uniform(q_before + block_sum(qg, s_red));
       continue;
     }
     // cells: bucket b's entries spread over as many cells as there are, linearly in ln r between its
@@ -910,33 +921,29 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
     while (top * 2 < b1 - b0) top *= 2;
 #pragma unroll
     for (int e = 0; e < kR; ++e) {
-      const int i = e * kThreads + tid;
-      if (i < n) mass[e] = bucketed[first + i];
+      const int i = e * kThreads + me;
+      mass[e] = bucketed[first + min(i, n - 1)];
     }
     __syncthreads();  // the group before is done with
-    for (int c = tid; c < padded(n) + 1; c += kThreads) s_cell[c] = 0;
+    for (int c = me; c < padded(n) + 1; c += kThreads) s_cell[c] = 0;
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < kR; ++e) {
-      const int i = e * kThreads + tid;
-      cell[e] = -1;
-      rank[e] = 0;
-      if (i < n) {
-        int b = b0;  // the bucket it lies in
-        for (int step = top; step >= 1; step >>= 1)
-          if (b + step < b1 && s_off[b + step] - first <= i) b += step;
-        const float r = mass[e].y * __builtin_amdgcn_rcpf(mass[e].x);
-        const int low = s_split[b], high = b + 1 < nb ? s_split[b + 1] - 1 : 0x7FFFFFFE;
-        // (from fp32 masses: within its bucket whatever the rounding)
-        place[e] = max(low, min(high, pl.quanta((double)(__log2f(r) * 0.69314718f) + shift)));
-        cell[e] = i;  // in a bucket of one quantum the entries stay as they lie
-        if (high > low || b == 0) {
-          const int lo = s_off[b] - first, cnt = s_off[b + 1] - s_off[b];
-          const float f = (float)((double)place[e] - (double)(b > 0 ? low : left_edge)) * s_scale[b];
-          cell[e] = lo + max(0, min(cnt - 1, (int)f));
-        }
-        rank[e] = atomicAdd(&s_cell[padded(cell[e])], 1);
-      }
+      const int i = e * kThreads + me;
+      int b = b0;  // the bucket it lies in
+      for (int step = top; step >= 1; step >>= 1)
+        if (b + step < b1 && s_off[b + step] - first <= i) b += step;
+      const float r = mass[e].y * __builtin_amdgcn_rcpf(mass[e].x);
+      const int low = s_split[b], high = b + 1 < nb ? s_split[b + 1] - 1 : 0x7FFFFFFE;
+      // (from fp32 masses: within its bucket whatever the rounding)
+      place[e] = max(low, min(high, pl.quanta((double)(__log2f(r) * 0.69314718f) + shift)));
+      const int lo = s_off[b] - first, cnt = s_off[b + 1] - s_off[b];
+      const float f = (float)((double)place[e] - (double)(b > 0 ? low : left_edge)) * s_scale[b];
+      const int spread = lo + max(0, min(cnt - 1, (int)f));
+      // (in a bucket of one quantum the entries stay as they lie)
+      cell[e] = i < n ? (high > low || b == 0 ? spread : i) : -1;
+      rank[e] = i < n ? atomicAdd(&s_cell[padded(cell[e])], 1) : 0;
+      __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
     {
@@ -944,27 +951,27 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
       int c[kR], sum = 0, total;
 #pragma unroll
       for (int e = 0; e < kR; ++e) {
-        const int j = tid * kR + e;
+        const int j = me * kR + e;
         c[e] = j < n ? s_cell[padded(j)] : 0;
         sum += c[e];
       }
       int start = block_prefix(sum, s_redi, &total);
 #pragma unroll
       for (int e = 0; e < kR; ++e) {
-        const int j = tid * kR + e;
+        const int j = me * kR + e;
         if (j < n) s_cell[padded(j)] = start;
         start += c[e];
       }
-      if (tid == 0) s_cell[padded(n)] = n;
+      if (me == 0) s_cell[padded(n)] = n;
     }
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < kR; ++e)
       if (cell[e] >= 0) {
         rank[e] += s_cell[padded(cell[e])];
-        s_key[rank[e]] = key_of(place[e], e * kThreads + tid);
+        s_key[rank[e]] = key_of(place[e], e * kThreads + me);
       }
-    if (tid < 4) s_key[n + tid] = ~0ull;
+    if (me < 4) s_key[n + me] = ~0ull;
     __syncthreads();
     // entries of one cell among themselves: by place, then as they lie in the bucket
     // (the thread's entries side by side, four steps at a time: what lies behind a cell has larger keys and
@@ -982,7 +989,7 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
       for (int t = 0; __any(t < longest); t += 4) {
 #pragma unroll
         for (int e = 0; e < kR; ++e) {
-          const unsigned long long mine = key_of(place[e], e * kThreads + tid);
+          const unsigned long long mine = key_of(place[e], e * kThreads + me);
           const unsigned long long *there = s_key + min(cell[e] + t, n);
 #pragma unroll
           for (int u = 0; u < 4; ++u) rank[e] += there[u] < mine ? 1 : 0;
@@ -992,11 +999,11 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < kR; ++e)
-      if (e * kThreads + tid < n) s_mass[padded(rank[e])] = mass[e];
+      if (e * kThreads + me < n) s_mass[padded(rank[e])] = mass[e];
     __syncthreads();
     {
       // running sums over the entries in order; thread t takes entries t kR .. t kR + kR - 1
-      const int mine = tid * kR;
+      const int mine = me * kR;
 #pragma unroll
       for (int e = 0; e < kR; ++e) {
         mass[e] = mine + e < n ? s_mass[padded(mine + e)] : make_float2(0.0f, 0.0f);
@@ -1014,8 +1021,8 @@ __global__ void __launch_bounds__(kThreads, 4) lml_bucket_kernel(const LmlParams
         qb += (double)mass[e].y;
         if (e % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (all at once does not fit the registers)
       }
-      p_before += p_sum;
-      q_before += q_sum;
+      p_before = uniform(p_before + p_sum);
+      q_before = uniform(q_before + q_sum);
     }
   }
 #pragma unroll
