@@ -19,9 +19,12 @@ struct Plan {
 
 // Drafts per workgroup pass.  With one shared proposal the per-index work is amortised over the
 // drafts of a pass, so wider is better; with per-draft rows each draft brings its own loads and
-// thresholds and four keep the kernel within 128 VGPRs.
-int auto_ktile(long long K, bool shared) {
-  if (K >= 5 && shared) return 8;
+// thresholds and four keep the kernel within 128 VGPRs.  Six where that takes no more passes than eight
+// (5, 6, 9 to 12, 17, 18 drafts): the generator's work, most of the scan's, is per pair of drafts, padded
+// ones included (300 rows x 50 257, K = 5, with keys: 73 us with eight, 61 with six).  Drawn min-first the
+// main loop's work does not depend on it.
+int auto_ktile(long long K, bool shared, bool min_first) {
+  if (K >= 5 && shared) return !min_first && (K + 5) / 6 == (K + 7) / 8 ? 6 : 8;
   return K >= 3 ? 4 : 2;
 }
 
@@ -179,7 +182,7 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   const bool shared = j.draft_stride_k == 0 && temp_draft == nullptr && !j.force_perk;
 
   Plan &pl = out->pl;
-  pl.kt = j.k_tile != 0 ? (j.k_tile == 1 ? 2 : j.k_tile) : auto_ktile(j.K, shared);
+  pl.kt = j.k_tile != 0 ? (j.k_tile == 1 ? 2 : j.k_tile) : auto_ktile(j.K, shared, j.min_first);
   pl.n_kgroups = (int)((j.K + pl.kt - 1) / pl.kt);
   const long long G = (j.V + 3) / 4;
   const bool masked = j.bins != nullptr || j.no_draft || j.same_race;

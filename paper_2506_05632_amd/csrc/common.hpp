@@ -246,7 +246,7 @@ struct LmlParams {
 };
 
 // One launcher per (element type, draft layout); defined in scan_*.hip.
-// kt: drafts per workgroup pass (2, 4, 8); probs: inputs are probabilities.
+// kt: drafts per workgroup pass (2, 4, 8; one word per (index, draft) and a shared proposal also 6); probs: inputs are probabilities.
 hipError_t launch_scan_f32_shared(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
 hipError_t launch_scan_f32_perk(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);
 hipError_t launch_scan_bf16_shared(int kt, bool probs, unsigned grid, hipStream_t s, const ScanParams &p);

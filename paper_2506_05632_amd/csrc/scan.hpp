@@ -1511,7 +1511,7 @@ scan_kernel(const ScanParams p) {
   }
 }
 
-// kt: drafts per workgroup pass (2, 4 or 8; 1 runs as 2: a draft pair shares its blocks).
+// kt: drafts per workgroup pass (2, 4, 6 or 8; 1 runs as 2: a draft pair shares its blocks).
 template <typename T, bool SHARED, bool MINF>
 hipError_t launch_scan(int kt, bool probs, unsigned grid, hipStream_t st, const ScanParams &p) {
   const bool masked = p.bins != nullptr || p.no_draft != 0 || p.same_race != 0;
@@ -1526,6 +1526,7 @@ hipError_t launch_scan(int kt, bool probs, unsigned grid, hipStream_t st, const 
   switch (kt) {                                 \
     case 2: LLC_LAUNCH(1, PR_, MK_, LS_)        \
     case 4: LLC_LAUNCH(2, PR_, MK_, LS_)        \
+    case 6: if constexpr (SHARED && !MINF) { LLC_LAUNCH(3, PR_, MK_, LS_) } break; \
     case 8: LLC_LAUNCH(4, PR_, MK_, LS_)        \
   }                                             \
   return hipErrorInvalidValue;

@@ -24,7 +24,9 @@ def _rows(g, lead, V, dtype):
 # (rows, drafts, entries): one row of every split; the last row count of 1024 threads, of 512, and the
 # next one; a row shorter than a workgroup, a last tile of one group, a tail of one entry
 SHAPES = [(1, 4, 40001), (1, 8, 70003), (3, 2, 4093), (16, 5, 9001), (100, 4, 8197), (256, 4, 4097), (257, 4, 4097),
-          (512, 3, 2051), (513, 3, 2051), (64, 16, 5003), (300, 8, 255), (256, 1, 1)]
+          (512, 3, 2051), (513, 3, 2051), (64, 16, 5003), (300, 8, 255), (256, 1, 1),
+          # drafts in passes of six: one full, two with a padded last, three
+          (40, 6, 5001), (33, 11, 4099), (7, 18, 2053)]
 
 
 @pytest.mark.parametrize("B,K,V", SHAPES)
