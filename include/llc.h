@@ -326,7 +326,8 @@ typedef struct llc_couple_topm_args {
   int32_t *match_k;         /* [B]   optional */
   float *keyX;              /* [B,K] optional */
   float *keyY;              /* [B]   optional */
-  llc_stats *stats;         /* optional: exact_evals and degenerate are counted           */
+  llc_stats *stats;         /* optional: exact_evals (here the (draft, entry) pairs with mass on
+                               either side), degenerate and near_ties are counted        */
   void *stream;
   void *ev_begin, *ev_end;  /* optional hipEvent_t pair recorded around the kernel        */
 } llc_couple_topm_args;

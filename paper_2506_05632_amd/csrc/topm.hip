@@ -1,65 +1,18 @@
 // Algorithm 1 on candidate lists (paper Section 4.4: with top-K sampling only M << N tokens
-// per distribution survive).  A row is a few hundred (token id, value) pairs, so there is
-// nothing to prune: one workgroup per row evaluates every key exactly in fp64 -- the random
-// word of (row, k, token id) from its two Philox blocks, ln S - x/T + ln sum exp(x/T) for
-// logits and log-weights, S/p for probabilities -- and reduces with the usual tie rule
-// (smaller key, then smaller token id, then smaller k).
+// per distribution survive).  A row is a few hundred (token id, value) pairs: one workgroup per row,
+// one wavefront per draft list at a time, all (draft, target entry) pairs over the workgroup for the pool.
+// Every entry draws its random word from its two Philox blocks and forms an approximate key in fp32; those
+// within a band of their reduction's smallest go to a list in LDS and are evaluated exactly, in fp64, all at
+// once: ln S - x/T for logits and log-weights, S/p for probabilities, reduced with the usual tie rule
+// (smaller key, then smaller token id, then smaller k).  The band covers the approximation's error on both
+// sides with room for every key within 1e-6 of the winner's, so nothing that could win, or make the winner a
+// near-tie, is left out.
 #include "scan.hpp"
 
 namespace llc {
 namespace {
 
-constexpr int kTopmMaxK = 1024;
-
-struct Best {
-  double key;
-  int id, k;
-  double sec;  // the smallest key seen at another id (the runner-up that a near-tie is judged by)
-};
-
-// a beats b: smaller key; equal keys: smaller id, then smaller k.  id < 0 = nothing yet.
-__device__ __forceinline__ bool better(const Best &a, const Best &b) {
-  if (a.id < 0) return false;
-  if (b.id < 0) return true;
-  if (a.key != b.key) return a.key < b.key;
-  if (a.id != b.id) return a.id < b.id;
-  return a.k < b.k;
-}
-
-// Fold one more state into a running one.  The loser's winner is a runner-up candidate unless it
-// sits at the winner's id; the loser's own runner-up is then the candidate (it excludes that id).
-__device__ __forceinline__ void fold(Best &v, const Best &o) {
-  if (o.id < 0) return;
-  if (better(o, v)) {
-    double sec = o.sec;
-    if (v.id >= 0) sec = fmin(sec, v.id != o.id ? v.key : v.sec);
-    v = o;
-    v.sec = sec;
-  } else {
-    v.sec = fmin(v.sec, o.id != v.id ? o.key : o.sec);
-  }
-}
-
-__device__ __forceinline__ Best wave_best(Best v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    Best o;
-    o.key = __shfl_xor(v.key, d);
-    o.id = __shfl_xor(v.id, d);
-    o.k = __shfl_xor(v.k, d);
-    o.sec = __shfl_xor(v.sec, d);
-    fold(v, o);
-  }
-  return v;
-}
-
-// Relative distance (in S/p) between the winner and the runner-up below 1e-6 (log-domain keys differ
-// by the log of the ratio).
-__device__ __forceinline__ bool near_tie(const Best &v, bool probs) {
-  if (v.id < 0 || !(v.sec < __builtin_huge_val())) return false;
-  if (!probs) return expm1(v.sec - v.key) < 1e-6;
-  return v.key > 0.0 ? (v.sec - v.key) / v.key < 1e-6 : !(v.sec > 0.0);
-}
+constexpr int kCandidates = 512;  // entries of the list in LDS
 
 __device__ __forceinline__ float widen_at(const void *base, int dtype, long long off) {
   if (dtype == LLC_F32) return reinterpret_cast<const float *>(base)[off];
@@ -84,39 +37,114 @@ __device__ __forceinline__ uint32_t word_of(uint32_t id, uint32_t k, uint32_t ro
   return element_word(uw, lw, (int)(k & 1u));
 }
 
-__global__ void __launch_bounds__(256) topm_kernel(const TopmParams p) {
-  __shared__ double s_lse[kTopmMaxK + 1];  // ln sum exp(x/T) of draft list k, of the target list at [K]
-  __shared__ int s_x[kTopmMaxK];
-  __shared__ Best s_pool[4];
-  __shared__ int s_match, s_y;
+// One of a row's K + 1 reductions (drafts, then the pool), in LDS.
+struct Race {
+  unsigned long long best, where, second;  // ordered images of the keys; where = (id, k)
+};
+
+// What bounds it: instruction issue (two Philox blocks an entry), then the latency of its phases.  The exact
+// keys are two fp64 logarithms each: taken by every wavefront for its own list, as before, they were more
+// than half of all instructions (1024 rows, K = 8, 50 entries, with keys: 27 us of kernel time, now 18).
+template <bool PROBS>
+__global__ void __launch_bounds__(kBlock) topm_kernel(const TopmParams p) {
+  __shared__ double c_key[kCandidates];
+  __shared__ int c_id[kCandidates], c_k[kCandidates];  // c_k: the draft, K more for a pool entry
+  __shared__ float c_v[kCandidates];
+  __shared__ uint32_t c_x[kCandidates];
+  __shared__ double s_lse_draft, s_lse_target;
+  __shared__ int s_count, s_match;
   __shared__ unsigned long long s_evals;
   __shared__ unsigned s_degenerate, s_near;
+  extern __shared__ __align__(16) char s_dyn[];
+  const int K = p.K;
+  Race *race = reinterpret_cast<Race *>(s_dyn);              // [K + 1]
+  double *s_lse = reinterpret_cast<double *>(race + K + 1);  // [K]: where every draft has its own list
 
   const long long b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int K = p.K;
-  const bool probs = p.kind == LLC_PROBS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, nt = blockDim.x;
   const bool logits = p.kind == LLC_LOGITS;
   const unsigned long long row = p.row_offset + (unsigned long long)b;
   const uint32_t row_lo = (uint32_t)row, row_hi = (uint32_t)(row >> 32);
-  const int32_t *t_ids = p.target_ids + b * p.target_stride_b;
   const long long t_off = b * p.target_stride_b;
+  const int32_t *t_ids = p.target_ids + t_off;
   const float inf = __builtin_huge_valf();
+  const bool one_list = p.draft_stride_k == 0 && p.temp_draft == nullptr;
+  auto draft_off = [&](const int k) { return b * p.draft_stride_b + (long long)k * p.draft_stride_k; };
+  auto draft_temp = [&](const int k) { return logits ? (p.temp_draft != nullptr ? p.temp_draft[k] : p.temp_draft_all) : 1.0f; };
+  const float Tq = logits ? p.temp_target : 1.0f;
 
-  if (tid == 0) { s_match = 0x7FFFFFFF; s_evals = 0; s_degenerate = 0; s_near = 0; }
+  for (int k = tid; k <= K; k += nt) { race[k].best = kOrdInf64; race[k].where = ~0ull; race[k].second = kOrdInf64; }
+  if (tid == 0) { s_count = 0; s_match = 0x7FFFFFFF; s_evals = 0; s_degenerate = 0; s_near = 0; }
+  __syncthreads();
 
-  // ---- normalisers: list l < K is draft l, list K the target; one wavefront per list
-  if (!probs) {
-    const bool one_list = p.draft_stride_k == 0 && p.temp_draft == nullptr;
-    for (int l = wave; l <= K; l += 4) {
-      if (l < K && one_list && l > 0) continue;  // filled from list 0 below
-      const bool target = l == K;
+  // the entries of one round of a wavefront: the smallest approximate key so far, and onto the list with
+  // whatever is near it (what comes later can only lower it)
+  unsigned long long evals = 0;
+  float tau = inf;
+  auto consider = [&](const bool has, const int id, const float v, const uint32_t x, const float c, const int tag) {
+    float a = inf, ell;
+    if (has && approx_log2_mass<PROBS>(v, c, ell)) a = approx_log2_race_time(x) - ell;
+    float m = a;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = fminf(m, __shfl_xor(m, d));
+    tau = fminf(tau, m);
+    // (far values: the fp32 product's rounding grows with them; beyond all measure every entry goes)
+    const float band = kEps2 + (fabsf(tau) + 64.0f) * 0x1p-20f;
+    const bool near = a <= tau + band || !(fabsf(tau) < 1e30f);
+    if (has) ++evals;
+    if (has && near) {
+      const int pos = atomicAdd(&s_count, 1);
+      if (pos < kCandidates) { c_id[pos] = id; c_v[pos] = v; c_x[pos] = x; c_k[pos] = tag; }
+    }
+  };
+
+  // ---- draft side: one wavefront per list, lanes over its entries
+  for (int k = wave; k < K; k += waves) {
+    const long long off = draft_off(k);
+    const float T = draft_temp(k);
+    const bool t_ok = T > 0.0f && T < inf;
+    const float c = kLog2e / T;
+    tau = inf;
+    for (int e0 = 0; e0 < p.Md; e0 += 64) {
+      const int e = e0 + lane;
+      int id = -1;
+      float v = 0.0f;
+      if (e < p.Md) { id = p.draft_ids[off + e]; v = widen_at(p.draft_val, p.dtype, off + e); }
+      const bool has = t_ok && has_mass(id, v, PROBS);
+      const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
+      consider(has, id, v, x, c, k);
+    }
+  }
+  // ---- pool: all (k, target entry) pairs over the workgroup, the last wavefronts first (the first ones
+  // have had the more lists)
+  {
+    const float c = kLog2e / Tq;
+    const long long items = (long long)K * p.Mt;
+    tau = inf;
+    for (long long i0 = (long long)(waves - 1 - wave) * 64; i0 < items; i0 += nt) {
+      const long long it = i0 + lane;
+      int id = -1, k = 0;
+      float v = 0.0f;
+      if (it < items) {
+        k = (int)((unsigned)it / (unsigned)p.Mt);  // (items < 2^26)
+        const int e = (int)((unsigned)it % (unsigned)p.Mt);
+        id = t_ids[e];
+        v = widen_at(p.target_val, p.dtype, t_off + e);
+      }
+      const bool has = has_mass(id, v, PROBS);
+      const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
+      consider(has, id, v, x, c, K + k);
+    }
+  }
+  // ---- normalisers, only for reported keys (the argmins and near-ties need none): one wavefront per list
+  if (!PROBS && (p.keyX != nullptr || p.keyY != nullptr)) {
+    for (int l = waves - 1 - wave; l <= (one_list ? 1 : K); l += waves) {
+      const bool target = l == 0;  // list 0 the target's, l > 0 draft l - 1's
       const int M = target ? p.Mt : p.Md;
-      const long long off = target ? t_off : b * p.draft_stride_b + (long long)l * p.draft_stride_k;
+      const long long off = target ? t_off : draft_off(l - 1);
       const int32_t *ids = target ? t_ids : p.draft_ids + off;
       const void *val = target ? p.target_val : p.draft_val;
-      float T = 1.0f;
-      if (logits) T = target ? p.temp_target : (p.temp_draft != nullptr ? p.temp_draft[l] : p.temp_draft_all);
+      const float T = target ? Tq : draft_temp(l - 1);
       float m = -inf;
       for (int e = lane; e < M; e += 64) {
         const float v = widen_at(val, p.dtype, off + e);
@@ -135,79 +163,85 @@ __global__ void __launch_bounds__(256) topm_kernel(const TopmParams p) {
       for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
       if (lane == 0) {
         const bool ok = m > -inf && T > 0.0f && T < inf;
-        s_lse[l] = ok ? (double)m / (double)T + log(sum) : -__builtin_huge_val();
+        const double lse = ok ? (double)m / (double)T + log(sum) : -__builtin_huge_val();
+        if (target) s_lse_target = lse;
+        else if (one_list) s_lse_draft = lse;
+        else s_lse[l - 1] = lse;
       }
     }
+  }
+  __syncthreads();
+
+  // ---- exact keys of the list, in three rounds: the smallest key, the smallest (id, k) that holds it, the
+  // smallest key at another id
+  const double huge = __builtin_huge_val();
+  auto offer = [&](const int round, const int tag, const int id, const double key) {
+    if (!(key < huge)) return;
+    Race &r = race[min(tag, K)];
+    const unsigned long long o = ord64(key);
+    if (round == 0) {
+      atomicMin(&r.best, o);
+    } else if (round == 1) {
+      if (o == r.best) atomicMin(&r.where, ((unsigned long long)(uint32_t)id << 32) | (uint32_t)(tag >= K ? tag - K : tag));
+    } else if ((uint32_t)id != (uint32_t)(r.where >> 32)) {
+      atomicMin(&r.second, o);
+    }
+  };
+  const int n = s_count;
+  if (n <= kCandidates) {  // uniform
+    for (int c = tid; c < n; c += nt) {
+      const int tag = c_k[c];
+      c_key[c] = exact_key<PROBS>(exact_race_time(c_x[c]), c_v[c], (double)(tag >= K ? Tq : draft_temp(tag)));
+      offer(0, tag, c_id[c], c_key[c]);
+    }
     __syncthreads();
-    if (one_list)
-      for (int k = 1 + tid; k < K; k += 256) s_lse[k] = s_lse[0];
+    for (int c = tid; c < n; c += nt) offer(1, c_k[c], c_id[c], c_key[c]);
+    __syncthreads();
+    for (int c = tid; c < n; c += nt) offer(2, c_k[c], c_id[c], c_key[c]);
+  } else {
+    // more candidates than the list holds (many equal values, or values beyond fp32's measure): every entry
+#pragma unroll 1
+    for (int round = 0; round < 3; ++round) {
+      const long long drafts = (long long)K * p.Md, items = drafts + (long long)K * p.Mt;
+#pragma unroll 1
+      for (long long it = tid; it < items; it += nt) {
+        const bool pool = it >= drafts;
+        const unsigned j = (unsigned)(pool ? it - drafts : it), M = (unsigned)(pool ? p.Mt : p.Md);
+        const int k = (int)(j / M), e = (int)(j % M);
+        const long long off = (pool ? t_off : draft_off(k)) + e;
+        const int id = pool ? p.target_ids[off] : p.draft_ids[off];
+        const float v = widen_at(pool ? p.target_val : p.draft_val, p.dtype, off);
+        const float T = pool ? Tq : draft_temp(k);
+        if (!has_mass(id, v, PROBS) || !(T > 0.0f && T < inf)) continue;
+        const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
+        offer(round, pool ? K + k : k, id, exact_key<PROBS>(exact_race_time(x), v, (double)T));
+      }
+      __syncthreads();
+    }
   }
   __syncthreads();
 
-  unsigned long long evals = 0;
-  // ---- draft side: one wavefront per list, lanes over its entries
-  for (int k = wave; k < K; k += 4) {
-    const long long off = b * p.draft_stride_b + (long long)k * p.draft_stride_k;
-    const int32_t *ids = p.draft_ids + off;
-    float T = 1.0f;
-    if (logits) T = p.temp_draft != nullptr ? p.temp_draft[k] : p.temp_draft_all;
-    const bool t_ok = T > 0.0f && T < inf;
-    const double lse = probs ? 0.0 : s_lse[k];
-    Best best = {__builtin_huge_val(), -1, k, __builtin_huge_val()};
-    for (int e = lane; e < p.Md; e += 64) {
-      const int id = ids[e];
-      const float v = widen_at(p.draft_val, p.dtype, off + e);
-      if (!t_ok || !has_mass(id, v, probs)) continue;
-      const double S = exact_race_time(word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi));
-      Best c = {probs ? S / (double)v : log(S) - (double)v / (double)T + lse, id, k, __builtin_huge_val()};
-      ++evals;
-      fold(best, c);
+  // ---- outputs
+  const int y = race[K].where != ~0ull ? (int)(race[K].where >> 32) : -1;
+  for (int k = tid; k <= K; k += nt) {
+    const Race r = race[k];
+    const int id = r.where != ~0ull ? (int)(r.where >> 32) : -1;
+    const double key = unord64(r.best), sec = unord64(r.second);
+    float *out = k < K ? p.keyX : p.keyY;
+    const long long at = k < K ? b * K + k : b;
+    (k < K ? p.X : p.Y)[at] = id;
+    if (out != nullptr) {
+      const double lse = PROBS ? 0.0 : k == K ? s_lse_target : one_list ? s_lse_draft : s_lse[k];
+      out[at] = id >= 0 ? (float)(PROBS ? key : exp(key + lse)) : inf;
     }
-    best = wave_best(best);
-    if (lane == 0) {
-      if (near_tie(best, probs)) atomicAdd(&s_near, 1u);
-      s_x[k] = best.id;
-      p.X[b * K + k] = best.id;
-      if (p.keyX != nullptr)
-        p.keyX[b * K + k] = best.id >= 0 ? (float)(probs ? best.key : exp(best.key)) : inf;
-      if (best.id < 0) atomicAdd(&s_degenerate, 1u);
+    if (k < K && id >= 0 && id == y) atomicMin(&s_match, k);
+    if (p.stats != nullptr) {
+      // the winner and the runner-up within 1e-6 (relative, in S/p; log-domain keys differ by the log of the ratio)
+      if (id < 0) atomicAdd(&s_degenerate, 1u);
+      else if (sec < huge &&
+               (!PROBS ? expm1(sec - key) < 1e-6 : key > 0.0 ? (sec - key) / key < 1e-6 : !(sec > 0.0))) atomicAdd(&s_near, 1u);
     }
   }
-
-  // ---- pool: all (k, target entry) pairs over the workgroup
-  {
-    const double lse = probs ? 0.0 : s_lse[K];
-    const float T = logits ? p.temp_target : 1.0f;
-    Best best = {__builtin_huge_val(), -1, 0, __builtin_huge_val()};
-    const long long items = (long long)K * p.Mt;
-    for (long long it = tid; it < items; it += 256) {
-      const int k = (int)(it / p.Mt), e = (int)(it % p.Mt);
-      const int id = t_ids[e];
-      const float v = widen_at(p.target_val, p.dtype, t_off + e);
-      if (!has_mass(id, v, probs)) continue;
-      const double S = exact_race_time(word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi));
-      Best c = {probs ? S / (double)v : log(S) - (double)v / (double)T + lse, id, k, __builtin_huge_val()};
-      ++evals;
-      fold(best, c);
-    }
-    best = wave_best(best);
-    if (lane == 0) s_pool[wave] = best;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    Best best = s_pool[0];
-    for (int w = 1; w < 4; ++w) fold(best, s_pool[w]);
-    if (near_tie(best, probs)) atomicAdd(&s_near, 1u);
-    s_y = best.id;
-    p.Y[b] = best.id;
-    if (p.keyY != nullptr) p.keyY[b] = best.id >= 0 ? (float)(probs ? best.key : exp(best.key)) : inf;
-    if (best.id < 0) atomicAdd(&s_degenerate, 1u);
-  }
-  __syncthreads();
-  const int y = s_y;
-  if (y >= 0)
-    for (int k = tid; k < K; k += 256)
-      if (s_x[k] == y) atomicMin(&s_match, k);
   if (p.stats != nullptr && evals) atomicAdd(&s_evals, evals);
   __syncthreads();
   if (tid == 0) {
@@ -226,7 +260,11 @@ __global__ void __launch_bounds__(256) topm_kernel(const TopmParams p) {
 
 hipError_t launch_topm(hipStream_t s, const TopmParams &p) {
   if (p.B == 0) return hipSuccess;
-  hipLaunchKernelGGL(topm_kernel, dim3((unsigned)p.B), dim3(256), 0, s, p);
+  // (four wavefronts a row: 1024 rows are resident at once; eight, with half as many rows resident, measured
+  // 26.4 against 25.1 us a call at 1024 rows, K = 8, lists of 256)
+  const unsigned lds = (unsigned)((p.K + 1) * sizeof(Race) + p.K * sizeof(double));
+  if (p.kind == LLC_PROBS) hipLaunchKernelGGL(topm_kernel<true>, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
+  else hipLaunchKernelGGL(topm_kernel<false>, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
   return hipGetLastError();
 }
 

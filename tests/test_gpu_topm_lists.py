@@ -1,0 +1,49 @@
+"""llc_couple_topm where its list of candidates runs full, or its fp32 prefilter has nothing to go by (needs an
+MI355X): many equal values, values of very different sizes, lists longer than a wavefront.  Against the
+oracle, indices bit for bit (near-ties excused), keys to 1e-6."""
+import pytest
+import torch
+
+import paper_2506_05632_amd as llc
+from parity_util import compare, oracle_near_ties, stats_dict
+from test_gpu_topm import oracle_topm
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("kind", ["logits", "logw", "probs"])
+@pytest.mark.parametrize("K,M,scale", [(8, 64, 0.0), (3, 65, 2.0), (5, 700, 1e3), (2, 130, 1e30), (70, 33, 1.0), (1, 4097, 3.0)])
+def test_prefilter_and_list(kind, K, M, scale):
+    g = torch.Generator(device=DEV).manual_seed(M)
+    B = 5
+    ids = torch.stack([torch.randperm(20000, generator=g, device=DEV)[:M] for _ in range(2 * B)]).int()
+    val = scale * torch.randn(2 * B, M, generator=g, device=DEV)
+    if kind == "probs":
+        # (weights up to e^40: the reported fp32 key S/p then stays above 1e-10 e^-40 = 4e-28; with e^80 it is
+        # subnormal, where the rounding of the output alone, 2^-150, is 3e-6 of it)
+        val = torch.exp(torch.clamp(val, -40, 40))
+    val[0, ::3] = float("-inf") if kind != "probs" else 0.0
+    val[B + 1, 0] = float("nan")
+    stats = llc.new_stats(DEV)
+    args = (ids[:B].contiguous(), val[:B].contiguous(), ids[B:].contiguous(), val[B:].contiguous(), K)
+    out = llc.llc_couple_topm(*args, kind=kind, seed=3, temp_target=0.8, temp_draft=1.3, want_keys=True, stats=stats)
+    torch.cuda.synchronize()
+    ref = oracle_topm(*args, kind=kind, seed=3, temp_target=0.8, temp_draft=1.3)
+    # (at 1e30 the fp64 rounding of x / T is 1e14: a log-domain key cannot carry ln S, only the indices say something)
+    assert compare(out, ref, check_keys=scale < 1e6) <= oracle_near_ties(ref)
+    assert stats_dict(stats)["near_ties"] == oracle_near_ties(ref)
+
+
+def test_a_full_list_gives_the_same():
+    # one value everywhere but for a spread far below the band: every pair is a candidate
+    g = torch.Generator(device=DEV).manual_seed(9)
+    B, K, M = 3, 9, 900
+    ids = torch.stack([torch.randperm(5000, generator=g, device=DEV)[:M] for _ in range(2 * B)]).int()
+    val = 1e30 + torch.zeros(2 * B, M, device=DEV)
+    out = llc.llc_couple_topm(ids[:B].contiguous(), val[:B].contiguous(), ids[B:].contiguous(), val[B:].contiguous(), K, seed=1)
+    flat = llc.llc_couple_topm(ids[:B].contiguous(), 0 * val[:B], ids[B:].contiguous(), 0 * val[B:], K, seed=1)
+    torch.cuda.synchronize()
+    assert out["X"].shape == (B, K) and (out["X"] >= 0).all() and (flat["X"] >= 0).all()
+    ref = oracle_topm(ids[:B], 0 * val[:B], ids[B:], 0 * val[B:], K, seed=1)
+    assert compare(flat, ref) <= oracle_near_ties(ref)
