@@ -225,7 +225,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream_handle(device):
-    return torch.cuda.current_stream(device).cuda_stream
+    # (the current stream's handle as it is: a Stream object around it takes 1.9 us of a call's 15)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def new_stats(device) -> torch.Tensor:
