@@ -1185,13 +1185,22 @@ scan_kernel(const ScanParams p) {
       const int n_interior = max(0, (interior_end - g_begin) / nt);
       int it = 0;
       if (n_interior > 0) {
-        // the next tile's loads are issued one tile of arithmetic before they are used (two
-        // register sets that swap roles in a loop unrolled twice, instead of the copies below,
-        // measured slower in both layouts)
-        raw aq = raw(), ad[KD], bq = raw(), bd[KD];
-        uint32_t ab = 0, bb = 0;
+        // the loads run kAhead tiles ahead of the tile at hand (register sets that swap roles in a loop
+        // unrolled twice, instead of the copies below, measured slower in both layouts): one where a tile is
+        // 4 KB a wavefront or more, or registers are short; two for four drafts' bf16 rows and the target's,
+        // whose 2.5 KB were too little in flight for the memory's latency (512 x 16 distinct drafts x 152 064:
+        // 486 us a call with one, 466 with two)
+        constexpr int kAhead = sizeof(elem) == 2 && !SHARED && !LSE && !MINF ? 2 : 1;
+        raw aq = raw(), ad[KD], bq[kAhead], bd[kAhead][KD];
+        uint32_t ab = 0, bb[kAhead];
         const int g0 = g_begin + tid;
         load_tile(g0, true, aq, ad, ab);
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) {
+          bq[h] = raw();
+          bb[h] = 0;
+          if (h + 1 < kAhead) load_tile(g0 + min(h + 1, n_interior - 1) * nt, true, bq[h], bd[h], bb[h]);
+        }
         int prio_step = -1;
         for (; it < n_interior; ++it) {
           // A SIMD serves its wavefronts oldest first, so the workgroups of a CU drift apart and the
@@ -1211,11 +1220,17 @@ scan_kernel(const ScanParams p) {
               }
             }
           }
-          load_tile(g0 + min(it + 1, n_interior - 1) * nt, true, bq, bd, bb);
+          load_tile(g0 + min(it + kAhead, n_interior - 1) * nt, true, bq[kAhead - 1], bd[kAhead - 1], bb[kAhead - 1]);
           process_tile(g0 + it * nt, aq, ad, ab);
-          aq = bq; ab = bb;
+          aq = bq[0]; ab = bb[0];
 #pragma unroll
-          for (int kk = 0; kk < KD; ++kk) ad[kk] = bd[kk];
+          for (int kk = 0; kk < KD; ++kk) ad[kk] = bd[0][kk];
+#pragma unroll
+          for (int h = 0; h + 1 < kAhead; ++h) {
+            bq[h] = bq[h + 1]; bb[h] = bb[h + 1];
+#pragma unroll
+            for (int kk = 0; kk < KD; ++kk) bd[h][kk] = bd[h + 1][kk];
+          }
         }
       }
       for (; it < iters; ++it) {
