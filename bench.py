@@ -60,7 +60,6 @@ MEASURED_TRAFFIC_BYTES = {
     "is_n65536_l4_f32_bins16": 2825.0e6 + 0.5e6,
     "specdec_v32000_k4_bf16": 33.4e6 + 0.5e6,
     "verify_largevocab_s128_l7_k8_v128256": 4207.1e6 + 1.6e6,
-    "lml_largevocab_v128256_k8_f32": 11557.8e6 + 9397.3e6,
 }
 
 
@@ -371,21 +370,19 @@ def bench_lml(args):
         torch.cuda.synchronize()
     kern_s = sum(kern_ms) / len(kern_ms) / 1e3
     elems = w.B * w.V
-    # what the kernel's own design moves per element: both inputs three times (normalisers twice,
-    # then the keys), the key and its two masses written once (12 bytes), four radix passes that
-    # read and write those 12 bytes, and the sorted masses read once more for the running sums
+    # what the kernel's own design moves per element: both inputs three times, a bucket byte and the two
+    # masses written once and read once
     esize = draft.element_size()
     alg_bytes = elems * (2 * esize + 8)          # inputs once, the sorted order written once
-    design_bytes = elems * (6 * esize + 12 + 4 * 24 + 8)
+    design_bytes = elems * (6 * esize + 2 + 16)
     hbm = alg_bytes / kern_s / 1e9
     launches = -(-w.B // max(1, min(w.B, (ws.numel() - 256) // (24 * w.V))))
     roofline = {"bound": "hbm", "achieved": hbm, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm / HBM_PEAK_GBS,
-                "kernel": "lml_kernel", "traffic": MEASURED_TRAFFIC_BYTES.get("lml_" + w.name), "kernel_ms": kern_s * 1e3, "kernel_ms_min": min(kern_ms),
+                "kernel": "lml_bucket_kernel", "traffic": MEASURED_TRAFFIC_BYTES.get("lml_" + w.name), "kernel_ms": kern_s * 1e3, "kernel_ms_min": min(kern_ms),
                 "kernel_launches_per_call": launches,
                 "algorithmic_bytes": alg_bytes, "design_bytes": design_bytes,
-                "note": "one workgroup sorts one row through memory (four stable 8-bit radix passes over 12-byte "
-                        "entries, tiles laid out in LDS so that stores are contiguous): a diagnostic, bound by the "
-                        "traffic of its own design (about 10x the algorithmic bytes), not by the streaming roofline; "
+                "note": "one workgroup per row: three passes over the inputs, every entry's bucket byte and masses written "
+                        "and read once, ordered in LDS: a diagnostic, bound by instruction issue and LDS latency; "
                         "kernel_ms, traffic and the byte counts are per call (kernel_launches_per_call launches of "
                         "at most 512 rows each, which is what the workspace holds)"}
     result = {
