@@ -401,6 +401,11 @@ constexpr int kMaxBuckets = 255;
 constexpr int kNoBucket = 255;        // of an entry that lacks mass on a side
 constexpr double kQuantum = 0x1p-22;  // a step of the places in ln r
 constexpr int kFar = 2147480000;      // places end here: 511 in ln r from the row's centre
+// An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within this of the centre
+// that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
+// ln z, which is at most ln 2^18.  So an entry beyond the places, from a centre that is near that one, has no
+// mass on one side, and which of such entries comes first is of no account.
+constexpr double kReach = 120.0;
 
 __device__ __forceinline__ float4 widen(const float4 &r) { return r; }
 __device__ __forceinline__ float4 widen(const uint2 &r) {
@@ -604,8 +609,12 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   // places that the sample holds several times get a bucket of their own quantum (inputs of few bits have
   // many ties)
   // (a row that is a single group needs none)
-  int nb = 1, n_valid;
-  {
+  int nb = 1, n_valid, left_most, right_most;
+  float mp, mq;
+  pl.center = 0.0;
+#pragma unroll 1
+  for (int attempt = 0;; ++attempt) {
+    nb = 1;
     auto sample = [&](const int j, float &xp, float &xq) {
       const unsigned jitter = (unsigned)j * 0x9E3779B9u;
       const int i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kSamples);
@@ -613,27 +622,27 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       xq = elem<E>(qrow, i);
       return pl.mass(xp) && pl.mass(xq);
     };
-    // the centre: a median of 64 of them (every wavefront finds the same one)
+    // the centre, at first: where an entry would lie that is the sample's largest on both sides (not a median:
+    // most of a row may be masked by a low value); probabilities of any size lie within 192 of 0
     float xp, xq;
-    {
-      const bool ok = sample(lane * (kSamples / 64), xp, xq);
-      const double lr = ok ? pl.log_ratio(xp, xq) : __builtin_huge_val();
-      int rank = 0;
-      for (int l = 0; l < 64; ++l) {
-        const double o = __shfl(lr, l);
-        rank += (o < lr || (o == lr && l < lane)) ? 1 : 0;
+    if (!PROBS && attempt == 0) {
+      mp = mq = ninf;
+      for (int j = tid; j < kSamples; j += kThreads) {
+        sample(j, xp, xq);
+        if (pl.mass(xp)) mp = fmaxf(mp, xp);
+        if (pl.mass(xq)) mq = fmaxf(mq, xq);
       }
-      const int n_ok = __popcll(__ballot(ok));
-      const unsigned long long at_rank = __ballot(rank == n_ok / 2);
-      pl.center = n_ok > 0 ? __shfl(lr, __ffsll((long long)at_rank) - 1) : 0.0;
-      if (!(fabs(pl.center) < __builtin_huge_val())) pl.center = 0.0;
+      mp = (float)block_max((double)mp, s_red);
+      mq = (float)block_max((double)mq, s_red);
+      if (mp > ninf && mq > ninf) pl.center = uniform(pl.log_ratio(mp, mq));
     }
     if (V > kGroup) {  // uniform
     int valid = 0;
     for (int j = tid; j < kSamples; j += kThreads) {
       const bool ok = sample(j, xp, xq);
-      s_sample[j] = ok ? pl.quanta(pl.log_ratio(xp, xq)) : 0x7FFFFFFF;
-      valid += ok ? 1 : 0;
+      const int place = ok ? pl.quanta(pl.log_ratio(xp, xq)) : kFar;
+      s_sample[j] = abs(place) < kFar ? place : 0x7FFFFFFF;
+      valid += abs(place) < kFar ? 1 : 0;
     }
     block_prefix(valid, s_redi, &n_valid);
     for (int size = 2; size <= kSamples; size <<= 1)
@@ -679,43 +688,56 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       }
     }
     }
+    for (int j = tid; j <= kMaxBuckets; j += kThreads) s_next[j] = 0;
+    if (tid == 0) { s_split[0] = (int)0x80000000; s_info[0] = 0; }
+    __syncthreads();
+
+    // ---- first pass: the rows' largest entries, and every entry's bucket and the buckets' counts
+    mp = mq = ninf;
+    left_most = kFar;
+    right_most = -kFar;
+    for (int i = tid * 4; i < V; i += kThreads * 4) {
+      const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+      uint32_t packed = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float xp = at(xp4, j), xq = at(xq4, j);
+        const bool hp = pl.mass(xp), hq = pl.mass(xq);
+        if (hp) mp = fmaxf(mp, xp);
+        if (hq) mq = fmaxf(mq, xq);
+        int b = kNoBucket;
+        if (hp && hq) {
+          const int place = pl.quanta(pl.log_ratio(xp, xq));
+          if (abs(place) < kFar) {
+            left_most = min(left_most, place);
+            right_most = max(right_most, place);
+            b = nb > 1 ? bucket_of(s_split, nb, place) : 0;
+            atomicAdd(&s_next[b], 1);
+          }
+        }
+        packed |= (uint32_t)b << (8 * j);
+      }
+      if (i + 3 < V) {
+        *reinterpret_cast<uint32_t *>(ids + i) = packed;
+      } else {
+        for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned char)(packed >> (8 * j));
+      }
+    }
+    if (PROBS) break;
+    // the centre that the rows' largest entries make: if the sample's was too far from it for kReach, once more
+    // from there
+    mp = (float)block_max((double)mp, s_red);
+    mq = (float)block_max((double)mq, s_red);
+    if (!(mp > ninf && mq > ninf)) break;  // (uniform, as the next) a side without mass
+    const double center = uniform(pl.log_ratio(mp, mq));
+    if (fabs(center - pl.center) < kFar * kQuantum - kReach) break;
+    pl.center = center;
   }
-  for (int j = tid; j <= kMaxBuckets; j += kThreads) s_next[j] = 0;
-  if (tid == 0) { s_split[0] = (int)0x80000000; s_info[0] = 0; }
-  __syncthreads();
+  nb = uniform(nb);
   // (not so at the ends of the places, where everything farther away gathers)
   auto of_one_quantum = [&](const int b) {
     return b >= 1 && b + 1 < nb && s_split[b + 1] - s_split[b] <= 1 && abs(s_split[b]) < kFar - 1;
   };
-
-  // ---- first pass: the rows' largest entries, and every entry's bucket and the buckets' counts
-  float mp = ninf, mq = ninf;
-  int left_most = kFar, right_most = -kFar;
-  for (int i = tid * 4; i < V; i += kThreads * 4) {
-    const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
-    uint32_t packed = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float xp = at(xp4, j), xq = at(xq4, j);
-      const bool hp = pl.mass(xp), hq = pl.mass(xq);
-      if (hp) mp = fmaxf(mp, xp);
-      if (hq) mq = fmaxf(mq, xq);
-      int b = kNoBucket;
-      if (hp && hq) {
-        const int place = pl.quanta(pl.log_ratio(xp, xq));
-        left_most = min(left_most, place);
-        right_most = max(right_most, place);
-        b = nb > 1 ? bucket_of(s_split, nb, place) : 0;
-        atomicAdd(&s_next[b], 1);
-      }
-      packed |= (uint32_t)b << (8 * j);
-    }
-    if (i + 3 < V) {
-      *reinterpret_cast<uint32_t *>(ids + i) = packed;
-    } else {
-      for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned char)(packed >> (8 * j));
-    }
-  }
   Side sp, sq;
   sp.probs = sq.probs = PROBS ? 1 : 0;
   sp.inv_t = pl.itp;
@@ -727,8 +749,9 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     left_edge = max(left_edge, max(s_split[1], (1 << 24) - kFar) - (1 << 23));
     right_edge = min(right_edge, min(s_split[nb - 1], kFar - (1 << 24)) + (1 << 23));
   }
-  sp.m = PROBS ? 0.0 : block_max((double)mp, s_red);
-  sq.m = PROBS ? 0.0 : block_max((double)mq, s_red);
+  left_edge = uniform(left_edge);
+  sp.m = PROBS ? 0.0 : uniform((double)mp);
+  sq.m = PROBS ? 0.0 : uniform((double)mq);
   __syncthreads();
   {
     const int mine = tid < nb ? s_next[tid] : 0;
@@ -846,16 +869,18 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       const float2 m = make_float2((float)pm, (float)qm);
       tv += fabs(pm - qm);
       q_total += (double)m.y;
-      if (hp && !hq) p_first += (double)m.x;  // ratio 0: before all others
+      // ratio 0, or near it: before all others (an entry without a bucket that has the larger ratio has no
+      // p-mass in fp32)
+      if (b == kNoBucket) p_first += (double)m.x;
       if (b != kNoBucket) {
         const int g = s_next[b] + (pos - s_start[b]);
         if (g < s_off[b + 1]) bucketed[g] = m;  // (always; a bucket is never written past its end)
-        if (p.relaxed != nullptr) {             // q / (1 + q / (K p)) = K p q / (K p + q)
-          const bool tiny = pm * qm < 0x1p-900;  // (out of the way of products that vanish)
-          if (tiny) { pm *= 0x1p300; qm *= 0x1p300; }
-          const double pq = pm * qm;
-          if (pq > 0.0) add_quotients<PAIRS>(sums, p, tiny ? pq * 0x1p-300 : pq, qm, 0.0, pm);
-        }
+      }
+      if (hp && hq && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
+        const bool tiny = pm * qm < 0x1p-900;  // (out of the way of products that vanish)
+        if (tiny) { pm *= 0x1p300; qm *= 0x1p300; }
+        const double pq = pm * qm;
+        if (pq > 0.0) add_quotients<PAIRS>(sums, p, tiny ? pq * 0x1p-300 : pq, qm, 0.0, pm);
       }
     }
     __syncthreads();
@@ -884,7 +909,9 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   auto add_term = [&](const float2 m, const double pb, const double qb) {
     if (!(m.x > 0.0f && m.y > 0.0f)) return;
     const double pm = (double)m.x, qm = (double)m.y;
-    add_quotients<PAIRS>(sums, p, pm * qm, fma(q_total - qb, pm, pb * qm), 1.0, q_total * pm);
+    double one = 1.0;
+    asm volatile("" : "+s"(one));  // (or the list sizes less one live, and spill, across the whole loop)
+    add_quotients<PAIRS>(sums, p, pm * qm, fma(q_total - qb, pm, pb * qm), one, q_total * pm);
   };
   // Placer's log_ratio of an entry from its masses: the normalisers and maxima taken off again
   const double shift = uniform((PROBS ? 0.0 : sq.m * sq.inv_t - sp.m * sp.inv_t) + (sq.ln_z - sp.ln_z));

@@ -68,3 +68,33 @@ def test_results_do_not_depend_on_the_workspace_or_the_run():
         torch.cuda.synchronize()
         for name in ("bound", "relaxed", "tv"):
             assert torch.equal(other[name], first[name]), (rows, name)
+
+
+def _keep(x, kept, low, g):
+    """x with all but `kept` random entries of every row at `low`."""
+    at = torch.rand(x.shape, generator=g, device=DEV).argsort(dim=1)[:, :kept]
+    return torch.full_like(x, low).scatter(1, at, x.gather(1, at))
+
+
+@pytest.mark.parametrize("V,dtype", [(32000, torch.float32), (50001, torch.bfloat16)])
+@pytest.mark.parametrize("temp_draft,temp_target", [(0.7, 0.7), (0.7, 1.0), (1.0, 0.01), (0.02, 1.0)])
+def test_rows_masked_by_a_finite_value_and_very_sharp_rows(V, dtype, temp_draft, temp_target):
+    # most of a row far away in ln r from the entries that have mass, on either side or both, and the
+    # temperatures alone doing the same: the order among the entries with mass decides the bound
+    g = torch.Generator(device=DEV).manual_seed(V)
+    target, draft = [], []
+    for low in (-1e4, -1e9, torch.finfo(dtype).min):
+        for kept in (3, 50, 2000, 10000):
+            q = -1.1 * torch.log(torch.rand(4, V, generator=g, device=DEV).argsort(dim=1) + 1.0)
+            q += 0.5 * torch.randn(4, V, generator=g, device=DEV)
+            p = q + torch.randn(4, V, generator=g, device=DEV)
+            same = torch.rand(1, V, generator=g, device=DEV).argsort(dim=1)[:, kept:]  # one mask for both
+            q[0] = _keep(q[:1], kept, low, g)[0]
+            p[1] = _keep(p[1:2], kept, low, g)[0]
+            q[2, same[0]] = low
+            p[2, same[0]] = low                                                        # (row 3 stays whole)
+            target.append(q)
+            draft.append(p)
+    target, draft = torch.cat(target).to(dtype), torch.cat(draft).to(dtype)
+    gpu, _ = check(draft, target, KS if temp_target == 1.0 else KS[:3], temp_draft=temp_draft, temp_target=temp_target)
+    assert (gpu["bound"] <= 1 + 1e-9).all()
