@@ -536,8 +536,8 @@ __device__ __forceinline__ double exp_of_negative(double x) {
   return __builtin_amdgcn_ldexp(s, (int)n);
 }
 
-// acc[n] += k[n] pq / (base + (k[n] - off) slope): two quotients per reciprocal (the denominators are
-// not so small that their product would vanish).  List sizes beyond n_k are 1.
+// acc[n] += k[n] pq / (base + (k[n] - off) slope): two quotients per reciprocal (the product of two
+// denominators has to be a normal number: each is 2^-450 or more in both uses).  List sizes beyond n_k are 1.
 template <int PAIRS>
 __device__ __forceinline__ void add_quotients(double (&acc)[2 * PAIRS], const LmlParams &p, double pq, double base,
                                               double off, double slope) {
@@ -877,10 +877,16 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
         if (g < s_off[b + 1]) bucketed[g] = m;  // (always; a bucket is never written past its end)
       }
       if (hp && hq && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
-        const bool tiny = pm * qm < 0x1p-900;  // (out of the way of products that vanish)
-        if (tiny) { pm *= 0x1p300; qm *= 0x1p300; }
-        const double pq = pm * qm;
-        if (pq > 0.0) add_quotients<PAIRS>(sums, p, tiny ? pq * 0x1p-300 : pq, qm, 0.0, pm);
+        // (where the product nears the smallest numbers, both are taken relative to the larger one: its
+        // denominators, and their product, are then at least 1/4)
+        int scale = 0;
+        if (pm * qm < 0x1p-900) {
+          scale = __builtin_amdgcn_frexp_exp(fmax(pm, qm));
+          pm = __builtin_amdgcn_ldexp(pm, -scale);
+          qm = __builtin_amdgcn_ldexp(qm, -scale);
+        }
+        const double pq = __builtin_amdgcn_ldexp(pm * qm, scale);
+        if (pq > 0.0) add_quotients<PAIRS>(sums, p, pq, qm, 0.0, pm);
       }
     }
     __syncthreads();

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_2506_05632_amd as llc
+from oracle import lml
 from test_gpu_lml import KS, check
 
 pytestmark = pytest.mark.gpu
@@ -98,3 +99,26 @@ def test_rows_masked_by_a_finite_value_and_very_sharp_rows(V, dtype, temp_draft,
     target, draft = torch.cat(target).to(dtype), torch.cat(draft).to(dtype)
     gpu, _ = check(draft, target, KS if temp_target == 1.0 else KS[:3], temp_draft=temp_draft, temp_target=temp_target)
     assert (gpu["bound"] <= 1 + 1e-9).all()
+
+
+@pytest.mark.parametrize("V", [12288, 40961])
+@pytest.mark.parametrize("kind,temp", [("logw", 1.0), ("logits", 0.7)])
+def test_masses_of_every_size_down_to_nothing(V, kind, temp):
+    # ln of either mass sweeps from 0 to -800, side by side and against each other, so that products and sums
+    # of two masses pass through the smallest normal numbers
+    g = torch.Generator(device=DEV).manual_seed(V)
+    sweep = -800.0 * torch.arange(V, device=DEV) / V
+    rows = [(sweep, sweep - 0.5), (sweep, sweep + 0.01 * torch.randn(V, generator=g, device=DEV)),
+            (sweep, sweep + 20.0 * torch.randn(V, generator=g, device=DEV)), (sweep, sweep.flip(0)),
+            (sweep, 0.5 * sweep), (2.0 * sweep, sweep)]
+    rows += [(q, p) for p, q in rows]
+    draft, target = (temp * torch.stack(side) for side in zip(*rows))
+    gpu, ref = check(draft, target, KS, kind=kind, temp_draft=temp, temp_target=temp)
+    assert torch.isfinite(gpu["relaxed"]).all()
+    # two sides that share next to nothing: the relaxed sum is e^-380 or so, and still has its digits
+    draft, target = torch.full((2, 1, V), -380.0 * temp, device=DEV)
+    draft, target = draft.clone(), target.clone()
+    draft[0, 3], draft[0, 5], target[0, 3], target[0, 5] = 0.0, -float("inf"), -float("inf"), 0.0
+    gpu = llc.llc_lml_bound(draft, target, KS, kind=kind, temp_draft=temp, temp_target=temp)
+    ref = lml.lml_rows(draft.cpu().numpy(), target.cpu().numpy(), KS, kind=kind, temp_draft=temp, temp_target=temp)
+    np.testing.assert_allclose(gpu["relaxed"].cpu().numpy(), ref["relaxed"], rtol=1e-6)
