@@ -734,10 +734,8 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     pl.center = center;
   }
   nb = uniform(nb);
-  // (not so at the ends of the places, where everything farther away gathers)
-  auto of_one_quantum = [&](const int b) {
-    return b >= 1 && b + 1 < nb && s_split[b + 1] - s_split[b] <= 1 && abs(s_split[b]) < kFar - 1;
-  };
+  // (two splitters can be farther apart than an int reaches; one more than a place, which is less than kFar, is one)
+  auto of_one_quantum = [&](const int b) { return b >= 1 && b + 1 < nb && s_split[b + 1] <= s_split[b] + 1; };
   Side sp, sq;
   sp.probs = sq.probs = PROBS ? 1 : 0;
   sp.inv_t = pl.itp;

@@ -122,3 +122,19 @@ def test_masses_of_every_size_down_to_nothing(V, kind, temp):
     gpu = llc.llc_lml_bound(draft, target, KS, kind=kind, temp_draft=temp, temp_target=temp)
     ref = lml.lml_rows(draft.cpu().numpy(), target.cpu().numpy(), KS, kind=kind, temp_draft=temp, temp_target=temp)
     np.testing.assert_allclose(gpu["relaxed"].cpu().numpy(), ref["relaxed"], rtol=1e-6)
+
+
+def test_splitters_farther_apart_than_an_int():
+    # the sample sees entries at the two ends only (ln r = -400 and 400, one of them at 0), the rest of the row
+    # lies between them: one bucket of all the entries that matter
+    g = torch.Generator(device=DEV).manual_seed(3)
+    V = 20011
+    td, tq = torch.zeros(2, V, device=DEV), 2.0 * torch.randn(2, V, generator=g, device=DEV)
+    at = torch.from_numpy(_sampled(V)).to(DEV)
+    tq[:, at] = 0.0
+    left = torch.arange(2048, device=DEV) % 64 < 32
+    tq[:, at[left]] = -400.0
+    td[:, at[~left]] = -400.0
+    td[:, at[1024]], tq[:, at[1024]] = 0.0, 0.0
+    check(td, tq, [1, 4])
+    check(tq, td, [1, 4])
