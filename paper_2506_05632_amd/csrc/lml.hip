@@ -11,17 +11,17 @@
 //
 //  by buckets (rows of about 10^4 to 2 10^5 entries): no entry is moved more than once.  A sample of the row
 //  gives splitters of ln r, a first pass counts the entries of every bucket between them, a second
-//  forms the normalisers, a third writes every entry's two masses (rounded to fp32) into its bucket's
-//  part of the workspace; then groups of up to 4096 entries are ordered in LDS (a counting sort on a
-//  linear map of ln r inside every bucket, entries of one cell compared one by one) and walked with
-//  running sums in fp64.  Entries that share a quantum of 2^-22 in ln r may form a bucket of any size,
+//  forms the normalisers, a third writes every entry's two masses (rounded to fp32) and its place (the fp32
+//  image of ln r) into its bucket's part of the workspace; then groups of up to 4096 entries are ordered in
+//  LDS (a counting sort on a linear map of ln r inside every bucket, entries of one cell compared one by
+//  one) and walked with running sums in fp64.  Entries that share a place may form a bucket of any size,
 //  which needs no order.
 //  by sorting (other rows, and a row in which a bucket came out larger than a group): four passes of a
 //  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses travel with their key
 //  through two buffers in the workspace.
 //
-// Indices whose r agree to 2^-22 may come out in either order, which together with the rounding of the
-// masses moves a result by a relative 2^-22 at most.
+// Indices whose r agree to fp32 precision may come out in either order, which together with the rounding of
+// the masses moves a result by a relative 2^-22 at most.
 // Entries without mass on one side follow the limits: p_j = 0 or q_j = 0 gives term j = 0; as a
 // summand i such an entry still counts with the mass it has on the other side.
 #include "common.hpp"
@@ -399,11 +399,10 @@ constexpr int kGroup = 4096;          // entries of a tile, and of a group that 
 constexpr int kR = kGroup / kThreads; // what a thread holds of it
 constexpr int kMaxBuckets = 255;
 constexpr int kNoBucket = 255;        // of an entry that lacks mass on a side
-constexpr double kQuantum = 0x1p-22;  // a step of the places in ln r
-constexpr int kFar = 2147480000;      // places end here: 511 in ln r from the row's centre
+constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
 // An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within this of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
-// ln z, which is at most ln 2^18.  So an entry beyond the places, from a centre that is near that one, has no
+// ln z, which is at most ln 2^18.  So an entry without a place, from a centre that is near that one, has no
 // mass on one side, and which of such entries comes first is of no account.
 constexpr double kReach = 120.0;
 
@@ -445,6 +444,7 @@ __device__ __forceinline__ N block_prefix(N v, N *scratch, N *total) {
 
 // A value that is the same in all lanes, held in scalar registers.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) { return __int_as_float(uniform(__float_as_int(v))); }
 __device__ __forceinline__ double uniform(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
   const uint32_t lo = (uint32_t)uniform((int)(uint32_t)b), hi = (uint32_t)uniform((int)(uint32_t)(b >> 32));
@@ -476,9 +476,18 @@ __device__ __forceinline__ void block_prefix2(double &a, double &b, double *scra
   b = before_b + ib - b;
 }
 
-// The place of an entry in the order, as a whole number of quanta of ln r = ln(q/p) relative to a
-// value of the row (the normalisers move all entries alike and are left out, so that the places are
-// known before they are).  Evaluated twice per entry, by the same instructions.
+// 1 / x to about an ulp, for normal x: the hardware's estimate and two Newton steps (the general fp64
+// division's scaling and fix-up instructions are what an entry's time went to).
+__device__ __forceinline__ double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// The place of an entry in the order: the fp32 image of ln r = ln(q/p) less the row's centre, as a whole
+// number that orders as it does (the normalisers move all entries alike and are left out, so that the places
+// are known before they are; from a centre near the one they make, the image has the digits that one of the
+// normalised ln r has).  Evaluated twice per entry, by the same instructions.
 template <bool PROBS>
 struct Placer {
   double itp, itq, center;
@@ -486,13 +495,35 @@ struct Placer {
     return x < __builtin_huge_valf() && (PROBS ? x > 0.0f : x > -__builtin_huge_valf());
   }
   __device__ __forceinline__ double log_ratio(float xp, float xq) const {
-    if (PROBS) return 0.6931471805599453 * ((double)log2f(xq) - (double)log2f(xp));
-    return __builtin_fma((double)xq, itq, -((double)xp * itp));
+    if (!PROBS) return __builtin_fma((double)xq, itq, -((double)xp * itp));
+    // ln(a/b) = 2 artanh((a - b) / (a + b)) of the mantissas, brought within a factor of 1.42 of each other (the
+    // argument is below 0.172: what follows the 13th power is below 2e-12 of the sum), plus the exponents
+    double a = __builtin_amdgcn_frexp_mant((double)xq), b = __builtin_amdgcn_frexp_mant((double)xp);
+    int e = __builtin_amdgcn_frexp_exp((double)xq) - __builtin_amdgcn_frexp_exp((double)xp);
+    if (a > 1.4143 * b) { a *= 0.5; ++e; }
+    if (b > 1.4143 * a) { b *= 0.5; --e; }
+    const double s = (a - b) * reciprocal(a + b), z = s * s;
+    double t = 2.0 / 13.0;
+    t = __builtin_fma(t, z, 2.0 / 11.0);
+    t = __builtin_fma(t, z, 2.0 / 9.0);
+    t = __builtin_fma(t, z, 2.0 / 7.0);
+    t = __builtin_fma(t, z, 2.0 / 5.0);
+    t = __builtin_fma(t, z, 2.0 / 3.0);
+    t = __builtin_fma(t, z, 2.0);
+    return __builtin_fma(t, s, 0.6931471805599453 * (double)e);
   }
-  __device__ __forceinline__ int quanta(double lr) const {
-    return (int)__builtin_rint(fmin(fmax((lr - center) * (1.0 / kQuantum), (double)-kFar), (double)kFar));
+  // (rounded to 2^-36 first: equal ratios of different entries, of which inputs of few bits have many, differ by
+  // fp64's rounding, which the image of a small distance would show)
+  __device__ __forceinline__ float distance(float xp, float xq) const {
+    constexpr double kStep = 0x1.8p16;  // the last of its 53 bits is worth 2^-36
+    return (float)(((log_ratio(xp, xq) - center) + kStep) - kStep);
   }
 };
+__device__ __forceinline__ int place_of(float distance) {
+  const int b = __float_as_int(distance);
+  return b ^ ((b >> 31) & 0x7FFFFFFF);
+}
+__device__ __forceinline__ float distance_of(int place) { return __int_as_float(place ^ ((place >> 31) & 0x7FFFFFFF)); }
 
 // The last bucket whose splitter is not above `place` (split[0] stands for minus infinity).
 __device__ __forceinline__ int bucket_of(const int *split, int nb, int place) {
@@ -501,14 +532,6 @@ __device__ __forceinline__ int bucket_of(const int *split, int nb, int place) {
   for (int step = 128; step >= 1; step >>= 1)
     if (b + step < nb && split[b + step] <= place) b += step;
   return b;
-}
-
-// 1 / x to about an ulp, for normal x: the hardware's estimate and two Newton steps (the general fp64
-// division's scaling and fix-up instructions are what an entry's time went to).
-__device__ __forceinline__ double reciprocal(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
 }
 
 // e^x for x <= 0 or so (what is below -800 comes out as 0) to about an ulp: x = n ln 2 + f, the Taylor
@@ -560,8 +583,8 @@ __device__ __forceinline__ unsigned long long key_of(int place, int number) {
 __device__ __forceinline__ int padded(int j) { return j + j / kR; }
 
 // One workgroup per row, two per CU.  What bounds it: instruction issue and the latency of LDS between
-// barriers, not memory: the row is read three times and a place byte and the masses are written and read
-// once (42 bytes an entry of 8 input bytes, where the sorting form moves 160).  Of the 1.6 ms that two rows of
+// barriers, not memory: the row is read three times and a bucket byte, the masses and the place are
+// written and read once (by count 50 bytes an entry of 8 input bytes, where the sorting form moves 160).  Of the 1.6 ms that two rows of
 // 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
 // third pass 0.4 (positions 0.22, masses 0.16), the groups 0.8 (cells and their starts 0.45, the order inside
 // cells 0.17, running sums 0.15, terms 0.05).  An order by the exact ratio, general divisions and a branch
@@ -578,7 +601,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   __shared__ int s_off[kMaxBuckets + 2];    // where bucket b starts in the workspace
   __shared__ int s_next[kMaxBuckets + 1];   // how far it has been written; before that its count
   __shared__ int s_start[kMaxBuckets + 1];  // where a bucket's entries start inside the tile at hand
-  __shared__ float s_scale[kMaxBuckets];    // cells per quantum of a bucket
+  __shared__ float s_scale[kMaxBuckets];    // cells of a bucket per unit of ln r
   __shared__ float2 s_mass[kGroup + kThreads];
   __shared__ int s_cell[kGroup + kThreads + 1];  // groups: entries of a cell, then where the cell starts
   __shared__ int s_info[2];
@@ -598,6 +621,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
   float2 *bucketed = reinterpret_cast<float2 *>(work);
   unsigned char *ids = reinterpret_cast<unsigned char *>(work + 8u * (size_t)V);
+  int *places = reinterpret_cast<int *>(work + 12u * (size_t)V);  // beside the masses
   const float none = PROBS ? 0.0f : -__builtin_huge_valf();
   const float ninf = -__builtin_huge_valf();
 
@@ -606,11 +630,10 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   pl.itq = 1.0 / (double)p.temp_target;
 
   // ---- splitters: every bucket gets about V / 126 entries, at least 1024, by the sample's quantiles, and
-  // places that the sample holds several times get a bucket of their own quantum (inputs of few bits have
-  // many ties)
+  // places that the sample holds several times get a bucket of their own (inputs of few bits have many ties)
   // (a row that is a single group needs none)
-  int nb = 1, n_valid, left_most, right_most;
-  float mp, mq;
+  int nb = 1, n_valid;
+  float mp, mq, left_most, right_most;  // the largest entries, the smallest and largest distance
   pl.center = 0.0;
 #pragma unroll 1
   for (int attempt = 0;; ++attempt) {
@@ -623,7 +646,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       return pl.mass(xp) && pl.mass(xq);
     };
     // the centre, at first: where an entry would lie that is the sample's largest on both sides (not a median:
-    // most of a row may be masked by a low value); probabilities of any size lie within 192 of 0
+    // most of a row may be masked by a low value); probabilities of any size lie within 193 of 0
     float xp, xq;
     if (!PROBS && attempt == 0) {
       mp = mq = ninf;
@@ -640,9 +663,9 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     int valid = 0;
     for (int j = tid; j < kSamples; j += kThreads) {
       const bool ok = sample(j, xp, xq);
-      const int place = ok ? pl.quanta(pl.log_ratio(xp, xq)) : kFar;
-      s_sample[j] = abs(place) < kFar ? place : 0x7FFFFFFF;
-      valid += abs(place) < kFar ? 1 : 0;
+      const float d = ok ? pl.distance(xp, xq) : kFar;
+      s_sample[j] = fabsf(d) < kFar ? place_of(d) : 0x7FFFFFFF;
+      valid += fabsf(d) < kFar ? 1 : 0;
     }
     block_prefix(valid, s_redi, &n_valid);
     for (int size = 2; size <= kSamples; size <<= 1)
@@ -658,7 +681,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     if (n_valid > 0) {  // uniform
       const int entries = (int)((long long)V * n_valid / kSamples);
       const int want = max(1, min(kMaxBuckets / 2, (entries + 1023) / 1024));
-      // a run of `many` equal places or more in the sample is two splitters (its quantum is a bucket), any
+      // a run of `many` equal places or more in the sample is two splitters (the place is a bucket), any
       // other place one, if a quantile falls on it; `many` is the least that keeps to the buckets there are
       // (with 32 there are at most want of either kind)
       constexpr int kPer = kSamples / kThreads;
@@ -707,11 +730,11 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
         if (hq) mq = fmaxf(mq, xq);
         int b = kNoBucket;
         if (hp && hq) {
-          const int place = pl.quanta(pl.log_ratio(xp, xq));
-          if (abs(place) < kFar) {
-            left_most = min(left_most, place);
-            right_most = max(right_most, place);
-            b = nb > 1 ? bucket_of(s_split, nb, place) : 0;
+          const float d = pl.distance(xp, xq);
+          if (fabsf(d) < kFar) {
+            left_most = fminf(left_most, d);
+            right_most = fmaxf(right_most, d);
+            b = nb > 1 ? bucket_of(s_split, nb, place_of(d)) : 0;
             atomicAdd(&s_next[b], 1);
           }
         }
@@ -730,22 +753,22 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     mq = (float)block_max((double)mq, s_red);
     if (!(mp > ninf && mq > ninf)) break;  // (uniform, as the next) a side without mass
     const double center = uniform(pl.log_ratio(mp, mq));
-    if (fabs(center - pl.center) < kFar * kQuantum - kReach) break;
+    if (fabs(center - pl.center) < (double)kFar - kReach) break;
     pl.center = center;
   }
   nb = uniform(nb);
-  // (two splitters can be farther apart than an int reaches; one more than a place, which is less than kFar, is one)
-  auto of_one_quantum = [&](const int b) { return b >= 1 && b + 1 < nb && s_split[b + 1] <= s_split[b] + 1; };
+  // (two places can be farther apart than an int reaches; one more than a place is one)
+  auto of_one_place = [&](const int b) { return b >= 1 && b + 1 < nb && s_split[b + 1] <= s_split[b] + 1; };
   Side sp, sq;
   sp.probs = sq.probs = PROBS ? 1 : 0;
   sp.inv_t = pl.itp;
   sq.inv_t = pl.itq;
   // the outer buckets' outer ends: those of the row, or two e-folds from the nearest splitter (an outlier
   // must not stretch a bucket so far that its other entries share a cell)
-  int left_edge = -(int)block_max(-(double)left_most, s_red), right_edge = (int)block_max((double)right_most, s_red);
+  float left_edge = -(float)block_max(-(double)left_most, s_red), right_edge = (float)block_max((double)right_most, s_red);
   if (nb > 1) {
-    left_edge = max(left_edge, max(s_split[1], (1 << 24) - kFar) - (1 << 23));
-    right_edge = min(right_edge, min(s_split[nb - 1], kFar - (1 << 24)) + (1 << 23));
+    left_edge = fmaxf(left_edge, distance_of(s_split[1]) - 2.0f);
+    right_edge = fminf(right_edge, distance_of(s_split[nb - 1]) + 2.0f);
   }
   left_edge = uniform(left_edge);
   sp.m = PROBS ? 0.0 : uniform((double)mp);
@@ -758,11 +781,11 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     if (tid < nb) {
       s_off[tid] = off;
       s_next[tid] = off;
-      if (mine > kGroup && !of_one_quantum(tid)) s_info[0] = 1;
+      if (mine > kGroup && !of_one_place(tid)) s_info[0] = 1;
       // (the outer buckets have no outer splitter: the sample's end stands for it)
-      const double left = (double)(tid > 0 ? s_split[tid] : left_edge);
-      const double right = (double)(tid + 1 < nb ? s_split[tid + 1] : right_edge);
-      s_scale[tid] = right > left ? (float)((double)mine / (right - left)) : 0.0f;
+      const float left = tid > 0 ? distance_of(s_split[tid]) : left_edge;
+      const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : right_edge;
+      s_scale[tid] = right > left ? (float)mine / (right - left) : 0.0f;
     }
     if (tid == 0) s_off[nb] = total;
   }
@@ -872,7 +895,10 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       if (b == kNoBucket) p_first += (double)m.x;
       if (b != kNoBucket) {
         const int g = s_next[b] + (pos - s_start[b]);
-        if (g < s_off[b + 1]) bucketed[g] = m;  // (always; a bucket is never written past its end)
+        if (g < s_off[b + 1]) {  // (always; a bucket is never written past its end)
+          bucketed[g] = m;
+          places[g] = place_of(pl.distance(in.x, in.y));
+        }
       }
       if (hp && hq && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
         // (where the product nears the smallest numbers, both are taken relative to the larger one: its
@@ -917,13 +943,11 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     asm volatile("" : "+s"(one));  // (or the list sizes less one live, and spill, across the whole loop)
     add_quotients<PAIRS>(sums, p, pm * qm, fma(q_total - qb, pm, pb * qm), one, q_total * pm);
   };
-  // Placer's log_ratio of an entry from its masses: the normalisers and maxima taken off again
-  const double shift = uniform((PROBS ? 0.0 : sq.m * sq.inv_t - sp.m * sp.inv_t) + (sq.ln_z - sp.ln_z));
   for (int b0 = 0, b1 = 0; b0 < nb; b0 = b1) {
     b1 = b0 + 1;
     const int first = uniform(s_off[b0]);
     int n = uniform(s_off[b1]) - first;
-    const bool tied = n > kGroup;  // (only a bucket of one quantum can be)
+    const bool tied = n > kGroup;  // (only a bucket of one place can be)
     if (!tied) {
       while (b1 < nb && uniform(s_off[b1 + 1]) - first <= kGroup) ++b1;
       n = uniform(s_off[b1]) - first;
@@ -933,7 +957,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     int me = tid;
     asm volatile("" : "+v"(me));  // (or two dozen addresses formed from it live, and spill, across the whole loop)
     if (tied) {
-      // one quantum: any order will do, so every entry counts as the first of them
+      // one place: any order will do, so every entry counts as the first of them
 #pragma unroll 1
       for (int i = me; i < n; i += kThreads) {
         const float2 m = bucketed[first + i];
@@ -954,6 +978,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     for (int e = 0; e < kR; ++e) {
       const int i = e * kThreads + me;
       mass[e] = bucketed[first + min(i, n - 1)];
+      place[e] = places[first + min(i, n - 1)];
     }
     __syncthreads();  // the group before is done with
     for (int c = me; c < padded(n) + 1; c += kThreads) s_cell[c] = 0;
@@ -964,14 +989,11 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       int b = b0;  // the bucket it lies in
       for (int step = top; step >= 1; step >>= 1)
         if (b + step < b1 && s_off[b + step] - first <= i) b += step;
-      const float r = mass[e].y * __builtin_amdgcn_rcpf(mass[e].x);
       const int low = s_split[b], high = b + 1 < nb ? s_split[b + 1] - 1 : 0x7FFFFFFE;
-      // (from fp32 masses: within its bucket whatever the rounding)
-      place[e] = max(low, min(high, pl.quanta((double)(__log2f(r) * 0.69314718f) + shift)));
       const int lo = s_off[b] - first, cnt = s_off[b + 1] - s_off[b];
-      const float f = (float)((double)place[e] - (double)(b > 0 ? low : left_edge)) * s_scale[b];
-      const int spread = lo + max(0, min(cnt - 1, (int)f));
-      // (in a bucket of one quantum the entries stay as they lie)
+      const float f = (distance_of(place[e]) - (b > 0 ? distance_of(low) : left_edge)) * s_scale[b];
+      const int spread = lo + (int)fminf(fmaxf(f, 0.0f), (float)(cnt - 1));
+      // (in a bucket of one place the entries stay as they lie)
       cell[e] = i < n ? (high > low || b == 0 ? spread : i) : -1;
       rank[e] = i < n ? atomicAdd(&s_cell[padded(cell[e])], 1) : 0;
       __builtin_amdgcn_sched_barrier(0);

@@ -1,7 +1,8 @@
 """GPU parity of llc_lml_bound on rows long enough for its bucketed form (needs an MI355X).
 
-Same oracle and same bound on the error as in test_gpu_lml.py: indices whose ratios agree to 2^-22 may
-be swapped and the masses are rounded to fp32, everything else is fp64 on both sides; rtol 1e-6."""
+Same oracle and same bound on the error as in test_gpu_lml.py: indices whose ratios agree to fp32
+precision may be swapped and the masses are rounded to fp32, everything else is fp64 on both sides; rtol
+1e-6."""
 import numpy as np
 import pytest
 import torch
@@ -138,3 +139,25 @@ def test_splitters_farther_apart_than_an_int():
     td[:, at[1024]], tq[:, at[1024]] = 0.0, 0.0
     check(td, tq, [1, 4])
     check(tq, td, [1, 4])
+
+
+# (not probabilities 1e-7 apart: in fp32 most of those are the same, and the order among equal ratios is free,
+# which the masses' rounding makes worth up to 2^-23 of a pair's share)
+@pytest.mark.parametrize("kind,width", [("logits", 1e-6), ("logits", 1e-7), ("probs", 1e-6)])
+def test_ratios_close_to_each_other_are_ordered_as_finely_as_by_sorting(kind, width):
+    # ratios within a few 1e-7 of each other, whose order fp32 still tells: the two forms (12 287 entries are
+    # sorted, 12 289 bucketed; the two more carry no mass) then sum the same masses in the same order, and
+    # differ by the rounding of fp64 sums and a rare mass that rounds the other way
+    g = torch.Generator(device=DEV).manual_seed(5)
+    B, V = 8, 12287
+    tq = -1.1 * torch.log(torch.rand(B, V, generator=g, device=DEV, dtype=torch.float64).argsort(dim=1) + 1.0)
+    if kind == "probs":
+        tq = torch.exp(tq).float()
+        td = (tq.double() * torch.exp(width * torch.randn(B, V, generator=g, device=DEV, dtype=torch.float64))).float()
+    else:
+        tq = (0.01 * tq).float()   # (so that fp32 logits can lie this close)
+        td = (tq.double() + width * torch.randn(B, V, generator=g, device=DEV, dtype=torch.float64)).float()
+    none = torch.full((B, 2), 0.0 if kind == "probs" else float("-inf"), device=DEV)
+    by_sorting = llc.llc_lml_bound(td, tq, [1, 4], kind=kind)["bound"]
+    by_buckets = llc.llc_lml_bound(torch.cat([td, none], 1), torch.cat([tq, none], 1), [1, 4], kind=kind)["bound"]
+    torch.testing.assert_close(by_buckets, by_sorting, rtol=1e-10, atol=0)
