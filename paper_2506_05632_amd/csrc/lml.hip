@@ -391,10 +391,15 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
 // The rows it takes.  Shorter ones are quicker sorted (fewer fixed steps), from about 40 000 entries on if the
 // inputs are bf16, whose many ties cost the ordering in LDS (us a call, buckets against sorting: fp32 8 192
 // entries, 1 row 114 : 102, 16 384: 171 : 184, 32 000: 281 : 346; bf16 32 000, 64 rows 401 : 386, 128 256: 1252 :
-// 1556; 1024 rows x 128 256: fp32 3245 : 7517, bf16 3700 : 5750).  Beyond the upper end a bucket's share of the
-// row nears a group's size.
+// 1556; 1024 rows x 128 256: fp32 3245 : 7517, bf16 3700 : 5750).
 constexpr int kBucketMinV = 12288, kBucketMinVNarrow = 40960, kBucketMaxV = 1 << 18;
-constexpr int kSamples = 2048;
+// The sample, and the buckets that its quantiles make.  A row is left to the sorting kernel if one bucket
+// outgrows a group, and one such row costs the call a whole sort: with 127 buckets of 16 samples each the
+// largest of a row's is about twice the average, which from kWideV entries on is too near a group's 4096.
+// Those rows take twice the sample and 190 buckets (512 rows of 200 064: 5047 us : 2711, 64 of 262 144 5383 :
+// 2109; 512 of 152 064, where it never happened, 1854 : 1904).
+constexpr int kSamples = 2048, kQuantiles = 127;
+constexpr int kWideV = 160000, kWideSamples = 4096, kWideQuantiles = 190;
 constexpr int kGroup = 4096;          // entries of a tile, and of a group that is ordered in LDS
 constexpr int kR = kGroup / kThreads; // what a thread holds of it
 constexpr int kMaxBuckets = 255;
@@ -611,7 +616,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   unsigned long long *s_key = reinterpret_cast<unsigned long long *>(s_mass);  // groups: the entries' keys
   unsigned char *s_tag = reinterpret_cast<unsigned char *>(s_cell);
   unsigned short(*s_cnt)[kMaxBuckets + 1] = reinterpret_cast<unsigned short(*)[kMaxBuckets + 1]>(s_cell + kGroup / 4);
-  static_assert(kSamples <= kGroup && kGroup + kWaves * (kMaxBuckets + 1) * 2 <= (int)sizeof(s_cell), "sizes");
+  static_assert(kWideSamples <= kGroup && kGroup + kWaves * (kMaxBuckets + 1) * 2 <= (int)sizeof(s_cell), "sizes");
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const long long b_row = p.row0 + blockIdx.x;
@@ -629,88 +634,92 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   pl.itp = 1.0 / (double)p.temp_draft;
   pl.itq = 1.0 / (double)p.temp_target;
 
-  // ---- splitters: every bucket gets about V / 126 entries, at least 1024, by the sample's quantiles, and
+  // ---- splitters: every bucket gets about V / kQuantiles entries, at least 1024, by the sample's quantiles, and
   // places that the sample holds several times get a bucket of their own (inputs of few bits have many ties)
-  // (a row that is a single group needs none)
-  int nb = 1, n_valid;
+  static_assert(kBucketMinV > kGroup, "a row that is a single group would need none");
+  int nb = 1;
   float mp, mq, left_most, right_most;  // the largest entries, the smallest and largest distance
   pl.center = 0.0;
-#pragma unroll 1
-  for (int attempt = 0;; ++attempt) {
-    nb = 1;
-    auto sample = [&](const int j, float &xp, float &xq) {
-      const unsigned jitter = (unsigned)j * 0x9E3779B9u;
-      const int i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kSamples);
-      xp = elem<E>(prow, i);
-      xq = elem<E>(qrow, i);
-      return pl.mass(xp) && pl.mass(xq);
-    };
+  auto pick_splitters = [&](auto wide, const bool first) {
+    constexpr int kPicks = wide.value ? kWideSamples : kSamples, kMost = wide.value ? kWideQuantiles : kQuantiles;
+    constexpr int kPer = kPicks / kThreads, kMany = wide.value ? 128 : 32;
+    static_assert(kMost + 2 * (kPicks / kMany) <= kMaxBuckets, "too many splitters");
+    float xp[kPer], xq[kPer];
+    int me = tid;
+    asm volatile("" : "+v"(me));  // (or the addresses are formed before the loop, for both sizes, and spill)
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const unsigned j = (unsigned)(e * kThreads + me), jitter = j * 0x9E3779B9u;
+      const int i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kPicks);
+      xp[e] = elem<E>(prow, i);
+      xq[e] = elem<E>(qrow, i);
+    }
     // the centre, at first: where an entry would lie that is the sample's largest on both sides (not a median:
     // most of a row may be masked by a low value); probabilities of any size lie within 193 of 0
-    float xp, xq;
-    if (!PROBS && attempt == 0) {
+    if (!PROBS && first) {
       mp = mq = ninf;
-      for (int j = tid; j < kSamples; j += kThreads) {
-        sample(j, xp, xq);
-        if (pl.mass(xp)) mp = fmaxf(mp, xp);
-        if (pl.mass(xq)) mq = fmaxf(mq, xq);
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        if (pl.mass(xp[e])) mp = fmaxf(mp, xp[e]);
+        if (pl.mass(xq[e])) mq = fmaxf(mq, xq[e]);
       }
       mp = (float)block_max((double)mp, s_red);
       mq = (float)block_max((double)mq, s_red);
       if (mp > ninf && mq > ninf) pl.center = uniform(pl.log_ratio(mp, mq));
     }
-    if (V > kGroup) {  // uniform
-    int valid = 0;
-    for (int j = tid; j < kSamples; j += kThreads) {
-      const bool ok = sample(j, xp, xq);
-      const float d = ok ? pl.distance(xp, xq) : kFar;
-      s_sample[j] = fabsf(d) < kFar ? place_of(d) : 0x7FFFFFFF;
+    int valid = 0, n_valid;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const float d = pl.mass(xp[e]) && pl.mass(xq[e]) ? pl.distance(xp[e], xq[e]) : kFar;
+      s_sample[e * kThreads + tid] = fabsf(d) < kFar ? place_of(d) : 0x7FFFFFFF;
       valid += fabsf(d) < kFar ? 1 : 0;
     }
     block_prefix(valid, s_redi, &n_valid);
-    for (int size = 2; size <= kSamples; size <<= 1)
+    for (int size = 2; size <= kPicks; size <<= 1)
       for (int stride = size >> 1; stride >= 1; stride >>= 1) {
         __syncthreads();
-        for (int t = tid; t < kSamples / 2; t += kThreads) {
+        for (int t = tid; t < kPicks / 2; t += kThreads) {
           const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;
           const int x = s_sample[lo], y = s_sample[hi];
           if ((x > y) == ((lo & size) == 0)) { s_sample[lo] = y; s_sample[hi] = x; }
         }
       }
     __syncthreads();
-    if (n_valid > 0) {  // uniform
-      const int entries = (int)((long long)V * n_valid / kSamples);
-      const int want = max(1, min(kMaxBuckets / 2, (entries + 1023) / 1024));
-      // a run of `many` equal places or more in the sample is two splitters (the place is a bucket), any
-      // other place one, if a quantile falls on it; `many` is the least that keeps to the buckets there are
-      // (with 32 there are at most want of either kind)
-      constexpr int kPer = kSamples / kThreads;
-      int emit[kPer], total, before = 0;
+    if (n_valid == 0) return;  // uniform
+    const int entries = (int)((long long)V * n_valid / kPicks);
+    const int want = max(1, min(kMost, (entries + 1023) / 1024));
+    // a run of `many` equal places or more in the sample is two splitters (the place is a bucket), any
+    // other place one, if a quantile falls on it; `many` is the least that keeps to the buckets there are
+    int emit[kPer], total, before = 0;
 #pragma unroll 1
-      for (int many = 4; many <= 32; many *= 2) {
-        int mine = 0;
-#pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-          const int j = tid * kPer + e, v = s_sample[j];
-          emit[e] = 0;
-          if (j < n_valid && (j == 0 || s_sample[j - 1] != v)) {
-            if (j + many - 1 < n_valid && s_sample[j + many - 1] == v) emit[e] = 2;
-            else if (j > 0 && (long long)j * want / n_valid != (long long)(j - 1) * want / n_valid) emit[e] = 1;
-          }
-          mine += emit[e];
-        }
-        before = block_prefix(mine, s_redi, &total);
-        if (total < kMaxBuckets) break;  // uniform
-      }
-      nb = 1 + min(total, kMaxBuckets - 1);
+    for (int many = 4; many <= kMany; many *= 2) {
+      int mine = 0;
 #pragma unroll
       for (int e = 0; e < kPer; ++e) {
-        const int v = s_sample[tid * kPer + e];
-        for (int c = 0; c < emit[e]; ++c, ++before)
-          if (1 + before < nb) s_split[1 + before] = v + c;
+        const int j = tid * kPer + e, v = s_sample[j];
+        emit[e] = 0;
+        if (j < n_valid && (j == 0 || s_sample[j - 1] != v)) {
+          if (j + many - 1 < n_valid && s_sample[j + many - 1] == v) emit[e] = 2;
+          else if (j > 0 && (long long)j * want / n_valid != (long long)(j - 1) * want / n_valid) emit[e] = 1;
+        }
+        mine += emit[e];
       }
+      before = block_prefix(mine, s_redi, &total);
+      if (total < kMaxBuckets) break;  // uniform
     }
+    nb = 1 + min(total, kMaxBuckets - 1);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const int v = s_sample[tid * kPer + e];
+      for (int c = 0; c < emit[e]; ++c, ++before)
+        if (1 + before < nb) s_split[1 + before] = v + c;
     }
+  };
+#pragma unroll 1
+  for (int attempt = 0;; ++attempt) {
+    nb = 1;
+    if (V > kWideV) pick_splitters(std::true_type(), attempt == 0);
+    else pick_splitters(std::false_type(), attempt == 0);
     for (int j = tid; j <= kMaxBuckets; j += kThreads) s_next[j] = 0;
     if (tid == 0) { s_split[0] = (int)0x80000000; s_info[0] = 0; }
     __syncthreads();

@@ -161,3 +161,22 @@ def test_ratios_close_to_each_other_are_ordered_as_finely_as_by_sorting(kind, wi
     by_sorting = llc.llc_lml_bound(td, tq, [1, 4], kind=kind)["bound"]
     by_buckets = llc.llc_lml_bound(torch.cat([td, none], 1), torch.cat([tq, none], 1), [1, 4], kind=kind)["bound"]
     torch.testing.assert_close(by_buckets, by_sorting, rtol=1e-10, atol=0)
+
+
+@pytest.mark.parametrize("V,dtype", [(160000, torch.float32), (160001, torch.float32), (1 << 18, torch.float32), (1 << 18, torch.bfloat16)])
+def test_ordinary_rows_up_to_the_longest_are_bucketed(V, dtype):
+    # (a row that is left to the sorting kernel has that kernel's second buffer of masses where the bucketing one
+    # writes a 0: behind 16 V bytes of the row's part of the workspace)
+    g = torch.Generator(device=DEV).manual_seed(4)
+    B = 48
+    tq = -1.1 * torch.log(torch.rand(B, V, generator=g, device=DEV).argsort(dim=1) + 1.0)
+    td = (tq + 0.5 * torch.randn(B, V, generator=g, device=DEV)).to(dtype)
+    ws = torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV)
+    tq = (tq + 0.5 * torch.randn(B, V, generator=g, device=DEV)).to(dtype)
+    check(td, tq, [1, 4], rows=[0, 17, B - 1], temp_draft=0.7, temp_target=0.7, workspace=ws)
+    left = torch.stack([ws[24 * V * b + 16 * V:24 * V * b + 16 * V + 4].view(torch.int32) for b in range(B)])
+    assert (left == 0).all()
+    # one more entry is one too many for the form
+    if V == 1 << 18:
+        more = [torch.cat([x[:2], torch.full((2, 1), float("-inf"), device=DEV, dtype=dtype)], 1) for x in (td, tq)]
+        check(*more, [1, 4], temp_draft=0.7, temp_target=0.7)
