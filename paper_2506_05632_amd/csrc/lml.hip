@@ -688,8 +688,8 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     if (n_valid == 0) return;  // uniform
     const int entries = (int)((long long)V * n_valid / kPicks);
     const int want = max(1, min(kMost, (entries + 1023) / 1024));
-    // a run of `many` equal places or more in the sample is two splitters (the place is a bucket), any
-    // other place one, if a quantile falls on it; `many` is the least that keeps to the buckets there are
+    // a run of `many` equal places or more in the sample is two splitters (the place is a bucket), a shorter
+    // one is one, if a quantile falls into it; `many` is the least that keeps to the buckets there are
     int emit[kPer], total, before = 0;
 #pragma unroll 1
     for (int many = 4; many <= kMany; many *= 2) {
@@ -699,8 +699,10 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
         const int j = tid * kPer + e, v = s_sample[j];
         emit[e] = 0;
         if (j < n_valid && (j == 0 || s_sample[j - 1] != v)) {
-          if (j + many - 1 < n_valid && s_sample[j + many - 1] == v) emit[e] = 2;
-          else if (j > 0 && (long long)j * want / n_valid != (long long)(j - 1) * want / n_valid) emit[e] = 1;
+          int last = j;
+          while (last + 1 < n_valid && last + 1 < j + many && s_sample[last + 1] == v) ++last;
+          if (last + 1 == j + many) emit[e] = 2;
+          else if (j > 0 && (long long)last * want / n_valid != (long long)(j - 1) * want / n_valid) emit[e] = 1;
         }
         mine += emit[e];
       }

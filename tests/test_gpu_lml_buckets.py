@@ -163,10 +163,14 @@ def test_ratios_close_to_each_other_are_ordered_as_finely_as_by_sorting(kind, wi
     torch.testing.assert_close(by_buckets, by_sorting, rtol=1e-10, atol=0)
 
 
+def _left_to_sorting(ws, B, V):
+    """Which rows the bucketing kernel left to the sorting one: those have that kernel's second buffer of masses
+    where the other writes a 0, behind 16 V bytes of the row's part of the workspace."""
+    return [b for b in range(B) if ws[24 * V * b + 16 * V:24 * V * b + 16 * V + 4].view(torch.int32).item() != 0]
+
+
 @pytest.mark.parametrize("V,dtype", [(160000, torch.float32), (160001, torch.float32), (1 << 18, torch.float32), (1 << 18, torch.bfloat16)])
 def test_ordinary_rows_up_to_the_longest_are_bucketed(V, dtype):
-    # (a row that is left to the sorting kernel has that kernel's second buffer of masses where the bucketing one
-    # writes a 0: behind 16 V bytes of the row's part of the workspace)
     g = torch.Generator(device=DEV).manual_seed(4)
     B = 48
     tq = -1.1 * torch.log(torch.rand(B, V, generator=g, device=DEV).argsort(dim=1) + 1.0)
@@ -174,9 +178,23 @@ def test_ordinary_rows_up_to_the_longest_are_bucketed(V, dtype):
     ws = torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV)
     tq = (tq + 0.5 * torch.randn(B, V, generator=g, device=DEV)).to(dtype)
     check(td, tq, [1, 4], rows=[0, 17, B - 1], temp_draft=0.7, temp_target=0.7, workspace=ws)
-    left = torch.stack([ws[24 * V * b + 16 * V:24 * V * b + 16 * V + 4].view(torch.int32) for b in range(B)])
-    assert (left == 0).all()
+    assert _left_to_sorting(ws, B, V) == []
     # one more entry is one too many for the form
     if V == 1 << 18:
         more = [torch.cat([x[:2], torch.full((2, 1), float("-inf"), device=DEV, dtype=dtype)], 1) for x in (td, tq)]
         check(*more, [1, 4], temp_draft=0.7, temp_target=0.7)
+
+
+@pytest.mark.parametrize("kind,dtype", [("logits", torch.float32), ("probs", torch.float32), ("logits", torch.bfloat16)])
+def test_rows_of_ratios_shared_by_a_hundred_entries_are_bucketed(kind, dtype):
+    # 1200 ratios: the sample holds most of them once, twice or three times, so quantiles fall inside such runs
+    g = torch.Generator(device=DEV).manual_seed(6)
+    B, V = 6, 128256
+    tq = torch.randint(-300, 300, (B, V), generator=g, device=DEV) / 64.0
+    td = tq + torch.randint(0, 1200, (B, V), generator=g, device=DEV) / (256.0 if dtype == torch.float32 else 64.0)
+    if kind == "probs":
+        td, tq = 2.0 ** td.double().round(), (2.0 ** tq.double().round())
+        td = td * (1.0 + torch.randint(0, 100, (B, V), generator=g, device=DEV) / 128.0)
+    ws = torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV)
+    check(td.to(dtype), tq.to(dtype), [1, 4], kind=kind, workspace=ws)
+    assert _left_to_sorting(ws, B, V) == []
