@@ -14,7 +14,7 @@
 //  forms the normalisers, a third writes every entry's two masses (rounded to fp32) and its place (the fp32
 //  image of ln r) into its bucket's part of the workspace; then groups of up to 4096 entries are ordered in
 //  LDS (a counting sort on a linear map of ln r inside every bucket, entries of one cell compared one by
-//  one) and walked with running sums in fp64.  Entries that share a place may form a bucket of any size,
+//  one, or the whole group sorted where cells are long) and walked with running sums in fp64.  Entries that share a place may form a bucket of any size,
 //  which needs no order.
 //  by sorting (other rows, and a row in which a bucket came out larger than a group): four passes of a
 //  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses travel with their key
@@ -404,6 +404,11 @@ constexpr int kGroup = 4096;          // entries of a tile, and of a group that 
 constexpr int kR = kGroup / kThreads; // what a thread holds of it
 constexpr int kMaxBuckets = 255;
 constexpr int kNoBucket = 255;        // of an entry that lacks mass on a side
+// Entries of one cell up to which they are compared with each other; a group with a larger cell (equal ratios
+// that the sample did not show, a far outlier in its bucket) is sorted whole.  512 rows of 128 256 bf16
+// probabilities: 5.6 ms with comparing alone, 4.1 sorting from 256 on, 3.1 from 96, 3.2 from 32; fp32 rows
+// without such a group 1.57 either way.
+constexpr int kLongCell = 96;
 constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
 // An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within this of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
@@ -582,6 +587,57 @@ __device__ __forceinline__ void add_quotients(double (&acc)[2 * PAIRS], const Lm
 // Place and number of a group's entry as one key.
 __device__ __forceinline__ unsigned long long key_of(int place, int number) {
   return ((unsigned long long)((uint32_t)place ^ 0x80000000u) << 32) | (uint32_t)number;
+}
+
+// Sorts the first n of the keys in LDS (a bitonic network; thread t holds entries t kR .. t kR + kR - 1, those
+// beyond n count as the largest) and says where each came to lie: s_to[number in the key] = position.
+__device__ __forceinline__ void sort_group(unsigned long long *s_key, int *s_to, const int n) {
+  const int me = threadIdx.x;
+  unsigned long long key[kR];
+#pragma unroll
+  for (int e = 0; e < kR; ++e) key[e] = me * kR + e < n ? s_key[me * kR + e] : ~0ull;
+  __syncthreads();
+  // (the smaller one stays where the index has no bit of `d`, the other way round in every second run of `size`)
+  auto keep = [](unsigned long long &mine, const unsigned long long other, const bool smaller) {
+    if ((other < mine) == smaller) mine = other;
+  };
+#pragma unroll 1
+  for (int size = 2; size < 2 * n; size <<= 1) {
+    const bool up = (me & (size / kR)) == 0;  // (of runs of kR entries and more)
+#pragma unroll 1
+    for (int d = size >> 1; d >= 64 * kR; d >>= 1) {  // other wavefronts' entries
+      const bool smaller = ((me & (d / kR)) == 0) == up;
+#pragma unroll
+      for (int e = 0; e < kR; ++e) s_key[e * kThreads + me] = key[e];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < kR; ++e) keep(key[e], s_key[e * kThreads + (me ^ (d / kR))], smaller);
+      __syncthreads();
+    }
+#pragma unroll 1
+    for (int d = min(size >> 1, 32 * kR); d >= kR; d >>= 1) {  // other lanes'
+      const bool smaller = ((me & (d / kR)) == 0) == up;
+#pragma unroll
+      for (int e = 0; e < kR; ++e) keep(key[e], __shfl_xor(key[e], d / kR), smaller);
+    }
+#pragma unroll
+    for (int d = kR / 2; d >= 1; d >>= 1)  // the thread's own
+      if (d < size) {
+#pragma unroll
+        for (int e = 0; e < kR; ++e)
+          if ((e & d) == 0) {
+            const bool rising = size < kR ? (e & size) == 0 : up;
+            const unsigned long long a = key[e], b = key[e | d];
+            const bool swap = (b < a) == rising;
+            key[e] = swap ? b : a;
+            key[e | d] = swap ? a : b;
+          }
+      }
+  }
+#pragma unroll
+  for (int e = 0; e < kR; ++e)
+    if (me * kR + e < n) s_to[(uint32_t)key[e]] = me * kR + e;
+  __syncthreads();
 }
 
 // LDS index of entry j where threads read kR neighbouring entries each (spreads them over the banks).
@@ -992,6 +1048,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       place[e] = places[first + min(i, n - 1)];
     }
     __syncthreads();  // the group before is done with
+    if (me == 0) s_info[1] = 0;
     for (int c = me; c < padded(n) + 1; c += kThreads) s_cell[c] = 0;
     __syncthreads();
 #pragma unroll
@@ -1036,20 +1093,25 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
         s_key[rank[e]] = key_of(place[e], e * kThreads + me);
       }
     if (me < 4) s_key[n + me] = ~0ull;
+    int longest = 0;
+#pragma unroll
+    for (int e = 0; e < kR; ++e) {
+      const int from = cell[e] >= 0 ? s_cell[padded(cell[e])] : n;
+      const int len = cell[e] >= 0 ? s_cell[padded(cell[e] + 1)] - from : 0;
+      longest = max(longest, len > 1 ? len : 0);
+      cell[e] = from;
+      rank[e] = from;
+    }
+    if (longest > kLongCell) s_info[1] = 1;
     __syncthreads();
     // entries of one cell among themselves: by place, then as they lie in the bucket
-    // (the thread's entries side by side, four steps at a time: what lies behind a cell has larger keys and
-    // counts for nothing, so only the longest cell of the wavefront ends the loop)
-    {
-      int longest = 0;
+    if (s_info[1] != 0) {  // (uniform)
+      sort_group(s_key, s_cell, n);
 #pragma unroll
-      for (int e = 0; e < kR; ++e) {
-        const int from = cell[e] >= 0 ? s_cell[padded(cell[e])] : n;
-        const int len = cell[e] >= 0 ? s_cell[padded(cell[e] + 1)] - from : 0;
-        longest = max(longest, len > 1 ? len : 0);
-        cell[e] = from;
-        rank[e] = from;
-      }
+      for (int e = 0; e < kR; ++e) rank[e] = e * kThreads + me < n ? s_cell[e * kThreads + me] : n;
+    } else {
+      // (the thread's entries side by side, four steps at a time: what lies behind a cell has larger keys and
+      // counts for nothing, so only the longest cell of the wavefront ends the loop)
       for (int t = 0; __any(t < longest); t += 4) {
 #pragma unroll
         for (int e = 0; e < kR; ++e) {

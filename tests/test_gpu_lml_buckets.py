@@ -198,3 +198,24 @@ def test_rows_of_ratios_shared_by_a_hundred_entries_are_bucketed(kind, dtype):
     ws = torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV)
     check(td.to(dtype), tq.to(dtype), [1, 4], kind=kind, workspace=ws)
     assert _left_to_sorting(ws, B, V) == []
+
+
+@pytest.mark.parametrize("V,dtype", [(12288, torch.float32), (20011, torch.float32), (70003, torch.float32), (41011, torch.bfloat16)])
+def test_groups_whose_cells_are_long(V, dtype):
+    # entries of a bucket that share a cell by the hundred: a crowd beside ratios far from it, at several
+    # distances, and values of few bits; groups of every size up to a full one are sorted whole
+    g = torch.Generator(device=DEV).manual_seed(V)
+    B = 6
+    tq = torch.randn(B, V, generator=g, device=DEV)
+    at = torch.rand(B, V, generator=g, device=DEV)
+    near, far = torch.randn(B, V, generator=g, device=DEV), 9.0 * torch.randn(B, V, generator=g, device=DEV)
+    td = tq + torch.where(at < 0.5, 1e-4 * near, far)
+    td[1] = tq[1] + torch.where(at[1] < 0.9, 1e-6 * near[1], far[1])
+    td[2] = tq[2] + far[2].sign() * torch.exp(far[2].abs()).clamp(max=60.0)       # tails
+    td[3], tq[3] = (4.0 * near[3]).bfloat16().float(), tq[3].bfloat16().float()
+    td[4] = tq[4] + 0.37 * torch.floor(40.0 * at[4] ** 3)
+    td, tq = td.to(dtype), tq.to(dtype)
+    first, _ = check(td, tq, KS, temp_draft=0.9)
+    again = llc.llc_lml_bound(td, tq, KS, temp_draft=0.9, workspace=torch.ones(24 * V + 256, dtype=torch.uint8, device=DEV))
+    for name in ("bound", "relaxed", "tv"):
+        assert torch.equal(again[name], first[name]), name
