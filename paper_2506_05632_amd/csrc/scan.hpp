@@ -723,6 +723,7 @@ scan_kernel(const ScanParams p) {
   unsigned long long my_survivors = 0;
 
   if (!p.force_exact) {
+    bool in_range;  // every bound the warm-up finds can be handled by the main loop
     // ---- warm-up: approximate keys of a few hundred elements give every reduction a finite
     // tau.  Each wave takes one draft pair (wave w: pair w mod KB) and 64 groups of the chunk's
     // first tile, so a lane evaluates 8 elements on both sides.
@@ -796,6 +797,7 @@ scan_kernel(const ScanParams p) {
         if (used && tau < __builtin_huge_valf() && !(fabsf(tau) <= kTauLimit)) s.unsafe = 1;
       }
       __syncthreads();
+      in_range = s.unsafe == 0;  // (before the next barrier: behind it a faster wavefront's main loop may set it)
       if (tid == 0) {
         if (SHARED) {
           int m = s.tau[0];
@@ -815,7 +817,7 @@ scan_kernel(const ScanParams p) {
     // ---- main loop: level 1 on the upper half-words of every element, the rest on survivors.
     // No branch depends on the draft index: a padded draft (kbase + kk >= K) reads the last
     // real row and its half-words are tested like the others; only its hits are masked off.
-    if (!s.unsafe) {
+    if (in_range) {
       lse_ran = true;
       constexpr int KD = SHARED ? 1 : KT;
       const elem *drow[KD];

@@ -65,3 +65,22 @@ def test_binned_selection_in_one_workgroup_and_in_several_agree():
                 torch.testing.assert_close(out[name], outs[0][name], rtol=1e-6, atol=0)
             else:
                 assert torch.equal(out[name], outs[0][name]), name
+
+
+@pytest.mark.parametrize("B,K,V,per_draft", [(2, 4, 70003, False), (300, 8, 9001, False), (600, 4, 4099, False), (40, 4, 9001, True)])
+def test_rows_whose_bounds_leave_the_range_in_mid_scan(B, K, V, per_draft):
+    # a logit far above the others that the warm-up has not seen: the wavefront that meets it sends the workgroup
+    # to the exact form while the others are anywhere in the main loop, and the normalisers have to hold too
+    g = torch.Generator(device=DEV).manual_seed(V)
+    target = _rows(g, (B,), V, torch.float32).clone()
+    draft = _rows(g, (B, K) if per_draft else (B,), V, torch.float32).clone()
+    target[::2, V - 1] = 3000.0
+    target[1::3, V // 2] = 2500.0
+    draft[::3, ..., V - 2] = 2800.0
+    draft[1::4, ..., 2 * V // 3] = 1500.0
+    stats = llc.new_stats(DEV)
+    out = llc.llc_couple(draft, target, K, temp_target=0.8, temp_draft=1.1, seed=5, want_keys=True, stats=stats)
+    torch.cuda.synchronize()
+    ref = oracle_rows(draft, target, K, (0, B), kind="logits", temp_target=0.8, temp_draft=1.1, seed=5)
+    assert compare(out, ref) <= oracle_near_ties(ref)
+    assert stats_dict(stats)["slow_blocks"] > 0
