@@ -358,10 +358,11 @@ constexpr int kStageWords = 8 * 44;
 constexpr int kQueueWords = 40 * 11;
 constexpr int kMaxWaves = kMaxThreads / 64;
 
-// Dynamic LDS of a launch, behind the static part: min-first, a staging area and a queue per wavefront;
-// fused normalisers with one shared proposal, the lanes' two running sums.
+// Dynamic LDS of a launch of the min-first variants, behind the static part: a staging area and a queue per
+// wavefront; fused normalisers with one shared proposal, the lanes' two running sums.
 inline unsigned dynamic_lds(bool min_first, bool lane_sums, int threads) {
-  return (min_first ? (unsigned)(threads / 64) * 4u * (kStageWords + kQueueWords) : 0u) +
+  if (!min_first) return 0u;
+  return (unsigned)(threads / 64) * 4u * (kStageWords + kQueueWords) +
          (lane_sums ? 2u * (unsigned)threads * (unsigned)sizeof(double) : 0u);
 }
 
@@ -563,8 +564,11 @@ scan_kernel(const ScanParams p) {
   static_assert(!(MINF && MASKED), "the binned and pool-only passes draw one word per (index, draft)");
   __shared__ Lds s;
   extern __shared__ __align__(16) char s_dyn[];  // see dynamic_lds
-  // (with per-draft rows the sums stay in registers: in LDS they measured slower there)
-  constexpr bool kSumsInLds = LSE && SHARED;
+  // The two running sums of the min-first variants with one shared proposal live in LDS: those have no
+  // registers to spare for them across the main loop, and the compiler's own choice, scratch memory, costs a
+  // round trip through the memory system per tile.  (Elsewhere they stay in registers: in LDS they measured
+  // slower.)
+  constexpr bool kSumsInLds = LSE && SHARED && MINF;
 
   const int tid = threadIdx.x;
   const int nt = p.threads;  // of this workgroup
@@ -686,9 +690,6 @@ scan_kernel(const ScanParams p) {
   float lse_n[NL];
 #pragma unroll
   for (int kk = 0; kk < NL; ++kk) { lse_acc[kk] = 0.0; lse_n[kk] = -__builtin_huge_valf(); }
-  // With one shared proposal the two running sums live in LDS: the kernel has no two registers to
-  // spare for them across the main loop, and the compiler's own choice, scratch memory, costs a
-  // round trip through the memory system per tile.
   if (kSumsInLds) {
 #pragma unroll
     for (int kk = 0; kk < NL; ++kk) s_sums[kk * nt] = 0.0;
@@ -1191,8 +1192,9 @@ scan_kernel(const ScanParams p) {
         // unrolled twice, instead of the copies below, measured slower in both layouts): one where a tile is
         // 4 KB a wavefront or more, or registers are short; two for four drafts' bf16 rows and the target's,
         // whose 2.5 KB were too little in flight for the memory's latency (512 x 16 distinct drafts x 152 064:
-        // 486 us a call with one, 466 with two)
-        constexpr int kAhead = sizeof(elem) == 2 && !SHARED && !LSE && !MINF ? 2 : 1;
+        // 486 us a call with one, 466 with two), and for one shared proposal with normalisers (2 KB; 1024 x
+        // 128 256, K = 8: fp32 270 us with one, 258 with two, bf16 258, 247; K = 4, bf16 181, 163)
+        constexpr int kAhead = !MINF && (SHARED ? LSE : sizeof(elem) == 2 && !LSE) ? 2 : 1;
         raw aq = raw(), ad[KD], bq[kAhead], bd[kAhead][KD];
         uint32_t ab = 0, bb[kAhead];
         const int g0 = g_begin + tid;
