@@ -219,6 +219,7 @@ struct TopmParams {
   uint8_t *accept;
   float *keyX, *keyY;
   llc_stats *stats;
+  int at_once;  // drafts whose candidates share the list (launcher)
 };
 
 // Theorem 1's bound per row (diagnostics): one workgroup sorts a row by q/p and sums.

@@ -6,7 +6,10 @@
 // once: ln S - x/T for logits and log-weights, S/p for probabilities, reduced with the usual tie rule
 // (smaller key, then smaller token id, then smaller k).  The band covers the approximation's error on both
 // sides with room for every key within 1e-6 of the winner's, so nothing that could win, or make the winner a
-// near-tie, is left out.
+// near-tie, is left out.  Where there are many drafts they go through the list in parts, so that it holds their
+// candidates however many there are; what overflows it all the same is evaluated exactly entry by entry.
+#include <cmath>
+
 #include "scan.hpp"
 
 namespace llc {
@@ -42,11 +45,44 @@ struct Race {
   unsigned long long best, where, second;  // ordered images of the keys; where = (id, k)
 };
 
+// The same in registers (id -1: nothing yet); fold takes one more entry, or what others found, into it.
+struct Best {
+  double key;
+  int id, k;
+  double sec;
+};
+__device__ __forceinline__ void fold(Best &v, const Best &c) {
+  if (c.id < 0) return;
+  const bool wins = v.id < 0 || c.key < v.key || (c.key == v.key && (c.id < v.id || (c.id == v.id && c.k < v.k)));
+  double sec = fmin(v.sec, c.sec);
+  if (v.id >= 0 && v.id != c.id) sec = fmin(sec, wins ? v.key : c.key);
+  if (wins) v = c;
+  v.sec = sec;
+}
+__device__ __forceinline__ Best wave_best(Best v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    Best o;
+    o.key = __shfl_xor(v.key, d);
+    o.id = __shfl_xor(v.id, d);
+    o.k = __shfl_xor(v.k, d);
+    o.sec = __shfl_xor(v.sec, d);
+    fold(v, o);
+  }
+  return v;
+}
+__device__ __forceinline__ void store_best(Race &r, const Best &v) {
+  if (v.id < 0) return;
+  r.best = ord64(v.key);
+  r.where = ((unsigned long long)(uint32_t)v.id << 32) | (uint32_t)v.k;
+  r.second = ord64(v.sec);
+}
+
 // What bounds it: instruction issue (two Philox blocks an entry), then the latency of its phases.  The exact
 // keys are two fp64 logarithms each: taken by every wavefront for its own list, as before, they were more
 // than half of all instructions (1024 rows, K = 8, 50 entries, with keys: 27 us of kernel time, now 18).
-template <bool PROBS>
-__global__ void __launch_bounds__(kBlock) topm_kernel(const TopmParams p) {
+template <bool PROBS, bool MANY>
+__global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   __shared__ double c_key[kCandidates];
   __shared__ int c_id[kCandidates], c_k[kCandidates];  // c_k: the draft, K more for a pool entry
   __shared__ float c_v[kCandidates];
@@ -61,7 +97,8 @@ __global__ void __launch_bounds__(kBlock) topm_kernel(const TopmParams p) {
   double *s_lse = reinterpret_cast<double *>(race + K + 1);  // [K]: where every draft has its own list
 
   const long long b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, nt = blockDim.x;
+  const int waves = blockDim.x >> 6, nt = blockDim.x;
+  int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool logits = p.kind == LLC_LOGITS;
   const unsigned long long row = p.row_offset + (unsigned long long)b;
   const uint32_t row_lo = (uint32_t)row, row_hi = (uint32_t)(row >> 32);
@@ -98,82 +135,6 @@ __global__ void __launch_bounds__(kBlock) topm_kernel(const TopmParams p) {
     }
   };
 
-  // ---- draft side: one wavefront per list, lanes over its entries
-  for (int k = wave; k < K; k += waves) {
-    const long long off = draft_off(k);
-    const float T = draft_temp(k);
-    const bool t_ok = T > 0.0f && T < inf;
-    const float c = kLog2e / T;
-    tau = inf;
-    for (int e0 = 0; e0 < p.Md; e0 += 64) {
-      const int e = e0 + lane;
-      int id = -1;
-      float v = 0.0f;
-      if (e < p.Md) { id = p.draft_ids[off + e]; v = widen_at(p.draft_val, p.dtype, off + e); }
-      const bool has = t_ok && has_mass(id, v, PROBS);
-      const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
-      consider(has, id, v, x, c, k);
-    }
-  }
-  // ---- pool: all (k, target entry) pairs over the workgroup, the last wavefronts first (the first ones
-  // have had the more lists)
-  {
-    const float c = kLog2e / Tq;
-    const long long items = (long long)K * p.Mt;
-    tau = inf;
-    for (long long i0 = (long long)(waves - 1 - wave) * 64; i0 < items; i0 += nt) {
-      const long long it = i0 + lane;
-      int id = -1, k = 0;
-      float v = 0.0f;
-      if (it < items) {
-        k = (int)((unsigned)it / (unsigned)p.Mt);  // (items < 2^26)
-        const int e = (int)((unsigned)it % (unsigned)p.Mt);
-        id = t_ids[e];
-        v = widen_at(p.target_val, p.dtype, t_off + e);
-      }
-      const bool has = has_mass(id, v, PROBS);
-      const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
-      consider(has, id, v, x, c, K + k);
-    }
-  }
-  // ---- normalisers, only for reported keys (the argmins and near-ties need none): one wavefront per list
-  if (!PROBS && (p.keyX != nullptr || p.keyY != nullptr)) {
-    for (int l = waves - 1 - wave; l <= (one_list ? 1 : K); l += waves) {
-      const bool target = l == 0;  // list 0 the target's, l > 0 draft l - 1's
-      const int M = target ? p.Mt : p.Md;
-      const long long off = target ? t_off : draft_off(l - 1);
-      const int32_t *ids = target ? t_ids : p.draft_ids + off;
-      const void *val = target ? p.target_val : p.draft_val;
-      const float T = target ? Tq : draft_temp(l - 1);
-      float m = -inf;
-      for (int e = lane; e < M; e += 64) {
-        const float v = widen_at(val, p.dtype, off + e);
-        if (has_mass(ids[e], v, false)) m = fmaxf(m, v);
-      }
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-      double sum = 0.0;
-      if (m > -inf) {
-        for (int e = lane; e < M; e += 64) {
-          const float v = widen_at(val, p.dtype, off + e);
-          if (has_mass(ids[e], v, false)) sum += exp(((double)v - (double)m) / (double)T);
-        }
-      }
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
-      if (lane == 0) {
-        const bool ok = m > -inf && T > 0.0f && T < inf;
-        const double lse = ok ? (double)m / (double)T + log(sum) : -__builtin_huge_val();
-        if (target) s_lse_target = lse;
-        else if (one_list) s_lse_draft = lse;
-        else s_lse[l - 1] = lse;
-      }
-    }
-  }
-  __syncthreads();
-
-  // ---- exact keys of the list, in three rounds: the smallest key, the smallest (id, k) that holds it, the
-  // smallest key at another id
   const double huge = __builtin_huge_val();
   auto offer = [&](const int round, const int tag, const int id, const double key) {
     if (!(key < huge)) return;
@@ -187,39 +148,149 @@ __global__ void __launch_bounds__(kBlock) topm_kernel(const TopmParams p) {
       atomicMin(&r.second, o);
     }
   };
-  const int n = s_count;
-  if (n <= kCandidates) {  // uniform
-    for (int c = tid; c < n; c += nt) {
-      const int tag = c_k[c];
-      c_key[c] = exact_key<PROBS>(exact_race_time(c_x[c]), c_v[c], (double)(tag >= K ? Tq : draft_temp(tag)));
-      offer(0, tag, c_id[c], c_key[c]);
+  // entry e of list (k, or the target's for all k): its exact key as a reduction of its own
+  auto exact_entry = [&](const bool pool, const int k, const int e) {
+    const long long off = (pool ? t_off : draft_off(k)) + e;
+    const int id = pool ? p.target_ids[off] : p.draft_ids[off];
+    const float v = widen_at(pool ? p.target_val : p.draft_val, p.dtype, off);
+    const float T = pool ? Tq : draft_temp(k);
+    Best c = {huge, -1, k, huge};
+    if (has_mass(id, v, PROBS) && T > 0.0f && T < inf) {
+      const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
+      c.key = exact_key<PROBS>(exact_race_time(x), v, (double)T);
+      c.id = id;
+    }
+    return c;
+  };
+  int k0 = 0;
+  do {
+    if (MANY) {  // (or what is formed from them for every part below is kept, and spills, across the whole loop)
+      asm volatile("" : "+v"(tid));
+      lane = tid & 63;
+      wave = tid >> 6;
+    }
+    const int k1 = MANY ? min(k0 + p.at_once, K) : K;
+    const bool last = !MANY || k1 == K;  // with the pool and the normalisers
+    // ---- draft side: one wavefront per list, lanes over its entries
+    for (int k = k0 + wave; k < k1; k += waves) {
+      const long long off = draft_off(k);
+      const float T = draft_temp(k);
+      const bool t_ok = T > 0.0f && T < inf;
+      const float c = kLog2e / T;
+      tau = inf;
+      for (int e0 = 0; e0 < p.Md; e0 += 64) {
+        const int e = e0 + lane;
+        int id = -1;
+        float v = 0.0f;
+        if (e < p.Md) { id = p.draft_ids[off + e]; v = widen_at(p.draft_val, p.dtype, off + e); }
+        const bool has = t_ok && has_mass(id, v, PROBS);
+        const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
+        consider(has, id, v, x, c, k);
+      }
+    }
+    if (last) {
+      // ---- pool: all (k, target entry) pairs over the workgroup, the last wavefronts first (the first ones
+      // have had the more lists)
+      {
+        const float c = kLog2e / Tq;
+        const long long items = (long long)K * p.Mt;
+        tau = inf;
+        for (long long i0 = (long long)(waves - 1 - wave) * 64; i0 < items; i0 += nt) {
+          const long long it = i0 + lane;
+          int id = -1, k = 0;
+          float v = 0.0f;
+          if (it < items) {
+            k = (int)((unsigned)it / (unsigned)p.Mt);  // (items < 2^26)
+            const int e = (int)((unsigned)it % (unsigned)p.Mt);
+            id = t_ids[e];
+            v = widen_at(p.target_val, p.dtype, t_off + e);
+          }
+          const bool has = has_mass(id, v, PROBS);
+          const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
+          consider(has, id, v, x, c, K + k);
+        }
+      }
+      // ---- normalisers, only for reported keys (the argmins and near-ties need none): one wavefront per list
+      if (!PROBS && (p.keyX != nullptr || p.keyY != nullptr)) {
+        for (int l = waves - 1 - wave; l <= (one_list ? 1 : K); l += waves) {
+          const bool target = l == 0;  // list 0 the target's, l > 0 draft l - 1's
+          const int M = target ? p.Mt : p.Md;
+          const long long off = target ? t_off : draft_off(l - 1);
+          const int32_t *ids = target ? t_ids : p.draft_ids + off;
+          const void *val = target ? p.target_val : p.draft_val;
+          const float T = target ? Tq : draft_temp(l - 1);
+          float m = -inf;
+          for (int e = lane; e < M; e += 64) {
+            const float v = widen_at(val, p.dtype, off + e);
+            if (has_mass(ids[e], v, false)) m = fmaxf(m, v);
+          }
+#pragma unroll
+          for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+          double sum = 0.0;
+          if (m > -inf) {
+            for (int e = lane; e < M; e += 64) {
+              const float v = widen_at(val, p.dtype, off + e);
+              if (has_mass(ids[e], v, false)) sum += exp(((double)v - (double)m) / (double)T);
+            }
+          }
+#pragma unroll
+          for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+          if (lane == 0) {
+            const bool ok = m > -inf && T > 0.0f && T < inf;
+            const double lse = ok ? (double)m / (double)T + log(sum) : -__builtin_huge_val();
+            if (target) s_lse_target = lse;
+            else if (one_list) s_lse_draft = lse;
+            else s_lse[l - 1] = lse;
+          }
+        }
+      }
     }
     __syncthreads();
-    for (int c = tid; c < n; c += nt) offer(1, c_k[c], c_id[c], c_key[c]);
-    __syncthreads();
-    for (int c = tid; c < n; c += nt) offer(2, c_k[c], c_id[c], c_key[c]);
-  } else {
-    // more candidates than the list holds (many equal values, or values beyond fp32's measure): every entry
-#pragma unroll 1
-    for (int round = 0; round < 3; ++round) {
-      const long long drafts = (long long)K * p.Md, items = drafts + (long long)K * p.Mt;
-#pragma unroll 1
-      for (long long it = tid; it < items; it += nt) {
-        const bool pool = it >= drafts;
-        const unsigned j = (unsigned)(pool ? it - drafts : it), M = (unsigned)(pool ? p.Mt : p.Md);
-        const int k = (int)(j / M), e = (int)(j % M);
-        const long long off = (pool ? t_off : draft_off(k)) + e;
-        const int id = pool ? p.target_ids[off] : p.draft_ids[off];
-        const float v = widen_at(pool ? p.target_val : p.draft_val, p.dtype, off);
-        const float T = pool ? Tq : draft_temp(k);
-        if (!has_mass(id, v, PROBS) || !(T > 0.0f && T < inf)) continue;
-        const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
-        offer(round, pool ? K + k : k, id, exact_key<PROBS>(exact_race_time(x), v, (double)T));
+
+    // ---- exact keys of the list, in three rounds: the smallest key, the smallest (id, k) that holds it, the
+    // smallest key at another id
+    const int n = s_count;
+    if (n <= kCandidates) {  // uniform
+      for (int c = tid; c < n; c += nt) {
+        const int tag = c_k[c];
+        c_key[c] = exact_key<PROBS>(exact_race_time(c_x[c]), c_v[c], (double)(tag >= K ? Tq : draft_temp(tag)));
+        offer(0, tag, c_id[c], c_key[c]);
       }
       __syncthreads();
+      for (int c = tid; c < n; c += nt) offer(1, c_k[c], c_id[c], c_key[c]);
+      __syncthreads();
+      for (int c = tid; c < n; c += nt) offer(2, c_k[c], c_id[c], c_key[c]);
+    } else {
+      // more candidates than the list holds (one id over and over, or values beyond fp32's measure): every entry
+#pragma unroll 1
+      for (int k = k0 + wave; k < k1; k += waves) {
+        Best v = {huge, -1, k, huge};
+#pragma unroll 1
+        for (int e = lane; e < p.Md; e += 64) fold(v, exact_entry(false, k, e));
+        v = wave_best(v);
+        if (lane == 0) store_best(race[k], v);
+      }
+      if (last) {  // uniform
+        Best v = {huge, -1, 0, huge};
+        const unsigned items = (unsigned)K * (unsigned)p.Mt;
+#pragma unroll 1
+        for (unsigned it = tid; it < items; it += nt) fold(v, exact_entry(true, (int)(it / (unsigned)p.Mt), (int)(it % (unsigned)p.Mt)));
+        v = wave_best(v);
+        if (lane == 0) { c_key[2 * wave] = v.key; c_key[2 * wave + 1] = v.sec; c_id[wave] = v.id; c_k[wave] = v.k; }
+        __syncthreads();
+        if (tid == 0) {
+          for (int w = 1; w < waves; ++w) fold(v, Best{c_key[2 * w], c_id[w], c_k[w], c_key[2 * w + 1]});
+          store_best(race[K], v);
+        }
+      }
     }
-  }
-  __syncthreads();
+    __syncthreads();
+    if (MANY) {
+      if (tid == 0) s_count = 0;
+      __syncthreads();
+      k0 = k1;
+    }
+  } while (MANY && k0 < K);
 
   // ---- outputs
   const int y = race[K].where != ~0ull ? (int)(race[K].where >> 32) : -1;
@@ -258,13 +329,21 @@ __global__ void __launch_bounds__(kBlock) topm_kernel(const TopmParams p) {
 
 }  // namespace
 
-hipError_t launch_topm(hipStream_t s, const TopmParams &p) {
-  if (p.B == 0) return hipSuccess;
+hipError_t launch_topm(hipStream_t s, const TopmParams &params) {
+  if (params.B == 0) return hipSuccess;
+  TopmParams p = params;
+  // How many drafts share the list at a time: a list of r rounds of 64 entries leaves 1 + 1/2 + .. + 1/r
+  // candidates on average, and the list has room for the pool's few dozen besides.  All at once up to 400 drafts
+  // of 64 entries, 167 of 256, 50 of the longest.  (K = 512, lists of 50, 1024 rows, where all at once overflows:
+  // 1874 us, now 350; K = 256 in parts of 64 measured 182 against 166.)
+  p.at_once = (int)(400.0 / (1.0 + std::log((double)((p.Md + 63) / 64))));
   // (four wavefronts a row: 1024 rows are resident at once; eight, with half as many rows resident, measured
   // 26.4 against 25.1 us a call at 1024 rows, K = 8, lists of 256)
   const unsigned lds = (unsigned)((p.K + 1) * sizeof(Race) + p.K * sizeof(double));
-  if (p.kind == LLC_PROBS) hipLaunchKernelGGL(topm_kernel<true>, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
-  else hipLaunchKernelGGL(topm_kernel<false>, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
+  const bool probs = p.kind == LLC_PROBS, many = p.K > p.at_once;
+  auto *kernel = probs ? (many ? topm_kernel<true, true> : topm_kernel<true, false>)
+                       : (many ? topm_kernel<false, true> : topm_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
   return hipGetLastError();
 }
 

@@ -47,3 +47,49 @@ def test_a_full_list_gives_the_same():
     assert out["X"].shape == (B, K) and (out["X"] >= 0).all() and (flat["X"] >= 0).all()
     ref = oracle_topm(ids[:B], 0 * val[:B], ids[B:], 0 * val[B:], K, seed=1)
     assert compare(flat, ref) <= oracle_near_ties(ref)
+
+
+@pytest.mark.parametrize("kind,dtype", [("logits", torch.float32), ("logits", torch.bfloat16), ("probs", torch.float32)])
+@pytest.mark.parametrize("K,M", [(400, 50), (401, 50), (167, 256), (168, 256), (1024, 60), (130, 1100)])
+def test_many_drafts(kind, dtype, K, M):
+    # as many drafts as share the list of candidates, one more, many
+    g = torch.Generator(device=DEV).manual_seed(K)
+    B = 3
+    ids = torch.stack([torch.randperm(20000, generator=g, device=DEV)[:M] for _ in range(2 * B)]).int()
+    val = torch.randn(2 * B, M, generator=g, device=DEV)
+    if kind == "probs":
+        val = torch.softmax(2 * val, dim=1)
+    val = val.to(dtype)
+    val[0, 3:] = 0.0 if kind == "probs" else float("-inf")
+    stats = llc.new_stats(DEV)
+    args = (ids[:B].contiguous(), val[:B].contiguous(), ids[B:].contiguous(), val[B:].contiguous(), K)
+    out = llc.llc_couple_topm(*args, kind=kind, seed=3, want_keys=True, stats=stats)
+    torch.cuda.synchronize()
+    ref = oracle_topm(*args, kind=kind, seed=3)
+    assert compare(out, ref) <= oracle_near_ties(ref)
+    assert stats_dict(stats)["near_ties"] == oracle_near_ties(ref)
+    assert stats_dict(stats)["exact_evals"] == 2 * K * M * B - K * (M - 3)
+
+
+@pytest.mark.parametrize("kind", ["logits", "logw", "probs"])
+@pytest.mark.parametrize("K", [2, 70])
+def test_a_list_of_candidates_that_overflows_with_finite_keys(kind, K):
+    # one id over and over with one value (700 equal keys, all of them the winner's if it wins), others beside it,
+    # on either side: every entry is evaluated, and only other ids count as runners-up
+    g = torch.Generator(device=DEV).manual_seed(K)
+    B, M = 4, 760
+    ids = torch.stack([torch.randperm(9000, generator=g, device=DEV)[:M] for _ in range(2 * B)]).int()
+    val = torch.randn(2 * B, M, generator=g, device=DEV)
+    val[:, 40:740] = 9.0
+    ids[:, 40:740] = ids[:, 40:41]
+    val[1] = torch.randn(M, generator=g, device=DEV)   # (rows in which one side's candidates are few)
+    val[B + 2] = torch.randn(M, generator=g, device=DEV)
+    if kind == "probs":
+        val = torch.exp(val)
+    stats = llc.new_stats(DEV)
+    args = (ids[:B].contiguous(), val[:B].contiguous(), ids[B:].contiguous(), val[B:].contiguous(), K)
+    out = llc.llc_couple_topm(*args, kind=kind, seed=5, temp_target=0.8, temp_draft=1.3, want_keys=True, stats=stats)
+    torch.cuda.synchronize()
+    ref = oracle_topm(*args, kind=kind, seed=5, temp_target=0.8, temp_draft=1.3)
+    assert compare(out, ref) <= oracle_near_ties(ref)
+    assert stats_dict(stats)["near_ties"] == oracle_near_ties(ref)
