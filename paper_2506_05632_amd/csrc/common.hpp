@@ -200,7 +200,7 @@ struct StrongStepParams {
   llc_stats *stats;          // optional: near_ties of the emitted positions
 };
 
-// Algorithm 1 on candidate lists: one workgroup per row, every key exact.
+// Algorithm 1 on candidate lists: one workgroup per row, exact keys for the entries an fp32 key lets through.
 struct TopmParams {
   long long B;
   int K, Md, Mt;
@@ -222,7 +222,7 @@ struct TopmParams {
   int at_once;  // drafts whose candidates share the list (launcher)
 };
 
-// Theorem 1's bound per row (diagnostics): one workgroup sorts a row by q/p and sums.
+// Theorem 1's bound per row (diagnostics): one workgroup orders a row by q/p, by buckets or by sorting, and sums.
 constexpr int kLmlMaxK = LLC_LML_MAX_K;
 constexpr int kLmlSlots = 512;  // two 512-thread workgroups on each of 256 CUs: more cannot be resident
 struct LmlParams {

@@ -390,8 +390,8 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
 
 // The rows it takes.  Shorter ones are quicker sorted (fewer fixed steps), from about 40 000 entries on if the
 // inputs are bf16, whose many ties cost the ordering in LDS (us a call, buckets against sorting: fp32 8 192
-// entries, 1 row 114 : 102, 16 384: 171 : 184, 32 000: 281 : 346; bf16 32 000, 64 rows 401 : 386, 128 256: 1252 :
-// 1556; 1024 rows x 128 256: fp32 3245 : 7517, bf16 3700 : 5750).
+// entries, 1 row 114 : 102, 12 288: 136 : 140, 32 000: 274 : 347; bf16 40 960, 64 rows 473 : 484, 512 rows 662 :
+// 895, 128 256: 64 rows 1219 : 1555, 512 rows 1740 : 2885; 1024 rows x 128 256 fp32 3150 : 7515).
 constexpr int kBucketMinV = 12288, kBucketMinVNarrow = 40960, kBucketMaxV = 1 << 18;
 // The sample, and the buckets that its quantiles make.  A row is left to the sorting kernel if one bucket
 // outgrows a group, and one such row costs the call a whole sort: with 127 buckets of 16 samples each the
@@ -645,11 +645,11 @@ __device__ __forceinline__ int padded(int j) { return j + j / kR; }
 
 // One workgroup per row, two per CU.  What bounds it: instruction issue and the latency of LDS between
 // barriers, not memory: the row is read three times and a bucket byte, the masses and the place are
-// written and read once (by count 50 bytes an entry of 8 input bytes, where the sorting form moves 160).  Of the 1.6 ms that two rows of
-// 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
+// written and read once (by the memory counters 57 bytes an entry of 8 input bytes, 159 in the sorting
+// form).  Of the 1.6 ms that two rows of 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
 // third pass 0.4 (positions 0.22, masses 0.16), the groups 0.8 (cells and their starts 0.45, the order inside
 // cells 0.17, running sums 0.15, terms 0.05).  An order by the exact ratio, general divisions and a branch
-// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.05.
+// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.15.
 // All sums run in an order that does not depend on how the wavefronts interleave: entries keep the row's
 // order within a bucket, and within a group they are ordered by their places, then as they lie in the bucket.
 // PAIRS: room for that many pairs of list sizes (more than four sizes do not fit 128 registers with the

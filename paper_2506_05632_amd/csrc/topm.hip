@@ -80,7 +80,7 @@ __device__ __forceinline__ void store_best(Race &r, const Best &v) {
 
 // What bounds it: instruction issue (two Philox blocks an entry), then the latency of its phases.  The exact
 // keys are two fp64 logarithms each: taken by every wavefront for its own list, as before, they were more
-// than half of all instructions (1024 rows, K = 8, 50 entries, with keys: 27 us of kernel time, now 18).
+// than half of all instructions (1024 rows, K = 8, 50 entries, with keys: 26 us under the profiler, now 11 to 14).
 template <bool PROBS, bool MANY>
 __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   __shared__ double c_key[kCandidates];

@@ -45,6 +45,10 @@ def test_a_full_list_gives_the_same():
     flat = llc.llc_couple_topm(ids[:B].contiguous(), 0 * val[:B], ids[B:].contiguous(), 0 * val[B:], K, seed=1)
     torch.cuda.synchronize()
     assert out["X"].shape == (B, K) and (out["X"] >= 0).all() and (flat["X"] >= 0).all()
+    # (at 1e30 ln S is lost in the fp64 of x / T: every key of a reduction is the same, and the smallest id wins)
+    assert (out["X"] == ids[:B].amin(dim=1, keepdim=True)).all() and torch.equal(out["Y"], ids[B:].amin(dim=1))
+    assert torch.equal(out["accept"].bool(), out["X"][:, 0] == out["Y"])
+    assert torch.equal(out["match_k"], torch.where(out["X"][:, 0] == out["Y"], 0, -1).int())
     ref = oracle_topm(ids[:B], 0 * val[:B], ids[B:], 0 * val[B:], K, seed=1)
     assert compare(flat, ref) <= oracle_near_ties(ref)
 

@@ -36,8 +36,8 @@ def _both(draft, target, K, **kw):
 
 
 def test_two_calls_in_a_row_the_second_smaller():
-    # first call: config 2's shape (bf16, rows spread over several workgroups, so the rows' shared
-    # running bests in the scratch are in use); second call: fewer, shorter rows, other layout
+    # first call: config 2's shape (bf16); second call: fewer, shorter rows, other layout, its rows spread over
+    # several workgroups, so that their partial results in the scratch are in use
     w = workloads.make(2, DEV)
     _both(w.draft, w.target, w.K, temp_target=w.temp_target, temp_draft=w.temp_draft, seed=w.seed)
     g = torch.Generator(device=DEV).manual_seed(5)
