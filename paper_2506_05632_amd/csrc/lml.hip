@@ -820,7 +820,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
     mq = (float)block_max((double)mq, s_red);
     if (!(mp > ninf && mq > ninf)) break;  // (uniform, as the next) a side without mass
     const double center = uniform(pl.log_ratio(mp, mq));
-    if (fabs(center - pl.center) < (double)kFar - kReach) break;
+    if (attempt > 0 || fabs(center - pl.center) < (double)kFar - kReach) break;
     pl.center = center;
   }
   nb = uniform(nb);
