@@ -535,6 +535,12 @@ __device__ __forceinline__ int place_of(float distance) {
 }
 __device__ __forceinline__ float distance_of(int place) { return __int_as_float(place ^ ((place >> 31) & 0x7FFFFFFF)); }
 
+// An entry on its way to its bucket.
+struct Entry {
+  float p, q;
+  int place;
+};
+
 // The last bucket whose splitter is not above `place` (split[0] stands for minus infinity).
 __device__ __forceinline__ int bucket_of(const int *split, int nb, int place) {
   int b = 0;
@@ -645,11 +651,11 @@ __device__ __forceinline__ int padded(int j) { return j + j / kR; }
 
 // One workgroup per row, two per CU.  What bounds it: instruction issue and the latency of LDS between
 // barriers, not memory: the row is read three times and a bucket byte, the masses and the place are
-// written and read once (by the memory counters 57 bytes an entry of 8 input bytes, 159 in the sorting
+// written and read once (by the memory counters 56 bytes an entry of 8 input bytes, 159 in the sorting
 // form).  Of the 1.6 ms that two rows of 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
 // third pass 0.4 (positions 0.22, masses 0.16), the groups 0.8 (cells and their starts 0.45, the order inside
 // cells 0.17, running sums 0.15, terms 0.05).  An order by the exact ratio, general divisions and a branch
-// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.15.
+// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.13.
 // All sums run in an order that does not depend on how the wavefronts interleave: entries keep the row's
 // order within a bucket, and within a group they are ordered by their places, then as they lie in the bucket.
 // PAIRS: room for that many pairs of list sizes (more than four sizes do not fit 128 registers with the
@@ -680,9 +686,8 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
   const E *prow = reinterpret_cast<const E *>(p.draft) + b_row * p.draft_stride_b;
   const E *qrow = reinterpret_cast<const E *>(p.target) + b_row * p.target_stride_b;
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
-  float2 *bucketed = reinterpret_cast<float2 *>(work);
-  unsigned char *ids = reinterpret_cast<unsigned char *>(work + 8u * (size_t)V);
-  int *places = reinterpret_cast<int *>(work + 12u * (size_t)V);  // beside the masses
+  Entry *bucketed = reinterpret_cast<Entry *>(work);
+  unsigned char *ids = reinterpret_cast<unsigned char *>(work + 12u * (size_t)V);
   const float none = PROBS ? 0.0f : -__builtin_huge_valf();
   const float ninf = -__builtin_huge_valf();
 
@@ -963,8 +968,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       if (b != kNoBucket) {
         const int g = s_next[b] + (pos - s_start[b]);
         if (g < s_off[b + 1]) {  // (always; a bucket is never written past its end)
-          bucketed[g] = m;
-          places[g] = place_of(pl.distance(in.x, in.y));
+          bucketed[g] = Entry{m.x, m.y, place_of(pl.distance(in.x, in.y))};
         }
       }
       if (hp && hq && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
@@ -1027,7 +1031,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       // one place: any order will do, so every entry counts as the first of them
 #pragma unroll 1
       for (int i = me; i < n; i += kThreads) {
-        const float2 m = bucketed[first + i];
+        const float2 m = make_float2(bucketed[first + i].p, bucketed[first + i].q);
         pg += (double)m.x;
         qg += (double)m.y;
         add_term(m, p_before, q_before);
@@ -1044,8 +1048,9 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
 #pragma unroll
     for (int e = 0; e < kR; ++e) {
       const int i = e * kThreads + me;
-      mass[e] = bucketed[first + min(i, n - 1)];
-      place[e] = places[first + min(i, n - 1)];
+      const Entry in = bucketed[first + min(i, n - 1)];
+      mass[e] = make_float2(in.p, in.q);
+      place[e] = in.place;
     }
     __syncthreads();  // the group before is done with
     if (me == 0) s_info[1] = 0;
