@@ -54,7 +54,7 @@ __device__ __forceinline__ void finish_row(const FinalizeParams &p, const long l
       y = pool.idx;
       if (lane == 0) {
         p.Y[b] = y;
-        if (p.count_pool) {
+        if (p.count_pool && p.stats != nullptr) {
           if (y < 0) ++degenerate;
           else if (near_tie(pool.key, pool.sec, p.log_kind)) ++near;
         }
@@ -74,7 +74,7 @@ __device__ __forceinline__ void finish_row(const FinalizeParams &p, const long l
     const bool mine = k < p.K && (lane & (width - 1)) == 0;
     if (mine) {
       p.X[b * p.K + k] = m.idx;
-      if (p.count_draft) {
+      if (p.count_draft && p.stats != nullptr) {
         if (m.idx < 0) ++degenerate;
         else if (near_tie(m.key, m.sec, p.log_kind)) ++near;
       }

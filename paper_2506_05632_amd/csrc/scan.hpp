@@ -131,6 +131,32 @@ __device__ __forceinline__ void philox_blocks(uint32_t g, uint32_t pair_base, ui
   for (int m = 0; m < KB; ++m) { out[m][0] = c0[m]; out[m][1] = c1[m]; out[m][2] = c2[m]; out[m][3] = c3[m]; }
 }
 
+// The upper-half and the lower-half block of one draft pair and index group, as a loop: for the code that a
+// workgroup runs once (warm-up, exact keys), where instructions that are met for the first time cost more
+// than the loop's branches.
+__device__ __forceinline__ void philox_both_halves(uint32_t g, uint32_t pair, uint32_t row_lo, uint32_t row_hi, uint32_t k0,
+                                                   uint32_t k1, uint32_t (&up)[4], uint32_t (&lo)[4]) {
+  uint32_t c0[2] = {row_lo, row_lo}, c1[2] = {g, g}, c2[2] = {row_hi, row_hi}, c3[2] = {pair, pair | kLowBlock};
+#pragma unroll 1
+  for (int r = 0; r < 10; ++r) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const uint64_t pa = (uint64_t)c0[m] * 0xD2511F53ull;
+      const uint64_t pb = (uint64_t)c2[m] * 0xCD9E8D57ull;
+      const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1[m], k0);
+      const uint32_t n2 = xor3((uint32_t)(pa >> 32), c3[m], k1);
+      c1[m] = (uint32_t)pb;
+      c3[m] = (uint32_t)pa;
+      c0[m] = n0;
+      c2[m] = n2;
+    }
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+  up[0] = c0[0]; up[1] = c1[0]; up[2] = c2[0]; up[3] = c3[0];
+  lo[0] = c0[1]; lo[1] = c1[1]; lo[2] = c2[1]; lo[3] = c3[1];
+}
+
 // The 32-bit word of one element from the words its index selects in the upper-half and the
 // lower-half block of its draft pair: even drafts read the lower 16 bits, odd drafts the upper.
 __device__ __forceinline__ uint32_t element_word(uint32_t upper_word, uint32_t lower_word, int odd) {
@@ -248,6 +274,8 @@ __device__ __forceinline__ void unpack(const uint2 &r, float (&v)[4]) {
 __device__ __forceinline__ float in_scalar(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
+
+__device__ __forceinline__ int in_scalar_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Bins of four consecutive candidates (one byte each) and the mask they imply: a candidate whose
 // bin differs from the announced one carries no mass on the draft (decoder) side (paper Section
@@ -373,17 +401,13 @@ struct Lds {
   float lgK;             // min-first: log2 K, by which the level-1 bounds on the smallest time are raised (else 0)
   int count;             // records appended (may exceed kListCap)
   int unsafe;            // chunk must be redone in fp64
+  int in_range;          // every bound that the warm-up found can be handled by the main loop
   unsigned long long best[9];
   unsigned long long where[9];
   unsigned long long second[9];  // smallest exact key among entries whose index differs from the winner's
   unsigned long long n_survivors, n_exact;
   float cd23[8];         // per draft of this pass: log2(e) / T_k scaled by 2^23 ...
   int kok[8];            // ... and whether its temperature is usable (for lanes that pick a draft at run time)
-  struct Stage {         // one lane's tile, laid out for the wave (survivors' path)
-    uint32_t up[16];
-    float vq[4];
-    float vd[32];
-  } stage[kMaxWaves];
   int qn[kMaxWaves];     // min-first: candidates in each wavefront's queue
   int lse_redo;          // LSE: the running sums were not formed (the main loop was skipped) or are not finite
   float lse_wmax[kMaxWaves][9];  // LSE: per-wave references (whole numbers, in powers of two) ...
@@ -468,6 +492,18 @@ __device__ __forceinline__ void level2(Lds &s, float l2S, float vd, float vq, in
       if (a < tau_p) publish<KT, SHARED, PROBS, MINF>(s, KT, a);
     }
   }
+}
+
+// The smallest of the wavefront's values, in lane 63 (row and bank shifts instead of a trip through LDS
+// per step; a lane that a shift leaves without a neighbour keeps its own value).
+__device__ __forceinline__ int wave_min_to_last(int v) {
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));  // row_bcast:15 into rows 1 and 3
+  v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));  // row_bcast:31 into rows 2 and 3
+  return v;
 }
 
 // Offer an exact key to reduction `slot` (phase 1: smallest key).
@@ -563,6 +599,11 @@ scan_kernel(const ScanParams p) {
   constexpr int KT = 2 * KB;
   static_assert(!(MINF && MASKED), "the binned and pool-only passes draw one word per (index, draft)");
   __shared__ Lds s;
+  // survivors' path: tiles of as many lanes as a wavefront has lanes for the elements of (a lane's half-words of
+  // KB pairs, four target values, the group's number (padded), the draft values)
+  constexpr int kCand = 64 / (8 * KB), kCandWords = 4 * KB + 8 + 4 * (SHARED ? 1 : KT);
+  constexpr int kWaves = lean_variant(SHARED, KB, LSE) ? kMaxWaves : kMaxWaves / 2;
+  __shared__ __align__(16) uint32_t s_stage[MINF ? 4 : kWaves * kCand * kCandWords];
   extern __shared__ __align__(16) char s_dyn[];  // see dynamic_lds
   // The two running sums of the min-first variants with one shared proposal live in LDS: those have no
   // registers to spare for them across the main loop, and the compiler's own choice, scratch memory, costs a
@@ -583,9 +624,22 @@ scan_kernel(const ScanParams p) {
     const unsigned per_xcd = gridDim.x >> 3;
     if (bid < (per_xcd << 3)) bid = (bid & 7u) * per_xcd + (bid >> 3);
   }
-  const int chunk = (int)(bid % (unsigned)p.n_chunks);
-  const int kg = (int)((bid / (unsigned)p.n_chunks) % (unsigned)p.n_kgroups);
-  const long long b = (long long)(bid / ((unsigned)p.n_chunks * (unsigned)p.n_kgroups));
+  int chunk = 0, kg = 0;
+  if (p.n_chunks > 1) {  // uniform, as below: a batch whose rows are one workgroup each divides nothing
+    chunk = (int)(bid % (unsigned)p.n_chunks);
+    bid /= (unsigned)p.n_chunks;
+  }
+  if (p.n_kgroups > 1) {
+    kg = (int)(bid % (unsigned)p.n_kgroups);
+    bid /= (unsigned)p.n_kgroups;
+  }
+  const long long b = (long long)bid;
+  // (a row's place in its tensors: b = outer * inner_count + inner, see RowMap)
+  unsigned b_outer = bid, b_inner = 0;
+  if (p.map.inner_count > 1) {
+    b_outer = bid / (unsigned)p.map.inner_count;
+    b_inner = bid - b_outer * (unsigned)p.map.inner_count;
+  }
   const int kbase = kg * KT;
   // same_race: every draft of the row uses the race times of draft 0 (the compression scheme's
   // baseline, in which all decoders share one set of random numbers; paper Section 5.3)
@@ -599,11 +653,11 @@ scan_kernel(const ScanParams p) {
   const bool with_pool = p.no_pool == 0;  // false: draft-side reductions only, the target is not read
   const float fill = PROBS ? 0.0f : -__builtin_huge_valf();
 
-  const unsigned long long row = p.row_offset + p.map.row_of(b);
+  const unsigned long long row = p.row_offset + (unsigned long long)(b_outer * p.map.row_outer + b_inner * p.map.row_inner);
   const uint32_t row_lo = (uint32_t)row, row_hi = (uint32_t)(row >> 32);
 
-  const elem *trow = reinterpret_cast<const elem *>(p.target) + p.map.target_off(b);
-  const elem *drow0 = reinterpret_cast<const elem *>(p.draft) + p.map.draft_off(b);
+  const elem *trow = reinterpret_cast<const elem *>(p.target) + (b_outer * p.map.target_outer + b_inner * p.map.target_inner);
+  const elem *drow0 = reinterpret_cast<const elem *>(p.draft) + (b_outer * p.map.draft_outer + b_inner * p.map.draft_inner);
   if (p.draft_row_off != nullptr) {
     const long long off = p.draft_row_off[b];
     if (off < 0) {
@@ -631,6 +685,44 @@ scan_kernel(const ScanParams p) {
   // on the draft side
   const bool binned = MASKED && p.bins != nullptr;
   const uint8_t *brow = binned ? p.bins + b * p.bins_stride_b : nullptr;
+  const bool no_draft = MASKED && p.no_draft != 0;  // pool only, see below
+
+  // One tile (one group per thread).  Without a pool the target-side exponent is pinned at 0 (threshold 0:
+  // never a hit).
+  using raw = typename T::raw;
+  constexpr int KD = SHARED ? 1 : KT;
+  const elem *drow[KD];
+#pragma unroll
+  for (int kk = 0; kk < KD; ++kk)
+    drow[kk] = drow0 + (SHARED ? 0 : (long long)min(kbase + kk, p.K - 1) * p.draft_stride_k);
+  auto load_tile = [&](const int g, const bool interior, raw &rq, raw (&rd)[KD], uint32_t &rb) {
+    if (binned && !no_draft) rb = load_bins4(brow, g * 4, V);
+    if (interior) {
+      if (with_pool) rq = load_raw<T>(trow, g * 4);
+      if (!no_draft) {
+#pragma unroll
+        for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw<T>(drow[kk], g * 4);
+      }
+    } else {
+      if (with_pool) rq = load_raw_checked<T>(trow, g * 4, V, fill);
+      if (!no_draft) {
+#pragma unroll
+        for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw_checked<T>(drow[kk], g * 4, V, fill);
+      }
+    }
+  };
+  // A tile is interior when every lane's group is complete and inside the chunk: all rows
+  // are then read with unconditional vector loads.
+  const int n_interior = max(0, (min(g_end, V >> 2) - g_begin) / nt);
+  // The first tile's loads leave before anything else is set up.  It is also what the warm-up looks at
+  // (a chunk without an interior tile: every draft pair's first wavefront looks at its first 64 groups).
+  const int g_first = g_begin + (n_interior > 0 ? tid : ((tid >> 6) / KB) * 64 + (tid & 63));
+  raw aq = raw(), ad[KD];
+#pragma unroll
+  for (int kk = 0; kk < KD; ++kk) ad[kk] = raw();
+  uint32_t ab = 0;
+  if (!p.force_exact) load_tile(g_first, n_interior > 0, aq, ad, ab);
+
   int announced = -1;
   if (binned) {
     const int y = p.bin_of[b];
@@ -638,7 +730,6 @@ scan_kernel(const ScanParams p) {
   }
   // pool only (the encoder's pass of the binned selection): the draft rows are not read and no
   // candidate counts on the draft side, as if every bin differed from the announced one
-  const bool no_draft = MASKED && p.no_draft != 0;
   const bool draft_masked = binned || no_draft;
   if (no_draft) announced = -2;
 
@@ -648,8 +739,8 @@ scan_kernel(const ScanParams p) {
 #pragma unroll
   for (int kk = 0; kk < KT; ++kk) {
     const int k = kbase + kk;
-    float t = p.temp_draft_all;
-    if (p.temp_draft != nullptr && k < p.K) t = p.temp_draft[k];
+    float t = p.temp_draft_all;  // (one proposal for all drafts has one temperature)
+    if (!SHARED && p.temp_draft != nullptr && k < p.K) t = p.temp_draft[k];
     kok[kk] = (k < p.K) && (t > 0.0f) && (t < __builtin_huge_valf());
     cd23[kk] = PROBS ? 1.0f : in_scalar((kLog2e / t) * kTwo23);
   }
@@ -668,7 +759,7 @@ scan_kernel(const ScanParams p) {
 #pragma unroll
     for (int kk = 0; kk <= KT; ++kk) {
       float t = kk == KT ? Tq : p.temp_draft_all;
-      if (kk < KT && p.temp_draft != nullptr && kbase + kk < p.K) t = p.temp_draft[kbase + kk];
+      if (!SHARED && kk < KT && p.temp_draft != nullptr && kbase + kk < p.K) t = p.temp_draft[kbase + kk];
       const double c64 = 1.4426950408889634 / (double)t;
       // (hi rounded towards zero and lo kept above zero, so that lo has hi's sign and is not 0: an
       // entry of -inf then gives -inf in both products, never NaN)
@@ -701,10 +792,12 @@ scan_kernel(const ScanParams p) {
     s.tau[tid] = used ? 0x7F800000 : (int)0x80800000;  // ord32(+inf) : ord32(-inf)
     s.O[tid] = 0x7F800000;
     bool live = tid == KT && with_pool;
-    if (tid < KT && kbase + tid < p.K) {
+    if (tid < KT) {
       float t = p.temp_draft_all;
-      if (p.temp_draft != nullptr) t = p.temp_draft[kbase + tid];
-      live = (t > 0.0f) && (t < __builtin_huge_valf());
+      if (!SHARED && p.temp_draft != nullptr && kbase + tid < p.K) t = p.temp_draft[kbase + tid];
+      live = kbase + tid < p.K && (t > 0.0f) && (t < __builtin_huge_valf());
+      s.cd23[tid] = PROBS ? 1.0f : (kLog2e / t) * kTwo23;
+      s.kok[tid] = live ? 1 : 0;
     }
     s.OL[tid] = live ? 0x7F800000 : (int)0xFF800000;  // +inf until the warm-up has a bound : -inf
     s.best[tid] = kOrdInf64;
@@ -713,8 +806,6 @@ scan_kernel(const ScanParams p) {
   }
   if (tid < kMaxWaves) s.qn[tid] = 0;
   if (tid == 0) {
-#pragma unroll
-    for (int kk = 0; kk < KT; ++kk) { s.cd23[kk] = cd23[kk]; s.kok[kk] = kok[kk] ? 1 : 0; }
     s.lgK = lgK;
     s.count = 0; s.unsafe = p.force_exact ? 1 : 0; s.n_survivors = 0; s.n_exact = 0;
     s.lse_redo = 0;
@@ -724,28 +815,30 @@ scan_kernel(const ScanParams p) {
   unsigned long long my_survivors = 0;
 
   if (!p.force_exact) {
-    bool in_range;  // every bound the warm-up finds can be handled by the main loop
     // ---- warm-up: approximate keys of a few hundred elements give every reduction a finite
-    // tau.  Each wave takes one draft pair (wave w: pair w mod KB) and 64 groups of the chunk's
-    // first tile, so a lane evaluates 8 elements on both sides.
+    // tau.  Each wave takes one draft pair (wave w: pair w mod KB) of the chunk's first tile, whose
+    // loads are on their way, so a lane evaluates 8 elements on both sides.
+    // What bounds a small batch is the latency of a workgroup's phases, so they are kept short: the tile's
+    // loads leave first, blocks are drawn in a loop (above), two barriers, nothing done by one thread for all.
+    // Before that (groups of the warm-up's own, fetched here, and three barriers; the exact keys' entries
+    // fetched after their words; survivors' lanes one at a time) a call took, in us: 4 x 32 000, K = 4, bf16
+    // 20.2 -> 17.3; 256 rows 22.4 -> 19.1; 300 x 50 257, K = 5, with keys 58.7 -> 55.0; binned 1024 x 32 768
+    // 158 -> 148; 1024 x 128 256, K = 8 214 -> 211.
     {
       const int wv = tid >> 6;
-      const int m = wv % KB;
-      const int g = g_begin + (wv / KB) * 64 + (tid & 63);
+      const int m = in_scalar_int(wv % KB);
       float a_even = __builtin_huge_valf(), a_odd = __builtin_huge_valf(), a_pool = __builtin_huge_valf();
-      if (g < g_end && kbase + 2 * m < p.K) {
-        float vq[4] = {fill, fill, fill, fill};
-        if (with_pool) load4<T>(trow, g * 4, V, fill, vq);
+      if (g_first < g_end && kbase + 2 * m < p.K) {
         uint32_t up[4], lo[4];
-        const uint32_t pair = same_race ? 0u : pair_base + m;
-        philox_block(row_lo, (uint32_t)g, row_hi, pair, p.seed_lo, p.seed_hi, up);
-        philox_block(row_lo, (uint32_t)g, row_hi, pair | kLowBlock, p.seed_lo, p.seed_hi, lo);
+        philox_both_halves((uint32_t)g_first, same_race ? 0u : pair_base + m, row_lo, row_hi, p.seed_lo, p.seed_hi, up, lo);
+        float vq[4] = {fill, fill, fill, fill};
+        if (with_pool) unpack(aq, vq);
         float Mj[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // min-first: the indices' smallest times ...
         int holder[4] = {-1, -1, -1, -1};        // ... and the drafts that hold them
         if (MINF) {
           uint32_t mn[4], hd[4];
-          philox_block(row_lo, (uint32_t)g, row_hi, kMinBlock, p.seed_lo, p.seed_hi, mn);
-          philox_block(row_lo, (uint32_t)g, row_hi, kHolderBlock, p.seed_lo, p.seed_hi, hd);
+          philox_block(row_lo, (uint32_t)g_first, row_hi, kMinBlock, p.seed_lo, p.seed_hi, mn);
+          philox_block(row_lo, (uint32_t)g_first, row_hi, kHolderBlock, p.seed_lo, p.seed_hi, hd);
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             Mj[j] = approx_race_time(mn[j]) * invK;
@@ -758,13 +851,19 @@ scan_kernel(const ScanParams p) {
         for (int h = 0; h < 2; ++h) {
           const int k = kbase + 2 * m + h;
           if (k < p.K) {
-            float tk = p.temp_draft_all;
-            if (p.temp_draft != nullptr) tk = p.temp_draft[k];
-            const bool ok = (tk > 0.0f) && (tk < __builtin_huge_valf());
-            const float ck = PROBS ? 1.0f : kLog2e / tk;
+            raw rd = ad[0];
+            float ck = cd23[0];
+            bool ok = kok[0];
+#pragma unroll
+            for (int kk = 1; kk < KT; ++kk)
+              if (kk == 2 * m + h) {
+                if (!SHARED) { rd = ad[SHARED ? 0 : kk]; ck = cd23[kk]; }
+                ok = kok[kk];
+              }
+            if (!PROBS) ck *= 1.0f / kTwo23;
             float vd[4];
-            load4<T>(drow0 + (SHARED ? 0 : (long long)k * p.draft_stride_k), g * 4, V, fill, vd);
-            if (draft_masked) mask_bins(no_draft ? 0u : load_bins4(brow, g * 4, V), announced, fill, vd);
+            unpack(rd, vd);
+            if (draft_masked) mask_bins(no_draft ? 0u : ab, announced, fill, vd);
             float a_k = __builtin_huge_valf();
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -779,38 +878,31 @@ scan_kernel(const ScanParams p) {
           }
         }
       }
-      int oe = ord32(a_even), oo = ord32(a_odd), op = ord32(a_pool);
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) {
-        oe = min(oe, __shfl_xor(oe, d));
-        oo = min(oo, __shfl_xor(oo, d));
-        op = min(op, __shfl_xor(op, d));
-      }
-      if ((tid & 63) == 0) {
+      const int oe = wave_min_to_last(ord32(a_even)), oo = wave_min_to_last(ord32(a_odd)), op = wave_min_to_last(ord32(a_pool));
+      if ((tid & 63) == 63) {
         if (oe < 0x7F800000) atomicMin(&s.tau[2 * m], oe);
         if (oo < 0x7F800000) atomicMin(&s.tau[2 * m + 1], oo);
         if (op < 0x7F800000) atomicMin(&s.tau[KT], op);
       }
       __syncthreads();
-      if (tid <= KT) {
-        const bool used = tid == KT ? with_pool : (kbase + tid < p.K);
-        const float tau = unord32(s.tau[tid]);
-        if (used && tau < __builtin_huge_valf() && !(fabsf(tau) <= kTauLimit)) s.unsafe = 1;
-      }
-      __syncthreads();
-      in_range = s.unsafe == 0;  // (before the next barrier: behind it a faster wavefront's main loop may set it)
-      if (tid == 0) {
+      // The first wavefront forms the offsets (lane k: draft k, lane KT: the pool) and settles whether the main
+      // loop runs at all; in_range is not s.unsafe, which a faster wavefront's main loop may set at once.
+      if (tid < 64) {
+        const bool used = tid < KT ? kbase + tid < p.K : tid == KT && with_pool;
+        const float tau = unord32(s.tau[min(tid, KT)]);
+        const bool bad = used && tau < __builtin_huge_valf() && !(fabsf(tau) <= kTauLimit);
+        const bool any_bad = __ballot(bad) != 0ull;
+        float most = tau;  // the loosest bound (unused slots sit at -inf)
         if (SHARED) {
-          int m = s.tau[0];
 #pragma unroll
-          for (int kk = 1; kk < KT; ++kk) m = max(m, s.tau[kk]);
-          if (kok[0]) store_offsets<MINF>(s, 0, make_offset<PROBS>(unord32(m), lgK));
-        } else {
-#pragma unroll
-          for (int kk = 0; kk < KT; ++kk)
-            if (kok[kk]) store_offsets<MINF>(s, kk, make_offset<PROBS>(unord32(s.tau[kk]), lgK));
+          for (int kk = 0; kk < KT; ++kk) most = fmaxf(most, unord32(s.tau[kk]));
         }
-        if (with_pool) store_offsets<MINF>(s, KT, make_offset<PROBS>(unord32(s.tau[KT]), lgK));
+        if (tid == 0) {
+          s.in_range = any_bad ? 0 : 1;
+          if (any_bad) s.unsafe = 1;
+        }
+        if (tid < KT ? s.kok[tid] != 0 && (!SHARED || tid == 0) : used)
+          store_offsets<MINF>(s, tid, make_offset<PROBS>(SHARED && tid == 0 ? most : tau, lgK));
       }
       __syncthreads();
     }
@@ -818,33 +910,10 @@ scan_kernel(const ScanParams p) {
     // ---- main loop: level 1 on the upper half-words of every element, the rest on survivors.
     // No branch depends on the draft index: a padded draft (kbase + kk >= K) reads the last
     // real row and its half-words are tested like the others; only its hits are masked off.
-    if (in_range) {
+    if (s.in_range != 0) {
       lse_ran = true;
-      constexpr int KD = SHARED ? 1 : KT;
-      const elem *drow[KD];
-#pragma unroll
-      for (int kk = 0; kk < KD; ++kk)
-        drow[kk] = drow0 + (SHARED ? 0 : (long long)min(kbase + kk, p.K - 1) * p.draft_stride_k);
-      // One tile (one group per thread).  The next tile's loads are issued before this tile's Philox
+      // The next tile's loads are issued before this tile's Philox
       // chains, thresholds and compares, so they have a whole tile of arithmetic to arrive.
-      // Without a pool the target-side exponent is pinned at 0 (threshold 0: never a hit).
-      using raw = typename T::raw;
-      auto load_tile = [&](const int g, const bool interior, raw &rq, raw (&rd)[KD], uint32_t &rb) {
-        if (binned && !no_draft) rb = load_bins4(brow, g * 4, V);
-        if (interior) {
-          if (with_pool) rq = load_raw<T>(trow, g * 4);
-          if (!no_draft) {
-#pragma unroll
-            for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw<T>(drow[kk], g * 4);
-          }
-        } else {
-          if (with_pool) rq = load_raw_checked<T>(trow, g * 4, V, fill);
-          if (!no_draft) {
-#pragma unroll
-            for (int kk = 0; kk < KD; ++kk) rd[kk] = load_raw_checked<T>(drow[kk], g * 4, V, fill);
-          }
-        }
-      };
       // The tile is kept in its raw form and widened where it is used, so that few registers
       // are live across the (rare) branch to the survivors' path, which widens it again.
       // LSE: four more terms of one slot's sum of exp(x/T), as 2^(x c - n) with c = log2(e)/T a
@@ -1111,45 +1180,46 @@ scan_kernel(const ScanParams p) {
           }
         }
         // Rare (about one wave and tile in ten): some lane has a half-word that passed, or a hot
-        // element.  The wave takes such lanes one at a time: the lane lays its tile out in LDS and
-        // the first 8 KB lanes each take one of its elements (index j of draft 2m + h), redo the
+        // element.  The wave takes as many such lanes at a time as it has lanes for their elements: they lay
+        // their tiles out in LDS and 8 KB lanes each take one tile's elements (index j of draft 2m + h), redo the
         // test with that draft's own bound (the shared layout's main loop used the loosest one),
         // draw the lower half-word where it still passes, and run the full-word test.  Bounds are
         // read again here: they only ever tighten, and a tighter bound is still valid.
         unsigned long long todo = __ballot((most & 0xFFFFu) == 0xFFFFu || (most >> 16) == 0xFFFFu);
         if (todo != 0ull) {
-          const int lane = tid & 63;
-          Lds::Stage &st = s.stage[tid >> 6];
+          uint32_t *const st = s_stage + wv * (kCand * kCandWords);
           while (todo != 0ull) {
-            const int src = __ffsll((long long)todo) - 1;
-            todo &= todo - 1ull;
-            if (lane == src) {
+            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u));
+            const bool mine = ((todo >> lane) & 1ull) != 0ull && rank < kCand;
+            const unsigned long long taken = __ballot(mine);
+            todo &= ~taken;
+            if (mine) {
+              uint32_t *o = st + rank * kCandWords;
 #pragma unroll
-              for (int m = 0; m < KB; ++m)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) st.up[m * 4 + j] = up[m][j];
+              for (int m = 0; m < KB; ++m) *reinterpret_cast<uint4 *>(o + 4 * m) = make_uint4(up[m][0], up[m][1], up[m][2], up[m][3]);
               float vq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
               if (with_pool) unpack(rq, vq);
-#pragma unroll
-              for (int j = 0; j < 4; ++j) st.vq[j] = vq[j];
+              *reinterpret_cast<float4 *>(o + 4 * KB) = make_float4(vq[0], vq[1], vq[2], vq[3]);
+              o[4 * KB + 4] = (uint32_t)g;
 #pragma unroll
               for (int kk = 0; kk < KD; ++kk) {
                 float vd[4];
                 unpack(rd[kk], vd);
                 if (draft_masked) mask_bins(rb, announced, fill, vd);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) st.vd[kk * 4 + j] = vd[j];
+                *reinterpret_cast<float4 *>(o + 4 * KB + 8 + 4 * kk) = make_float4(vd[0], vd[1], vd[2], vd[3]);
               }
             }
             __builtin_amdgcn_wave_barrier();
-            const int gs = g - lane + src;  // the lanes of a wave hold consecutive groups
-            if (lane < 8 * KB) {
-              const int m = lane >> 3, j = (lane >> 1) & 3, h = lane & 1;
+            if (lane < 8 * KB * __popcll(taken)) {
+              const uint32_t *o = st + (lane / (8 * KB)) * kCandWords;
+              const int el = lane % (8 * KB);
+              const int m = el >> 3, j = (el >> 1) & 3, h = el & 1;
               const int kk = 2 * m + h;
-              const int i = gs * 4 + j;
+              const uint32_t gs = o[4 * KB + 4];
+              const int i = (int)gs * 4 + j;
               if (kbase + kk < p.K && i < V) {
-                const uint32_t uw = st.up[m * 4 + j];
-                const float ds = st.vd[(SHARED ? 0 : kk) * 4 + j], qs = st.vq[j];
+                const uint32_t uw = o[m * 4 + j];
+                const float qs = __uint_as_float(o[4 * KB + j]), ds = __uint_as_float(o[4 * KB + 8 + (SHARED ? 0 : kk) * 4 + j]);
                 const float c23 = s.cd23[kk];
                 const bool okk = s.kok[kk] != 0;
                 const float tau_d = unord32(__atomic_load_n(&s.tau[kk], __ATOMIC_RELAXED));
@@ -1163,7 +1233,7 @@ scan_kernel(const ScanParams p) {
                 const uint32_t hw = h ? (uw >> 16) : (uw & 0xFFFFu);
                 if (F >= kCapHot || hw >= 0xFFFFu - (t >> 16)) {
                   uint32_t lo[4];
-                  philox_block(row_lo, (uint32_t)gs, row_hi, (same_race ? 0u : pair_base + m) | kLowBlock, p.seed_lo, p.seed_hi, lo);
+                  philox_block(row_lo, gs, row_hi, (same_race ? 0u : pair_base + m) | kLowBlock, p.seed_lo, p.seed_hi, lo);
                   const uint32_t lw = j == 0 ? lo[0] : j == 1 ? lo[1] : j == 2 ? lo[2] : lo[3];
                   const uint32_t x = element_word(uw, lw, same_race ? 0 : h);
                   if (F >= kCapHot || x >= ~t) {
@@ -1182,10 +1252,6 @@ scan_kernel(const ScanParams p) {
         if constexpr (MINF) process_tile_minf(g, rq, rd, rb);
         else process_tile_words(g, rq, rd, rb);
       };
-      // A tile is interior when every lane's group is complete and inside the chunk: all rows
-      // are then read with unconditional vector loads.
-      const int interior_end = min(g_end, V >> 2);
-      const int n_interior = max(0, (interior_end - g_begin) / nt);
       int it = 0;
       if (n_interior > 0) {
         // the loads run kAhead tiles ahead of the tile at hand (register sets that swap roles in a loop
@@ -1195,10 +1261,9 @@ scan_kernel(const ScanParams p) {
         // 486 us a call with one, 466 with two), and for one shared proposal with normalisers (2 KB; 1024 x
         // 128 256, K = 8: fp32 270 us with one, 258 with two, bf16 258, 247; K = 4, bf16 181, 163)
         constexpr int kAhead = !MINF && (SHARED ? LSE : sizeof(elem) == 2 && !LSE) ? 2 : 1;
-        raw aq = raw(), ad[KD], bq[kAhead], bd[kAhead][KD];
-        uint32_t ab = 0, bb[kAhead];
+        raw bq[kAhead], bd[kAhead][KD];
+        uint32_t bb[kAhead];
         const int g0 = g_begin + tid;
-        load_tile(g0, true, aq, ad, ab);
 #pragma unroll
         for (int h = 0; h < kAhead; ++h) {
           bq[h] = raw();
@@ -1249,8 +1314,6 @@ scan_kernel(const ScanParams p) {
       if constexpr (MINF) drain();  // what is still queued
     }
     __syncthreads();
-    if (tid == 0 && s.count > kListCap) s.unsafe = 1;
-    __syncthreads();
   }
 
   // ---- LSE: the lanes' running sums become per-wave sums in LDS right away (they are merged after
@@ -1275,7 +1338,7 @@ scan_kernel(const ScanParams p) {
   // they would sit in scalar registers through the main loop, which spilled there.
   const ScanParams &q = fetch_params_again();
   unsigned long long my_exact = 0;
-  const bool exact_all = s.unsafe != 0;  // uniform: read after the barrier
+  const bool exact_all = s.unsafe != 0 || s.count > kListCap;  // uniform: read after the barrier
 
   if (!exact_all) {
     // ---- level 3: exact keys of the records that are still within the band
@@ -1293,10 +1356,13 @@ scan_kernel(const ScanParams p) {
         if ((float)s.rec_key[r] <= tau + kEps2) {
           const int i = s.rec_i[r];
           const int k = kbase + kk;
+          // (the entry is fetched first: it arrives while its word is drawn)
+          const float v = load1<T>(pool ? trow : drow0 + (SHARED ? 0 : (long long)k * q.draft_stride_k), i);
+          float temp = Tq;
+          if (!pool) temp = !SHARED && q.temp_draft != nullptr ? q.temp_draft[k] : q.temp_draft_all;
           uint32_t up[4], lo[4];
           const int kr = same_race ? 0 : k;  // the draft whose race times this one uses
-          philox_block(row_lo, (uint32_t)(i >> 2), row_hi, (uint32_t)(kr >> 1), q.seed_lo, q.seed_hi, up);
-          philox_block(row_lo, (uint32_t)(i >> 2), row_hi, (uint32_t)(kr >> 1) | kLowBlock, q.seed_lo, q.seed_hi, lo);
+          philox_both_halves((uint32_t)(i >> 2), (uint32_t)(kr >> 1), row_lo, row_hi, q.seed_lo, q.seed_hi, up, lo);
           const int j = i & 3;
           const uint32_t uw = j == 0 ? up[0] : j == 1 ? up[1] : j == 2 ? up[2] : up[3];
           const uint32_t lw = j == 0 ? lo[0] : j == 1 ? lo[1] : j == 2 ? lo[2] : lo[3];
@@ -1308,14 +1374,6 @@ scan_kernel(const ScanParams p) {
             const double M = exact_race_time(j == 0 ? mn[0] : j == 1 ? mn[1] : j == 2 ? mn[2] : mn[3]) / (double)q.K;
             const int holder = holder_of(j == 0 ? hd[0] : j == 1 ? hd[1] : j == 2 ? hd[2] : hd[3], q.K);
             S = (pool || holder == k) ? M : M + S;  // (a pool record is the holder's: the index's smallest time)
-          }
-          float temp = Tq;
-          float v;
-          if (pool) {
-            v = load1<T>(trow, i);
-          } else {
-            v = load1<T>(drow0 + (SHARED ? 0 : (long long)k * q.draft_stride_k), i);
-            temp = q.temp_draft != nullptr ? q.temp_draft[k] : q.temp_draft_all;
           }
           key = exact_key<PROBS>(S, v, (double)temp);
           ++my_exact;

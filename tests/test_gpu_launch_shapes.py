@@ -84,3 +84,21 @@ def test_rows_whose_bounds_leave_the_range_in_mid_scan(B, K, V, per_draft):
     ref = oracle_rows(draft, target, K, (0, B), kind="logits", temp_target=0.8, temp_draft=1.1, seed=5)
     assert compare(out, ref) <= oracle_near_ties(ref)
     assert stats_dict(stats)["slow_blocks"] > 0
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 6, 8])
+@pytest.mark.parametrize("V", [1024, 1025, 2048, 3077])  # exactly the first tile, one entry more, two, a ragged third
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tiles_in_which_every_lane_has_candidates(K, V, dtype):
+    # entries far above those of the first tile, which the warm-up looks at: whole wavefronts meet them at once
+    B = 5
+    g = torch.Generator(device=DEV).manual_seed(K + V)
+    target, shared, own = (_rows(g, lead, V, dtype).clone() for lead in ((B,), (B,), (B, K)))
+    for t in (target, shared, own):
+        t[..., 1024:1024 + 700] += 9.0
+    for draft in (shared, own):
+        for keys in (False, True):
+            out = llc.llc_couple(draft, target, K, temp_target=0.8, temp_draft=1.1, seed=5, want_keys=keys, v_chunks=1)
+            torch.cuda.synchronize()
+            ref = oracle_rows(draft, target, K, (0, B), kind="logits", temp_target=0.8, temp_draft=1.1, seed=5)
+            assert compare(out, ref) <= oracle_near_ties(ref)
