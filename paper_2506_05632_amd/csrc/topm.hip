@@ -1,8 +1,9 @@
 // Algorithm 1 on candidate lists (paper Section 4.4: with top-K sampling only M << N tokens
 // per distribution survive).  A row is a few hundred (token id, value) pairs: one workgroup per row,
 // one wavefront per draft list at a time, all (draft, target entry) pairs over the workgroup for the pool.
-// Every entry draws its random word from its two Philox blocks and forms an approximate key in fp32; those
-// within a band of their reduction's smallest go to a list in LDS and are evaluated exactly, in fp64, all at
+// Every entry draws the upper half of its random word (the block it is in also holds the half of the entry's
+// other draft of the pair) and bounds its key from both sides in fp32; those whose lower bound is within a band
+// of their reduction's smallest upper bound go to a list in LDS, where the lower half is drawn, and are evaluated exactly, in fp64, all at
 // once: ln S - x/T for logits and log-weights, S/p for probabilities, reduced with the usual tie rule
 // (smaller key, then smaller token id, then smaller k).  The band covers the approximation's error on both
 // sides with room for every key within 1e-6 of the winner's, so nothing that could win, or make the winner a
@@ -29,15 +30,25 @@ __device__ __forceinline__ bool has_mass(int id, float v, bool probs) {
   return v < __builtin_huge_valf() && v > -__builtin_huge_valf();
 }
 
+// The word of a block that holds the half-words of `id`.
+__device__ __forceinline__ uint32_t pick(const uint32_t (&w)[4], uint32_t id) {
+  const int j = (int)(id & 3u);
+  return j == 0 ? w[0] : j == 1 ? w[1] : j == 2 ? w[2] : w[3];
+}
 __device__ __forceinline__ uint32_t word_of(uint32_t id, uint32_t k, uint32_t row_lo, uint32_t row_hi,
                                             uint32_t k0, uint32_t k1) {
   uint32_t up[4], lo[4];
   philox_block(row_lo, id >> 2, row_hi, k >> 1, k0, k1, up);
   philox_block(row_lo, id >> 2, row_hi, (k >> 1) | kLowBlock, k0, k1, lo);
-  const int j = (int)(id & 3u);
-  const uint32_t uw = j == 0 ? up[0] : j == 1 ? up[1] : j == 2 ? up[2] : up[3];
-  const uint32_t lw = j == 0 ? lo[0] : j == 1 ? lo[1] : j == 2 ? lo[2] : lo[3];
-  return element_word(uw, lw, (int)(k & 1u));
+  return element_word(pick(up, id), pick(lo, id), (int)(k & 1u));
+}
+
+// The upper half-words of (id, draft pair): the even draft's in the lower 16 bits, the odd one's in the upper.
+__device__ __forceinline__ uint32_t upper_of(uint32_t id, uint32_t pair, uint32_t row_lo, uint32_t row_hi,
+                                             uint32_t k0, uint32_t k1) {
+  uint32_t up[4];
+  philox_block(row_lo, id >> 2, row_hi, pair, k0, k1, up);
+  return pick(up, id);
 }
 
 // One of a row's K + 1 reductions (drafts, then the pool), in LDS.
@@ -78,15 +89,17 @@ __device__ __forceinline__ void store_best(Race &r, const Best &v) {
   r.second = ord64(v.sec);
 }
 
-// What bounds it: instruction issue (two Philox blocks an entry), then the latency of its phases.  The exact
-// keys are two fp64 logarithms each: taken by every wavefront for its own list, as before, they were more
-// than half of all instructions (1024 rows, K = 8, 50 entries, with keys: 26 us under the profiler, now 11 to 14).
+// What bounds it: the latency of its phases (reductions across lanes, the exact keys' logarithms), then
+// instruction issue.  Exact keys for all entries took more than half of all instructions; both halves of every
+// entry's word, two blocks for each draft, most of the rest: 1024 rows, K = 8, one list of 50, with keys 13.0 us, now
+// 10.9; lists of 256, own for each draft 36.1, 30.3, shared 28.4, 21.0.  (Fetching ahead of use, and a shorter
+// exponential for the normalisers, changed nothing.)
 template <bool PROBS, bool MANY>
 __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   __shared__ double c_key[kCandidates];
   __shared__ int c_id[kCandidates], c_k[kCandidates];  // c_k: the draft, K more for a pool entry
   __shared__ float c_v[kCandidates];
-  __shared__ uint32_t c_x[kCandidates];
+  __shared__ uint32_t c_x[kCandidates];  // the upper half of its word
   __shared__ double s_lse_draft, s_lse_target;
   __shared__ int s_count, s_match;
   __shared__ unsigned long long s_evals;
@@ -110,28 +123,56 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   auto draft_temp = [&](const int k) { return logits ? (p.temp_draft != nullptr ? p.temp_draft[k] : p.temp_draft_all) : 1.0f; };
   const float Tq = logits ? p.temp_target : 1.0f;
 
+  // The first entries of a wavefront's first list and of its share of the pool leave before anything is set up.
+  // A wavefront takes a draft's list, or where all drafts have one list, a pair of drafts', which share their blocks.
+  const int step = one_list ? 2 : 1;
+  const unsigned pool_items = (unsigned)((K + 1) >> 1) * (unsigned)p.Mt;  // (draft pair, target entry); below 2^25
+  struct Slot { int id; float v; };
+  auto draft_slot = [&](const int k, const int e) {
+    Slot x = {-1, 0.0f};
+    if (e < p.Md) { const long long off = draft_off(k) + e; x.id = p.draft_ids[off]; x.v = widen_at(p.draft_val, p.dtype, off); }
+    return x;
+  };
+  auto pool_slot = [&](const unsigned it) {
+    Slot x = {-1, 0.0f};
+    if (it < pool_items) { const int e = (int)(it % (unsigned)p.Mt); x.id = t_ids[e]; x.v = widen_at(p.target_val, p.dtype, t_off + e); }
+    return x;
+  };
+  Slot first_draft = {-1, 0.0f}, first_pool = {-1, 0.0f};
+  if (!MANY) {
+    if (wave * step < K) first_draft = draft_slot(wave * step, lane);
+    first_pool = pool_slot((unsigned)((waves - 1 - wave) * 64 + lane));
+  }
+
   for (int k = tid; k <= K; k += nt) { race[k].best = kOrdInf64; race[k].where = ~0ull; race[k].second = kOrdInf64; }
   if (tid == 0) { s_count = 0; s_match = 0x7FFFFFFF; s_evals = 0; s_degenerate = 0; s_near = 0; }
   __syncthreads();
 
-  // the entries of one round of a wavefront: the smallest approximate key so far, and onto the list with
-  // whatever is near it (what comes later can only lower it)
+  // the entries of one round of a wavefront, a pair of drafts' half-words at a time: the smallest upper bound of
+  // a key so far (tau), and onto the list with whatever may be below it or near it (what comes later can only
+  // lower it)
   unsigned long long evals = 0;
-  float tau = inf;
-  auto consider = [&](const bool has, const int id, const float v, const uint32_t x, const float c, const int tag) {
-    float a = inf, ell;
-    if (has && approx_log2_mass<PROBS>(v, c, ell)) a = approx_log2_race_time(x) - ell;
-    float m = a;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) m = fminf(m, __shfl_xor(m, d));
-    tau = fminf(tau, m);
+  struct Bounds { float low, high; };
+  auto bounds = [&](const bool has, const float v, const uint32_t half, const float c) {
+    Bounds a = {inf, inf};
+    float ell;
+    if (has && approx_log2_mass<PROBS>(v, c, ell)) {  // (the race time falls as the word grows)
+      a.low = approx_log2_race_time((half << 16) | 0xFFFFu) - ell;
+      a.high = approx_log2_race_time(half << 16) - ell;
+    }
+    return a;
+  };
+  auto lower_tau = [&](float &tau, const float a) {
+    tau = fminf(tau, unord32(__builtin_amdgcn_readlane(wave_min_to_last(ord32(a)), 63)));
+  };
+  auto list = [&](const bool has, const int id, const float v, const uint32_t half, const int tag, const float low, const float tau) {
     // (far values: the fp32 product's rounding grows with them; beyond all measure every entry goes)
     const float band = kEps2 + (fabsf(tau) + 64.0f) * 0x1p-20f;
-    const bool near = a <= tau + band || !(fabsf(tau) < 1e30f);
+    const bool near = low <= tau + band || !(fabsf(tau) < 1e30f);
     if (has) ++evals;
     if (has && near) {
       const int pos = atomicAdd(&s_count, 1);
-      if (pos < kCandidates) { c_id[pos] = id; c_v[pos] = v; c_x[pos] = x; c_k[pos] = tag; }
+      if (pos < kCandidates) { c_id[pos] = id; c_v[pos] = v; c_x[pos] = half; c_k[pos] = tag; }
     }
   };
 
@@ -172,42 +213,43 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
     const int k1 = MANY ? min(k0 + p.at_once, K) : K;
     const bool last = !MANY || k1 == K;  // with the pool and the normalisers
     // ---- draft side: one wavefront per list, lanes over its entries
-    for (int k = k0 + wave; k < k1; k += waves) {
-      const long long off = draft_off(k);
+    for (int k = k0 + wave * step; k < k1; k += waves * step) {
       const float T = draft_temp(k);
       const bool t_ok = T > 0.0f && T < inf;
+      const bool two = one_list && k + 1 < k1;  // uniform
       const float c = kLog2e / T;
-      tau = inf;
+      float tau[2] = {inf, inf};
       for (int e0 = 0; e0 < p.Md; e0 += 64) {
-        const int e = e0 + lane;
-        int id = -1;
-        float v = 0.0f;
-        if (e < p.Md) { id = p.draft_ids[off + e]; v = widen_at(p.draft_val, p.dtype, off + e); }
-        const bool has = t_ok && has_mass(id, v, PROBS);
-        const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
-        consider(has, id, v, x, c, k);
+        const Slot x = !MANY && e0 == 0 && k == wave * step ? first_draft : draft_slot(k, e0 + lane);
+        const bool has = t_ok && has_mass(x.id, x.v, PROBS);
+        const uint32_t halves = upper_of((uint32_t)x.id, (uint32_t)(k >> 1), row_lo, row_hi, p.seed_lo, p.seed_hi);
+        const uint32_t mine = (k & 1) ? halves >> 16 : halves & 0xFFFFu;
+        const Bounds a = bounds(has, x.v, mine, c);
+        lower_tau(tau[0], a.high);
+        list(has, x.id, x.v, mine, k, a.low, tau[0]);
+        if (two) {  // (k is even)
+          const Bounds o = bounds(has, x.v, halves >> 16, c);
+          lower_tau(tau[1], o.high);
+          list(has, x.id, x.v, halves >> 16, k + 1, o.low, tau[1]);
+        }
       }
     }
     if (last) {
-      // ---- pool: all (k, target entry) pairs over the workgroup, the last wavefronts first (the first ones
-      // have had the more lists)
+      // ---- pool: all (k, target entry) pairs over the workgroup, two drafts at a time, the last wavefronts
+      // first (the first ones have had the more lists)
       {
         const float c = kLog2e / Tq;
-        const long long items = (long long)K * p.Mt;
-        tau = inf;
-        for (long long i0 = (long long)(waves - 1 - wave) * 64; i0 < items; i0 += nt) {
-          const long long it = i0 + lane;
-          int id = -1, k = 0;
-          float v = 0.0f;
-          if (it < items) {
-            k = (int)((unsigned)it / (unsigned)p.Mt);  // (items < 2^26)
-            const int e = (int)((unsigned)it % (unsigned)p.Mt);
-            id = t_ids[e];
-            v = widen_at(p.target_val, p.dtype, t_off + e);
-          }
-          const bool has = has_mass(id, v, PROBS);
-          const uint32_t x = word_of((uint32_t)id, (uint32_t)k, row_lo, row_hi, p.seed_lo, p.seed_hi);
-          consider(has, id, v, x, c, K + k);
+        float tau = inf;
+        for (unsigned i0 = (unsigned)(waves - 1 - wave) * 64; i0 < pool_items; i0 += (unsigned)nt) {
+          const unsigned it = i0 + (unsigned)lane;
+          const Slot x = !MANY && i0 < (unsigned)nt ? first_pool : pool_slot(it);
+          const int k = it < pool_items ? 2 * (int)(it / (unsigned)p.Mt) : 0;
+          const bool has = has_mass(x.id, x.v, PROBS), two = has && k + 1 < K;
+          const uint32_t halves = upper_of((uint32_t)x.id, (uint32_t)(k >> 1), row_lo, row_hi, p.seed_lo, p.seed_hi);
+          const Bounds a = bounds(has, x.v, halves & 0xFFFFu, c), o = bounds(two, x.v, halves >> 16, c);
+          lower_tau(tau, fminf(a.high, o.high));
+          list(has, x.id, x.v, halves & 0xFFFFu, K + k, a.low, tau);
+          list(two, x.id, x.v, halves >> 16, K + k + 1, o.low, tau);
         }
       }
       // ---- normalisers, only for reported keys (the argmins and near-ties need none): one wavefront per list
@@ -253,7 +295,12 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
     if (n <= kCandidates) {  // uniform
       for (int c = tid; c < n; c += nt) {
         const int tag = c_k[c];
-        c_key[c] = exact_key<PROBS>(exact_race_time(c_x[c]), c_v[c], (double)(tag >= K ? Tq : draft_temp(tag)));
+        const uint32_t k = (uint32_t)(tag >= K ? tag - K : tag), id = (uint32_t)c_id[c];
+        uint32_t lo[4];
+        philox_block(row_lo, id >> 2, row_hi, (k >> 1) | kLowBlock, p.seed_lo, p.seed_hi, lo);
+        const uint32_t lw = pick(lo, id);
+        const uint32_t x = (c_x[c] << 16) | ((k & 1u) ? lw >> 16 : lw & 0xFFFFu);
+        c_key[c] = exact_key<PROBS>(exact_race_time(x), c_v[c], (double)(tag >= K ? Tq : draft_temp(tag)));
         offer(0, tag, c_id[c], c_key[c]);
       }
       __syncthreads();
@@ -336,7 +383,8 @@ hipError_t launch_topm(hipStream_t s, const TopmParams &params) {
   // candidates on average, and the list has room for the pool's few dozen besides.  All at once up to 400 drafts
   // of 64 entries, 167 of 256, 50 of the longest.  (K = 512, lists of 50, 1024 rows, where all at once overflows:
   // 1874 us, now 350; K = 256 in parts of 64 measured 182 against 166.)
-  p.at_once = (int)(400.0 / (1.0 + std::log((double)((p.Md + 63) / 64))));
+  // (an even number: a pair of drafts is not divided)
+  p.at_once = (int)(400.0 / (1.0 + std::log((double)((p.Md + 63) / 64)))) & ~1;
   // (four wavefronts a row: 1024 rows are resident at once; eight, with half as many rows resident, measured
   // 26.4 against 25.1 us a call at 1024 rows, K = 8, lists of 256)
   const unsigned lds = (unsigned)((p.K + 1) * sizeof(Race) + p.K * sizeof(double));
