@@ -370,26 +370,26 @@ def bench_lml(args):
         torch.cuda.synchronize()
     kern_s = sum(kern_ms) / len(kern_ms) / 1e3
     elems = w.B * w.V
-    # what the kernel's own design moves per element: both inputs three times, a bucket byte and the two
-    # masses written once and read once
+    # what the kernel's own design moves per element: both inputs three times, the two bytes of a cell's number
+    # written once and read once
     esize = draft.element_size()
-    alg_bytes = elems * (2 * esize + 8)          # inputs once, the sorted order written once
-    design_bytes = elems * (6 * esize + 2 + 24)
+    alg_bytes = elems * 2 * esize                # inputs once
+    design_bytes = elems * (6 * esize + 4)
     hbm = alg_bytes / kern_s / 1e9
     launches = -(-w.B // max(1, min(w.B, (ws.numel() - 256) // (24 * w.V))))
     roofline = {"bound": "hbm", "achieved": hbm, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hbm / HBM_PEAK_GBS,
-                "kernel": "lml_bucket_kernel", "traffic": MEASURED_TRAFFIC_BYTES.get("lml_" + w.name), "kernel_ms": kern_s * 1e3, "kernel_ms_min": min(kern_ms),
+                "kernel": "lml_cell_kernel", "traffic": MEASURED_TRAFFIC_BYTES.get("lml_" + w.name), "kernel_ms": kern_s * 1e3, "kernel_ms_min": min(kern_ms),
                 "kernel_launches_per_call": launches,
                 "algorithmic_bytes": alg_bytes, "design_bytes": design_bytes,
-                "note": "one workgroup per row: three passes over the inputs, every entry's bucket byte, masses and place written "
-                        "and read once, ordered in LDS: a diagnostic, bound by instruction issue and LDS latency; "
+                "note": "one workgroup per row: three passes over the inputs, every entry's cell written and read once, cells' "
+                        "masses summed in LDS: a diagnostic, bound by instruction issue in fp64 and LDS latency; "
                         "kernel_ms, traffic and the byte counts are per call (kernel_launches_per_call launches of "
                         "at most 512 rows each, which is what the workspace holds)"}
     result = {
         "metric": "Melem/s (B*V) of Theorem 1's bound for four list sizes", "value": elems / (wall / args.steps) / 1e6,
         "unit": "Melem/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": wall / args.steps * 1e3, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "u32 sort keys + f64 sums", "data": "synthetic",
+        "dtype": "f64 masses and sums", "data": "synthetic",
         "config": {"workload": "lml_" + w.name, "B": w.B, "V": w.V, "list_sizes": ks, "input_dtype": str(draft.dtype),
                    "mean_bound": [float(v) for v in out["bound"].mean(0)], "mean_tv": float(out["tv"].mean())},
         "roofline": roofline,

@@ -222,9 +222,9 @@ struct TopmParams {
   int at_once;  // drafts whose candidates share the list (launcher)
 };
 
-// Theorem 1's bound per row (diagnostics): one workgroup orders a row by q/p, by buckets or by sorting, and sums.
+// Theorem 1's bound per row (diagnostics): one workgroup sums a row, by cells of ln(q/p) or by sorting.
 constexpr int kLmlMaxK = LLC_LML_MAX_K;
-constexpr int kLmlSlots = 512;  // two 512-thread workgroups on each of 256 CUs: more cannot be resident
+constexpr int kLmlSlots = 512;  // (sorting runs two 512-thread workgroups on each of 256 CUs: more cannot be resident)
 struct LmlParams {
   long long B;
   int V;
@@ -240,10 +240,10 @@ struct LmlParams {
   double *bound;    // [B][n_k]
   double *relaxed;  // [B][n_k] or nullptr
   double *tv;       // [B] or nullptr
-  char *work;       // workspace: per slot two buffers of V sort keys, then two of V (p-mass, q-mass) pairs
+  char *work;       // workspace: 24 V bytes per slot (see the kernels)
   int slots;        // rows the workspace holds at a time (= rows per launch; a call is ceil(B / slots) launches)
   long long row0;   // first row of this launch (set by the launcher)
-  int only_flagged; // the sorting kernel takes only the rows that the bucket kernel left (launcher)
+  int only_flagged; // the sorting kernel takes only the rows that the cell kernel left (launcher)
 };
 
 // One launcher per (element type, draft layout); defined in scan_*.hip.

@@ -9,19 +9,16 @@
 // r = q/p the inner sum is (the q-mass from j on)/q_j + (the p-mass before j)/p_j + (K-1) Q/q_j:
 // an order by r and running sums per row.  One workgroup does a whole row.  Two forms:
 //
-//  by buckets (rows of about 10^4 to 2 10^5 entries): no entry is moved more than once.  A sample of the row
-//  gives splitters of ln r, a first pass counts the entries of every bucket between them, a second
-//  forms the normalisers, a third writes every entry's two masses (rounded to fp32) and its place (the fp32
-//  image of ln r) into its bucket's part of the workspace; then groups of up to 4096 entries are ordered in
-//  LDS (a counting sort on a linear map of ln r inside every bucket, entries of one cell compared one by
-//  one, or the whole group sorted where cells are long) and walked with running sums in fp64.  Entries that share a place may form a bucket of any size,
-//  which needs no order.
-//  by sorting (other rows, and a row in which a bucket came out larger than a group): four passes of a
-//  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses travel with their key
-//  through two buffers in the workspace.
+//  by cells (rows of about 10^4 to 2.6 10^5 entries): nothing is ordered or moved.  ln r is divided into some 6000
+//  cells, finely where a sample of the row has many entries or much mass; one pass adds every cell's masses up, as
+//  whole numbers in LDS, and the next takes the terms, for which only the order inside an entry's own cell is not
+//  known.  That is bounded per entry (see lml_cell_kernel); where it matters it is resolved exactly.
+//  by sorting (other rows, and a row that the cells do not resolve): four passes of a
+//  stable 8-bit radix sort on the fp32 image of ln r, in which the entries' numbers travel with their key
+//  through two buffers in the workspace; masses in fp64.
 //
-// Indices whose r agree to fp32 precision may come out in either order, which together with the rounding of
-// the masses moves a result by a relative 2^-22 at most.
+// Indices whose r agree to fp32 precision may come out in either order, and what the cells leave open is less than
+// 2e-7 of a result.  Against 64 bits: 1024 rows of 128 256 are 2e-10 off (5e-9 when masses were rounded to fp32).
 // Entries without mass on one side follow the limits: p_j = 0 or q_j = 0 gives term j = 0; as a
 // summand i such an entry still counts with the mass it has on the other side.
 #include "common.hpp"
@@ -128,30 +125,28 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
   __shared__ int s_tstart[256];        // where a digit's run starts inside the tile
   __shared__ int s_gbase[256];         // s_goff - s_tstart of the tile at hand
   __shared__ uint32_t st_key[kTile];   // the tile in digit order, on its way out
-  __shared__ float2 st_mass[kTile];
+  __shared__ int st_at[kTile];
   __shared__ double s_seg[kWaves][2];
   __shared__ int s_total[4][256];      // how often every digit of every pass occurs in the row
-  // while the keys are made the staging area holds the counters: per pass, wavefront and digit
-  static_assert(sizeof(st_mass) >= 4 * kWaves * 256 * sizeof(int), "the counters do not fit");
-  int (*hist)[kWaves][256] = reinterpret_cast<int (*)[kWaves][256]>(st_mass);
+  __shared__ int hist[4][kWaves][256];  // per pass, wavefront and digit, while the keys are made
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const long long b = p.row0 + blockIdx.x;
   const int V = p.V;
   const E *prow = reinterpret_cast<const E *>(p.draft) + b * p.draft_stride_b;
   const E *qrow = reinterpret_cast<const E *>(p.target) + b * p.target_stride_b;
-  // A launch takes as many rows as the workspace has slots (two key buffers, then two buffers of
-  // (p-mass, q-mass) each); the launches of one call follow each other on the stream, so the
+  // A launch takes as many rows as the workspace has slots (two key buffers and, from 16 V on, two buffers of
+  // the entries' numbers; when they are in order, the masses in fp64 from the start on); the launches of one call follow each other on the stream, so the
   // workspace is as large as the workgroups that can be resident need, not as the batch.
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
   if (p.only_flagged && *flag_of(work, V) == 0) return;  // (uniform) the other kernel has done the row
   uint32_t *key_a = reinterpret_cast<uint32_t *>(work), *key_b = key_a + V;
-  float2 *mass_a = reinterpret_cast<float2 *>(work + 8u * (size_t)V), *mass_b = mass_a + V;
+  int *at_b = reinterpret_cast<int *>(work + 16u * (size_t)V), *at_a = at_b + V;
 
   const Side sp = normalise<E>(prow, V, p.probs, p.temp_draft, s_red);
   const Side sq = normalise<E>(qrow, V, p.probs, p.temp_target, s_red);
 
-  // ---- sort keys with the masses that travel with them, how often every digit occurs (the
+  // ---- sort keys with the numbers that travel with them, how often every digit occurs (the
   // arithmetic around them hides the counters' collisions), and the sums that need no order
   for (int j = tid; j < 4 * kWaves * 256; j += kThreads) (&hist[0][0][0])[j] = 0;
   __syncthreads();
@@ -168,14 +163,14 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     key_a[i] = key;
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) atomicAdd(&hist[pass][wv][(key >> (8 * pass)) & 255u], 1);
-    mass_a[i] = make_float2((float)pm, (float)qm);
+    at_a[i] = i;
     tv += fabs(pm - qm);
     if (hp && hq) {
 #pragma unroll
       for (int kk = 0; kk < kLmlMaxK; ++kk)
         if (kk < p.n_k) {  // q / (1 + q / (K p)) with one division
           const double kp = (double)p.k[kk] * pm;
-          relaxed[kk] += kp * qm / (kp + qm);
+          if (kp * qm > 0.0) relaxed[kk] += kp * qm / (kp + qm);
         }
     }
   }
@@ -202,7 +197,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
   // in LDS, and is written from there so that neighbouring threads write neighbouring addresses
   // (a digit's entries of one tile are contiguous in the output).
   uint32_t *kin = key_a, *kout = key_b;
-  float2 *min_ = mass_a, *mout = mass_b;
+  int *ain = at_a, *aout = at_b;
 #pragma unroll 1
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 8 * pass;
@@ -231,14 +226,14 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
       for (int j = tid; j < kWaves * 256; j += kThreads) (&s_cnt[0][0])[j] = 0;
       __syncthreads();
       uint32_t key[kRounds];
-      float2 mass[kRounds];
+      int number[kRounds];
       int where[kRounds];  // rank among the wavefront's entries of the same digit
 #pragma unroll
       for (int e = 0; e < kRounds; ++e) {
         const int i = t0 + wv * (64 * kRounds) + e * 64 + lane;
         const bool valid = FULL || i < V;
         key[e] = valid ? kin[i] : 0u;
-        mass[e] = valid ? min_[i] : make_float2(0.0f, 0.0f);
+        number[e] = valid ? ain[i] : 0;
       }
 #pragma unroll
       for (int e = 0; e < kRounds; ++e) {
@@ -299,7 +294,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
           const uint32_t d = (key[e] >> shift) & 255u;
           const int pos = s_tstart[d] + s_cnt[wv][d] + where[e];
           st_key[pos] = key[e];
-          st_mass[pos] = mass[e];
+          st_at[pos] = number[e];
         }
       }
       __syncthreads();
@@ -311,7 +306,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
           const uint32_t k = st_key[pos];
           const int g = s_gbase[(k >> shift) & 255u] + pos;
           kout[g] = k;
-          mout[g] = st_mass[pos];
+          aout[g] = st_at[pos];
         }
       }
     };
@@ -320,22 +315,25 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     for (; t0 + kTile <= V; t0 += kTile) sort_tile(std::true_type(), t0);
     if (t0 < V) sort_tile(std::false_type(), t0);
     { uint32_t *t = kin; kin = kout; kout = t; }
-    { float2 *t = min_; min_ = mout; mout = t; }
+    { int *t = ain; ain = aout; aout = t; }
   }
   __syncthreads();
-  // after four passes the sorted order is back in the first buffers (min_ == mass_a)
+  // after four passes the sorted order is back in the first buffers (ain == at_a)
 
   // ---- running sums over the sorted order.  Wavefront w takes the w-th part of the row: first
   // every part's masses are added up, then every wavefront walks its part with the masses of the
   // parts before it as the carry.
   const int seg = (V + kWaves - 1) / kWaves;
   const int seg_begin = min(wv * seg, V), seg_end = min(seg_begin + seg, V);
-  const float2 *mass = min_;
+  double2 *mass = reinterpret_cast<double2 *>(work);  // (16 V bytes: where the keys were)
   double seg_p = 0.0, seg_q = 0.0;
   for (int j = seg_begin + lane; j < seg_end; j += 64) {
-    const float2 m = mass[j];
-    seg_p += (double)m.x;
-    seg_q += (double)m.y;
+    const int i = at_a[j];
+    const double lp = sp.log_mass(elem<E>(prow, i)), lq = sq.log_mass(elem<E>(qrow, i));
+    const double pm = lp > -__builtin_huge_val() ? exp(lp) : 0.0, qm = lq > -__builtin_huge_val() ? exp(lq) : 0.0;
+    mass[j] = make_double2(pm, qm);
+    seg_p += pm;
+    seg_q += qm;
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) { seg_p += __shfl_xor(seg_p, d); seg_q += __shfl_xor(seg_q, d); }
@@ -353,9 +351,9 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     const int j = j0 + lane;
     double pm = 0.0, qm = 0.0;
     if (j < seg_end) {
-      const float2 m = mass[j];
-      pm = (double)m.x;
-      qm = (double)m.y;
+      const double2 m = mass[j];
+      pm = m.x;
+      qm = m.y;
     }
     double pin = pm, qin = qm;  // inclusive sums over the lanes of this tile
 #pragma unroll
@@ -363,7 +361,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
       const double up_p = __shfl_up(pin, d), up_q = __shfl_up(qin, d);
       if (lane >= d) { pin += up_p; qin += up_q; }
     }
-    if (pm > 0.0 && qm > 0.0) {
+    if (pm >= 0x1p-150 && qm >= 0x1p-150) {
       const double p_pre = p_before + (pin - pm);             // mass of p strictly before j
       const double q_suf = q_total - (q_before + (qin - qm));  // mass of q from j on
       // K / (q_suf/q_j + p_pre/p_j + (K - 1) Q/q_j), numerator and denominator times q_j
@@ -393,28 +391,22 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
 // entries, 1 row 114 : 102, 12 288: 136 : 140, 32 000: 274 : 347; bf16 40 960, 64 rows 473 : 484, 512 rows 662 :
 // 895, 128 256: 64 rows 1219 : 1555, 512 rows 1740 : 2885; 1024 rows x 128 256 fp32 3150 : 7515).
 constexpr int kBucketMinV = 12288, kBucketMinVNarrow = 40960, kBucketMaxV = 1 << 18;
-// The sample, and the buckets that its quantiles make.  A row is left to the sorting kernel if one bucket
-// outgrows a group, and one such row costs the call a whole sort: with 127 buckets of 16 samples each the
-// largest of a row's is about twice the average, which from kWideV entries on is too near a group's 4096.
-// Those rows take twice the sample and 190 buckets (512 rows of 200 064: 5047 us : 2711, 64 of 262 144 5383 :
-// 2109; 512 of 152 064, where it never happened, 1854 : 1904).
-constexpr int kSamples = 2048, kQuantiles = 127;
-constexpr int kWideV = 160000, kWideSamples = 4096, kWideQuantiles = 190;
-constexpr int kGroup = 4096;          // entries of a tile, and of a group that is ordered in LDS
-constexpr int kR = kGroup / kThreads; // what a thread holds of it
+// The sample, and the buckets that its quantiles make.  Half of it are entries spread over the row, half the largest
+// that every two threads met on either side (those near enough the row's largest to count): where a row is masked by a finite
+// value, or is very sharp, what has mass would otherwise lie between two splitters.
+constexpr int kSpread = 1024, kSamples = 2 * kSpread, kQuantiles = 127;
+constexpr double kCounts = 0x1p-40;  // of the row's largest
 constexpr int kMaxBuckets = 255;
-constexpr int kNoBucket = 255;        // of an entry that lacks mass on a side
-// Entries of one cell up to which they are compared with each other; a group with a larger cell (equal ratios
-// that the sample did not show, a far outlier in its bucket) is sorted whole.  512 rows of 128 256 bf16
-// probabilities: 5.6 ms with comparing alone, 4.1 sorting from 256 on, 3.1 from 96, 3.2 from 32; fp32 rows
-// without such a group 1.57 either way.
-constexpr int kLongCell = 96;
+constexpr int kCellThreads = 1024;
+constexpr int kCells = 6144, kOuterCells = 384;
+constexpr uint32_t kNoCell = 0xFFFFu;  // of an entry that lacks mass on a side
+constexpr int kListed = 128;           // entries of a row whose sums are formed exactly
+constexpr double kEntryError = 2e-9, kRowError = 2e-7;  // of the result
 constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
 // An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within this of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
 // ln z, which is at most ln 2^18.  So an entry without a place, from a centre that is near that one, has no
 // mass on one side, and which of such entries comes first is of no account.
-constexpr double kReach = 120.0;
 
 __device__ __forceinline__ float4 widen(const float4 &r) { return r; }
 __device__ __forceinline__ float4 widen(const uint2 &r) {
@@ -459,31 +451,6 @@ __device__ __forceinline__ double uniform(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
   const uint32_t lo = (uint32_t)uniform((int)(uint32_t)b), hi = (uint32_t)uniform((int)(uint32_t)(b >> 32));
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// The same for two sums at once, in place.
-__device__ __forceinline__ void block_prefix2(double &a, double &b, double *scratch_a, double *scratch_b, double *total_a,
-                                              double *total_b) {
-  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  double ia = a, ib = b;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const double ua = __shfl_up(ia, d), ub = __shfl_up(ib, d);
-    if (lane >= d) { ia += ua; ib += ub; }
-  }
-  __syncthreads();
-  if (lane == 63) { scratch_a[threadIdx.x >> 6] = ia; scratch_b[threadIdx.x >> 6] = ib; }
-  __syncthreads();
-  double before_a = 0.0, before_b = 0.0, sum_a = 0.0, sum_b = 0.0;
-  for (int w = 0; w < waves; ++w) {
-    if (w == (int)(threadIdx.x >> 6)) { before_a = sum_a; before_b = sum_b; }
-    sum_a += scratch_a[w];
-    sum_b += scratch_b[w];
-  }
-  *total_a = sum_a;
-  *total_b = sum_b;
-  a = before_a + ia - a;
-  b = before_b + ib - b;
 }
 
 // 1 / x to about an ulp, for normal x: the hardware's estimate and two Newton steps (the general fp64
@@ -535,12 +502,6 @@ __device__ __forceinline__ int place_of(float distance) {
 }
 __device__ __forceinline__ float distance_of(int place) { return __int_as_float(place ^ ((place >> 31) & 0x7FFFFFFF)); }
 
-// An entry on its way to its bucket.
-struct Entry {
-  float p, q;
-  int place;
-};
-
 // The last bucket whose splitter is not above `place` (split[0] stands for minus infinity).
 __device__ __forceinline__ int bucket_of(const int *split, int nb, int place) {
   int b = 0;
@@ -578,168 +539,130 @@ __device__ __forceinline__ double exp_of_negative(double x) {
 // acc[n] += k[n] pq / (base + (k[n] - off) slope): two quotients per reciprocal (the product of two
 // denominators has to be a normal number: each is 2^-450 or more in both uses).  List sizes beyond n_k are 1.
 template <int PAIRS>
-__device__ __forceinline__ void add_quotients(double (&acc)[2 * PAIRS], const LmlParams &p, double pq, double base,
+__device__ __forceinline__ void add_quotients(double (&acc)[2 * PAIRS], const LmlParams &p, int n0, double pq, double base,
                                               double off, double slope) {
 #pragma unroll
   for (int n = 0; n < 2 * PAIRS; n += 2) {
-    const double k0 = p.kd[n], d0 = fma(k0 - off, slope, base);
-    const double k1 = p.kd[n + 1], d1 = fma(k1 - off, slope, base);
+    const double k0 = p.kd[n0 + n], d0 = fma(k0 - off, slope, base);
+    const double k1 = p.kd[n0 + n + 1], d1 = fma(k1 - off, slope, base);
     const double t = pq * reciprocal(d0 * d1);
     acc[n] = fma(k0 * t, d1, acc[n]);
     acc[n + 1] = fma(k1 * t, d0, acc[n + 1]);
   }
 }
 
-// Place and number of a group's entry as one key.
-__device__ __forceinline__ unsigned long long key_of(int place, int number) {
-  return ((unsigned long long)((uint32_t)place ^ 0x80000000u) << 32) | (uint32_t)number;
+// A mass relative to its row's largest as a whole number of 2^-45ths (the sum of 2^18 of them fits 64 bits).  Whole
+// numbers add up to the same sum in any order, so LDS atomics can form the cells' masses.
+__device__ __forceinline__ unsigned long long fixed_mass(double e) {
+  asm("" : "+v"(e));  // (the same rounding wherever it is taken)
+  return (unsigned long long)__double_as_longlong(e + 128.0) - (unsigned long long)__double_as_longlong(128.0);
 }
 
-// Sorts the first n of the keys in LDS (a bitonic network; thread t holds entries t kR .. t kR + kR - 1, those
-// beyond n count as the largest) and says where each came to lie: s_to[number in the key] = position.
-__device__ __forceinline__ void sort_group(unsigned long long *s_key, int *s_to, const int n) {
-  const int me = threadIdx.x;
-  unsigned long long key[kR];
-#pragma unroll
-  for (int e = 0; e < kR; ++e) key[e] = me * kR + e < n ? s_key[me * kR + e] : ~0ull;
-  __syncthreads();
-  // (the smaller one stays where the index has no bit of `d`, the other way round in every second run of `size`)
-  auto keep = [](unsigned long long &mine, const unsigned long long other, const bool smaller) {
-    if ((other < mine) == smaller) mine = other;
-  };
-#pragma unroll 1
-  for (int size = 2; size < 2 * n; size <<= 1) {
-    const bool up = (me & (size / kR)) == 0;  // (of runs of kR entries and more)
-#pragma unroll 1
-    for (int d = size >> 1; d >= 64 * kR; d >>= 1) {  // other wavefronts' entries
-      const bool smaller = ((me & (d / kR)) == 0) == up;
-#pragma unroll
-      for (int e = 0; e < kR; ++e) s_key[e * kThreads + me] = key[e];
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < kR; ++e) keep(key[e], s_key[e * kThreads + (me ^ (d / kR))], smaller);
-      __syncthreads();
-    }
-#pragma unroll 1
-    for (int d = min(size >> 1, 32 * kR); d >= kR; d >>= 1) {  // other lanes'
-      const bool smaller = ((me & (d / kR)) == 0) == up;
-#pragma unroll
-      for (int e = 0; e < kR; ++e) keep(key[e], __shfl_xor(key[e], d / kR), smaller);
-    }
-#pragma unroll
-    for (int d = kR / 2; d >= 1; d >>= 1)  // the thread's own
-      if (d < size) {
-#pragma unroll
-        for (int e = 0; e < kR; ++e)
-          if ((e & d) == 0) {
-            const bool rising = size < kR ? (e & size) == 0 : up;
-            const unsigned long long a = key[e], b = key[e | d];
-            const bool swap = (b < a) == rising;
-            key[e] = swap ? b : a;
-            key[e | d] = swap ? a : b;
-          }
-      }
-  }
-#pragma unroll
-  for (int e = 0; e < kR; ++e)
-    if (me * kR + e < n) s_to[(uint32_t)key[e]] = me * kR + e;
-  __syncthreads();
-}
+// One workgroup per row, one per CU (the cells' masses fill its LDS).  Nothing is sorted or moved.  The inner sum of term j
+// over entries of other cells needs the masses before and behind j's cell only.  Over the other entries of its own cell,
+// with masses P and Q in all, the sum of max(q_i p_j, p_i q_j) lies between max(Q p_j, P q_j) and that plus a quarter of
+// P q_j times the cell's width in ln r (the maximum is convex in r_i), and is taken as if they lay evenly in it.  Where
+// that uncertainty times the entry's share of the result is more than kEntryError the entry's own sum is formed exactly by one more
+// walk over the row's cell numbers (two large masses in one cell: a few rows in a hundred); a row whose uncertainties
+// sum to more than kRowError of the result is left to the sorting kernel.
+// What bounds it: instruction issue in fp64 (two exponentials an entry and pass), the latency of LDS atomics and reads.
+// The row is read three times, and two bytes an entry are written and read.  1024 rows of 128 256, four sizes: 2.12 ms,
+// against 3.13 with entries moved to buckets of about 1000 and those ordered in LDS; 1024 x 32 000 0.63 : 0.87,
+// 512 x 152 064 bf16 1.37 : 1.94, one row 0.43 : 1.00, 64 x 262 144 0.96 : 2.11, eight sizes 512 rows 1.56 : 2.26.
+// All sums run in an order that does not depend on how the wavefronts interleave.
+template <typename E, bool PROBS>
+__global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlParams p) {
+  __shared__ unsigned long long s_p[kCells + 1], s_q[kCells + 1];  // a cell's masses, then what lies before it
+  __shared__ float4 s_bucket[kMaxBuckets + 1];  // left end, cells per unit of ln r, first cell, last cell
+  __shared__ int s_low[kCells], s_high[kCells]; // the smallest and largest place in a cell
+  __shared__ int s_split[kMaxBuckets + 1];      // bucket b holds the places from s_split[b] up to s_split[b + 1]
+  __shared__ double s_red[kCellThreads / 64];
+  __shared__ unsigned long long s_redu[kCellThreads / 64];
+  __shared__ int s_redi[kCellThreads / 64];
+  __shared__ int s_listed, s_at[kListed], s_list_cell[kListed], s_order[kListed];  // entries whose sums are formed exactly
+  __shared__ unsigned long long s_above[kListed], s_below[kListed];
+  __shared__ double s_ratio[kListed];
+  __shared__ uint32_t s_mark[kCells / 32];
+  __shared__ int s_far[2];
+  int *s_sample = reinterpret_cast<int *>(s_p);  // (before the cells)
+  static_assert(kSamples * sizeof(int) <= sizeof(s_p) && kSamples == 2 * kCellThreads, "sizes");
 
-// LDS index of entry j where threads read kR neighbouring entries each (spreads them over the banks).
-__device__ __forceinline__ int padded(int j) { return j + j / kR; }
-
-// One workgroup per row, two per CU.  What bounds it: instruction issue and the latency of LDS between
-// barriers, not memory: the row is read three times and a bucket byte, the masses and the place are
-// written and read once (by the memory counters 56 bytes an entry of 8 input bytes, 159 in the sorting
-// form).  Of the 1.6 ms that two rows of 128 256 take on a CU (four list sizes) the sample has 0.07, the first pass 0.2, the normalisers 0.13, the
-// third pass 0.4 (positions 0.22, masses 0.16), the groups 0.8 (cells and their starts 0.45, the order inside
-// cells 0.17, running sums 0.15, terms 0.05).  An order by the exact ratio, general divisions and a branch
-// around every exponential made it 6.3 ms for 1024 rows; as it is, 3.13.
-// All sums run in an order that does not depend on how the wavefronts interleave: entries keep the row's
-// order within a bucket, and within a group they are ordered by their places, then as they lie in the bucket.
-// PAIRS: room for that many pairs of list sizes (more than four sizes do not fit 128 registers with the
-// rest, so that variant runs one workgroup per CU).
-template <typename E, bool PROBS, int PAIRS>
-__global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel(const LmlParams p) {
-  __shared__ double s_red[kWaves], s_red2[kWaves];
-  __shared__ int s_redi[kWaves];
-  __shared__ int s_split[kMaxBuckets + 1];  // bucket b holds the places from s_split[b] up to s_split[b + 1]
-  __shared__ int s_off[kMaxBuckets + 2];    // where bucket b starts in the workspace
-  __shared__ int s_next[kMaxBuckets + 1];   // how far it has been written; before that its count
-  __shared__ int s_start[kMaxBuckets + 1];  // where a bucket's entries start inside the tile at hand
-  __shared__ float s_scale[kMaxBuckets];    // cells of a bucket per unit of ln r
-  __shared__ float2 s_mass[kGroup + kThreads];
-  __shared__ int s_cell[kGroup + kThreads + 1];  // groups: entries of a cell, then where the cell starts
-  __shared__ int s_info[2];
-  // the cells' room also serves the sample, and the third pass: an entry's bucket in the tile's order, and
-  // per wavefront and bucket the entries of the tile
-  int *s_sample = s_cell;
-  unsigned long long *s_key = reinterpret_cast<unsigned long long *>(s_mass);  // groups: the entries' keys
-  unsigned char *s_tag = reinterpret_cast<unsigned char *>(s_cell);
-  unsigned short(*s_cnt)[kMaxBuckets + 1] = reinterpret_cast<unsigned short(*)[kMaxBuckets + 1]>(s_cell + kGroup / 4);
-  static_assert(kWideSamples <= kGroup && kGroup + kWaves * (kMaxBuckets + 1) * 2 <= (int)sizeof(s_cell), "sizes");
-
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x;
   const long long b_row = p.row0 + blockIdx.x;
   const int V = p.V;
   const E *prow = reinterpret_cast<const E *>(p.draft) + b_row * p.draft_stride_b;
   const E *qrow = reinterpret_cast<const E *>(p.target) + b_row * p.target_stride_b;
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
-  Entry *bucketed = reinterpret_cast<Entry *>(work);
-  unsigned char *ids = reinterpret_cast<unsigned char *>(work + 12u * (size_t)V);
+  unsigned short *ids = reinterpret_cast<unsigned short *>(work);
   const float none = PROBS ? 0.0f : -__builtin_huge_valf();
   const float ninf = -__builtin_huge_valf();
 
   Placer<PROBS> pl;
   pl.itp = 1.0 / (double)p.temp_draft;
   pl.itq = 1.0 / (double)p.temp_target;
-
-  // ---- splitters: every bucket gets about V / kQuantiles entries, at least 1024, by the sample's quantiles, and
-  // places that the sample holds several times get a bucket of their own (inputs of few bits have many ties)
-  static_assert(kBucketMinV > kGroup, "a row that is a single group would need none");
-  int nb = 1;
-  float mp, mq, left_most, right_most;  // the largest entries, the smallest and largest distance
   pl.center = 0.0;
-  auto pick_splitters = [&](auto wide, const bool first) {
-    constexpr int kPicks = wide.value ? kWideSamples : kSamples, kMost = wide.value ? kWideQuantiles : kQuantiles;
-    constexpr int kPer = kPicks / kThreads, kMany = wide.value ? 128 : 32;
-    static_assert(kMost + 2 * (kPicks / kMany) <= kMaxBuckets, "too many splitters");
-    float xp[kPer], xq[kPer];
-    int me = tid;
-    asm volatile("" : "+v"(me));  // (or the addresses are formed before the loop, for both sizes, and spill)
+
+  // ---- first pass: the rows' largest entries, which masses are taken relative to, and the centre that they make
+  float mp = ninf, mq = ninf;
+  int at_p = 0, at_q = 0;  // where
+  for (int i = tid * 4; i < V; i += kCellThreads * 4) {
+    const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const unsigned j = (unsigned)(e * kThreads + me), jitter = j * 0x9E3779B9u;
-      const int i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kPicks);
-      xp[e] = elem<E>(prow, i);
-      xq[e] = elem<E>(qrow, i);
+    for (int j = 0; j < 4; ++j) {
+      const float xp = at(xp4, j), xq = at(xq4, j);
+      if (pl.mass(xp) && xp > mp) { mp = xp; at_p = i + j; }
+      if (pl.mass(xq) && xq > mq) { mq = xq; at_q = i + j; }
     }
-    // the centre, at first: where an entry would lie that is the sample's largest on both sides (not a median:
-    // most of a row may be masked by a low value); probabilities of any size lie within 193 of 0
-    if (!PROBS && first) {
-      mp = mq = ninf;
-#pragma unroll
-      for (int e = 0; e < kPer; ++e) {
-        if (pl.mass(xp[e])) mp = fmaxf(mp, xp[e]);
-        if (pl.mass(xq[e])) mq = fmaxf(mq, xq[e]);
-      }
-      mp = (float)block_max((double)mp, s_red);
-      mq = (float)block_max((double)mq, s_red);
-      if (mp > ninf && mq > ninf) pl.center = uniform(pl.log_ratio(mp, mq));
-    }
+  }
+  // (every even thread stands for its neighbour too on the target's side, every odd one on the draft's)
+  const bool odd = (tid & 1) != 0;
+  float own = odd ? mp : mq;
+  int at_own = odd ? at_p : at_q;
+  {
+    const float given = odd ? mq : mp, other = __shfl_xor(given, 1);
+    const int at_other = __shfl_xor(odd ? at_q : at_p, 1);
+    if (other > own) { own = other; at_own = at_other; }
+  }
+  mp = (float)block_max((double)mp, s_red);
+  mq = (float)block_max((double)mq, s_red);
+  const bool some = mp > ninf && mq > ninf;  // (uniform) else a side without mass: no entry has a place
+  if (!PROBS && some) pl.center = uniform(pl.log_ratio(mp, mq));
+  const double top_p = uniform((double)mp), top_q = uniform((double)mq);
+  const double per_p = PROBS && some ? 1.0 / top_p : pl.itp, per_q = PROBS && some ? 1.0 / top_q : pl.itq;
+  // the masses relative to the rows' largest (0: none)
+  auto relative = [&](const float x, const double top, const double per) {
+    if (PROBS) return pl.mass(x) ? (double)x * per : 0.0;
+    return exp_of_negative(pl.mass(x) ? ((double)x - top) * per : -__builtin_huge_val());
+  };
+
+  // ---- splitters: the sample's quantiles, at least 16 of its entries to a bucket, and
+  // places that the sample holds several times get a bucket of their own (inputs of few bits have many ties)
+  int nb = 1;
+  float far_left = -kFar, far_right = kFar;  // the outer buckets' outer ends: two e-folds from the sample's
+  auto pick_splitters = [&]() {
+    constexpr int kPicks = kSamples, kPer = kPicks / kCellThreads, kMany = 32;
+    static_assert(kQuantiles + 2 * (kPicks / kMany) <= kMaxBuckets, "too many splitters");
     int valid = 0, n_valid;
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
-      const float d = pl.mass(xp[e]) && pl.mass(xq[e]) ? pl.distance(xp[e], xq[e]) : kFar;
-      s_sample[e * kThreads + tid] = fabsf(d) < kFar ? place_of(d) : 0x7FFFFFFF;
+      int i = at_own;
+      bool counts = some;
+      if (e < kPer - 1) {
+        const unsigned j = (unsigned)(e * kCellThreads + tid), jitter = j * 0x9E3779B9u;
+        i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kSpread);
+      } else {
+        counts = some && (odd ? relative(own, top_p, per_p) : relative(own, top_q, per_q)) >= kCounts;
+      }
+      const float xp = elem<E>(prow, i), xq = elem<E>(qrow, i);
+      const float d = counts && pl.mass(xp) && pl.mass(xq) ? pl.distance(xp, xq) : kFar;
+      s_sample[e * kCellThreads + tid] = fabsf(d) < kFar ? place_of(d) : 0x7FFFFFFF;
       valid += fabsf(d) < kFar ? 1 : 0;
     }
     block_prefix(valid, s_redi, &n_valid);
     for (int size = 2; size <= kPicks; size <<= 1)
       for (int stride = size >> 1; stride >= 1; stride >>= 1) {
         __syncthreads();
-        for (int t = tid; t < kPicks / 2; t += kThreads) {
+        for (int t = tid; t < kPicks / 2; t += kCellThreads) {
           const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;
           const int x = s_sample[lo], y = s_sample[hi];
           if ((x > y) == ((lo & size) == 0)) { s_sample[lo] = y; s_sample[hi] = x; }
@@ -747,8 +670,7 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       }
     __syncthreads();
     if (n_valid == 0) return;  // uniform
-    const int entries = (int)((long long)V * n_valid / kPicks);
-    const int want = max(1, min(kMost, (entries + 1023) / 1024));
+    const int want = max(1, min(kQuantiles, n_valid / 16));
     // a run of `many` equal places or more in the sample is two splitters (the place is a bucket), a shorter
     // one is one, if a quantile falls into it; `many` is the least that keeps to the buckets there are
     int emit[kPer], total, before = 0;
@@ -777,391 +699,229 @@ __global__ void __launch_bounds__(kThreads, PAIRS > 2 ? 2 : 4) lml_bucket_kernel
       for (int c = 0; c < emit[e]; ++c, ++before)
         if (1 + before < nb) s_split[1 + before] = v + c;
     }
+    far_left = uniform(distance_of(s_sample[0]) - 2.0f);
+    far_right = uniform(distance_of(s_sample[n_valid - 1]) + 2.0f);
   };
-#pragma unroll 1
-  for (int attempt = 0;; ++attempt) {
-    nb = 1;
-    if (V > kWideV) pick_splitters(std::true_type(), attempt == 0);
-    else pick_splitters(std::false_type(), attempt == 0);
-    for (int j = tid; j <= kMaxBuckets; j += kThreads) s_next[j] = 0;
-    if (tid == 0) { s_split[0] = (int)0x80000000; s_info[0] = 0; }
-    __syncthreads();
+  pick_splitters();
+  nb = uniform(nb);
+  __syncthreads();
+  // cells: the outer buckets, which are the longest, get kOuterCells each, the others share the rest evenly
+  const int outer = nb > 2 ? kOuterCells : kCells / nb, inner = nb > 2 ? (kCells - 2 * kOuterCells) / (nb - 2) : 0;
+  const int last_first = kCells - outer;  // the last bucket's first cell
+  if (tid < nb) {
+    const float left = tid > 0 ? distance_of(s_split[tid]) : far_left;
+    const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : far_right;
+    // (two places can be farther apart than an int reaches; one more than a place is one)
+    const bool one_place = tid >= 1 && tid + 1 < nb && s_split[tid + 1] <= s_split[tid] + 1;
+    const int cells = tid == 0 || tid + 1 == nb ? outer : inner;
+    const int first = tid == 0 ? 0 : tid + 1 == nb ? last_first : outer + (tid - 1) * inner;
+    const float scale = one_place || !(right > left) ? 0.0f : (float)cells / (right - left);
+    s_bucket[tid] = make_float4(left, scale, (float)first, (float)(first + cells - 1));
+  }
+  if (tid == 0) { s_split[0] = (int)0x80000000; s_listed = 0; }
+  if (tid < kCells / 32) s_mark[tid] = 0u;
+  __syncthreads();
+  for (int c = tid; c <= kCells; c += kCellThreads) {
+    s_p[c] = 0ull;
+    s_q[c] = 0ull;
+    if (c < kCells) { s_low[c] = 0x7FFFFFFF; s_high[c] = (int)0x80000000; }
+  }
+  __syncthreads();
 
-    // ---- first pass: the rows' largest entries, and every entry's bucket and the buckets' counts
-    mp = mq = ninf;
-    left_most = kFar;
-    right_most = -kFar;
-    for (int i = tid * 4; i < V; i += kThreads * 4) {
+  // ---- second pass: every entry's cell, the cells' masses, and the sums of all masses
+  double zp = 0.0, zq = 0.0, p_first = 0.0;
+  for (int i = tid * 4; i < V; i += kCellThreads * 4) {
+    const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+    uint32_t packed[2] = {0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float xp = at(xp4, j), xq = at(xq4, j);
+      const double ep = relative(xp, top_p, per_p), eq = relative(xq, top_q, per_q);
+      zp += ep;
+      zq += eq;
+      uint32_t cell = kNoCell;
+      if (some && pl.mass(xp) && pl.mass(xq)) {
+        const float d = pl.distance(xp, xq);
+        if (fabsf(d) < kFar) {
+          const int place = place_of(d);
+          const float4 bu = s_bucket[nb > 1 ? bucket_of(s_split, nb, place) : 0];
+          cell = (uint32_t)(int)fminf(fmaxf((d - bu.x) * bu.y, 0.0f) + bu.z, bu.w);
+          atomicAdd(&s_p[cell], fixed_mass(ep));
+          atomicAdd(&s_q[cell], fixed_mass(eq));
+          atomicMin(&s_low[cell], place);
+          atomicMax(&s_high[cell], place);
+        }
+      }
+      // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
+      // p-mass to speak of)
+      if (cell == kNoCell) p_first += ep;
+      packed[j >> 1] |= cell << (16 * (j & 1));
+    }
+    if (i + 3 < V) {
+      *reinterpret_cast<uint2 *>(ids + i) = make_uint2(packed[0], packed[1]);
+    } else {
+      for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned short)(packed[j >> 1] >> (16 * (j & 1)));
+    }
+  }
+  zp = uniform(block_sum(zp, s_red));
+  zq = uniform(block_sum(zq, s_red));
+  const double norm_p = zp > 0.0 ? 1.0 / zp : 0.0, norm_q = zq > 0.0 ? 1.0 / zq : 0.0;
+  const double first = uniform(block_sum(p_first, s_red) * norm_p);
+  const double unit_p = 0x1p-45 * norm_p, unit_q = 0x1p-45 * norm_q;
+  {
+    constexpr int kEach = kCells / kCellThreads;
+    unsigned long long all;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      unsigned long long *m = side == 0 ? s_p : s_q, mine[kEach], sum = 0ull;
+#pragma unroll
+      for (int e = 0; e < kEach; ++e) { mine[e] = m[tid * kEach + e]; sum += mine[e]; }
+      unsigned long long before = block_prefix(sum, s_redu, &all);
+#pragma unroll
+      for (int e = 0; e < kEach; ++e) { m[tid * kEach + e] = before; before += mine[e]; }
+      if (tid == kCellThreads - 1) m[kCells] = before;
+    }
+  }
+  __syncthreads();
+  // about what the result for K = 1 will be, every cell taken as one entry: errors are measured against it
+  double about = 0.0;
+  for (int c = tid; c < kCells; c += kCellThreads) {
+    const double pc = (double)(s_p[c + 1] - s_p[c]) * unit_p, qc = (double)(s_q[c + 1] - s_q[c]) * unit_q;
+    const double base = (1.0 - (double)s_q[c] * unit_q) * pc + ((double)s_p[c] * unit_p + first) * qc;
+    if (pc > 0.0 && qc > 0.0 && base > 0.0) about += pc * qc / base;
+  }
+  const float entry_error = (float)(kEntryError * uniform(block_sum(about, s_red)));
+
+  // ---- third pass: the terms (list sizes four at a time)
+  double tv = 0.0;
+  float doubt = 0.0f;
+#pragma unroll 1
+  for (int n0 = 0; n0 < p.n_k; n0 += 4) {
+    double sums[4] = {0.0, 0.0, 0.0, 0.0}, relaxed[4] = {0.0, 0.0, 0.0, 0.0};
+    // K pq / (base + (K - 1) pm) of one entry, base = D(r) p: numerator and denominator of K q / (D(r) + (K - 1) Q) times p
+#pragma unroll 1
+    for (int i = tid * 4; i < V; i += kCellThreads * 4) {
       const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
-      uint32_t packed = 0;
+      uint32_t cells[2] = {0u, 0u};
+      if (i + 3 < V) {
+        const uint2 c = *reinterpret_cast<const uint2 *>(ids + i);
+        cells[0] = c.x; cells[1] = c.y;
+      } else {
+        for (int j = 0; i + j < V; ++j) cells[j >> 1] |= (uint32_t)ids[i + j] << (16 * (j & 1));
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float xp = at(xp4, j), xq = at(xq4, j);
-        const bool hp = pl.mass(xp), hq = pl.mass(xq);
-        if (hp) mp = fmaxf(mp, xp);
-        if (hq) mq = fmaxf(mq, xq);
-        int b = kNoBucket;
-        if (hp && hq) {
-          const float d = pl.distance(xp, xq);
-          if (fabsf(d) < kFar) {
-            left_most = fminf(left_most, d);
-            right_most = fmaxf(right_most, d);
-            b = nb > 1 ? bucket_of(s_split, nb, place_of(d)) : 0;
-            atomicAdd(&s_next[b], 1);
+        if (i + j >= V) continue;
+        const double ep = relative(at(xp4, j), top_p, per_p), eq = relative(at(xq4, j), top_q, per_q);
+        double pm = ep * norm_p, qm = eq * norm_q;
+        if (n0 == 0) tv += fabs(pm - qm);
+        const uint32_t cell = (cells[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
+        if (cell != kNoCell && pm >= 0x1p-150 && qm >= 0x1p-150) {
+          const unsigned long long pb = s_p[cell], qb = s_q[cell + 1];
+          // what else is in the cell
+          const double po = fmax((double)(long long)(s_p[cell + 1] - pb - fixed_mass(ep)), 0.0) * unit_p;
+          const double qo = fmax((double)(long long)(qb - s_q[cell] - fixed_mass(eq)), 0.0) * unit_q;
+          const double a = qo * pm, c = po * qm;
+          const float width = distance_of(s_high[cell]) - distance_of(s_low[cell]);
+          const double rest = fma(fmax(1.0 - (double)qb * unit_q, 0.0), pm, fma((double)pb, unit_p, first) * qm) + pm * qm;
+          double inside = fmax(a, c);
+          const double base = rest + inside;
+          // relative to the denominator: in fp32, as small as they are
+          const double inv = reciprocal(base);
+          const float cw = (float)(c * inv) * width, side = (float)((a - c) * inv);
+          const float gap = fminf((float)(fmin(a, c) * inv), 0.25f * cw * (1.0f + width));
+          const float share = (float)(pm * qm * inv);
+          if (share * gap > entry_error) {
+            if (n0 == 0) {
+              const int pos = atomicAdd(&s_listed, 1);
+              if (pos < kListed) { s_at[pos] = i + j; s_list_cell[pos] = (int)cell; }
+            }
+          } else {
+            if (n0 == 0) doubt += share * gap;
+            if (width < 0.5f && 2.0f * fabsf(side) < cw) {
+              const float t = 0.5f * cw + side;  // > 0
+              inside = c + (double)(t * t / (2.0f * cw)) * base;
+            }
+            add_quotients<2>(sums, p, n0, pm * qm, rest + inside, 1.0, pm);
           }
         }
-        packed |= (uint32_t)b << (8 * j);
-      }
-      if (i + 3 < V) {
-        *reinterpret_cast<uint32_t *>(ids + i) = packed;
-      } else {
-        for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned char)(packed >> (8 * j));
-      }
-    }
-    if (PROBS) break;
-    // the centre that the rows' largest entries make: if the sample's was too far from it for kReach, once more
-    // from there
-    mp = (float)block_max((double)mp, s_red);
-    mq = (float)block_max((double)mq, s_red);
-    if (!(mp > ninf && mq > ninf)) break;  // (uniform, as the next) a side without mass
-    const double center = uniform(pl.log_ratio(mp, mq));
-    if (attempt > 0 || fabs(center - pl.center) < (double)kFar - kReach) break;
-    pl.center = center;
-  }
-  nb = uniform(nb);
-  // (two places can be farther apart than an int reaches; one more than a place is one)
-  auto of_one_place = [&](const int b) { return b >= 1 && b + 1 < nb && s_split[b + 1] <= s_split[b] + 1; };
-  Side sp, sq;
-  sp.probs = sq.probs = PROBS ? 1 : 0;
-  sp.inv_t = pl.itp;
-  sq.inv_t = pl.itq;
-  // the outer buckets' outer ends: those of the row, or two e-folds from the nearest splitter (an outlier
-  // must not stretch a bucket so far that its other entries share a cell)
-  float left_edge = -(float)block_max(-(double)left_most, s_red), right_edge = (float)block_max((double)right_most, s_red);
-  if (nb > 1) {
-    left_edge = fmaxf(left_edge, distance_of(s_split[1]) - 2.0f);
-    right_edge = fminf(right_edge, distance_of(s_split[nb - 1]) + 2.0f);
-  }
-  left_edge = uniform(left_edge);
-  sp.m = PROBS ? 0.0 : uniform((double)mp);
-  sq.m = PROBS ? 0.0 : uniform((double)mq);
-  __syncthreads();
-  {
-    const int mine = tid < nb ? s_next[tid] : 0;
-    int total;
-    const int off = block_prefix(mine, s_redi, &total);
-    if (tid < nb) {
-      s_off[tid] = off;
-      s_next[tid] = off;
-      if (mine > kGroup && !of_one_place(tid)) s_info[0] = 1;
-      // (the outer buckets have no outer splitter: the sample's end stands for it)
-      const float left = tid > 0 ? distance_of(s_split[tid]) : left_edge;
-      const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : right_edge;
-      s_scale[tid] = right > left ? (float)mine / (right - left) : 0.0f;
-    }
-    if (tid == 0) s_off[nb] = total;
-  }
-  __syncthreads();
-  const bool leave = s_info[0] != 0;
-  if (tid == 0) *flag_of(work, V) = leave ? 1 : 0;
-  if (leave) return;  // (uniform) a bucket larger than a group: the row is the sorting kernel's
-
-  // ---- second pass: the normalisers
-  {
-    double zp = 0.0, zq = 0.0;
-    for (int i = tid * 4; i < V; i += kThreads * 4) {
-      const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float xp = at(xp4, j), xq = at(xq4, j);
-        if (PROBS) {
-          zp += pl.mass(xp) ? (double)xp : 0.0;
-          zq += pl.mass(xq) ? (double)xq : 0.0;
-        } else {
-          zp += exp_of_negative(pl.mass(xp) ? ((double)xp - sp.m) * sp.inv_t : -__builtin_huge_val());
-          zq += exp_of_negative(pl.mass(xq) ? ((double)xq - sq.m) * sq.inv_t : -__builtin_huge_val());
+        if (ep > 0.0 && eq > 0.0 && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
+          // (where the product nears the smallest numbers, both are taken relative to the larger one: its
+          // denominators, and their product, are then at least 1/4)
+          int scale = 0;
+          if (pm * qm < 0x1p-900) {
+            scale = __builtin_amdgcn_frexp_exp(fmax(pm, qm));
+            pm = __builtin_amdgcn_ldexp(pm, -scale);
+            qm = __builtin_amdgcn_ldexp(qm, -scale);
+          }
+          const double pq = __builtin_amdgcn_ldexp(pm * qm, scale);
+          if (pq > 0.0) add_quotients<2>(relaxed, p, n0, pq, qm, 0.0, pm);
         }
       }
     }
-    sp.ln_z = log(block_sum(zp, s_red));
-    sq.ln_z = log(block_sum(zq, s_red));
-  }
-
-  // ---- third pass: every tile is laid out by bucket in LDS (its entries' positions follow from the bucket
-  // bytes alone), and taken from there: masses, the sums that need no order, and the masses to their
-  // bucket, neighbouring threads to neighbouring addresses
-  double tv = 0.0, p_first = 0.0, q_total = 0.0, sums[2 * PAIRS];
-#pragma unroll
-  for (int n = 0; n < 2 * PAIRS; ++n) sums[n] = 0.0;
-#pragma unroll 1
-  for (int t0 = 0; t0 < V; t0 += kGroup) {
-    const int n_tile = min(kGroup, V - t0);
-    const int base = t0 + wv * (64 * kR) + lane;  // wavefront w holds the w-th part of the tile
-    float2 x[kR];
-    int id[kR], where[kR];
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-      const int i = base + e * 64;
-      id[e] = i < V ? (int)ids[i] : -1;
-      x[e] = i < V ? make_float2(elem<E>(prow, i), elem<E>(qrow, i)) : make_float2(0.0f, 0.0f);
-    }
-    __syncthreads();  // the tile before is done with
-    for (int j = tid; j < kWaves * (kMaxBuckets + 1) / 2; j += kThreads) reinterpret_cast<int *>(&s_cnt[0][0])[j] = 0;
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-      // lanes of this round with the same bucket: bit by bit, keep those whose bit is like mine
-      const unsigned long long live = __ballot(id[e] >= 0);
-      uint32_t peers_lo = (uint32_t)live, peers_hi = (uint32_t)(live >> 32);
-#pragma unroll
-      for (int bit = 0; bit < 8; ++bit) {
-        const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe(id[e], bit, 1);  // all ones if the bit is set
-        const unsigned long long have = __ballot(mine != 0u);
-        peers_lo &= ~((uint32_t)have ^ mine);
-        peers_hi &= ~((uint32_t)(have >> 32) ^ mine);
-      }
-      where[e] = 0;
-      if (id[e] >= 0) {
-        const int rank = (int)__builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
-        const int seen = s_cnt[wv][id[e]];
-        if (rank == 0) s_cnt[wv][id[e]] = (unsigned short)(seen + __popc(peers_lo) + __popc(peers_hi));
-        where[e] = seen + rank;
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-    {
-      int mine = 0, all;
-      if (tid <= kMaxBuckets) {
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          const int c = s_cnt[w][tid];
-          s_cnt[w][tid] = (unsigned short)mine;
-          mine += c;
+    const int listed = s_listed;
+    if (listed > kListed) break;  // (uniform) the row is the sorting kernel's
+    if (listed > 0) {
+      // ---- the listed entries' cells, entry by entry: what is above each in the order, and what below
+      if (n0 == 0) {
+        if (tid < listed) {
+          s_ratio[tid] = pl.log_ratio(elem<E>(prow, s_at[tid]), elem<E>(qrow, s_at[tid]));
+          s_above[tid] = 0ull;
+          s_below[tid] = 0ull;
+          atomicOr(&s_mark[s_list_cell[tid] >> 5], 1u << (s_list_cell[tid] & 31));
         }
-      }
-      const int start = block_prefix(mine, s_redi, &all);
-      if (tid <= kMaxBuckets) s_start[tid] = start;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kR; ++e)
-      if (id[e] >= 0) {
-        const int pos = s_start[id[e]] + s_cnt[wv][id[e]] + where[e];
-        s_mass[pos] = x[e];
-        s_tag[pos] = (unsigned char)id[e];
-      }
-    __syncthreads();
-#pragma unroll 1
-    for (int pos = tid; pos < n_tile; pos += kThreads) {
-      const float2 in = s_mass[pos];
-      const int b = s_tag[pos];
-      const double lp = sp.log_mass(in.x), lq = sq.log_mass(in.y);
-      const bool hp = lp > -__builtin_huge_val(), hq = lq > -__builtin_huge_val();
-      double pm = exp_of_negative(lp), qm = exp_of_negative(lq);  // (-inf: no mass)
-      const float2 m = make_float2((float)pm, (float)qm);
-      tv += fabs(pm - qm);
-      q_total += (double)m.y;
-      // ratio 0, or near it: before all others (an entry without a bucket that has the larger ratio has no
-      // p-mass in fp32)
-      if (b == kNoBucket) p_first += (double)m.x;
-      if (b != kNoBucket) {
-        const int g = s_next[b] + (pos - s_start[b]);
-        if (g < s_off[b + 1]) {  // (always; a bucket is never written past its end)
-          bucketed[g] = Entry{m.x, m.y, place_of(pl.distance(in.x, in.y))};
+        __syncthreads();
+        for (int i = tid; i < V; i += kCellThreads) {
+          const uint32_t cell = ids[i];
+          if (cell == kNoCell || !((s_mark[cell >> 5] >> (cell & 31u)) & 1u)) continue;
+          const float xp = elem<E>(prow, i), xq = elem<E>(qrow, i);
+          const double r = pl.log_ratio(xp, xq);
+          for (int l = 0; l < listed; ++l) {
+            if (s_list_cell[l] != (int)cell || s_at[l] == i) continue;
+            if (r >= s_ratio[l])
+              atomicAdd(&s_above[l], fixed_mass(relative(xq, top_q, per_q)));
+            else
+              atomicAdd(&s_below[l], fixed_mass(relative(xp, top_p, per_p)));
+          }
         }
-      }
-      if (hp && hq && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
-        // (where the product nears the smallest numbers, both are taken relative to the larger one: its
-        // denominators, and their product, are then at least 1/4)
-        int scale = 0;
-        if (pm * qm < 0x1p-900) {
-          scale = __builtin_amdgcn_frexp_exp(fmax(pm, qm));
-          pm = __builtin_amdgcn_ldexp(pm, -scale);
-          qm = __builtin_amdgcn_ldexp(qm, -scale);
+        if (tid < listed) {
+          int before = 0;
+          for (int l = 0; l < listed; ++l) before += s_at[l] < s_at[tid] ? 1 : 0;
+          s_order[before] = tid;
         }
-        const double pq = __builtin_amdgcn_ldexp(pm * qm, scale);
-        if (pq > 0.0) add_quotients<PAIRS>(sums, p, pq, qm, 0.0, pm);
+        __syncthreads();
+      }
+      if (tid < listed) {  // thread t takes the t-th in the row's order
+        const int from = s_order[tid];
+        const int i = s_at[from], cell = s_list_cell[from];
+        const double pm = relative(elem<E>(prow, i), top_p, per_p) * norm_p, qm = relative(elem<E>(qrow, i), top_q, per_q) * norm_q;
+        const double behind = fmax(1.0 - (double)s_q[cell + 1] * unit_q, 0.0) + (double)s_above[from] * unit_q;
+        const double before = fma((double)s_p[cell] + (double)s_below[from], unit_p, first);
+        add_quotients<2>(sums, p, n0, pm * qm, fma(behind, pm, before * qm) + pm * qm, 1.0, pm);
       }
     }
-    __syncthreads();
-    if (tid < nb) {
-      int here = (tid < kMaxBuckets ? s_start[tid + 1] : n_tile) - s_start[tid];
-      s_next[tid] += here;
-    }
-  }
-  tv = block_sum(tv, s_red);
-  if (tid == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * tv;
+    double bound_0 = 0.0;
 #pragma unroll
-  for (int n = 0; n < 2 * PAIRS; ++n)
-    if (n < p.n_k) {  // uniform
-      if (p.relaxed != nullptr) {
+    for (int n = 0; n < 4; ++n)
+      if (n0 + n < p.n_k) {  // uniform
         const double r = block_sum(sums[n], s_red);
-        if (tid == 0) p.relaxed[b_row * p.n_k + n] = r;
-      }
-      sums[n] = 0.0;
-    }
-  q_total = uniform(block_sum(q_total, s_red));
-
-  // ---- the groups in order, with the masses of what came before
-  double p_before = uniform(block_sum(p_first, s_red)), q_before = 0.0;
-  // K q / (D(r) + (K - 1) Q) of one entry, D(r) the sum of max(q_i, r p_i) over the row: the q-mass from
-  // the entry on plus r times the p-mass before it (numerator and denominator times p)
-  auto add_term = [&](const float2 m, const double pb, const double qb) {
-    if (!(m.x > 0.0f && m.y > 0.0f)) return;
-    const double pm = (double)m.x, qm = (double)m.y;
-    double one = 1.0;
-    asm volatile("" : "+s"(one));  // (or the list sizes less one live, and spill, across the whole loop)
-    add_quotients<PAIRS>(sums, p, pm * qm, fma(q_total - qb, pm, pb * qm), one, q_total * pm);
-  };
-  for (int b0 = 0, b1 = 0; b0 < nb; b0 = b1) {
-    b1 = b0 + 1;
-    const int first = uniform(s_off[b0]);
-    int n = uniform(s_off[b1]) - first;
-    const bool tied = n > kGroup;  // (only a bucket of one place can be)
-    if (!tied) {
-      while (b1 < nb && uniform(s_off[b1 + 1]) - first <= kGroup) ++b1;
-      n = uniform(s_off[b1]) - first;
-    }
-    if (n == 0) continue;  // uniform
-    double pg = 0.0, qg = 0.0;  // the group's masses
-    int me = tid;
-    asm volatile("" : "+v"(me));  // (or two dozen addresses formed from it live, and spill, across the whole loop)
-    if (tied) {
-      // one place: any order will do, so every entry counts as the first of them
-#pragma unroll 1
-      for (int i = me; i < n; i += kThreads) {
-        const float2 m = make_float2(bucketed[first + i].p, bucketed[first + i].q);
-        pg += (double)m.x;
-        qg += (double)m.y;
-        add_term(m, p_before, q_before);
-      }
-      p_before = uniform(p_before + block_sum(pg, s_red));
-      q_before = uniform(q_before + block_sum(qg, s_red));
-      continue;
-    }
-    // cells: bucket b's entries spread over as many cells as there are, linearly in ln r between its
-    // splitters (so the map is monotone, which is all the order needs; one entry per cell on average)
-    float2 mass[kR];
-    int cell[kR], rank[kR], place[kR], top = 1;
-    while (top * 2 < b1 - b0) top *= 2;
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-      const int i = e * kThreads + me;
-      const Entry in = bucketed[first + min(i, n - 1)];
-      mass[e] = make_float2(in.p, in.q);
-      place[e] = in.place;
-    }
-    __syncthreads();  // the group before is done with
-    if (me == 0) s_info[1] = 0;
-    for (int c = me; c < padded(n) + 1; c += kThreads) s_cell[c] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-      const int i = e * kThreads + me;
-      int b = b0;  // the bucket it lies in
-      for (int step = top; step >= 1; step >>= 1)
-        if (b + step < b1 && s_off[b + step] - first <= i) b += step;
-      const int low = s_split[b], high = b + 1 < nb ? s_split[b + 1] - 1 : 0x7FFFFFFE;
-      const int lo = s_off[b] - first, cnt = s_off[b + 1] - s_off[b];
-      const float f = (distance_of(place[e]) - (b > 0 ? distance_of(low) : left_edge)) * s_scale[b];
-      const int spread = lo + (int)fminf(fmaxf(f, 0.0f), (float)(cnt - 1));
-      // (in a bucket of one place the entries stay as they lie)
-      cell[e] = i < n ? (high > low || b == 0 ? spread : i) : -1;
-      rank[e] = i < n ? atomicAdd(&s_cell[padded(cell[e])], 1) : 0;
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
-    {
-      // where every cell starts; thread t takes cells t kR .. t kR + kR - 1
-      int c[kR], sum = 0, total;
-#pragma unroll
-      for (int e = 0; e < kR; ++e) {
-        const int j = me * kR + e;
-        c[e] = j < n ? s_cell[padded(j)] : 0;
-        sum += c[e];
-      }
-      int start = block_prefix(sum, s_redi, &total);
-#pragma unroll
-      for (int e = 0; e < kR; ++e) {
-        const int j = me * kR + e;
-        if (j < n) s_cell[padded(j)] = start;
-        start += c[e];
-      }
-      if (me == 0) s_cell[padded(n)] = n;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kR; ++e)
-      if (cell[e] >= 0) {
-        rank[e] += s_cell[padded(cell[e])];
-        s_key[rank[e]] = key_of(place[e], e * kThreads + me);
-      }
-    if (me < 4) s_key[n + me] = ~0ull;
-    int longest = 0;
-#pragma unroll
-    for (int e = 0; e < kR; ++e) {
-      const int from = cell[e] >= 0 ? s_cell[padded(cell[e])] : n;
-      const int len = cell[e] >= 0 ? s_cell[padded(cell[e] + 1)] - from : 0;
-      longest = max(longest, len > 1 ? len : 0);
-      cell[e] = from;
-      rank[e] = from;
-    }
-    if (longest > kLongCell) s_info[1] = 1;
-    __syncthreads();
-    // entries of one cell among themselves: by place, then as they lie in the bucket
-    if (s_info[1] != 0) {  // (uniform)
-      sort_group(s_key, s_cell, n);
-#pragma unroll
-      for (int e = 0; e < kR; ++e) rank[e] = e * kThreads + me < n ? s_cell[e * kThreads + me] : n;
-    } else {
-      // (the thread's entries side by side, four steps at a time: what lies behind a cell has larger keys and
-      // counts for nothing, so only the longest cell of the wavefront ends the loop)
-      for (int t = 0; __any(t < longest); t += 4) {
-#pragma unroll
-        for (int e = 0; e < kR; ++e) {
-          const unsigned long long mine = key_of(place[e], e * kThreads + me);
-          const unsigned long long *there = s_key + min(cell[e] + t, n);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) rank[e] += there[u] < mine ? 1 : 0;
+        if (n == 0) bound_0 = r;
+        if (tid == 0) p.bound[b_row * p.n_k + n0 + n] = r;
+        if (p.relaxed != nullptr) {
+          const double x = block_sum(relaxed[n], s_red);
+          if (tid == 0) p.relaxed[b_row * p.n_k + n0 + n] = x;
         }
       }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kR; ++e)
-      if (e * kThreads + me < n) s_mass[padded(rank[e])] = mass[e];
-    __syncthreads();
-    {
-      // running sums over the entries in order; thread t takes entries t kR .. t kR + kR - 1
-      const int mine = me * kR;
-#pragma unroll
-      for (int e = 0; e < kR; ++e) {
-        mass[e] = mine + e < n ? s_mass[padded(mine + e)] : make_float2(0.0f, 0.0f);
-        pg += (double)mass[e].x;
-        qg += (double)mass[e].y;
-      }
-      double p_sum, q_sum, pb = pg, qb = qg;
-      block_prefix2(pb, qb, s_red, s_red2, &p_sum, &q_sum);
-      pb += p_before;
-      qb += q_before;
-#pragma unroll
-      for (int e = 0; e < kR; ++e) {
-        add_term(mass[e], pb, qb);
-        pb += (double)mass[e].x;
-        qb += (double)mass[e].y;
-        if (e % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // (all at once does not fit the registers)
-      }
-      p_before = uniform(p_before + p_sum);
-      q_before = uniform(q_before + q_sum);
+    if (n0 == 0) {
+      tv = block_sum(tv, s_red);
+      if (tid == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * tv;
+      const double d = block_sum((double)doubt, s_red);
+      if (tid == 0) s_far[0] = d > kRowError * bound_0 ? 1 : 0;
     }
   }
-#pragma unroll
-  for (int n = 0; n < 2 * PAIRS; ++n)
-    if (n < p.n_k) {  // uniform
-      const double r = block_sum(sums[n], s_red);
-      if (tid == 0) p.bound[b_row * p.n_k + n] = r;
-    }
+  __syncthreads();
+  if (tid == 0) *flag_of(work, V) = s_listed > kListed || s_far[0] != 0 ? 1 : 0;
 }
 
 }  // namespace
@@ -1175,9 +935,7 @@ hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
     const unsigned grid = (unsigned)(left < (long long)p.slots ? left : (long long)p.slots);
     const bool f32 = p.dtype == LLC_F32;
     if (buckets) {
-#define LLC_LML(E, PROBS)                                                                                  \
-  if (p.n_k <= 4) hipLaunchKernelGGL((lml_bucket_kernel<E, PROBS, 2>), dim3(grid), dim3(kThreads), 0, s, p); \
-  else hipLaunchKernelGGL((lml_bucket_kernel<E, PROBS, 4>), dim3(grid), dim3(kThreads), 0, s, p);
+#define LLC_LML(E, PROBS) hipLaunchKernelGGL((lml_cell_kernel<E, PROBS>), dim3(grid), dim3(kCellThreads), 0, s, p);
       if (f32 && p.probs) { LLC_LML(float, true) }
       else if (f32) { LLC_LML(float, false) }
       else if (p.probs) { LLC_LML(uint16_t, true) }
