@@ -1264,6 +1264,9 @@ scan_kernel(const ScanParams p) {
         raw bq[kAhead], bd[kAhead][KD];
         uint32_t bb[kAhead];
         const int g0 = g_begin + tid;
+        // (min-first with normalisers the first tile is fetched again: kept in registers from before the warm-up on, it
+        // made the compiler wait inside the loop for loads just issued, 43.9 -> 45.7 us at 120 x 128 256, K = 2)
+        if (MINF && LSE) load_tile(g0, true, aq, ad, ab);
 #pragma unroll
         for (int h = 0; h < kAhead; ++h) {
           bq[h] = raw();
