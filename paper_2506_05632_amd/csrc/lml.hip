@@ -9,16 +9,17 @@
 // r = q/p the inner sum is (the q-mass from j on)/q_j + (the p-mass before j)/p_j + (K-1) Q/q_j:
 // an order by r and running sums per row.  One workgroup does a whole row.  Two forms:
 //
-//  by cells (rows of about 10^4 to 2.6 10^5 entries): nothing is ordered or moved.  ln r is divided into some 6000
+//  by cells (rows of 6144 to 2.6 10^5 entries, bf16 from 8192 on): nothing is ordered or moved.  ln r is divided into some 6000
 //  cells, finely where a sample of the row has many entries or much mass; one pass adds every cell's masses up, as
 //  whole numbers in LDS, and the next takes the terms, for which only the order inside an entry's own cell is not
 //  known.  That is bounded per entry (see lml_cell_kernel); where it matters it is resolved exactly.
 //  by sorting (other rows, and a row that the cells do not resolve): four passes of a
-//  stable 8-bit radix sort on the fp32 image of ln r, in which the entries' numbers travel with their key
-//  through two buffers in the workspace; masses in fp64.
+//  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses, rounded to fp32, travel with their
+//  key through two buffers in the workspace.
 //
-// Indices whose r agree to fp32 precision may come out in either order, and what the cells leave open is less than
-// 2e-7 of a result.  Against 64 bits: 1024 rows of 128 256 are 2e-10 off (5e-9 when masses were rounded to fp32).
+// Indices whose r agree to fp32 precision may come out in either order, which together with the sorted masses' rounding
+// moves a result by a relative 2^-22 at most, and so does what the cells leave open (1024 rows of 128 256 come out
+// 2e-10 from the result in 64 bits, 5e-9 when sorted).
 // Entries without mass on one side follow the limits: p_j = 0 or q_j = 0 gives term j = 0; as a
 // summand i such an entry still counts with the mass it has on the other side.
 #include "common.hpp"
@@ -107,7 +108,7 @@ __device__ Side normalise(const E *row, int V, int probs, float temp, double *sc
   return s;
 }
 
-// Where the bucket kernel tells the sorting one, launched behind it, that it left a row: behind the
+// Where the cell kernel tells the sorting one, launched behind it, that it left a row: behind the
 // masses in the row's part of the workspace.
 __device__ __forceinline__ int *flag_of(char *work, int V) { return reinterpret_cast<int *>(work + 16u * (size_t)V); }
 
@@ -125,28 +126,30 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
   __shared__ int s_tstart[256];        // where a digit's run starts inside the tile
   __shared__ int s_gbase[256];         // s_goff - s_tstart of the tile at hand
   __shared__ uint32_t st_key[kTile];   // the tile in digit order, on its way out
-  __shared__ int st_at[kTile];
+  __shared__ float2 st_mass[kTile];
   __shared__ double s_seg[kWaves][2];
   __shared__ int s_total[4][256];      // how often every digit of every pass occurs in the row
-  __shared__ int hist[4][kWaves][256];  // per pass, wavefront and digit, while the keys are made
+  // while the keys are made the staging area holds the counters: per pass, wavefront and digit
+  static_assert(sizeof(st_mass) >= 4 * kWaves * 256 * sizeof(int), "the counters do not fit");
+  int (*hist)[kWaves][256] = reinterpret_cast<int (*)[kWaves][256]>(st_mass);
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const long long b = p.row0 + blockIdx.x;
   const int V = p.V;
   const E *prow = reinterpret_cast<const E *>(p.draft) + b * p.draft_stride_b;
   const E *qrow = reinterpret_cast<const E *>(p.target) + b * p.target_stride_b;
-  // A launch takes as many rows as the workspace has slots (two key buffers and, from 16 V on, two buffers of
-  // the entries' numbers; when they are in order, the masses in fp64 from the start on); the launches of one call follow each other on the stream, so the
+  // A launch takes as many rows as the workspace has slots (two key buffers, then two buffers of
+  // (p-mass, q-mass) each); the launches of one call follow each other on the stream, so the
   // workspace is as large as the workgroups that can be resident need, not as the batch.
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
   if (p.only_flagged && *flag_of(work, V) == 0) return;  // (uniform) the other kernel has done the row
   uint32_t *key_a = reinterpret_cast<uint32_t *>(work), *key_b = key_a + V;
-  int *at_b = reinterpret_cast<int *>(work + 16u * (size_t)V), *at_a = at_b + V;
+  float2 *mass_a = reinterpret_cast<float2 *>(work + 8u * (size_t)V), *mass_b = mass_a + V;
 
   const Side sp = normalise<E>(prow, V, p.probs, p.temp_draft, s_red);
   const Side sq = normalise<E>(qrow, V, p.probs, p.temp_target, s_red);
 
-  // ---- sort keys with the numbers that travel with them, how often every digit occurs (the
+  // ---- sort keys with the masses that travel with them, how often every digit occurs (the
   // arithmetic around them hides the counters' collisions), and the sums that need no order
   for (int j = tid; j < 4 * kWaves * 256; j += kThreads) (&hist[0][0][0])[j] = 0;
   __syncthreads();
@@ -163,7 +166,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     key_a[i] = key;
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) atomicAdd(&hist[pass][wv][(key >> (8 * pass)) & 255u], 1);
-    at_a[i] = i;
+    mass_a[i] = make_float2((float)pm, (float)qm);
     tv += fabs(pm - qm);
     if (hp && hq) {
 #pragma unroll
@@ -197,7 +200,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
   // in LDS, and is written from there so that neighbouring threads write neighbouring addresses
   // (a digit's entries of one tile are contiguous in the output).
   uint32_t *kin = key_a, *kout = key_b;
-  int *ain = at_a, *aout = at_b;
+  float2 *min_ = mass_a, *mout = mass_b;
 #pragma unroll 1
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 8 * pass;
@@ -226,14 +229,14 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
       for (int j = tid; j < kWaves * 256; j += kThreads) (&s_cnt[0][0])[j] = 0;
       __syncthreads();
       uint32_t key[kRounds];
-      int number[kRounds];
+      float2 mass[kRounds];
       int where[kRounds];  // rank among the wavefront's entries of the same digit
 #pragma unroll
       for (int e = 0; e < kRounds; ++e) {
         const int i = t0 + wv * (64 * kRounds) + e * 64 + lane;
         const bool valid = FULL || i < V;
         key[e] = valid ? kin[i] : 0u;
-        number[e] = valid ? ain[i] : 0;
+        mass[e] = valid ? min_[i] : make_float2(0.0f, 0.0f);
       }
 #pragma unroll
       for (int e = 0; e < kRounds; ++e) {
@@ -294,7 +297,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
           const uint32_t d = (key[e] >> shift) & 255u;
           const int pos = s_tstart[d] + s_cnt[wv][d] + where[e];
           st_key[pos] = key[e];
-          st_at[pos] = number[e];
+          st_mass[pos] = mass[e];
         }
       }
       __syncthreads();
@@ -306,7 +309,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
           const uint32_t k = st_key[pos];
           const int g = s_gbase[(k >> shift) & 255u] + pos;
           kout[g] = k;
-          aout[g] = st_at[pos];
+          mout[g] = st_mass[pos];
         }
       }
     };
@@ -315,25 +318,22 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     for (; t0 + kTile <= V; t0 += kTile) sort_tile(std::true_type(), t0);
     if (t0 < V) sort_tile(std::false_type(), t0);
     { uint32_t *t = kin; kin = kout; kout = t; }
-    { int *t = ain; ain = aout; aout = t; }
+    { float2 *t = min_; min_ = mout; mout = t; }
   }
   __syncthreads();
-  // after four passes the sorted order is back in the first buffers (ain == at_a)
+  // after four passes the sorted order is back in the first buffers (min_ == mass_a)
 
   // ---- running sums over the sorted order.  Wavefront w takes the w-th part of the row: first
   // every part's masses are added up, then every wavefront walks its part with the masses of the
   // parts before it as the carry.
   const int seg = (V + kWaves - 1) / kWaves;
   const int seg_begin = min(wv * seg, V), seg_end = min(seg_begin + seg, V);
-  double2 *mass = reinterpret_cast<double2 *>(work);  // (16 V bytes: where the keys were)
+  const float2 *mass = min_;
   double seg_p = 0.0, seg_q = 0.0;
   for (int j = seg_begin + lane; j < seg_end; j += 64) {
-    const int i = at_a[j];
-    const double lp = sp.log_mass(elem<E>(prow, i)), lq = sq.log_mass(elem<E>(qrow, i));
-    const double pm = lp > -__builtin_huge_val() ? exp(lp) : 0.0, qm = lq > -__builtin_huge_val() ? exp(lq) : 0.0;
-    mass[j] = make_double2(pm, qm);
-    seg_p += pm;
-    seg_q += qm;
+    const float2 m = mass[j];
+    seg_p += (double)m.x;
+    seg_q += (double)m.y;
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) { seg_p += __shfl_xor(seg_p, d); seg_q += __shfl_xor(seg_q, d); }
@@ -351,9 +351,9 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     const int j = j0 + lane;
     double pm = 0.0, qm = 0.0;
     if (j < seg_end) {
-      const double2 m = mass[j];
-      pm = m.x;
-      qm = m.y;
+      const float2 m = mass[j];
+      pm = (double)m.x;
+      qm = (double)m.y;
     }
     double pin = pm, qin = qm;  // inclusive sums over the lanes of this tile
 #pragma unroll
@@ -361,7 +361,7 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
       const double up_p = __shfl_up(pin, d), up_q = __shfl_up(qin, d);
       if (lane >= d) { pin += up_p; qin += up_q; }
     }
-    if (pm >= 0x1p-150 && qm >= 0x1p-150) {
+    if (pm > 0.0 && qm > 0.0) {
       const double p_pre = p_before + (pin - pm);             // mass of p strictly before j
       const double q_suf = q_total - (q_before + (qin - qm));  // mass of q from j on
       // K / (q_suf/q_j + p_pre/p_j + (K - 1) Q/q_j), numerator and denominator times q_j
@@ -384,13 +384,13 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
     }
 }
 
-// ---- the form by buckets
+// ---- the form by cells
 
-// The rows it takes.  Shorter ones are quicker sorted (fewer fixed steps), from about 40 000 entries on if the
-// inputs are bf16, whose many ties cost the ordering in LDS (us a call, buckets against sorting: fp32 8 192
-// entries, 1 row 114 : 102, 12 288: 136 : 140, 32 000: 274 : 347; bf16 40 960, 64 rows 473 : 484, 512 rows 662 :
-// 895, 128 256: 64 rows 1219 : 1555, 512 rows 1740 : 2885; 1024 rows x 128 256 fp32 3150 : 7515).
-constexpr int kBucketMinV = 12288, kBucketMinVNarrow = 40960, kBucketMaxV = 1 << 18;
+// The rows it takes.  Shorter ones are quicker sorted: two sorting workgroups share a CU, the cells fill its LDS (us a
+// call, cells against sorting, 1, 256 and 1024 rows: fp32 4 000 entries 54 : 56, 60 : 66, 220 : 186; 6 144: 59 : 84,
+// 67 : 102, 249 : 296; 8 192: 68 : 101, 76 : 121, 283 : 356; 32 000: 138 : 272, 179 : 309, 646 : 867; bf16 4 000: 61 : 56, 64 : 64, 237 : 181; 6 144: 60 : 82, 70 : 96, 271 : 259; 8 192: 67 : 98,
+// 83 : 117, 309 : 319; 32 000: 141 : 335, 196 : 403, 718 : 1347).
+constexpr int kCellMinV = 6144, kCellMinVNarrow = 8192, kCellMaxV = 1 << 18;
 // The sample, and the buckets that its quantiles make.  Half of it are entries spread over the row, half the largest
 // that every two threads met on either side (those near enough the row's largest to count): where a row is masked by a finite
 // value, or is very sharp, what has mass would otherwise lie between two splitters.
@@ -401,7 +401,7 @@ constexpr int kCellThreads = 1024;
 constexpr int kCells = 6144, kOuterCells = 384;
 constexpr uint32_t kNoCell = 0xFFFFu;  // of an entry that lacks mass on a side
 constexpr int kListed = 128;           // entries of a row whose sums are formed exactly
-constexpr double kEntryError = 2e-9, kRowError = 2e-7;  // of the result
+constexpr double kEntryError = 2e-9, kRowError = 0x1p-23;  // of the result
 constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
 // An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within this of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
@@ -928,13 +928,13 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
 
 hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
   LmlParams p = params;
-  const bool buckets = p.V >= (p.dtype == LLC_F32 ? kBucketMinV : kBucketMinVNarrow) && p.V <= kBucketMaxV;
-  p.only_flagged = buckets ? 1 : 0;
+  const bool cells = p.V >= (p.dtype == LLC_F32 ? kCellMinV : kCellMinVNarrow) && p.V <= kCellMaxV;
+  p.only_flagged = cells ? 1 : 0;
   for (p.row0 = 0; p.row0 < p.B; p.row0 += p.slots) {
     const long long left = p.B - p.row0;
     const unsigned grid = (unsigned)(left < (long long)p.slots ? left : (long long)p.slots);
     const bool f32 = p.dtype == LLC_F32;
-    if (buckets) {
+    if (cells) {
 #define LLC_LML(E, PROBS) hipLaunchKernelGGL((lml_cell_kernel<E, PROBS>), dim3(grid), dim3(kCellThreads), 0, s, p);
       if (f32 && p.probs) { LLC_LML(float, true) }
       else if (f32) { LLC_LML(float, false) }
@@ -944,7 +944,7 @@ hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
-    // (behind the bucket kernel: the rows that it left, as a rule none)
+    // (behind the cell kernel: the rows that it left, as a rule none)
     if (f32) hipLaunchKernelGGL(lml_sort_kernel<float>, dim3(grid), dim3(kThreads), 0, s, p);
     else hipLaunchKernelGGL(lml_sort_kernel<uint16_t>, dim3(grid), dim3(kThreads), 0, s, p);
     const hipError_t e = hipGetLastError();
