@@ -156,16 +156,20 @@ class LmlArgs(ctypes.Structure):
 
 
 _lib = None
+_empties = None
 
 
 def load():
     """Load the HIP library (built by paper_2506_05632_amd/build.py); raise if it is not there."""
-    global _lib
+    global _lib, _empties
     if _lib is None:
         path = LIB_PATH
-        if not os.path.exists(path):
-            raise RuntimeError(f"{path} is missing: run `python -m paper_2506_05632_amd.build` "
-                               "(there is no CPU fallback)")
+        for needed in (path, os.path.join(os.path.dirname(os.path.abspath(__file__)), "_outputs.so")):
+            if not os.path.exists(needed):
+                raise RuntimeError(f"{needed} is missing: run `python -m paper_2506_05632_amd.build` "
+                                   "(there is no CPU fallback)")
+        from . import _outputs
+        _empties = _outputs.empties
         lib = ctypes.CDLL(path)
         lib.llc_couple.argtypes = [ctypes.POINTER(CoupleArgs)]
         lib.llc_couple.restype = ctypes.c_int
@@ -224,6 +228,11 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+def _new(device, specs: dict) -> dict:
+    """Uninitialised tensors by name, from (dtype, size, ...) tuples."""
+    return dict(zip(specs, _empties(device.index, *specs.values())))
+
+
 def _stream_handle(device):
     # (the current stream's handle as it is: a Stream object around it takes 1.9 us of a call's 15)
     return torch._C._cuda_getCurrentRawStream(device.index)
@@ -271,16 +280,17 @@ def llc_couple(draft: torch.Tensor, target: torch.Tensor, K: int, *, kind="logit
         sb, sk = draft.stride(0), draft.stride(1)
     dev = draft.device
     if out is None:
-        out = {"X": torch.empty(B, K, dtype=torch.int32, device=dev)}
+        specs = {"X": (torch.int32, B, K)}
         if not draft_only:
-            out["Y"] = torch.empty(B, dtype=torch.int32, device=dev)
-            out["accept"] = torch.empty(B, dtype=torch.uint8, device=dev)
+            specs["Y"] = (torch.int32, B)
+            specs["accept"] = (torch.uint8, B)
             if want_match:
-                out["match_k"] = torch.empty(B, dtype=torch.int32, device=dev)
+                specs["match_k"] = (torch.int32, B)
         if want_keys:
-            out["keyX"] = torch.empty(B, K, dtype=torch.float32, device=dev)
+            specs["keyX"] = (torch.float32, B, K)
             if not draft_only:
-                out["keyY"] = torch.empty(B, dtype=torch.float32, device=dev)
+                specs["keyY"] = (torch.float32, B)
+        out = _new(dev, specs)
     if workspace is None and not _static:
         workspace = new_workspace(B, K, V, dev)
     a = CoupleArgs()
@@ -339,13 +349,14 @@ def llc_couple_is(logw_enc: torch.Tensor, logw_dec: torch.Tensor, *, seed: int =
     if tuple(logw_dec.shape) != (B, L, N) or logw_enc.stride(-1) != 1 or logw_dec.stride(-1) != 1:
         raise ValueError("logw_dec must be [B,L,N] with a contiguous last dimension")
     dev = logw_enc.device
-    out = {"X": torch.empty(B, L, dtype=torch.int32, device=dev),
-           "Y": torch.empty(B, dtype=torch.int32, device=dev),
-           "accept": torch.empty(B, dtype=torch.uint8, device=dev),
-           "match_k": torch.empty(B, dtype=torch.int32, device=dev)}
+    specs = {"X": (torch.int32, B, L),
+             "Y": (torch.int32, B),
+             "accept": (torch.uint8, B),
+             "match_k": (torch.int32, B)}
     if want_keys:
-        out["keyX"] = torch.empty(B, L, dtype=torch.float32, device=dev)
-        out["keyY"] = torch.empty(B, dtype=torch.float32, device=dev)
+        specs["keyX"] = (torch.float32, B, L)
+        specs["keyY"] = (torch.float32, B)
+    out = _new(dev, specs)
     if workspace is None:
         workspace = new_workspace(B, L, N, dev)
     a = CoupleIsArgs()
@@ -394,20 +405,21 @@ def llc_compress_select(logw_enc: torch.Tensor, logw_dec: torch.Tensor, bins: to
         raise ValueError("logw_dec must be [B,L,N], bins [B,N], last dimensions contiguous")
     dev = logw_enc.device
     if out is None:
-        out = {"X": torch.empty(B, L, dtype=torch.int32, device=dev),
-               "Y": torch.empty(B, dtype=torch.int32, device=dev),
-               "message": torch.empty(B, dtype=torch.int32, device=dev),
-               "accept": torch.empty(B, dtype=torch.uint8, device=dev),
-               "match_k": torch.empty(B, dtype=torch.int32, device=dev)}
+        specs = {"X": (torch.int32, B, L),
+                 "Y": (torch.int32, B),
+                 "message": (torch.int32, B),
+                 "accept": (torch.uint8, B),
+                 "match_k": (torch.int32, B)}
         if want_keys:
-            out["keyX"] = torch.empty(B, L, dtype=torch.float32, device=dev)
-            out["keyY"] = torch.empty(B, dtype=torch.float32, device=dev)
+            specs["keyX"] = (torch.float32, B, L)
+            specs["keyY"] = (torch.float32, B)
         if cand is not None:
-            out["W"] = torch.empty(B, L, dtype=torch.float32, device=dev)
+            specs["W"] = (torch.float32, B, L)
             if side is not None:
-                out["A_hat"] = torch.empty(B, L, dtype=torch.float32, device=dev)
+                specs["A_hat"] = (torch.float32, B, L)
                 if source is not None:
-                    out["sq_err"] = torch.empty(B, dtype=torch.float32, device=dev)
+                    specs["sq_err"] = (torch.float32, B)
+        out = _new(dev, specs)
     for t, shape in ((cand, (B, N)), (side, (B, L)), (source, (B,))):
         if t is not None and (not t.is_cuda or t.dtype != torch.float32 or tuple(t.shape) != shape
                               or t.stride(-1) != 1):
@@ -483,13 +495,14 @@ def llc_couple_topm(draft_ids: torch.Tensor, draft_val: torch.Tensor, target_ids
         sb, sk = draft_val.stride(0), draft_val.stride(1)
     dev = target_val.device
     if out is None:
-        out = {"X": torch.empty(B, K, dtype=torch.int32, device=dev),
-               "Y": torch.empty(B, dtype=torch.int32, device=dev),
-               "accept": torch.empty(B, dtype=torch.uint8, device=dev),
-               "match_k": torch.empty(B, dtype=torch.int32, device=dev)}
+        specs = {"X": (torch.int32, B, K),
+                 "Y": (torch.int32, B),
+                 "accept": (torch.uint8, B),
+                 "match_k": (torch.int32, B)}
         if want_keys:
-            out["keyX"] = torch.empty(B, K, dtype=torch.float32, device=dev)
-            out["keyY"] = torch.empty(B, dtype=torch.float32, device=dev)
+            specs["keyX"] = (torch.float32, B, K)
+            specs["keyY"] = (torch.float32, B)
+        out = _new(dev, specs)
     a = TopmArgs()
     a.B, a.K, a.Md, a.Mt = B, K, Md, Mt
     a.dtype = F32 if draft_val.dtype == torch.float32 else BF16
@@ -545,14 +558,15 @@ def llc_verify(target: torch.Tensor, tokens: torch.Tensor, *, kind="logits", tem
                 or tokens.stride(2) != 1):
             raise ValueError("tokens must be [S, L, K] int32 on the device, last dimension contiguous")
     if out is None:
-        out = {"Y": torch.empty(S, L1, dtype=torch.int32, device=dev),
-               "n_out": torch.empty(S, dtype=torch.int32, device=dev),
-               "active": torch.empty(S, K, dtype=torch.uint8, device=dev)}
+        specs = {"Y": (torch.int32, S, L1),
+                 "n_out": (torch.int32, S),
+                 "active": (torch.uint8, S, K)}
         if want_keys:
-            out["keyY"] = torch.empty(S, L1, dtype=torch.float32, device=dev)
+            specs["keyY"] = (torch.float32, S, L1)
         if want_partials:
-            out["Yk"] = torch.empty(S, L1, K, dtype=torch.int32, device=dev)
-            out["keyYk"] = torch.empty(S, L1, K, dtype=torch.float32, device=dev)
+            specs["Yk"] = (torch.int32, S, L1, K)
+            specs["keyYk"] = (torch.float32, S, L1, K)
+        out = _new(dev, specs)
     if workspace is None:
         workspace = torch.empty(max(llc_verify_workspace_size(S, L, K, V), 256), dtype=torch.uint8, device=dev)
     a = VerifyArgs()

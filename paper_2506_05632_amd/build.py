@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -9,6 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libllc_hip.so")
 PROBE_LIB = os.path.join(HERE, "libllc_probe.so")   # machine probes for bench.py --workload peaks
+OUTPUTS = os.path.join(HERE, "_outputs.so")          # the binding's output tensors (a Python module)
 SOURCES = ["api.hip", "static_scratch.hip", "finalize.hip", "topm.hip", "lml.hip", "scan_f32_shared.hip", "scan_f32_perk.hip",
            "scan_bf16_shared.hip", "scan_bf16_perk.hip", "scan_f32_shared_minf.hip", "scan_f32_perk_minf.hip",
            "scan_bf16_shared_minf.hip", "scan_bf16_perk_minf.hip"]
@@ -26,6 +28,17 @@ def _hipcc():
 
 def _newest_header():
     return max(os.path.getmtime(os.path.join(CSRC, h)) for h in HEADERS)
+
+
+def _build_outputs(run):
+    """The one piece that knows torch's C++ side; host code only."""
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+         *("-isystem" + i for i in include), os.path.join(CSRC, "outputs.cpp"), "-o", OUTPUTS,
+         "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"])
 
 
 def build(force: bool = False, verbose: bool = False, extra_flags=()) -> str:
@@ -56,6 +69,9 @@ def build(force: bool = False, verbose: bool = False, extra_flags=()) -> str:
     probe_src = os.path.join(CSRC, "probe.hip")
     if force or not os.path.exists(PROBE_LIB) or os.path.getmtime(PROBE_LIB) < os.path.getmtime(probe_src):
         run([hipcc, *FLAGS, *extra_flags, "-shared", probe_src, "-o", PROBE_LIB])
+    outputs_src = os.path.join(CSRC, "outputs.cpp")
+    if force or not os.path.exists(OUTPUTS) or os.path.getmtime(OUTPUTS) < os.path.getmtime(outputs_src):
+        _build_outputs(run)
     return LIB
 
 
