@@ -403,7 +403,7 @@ constexpr uint32_t kNoCell = 0xFFFFu;  // of an entry that lacks mass on a side
 constexpr int kListed = 128;           // entries of a row whose sums are formed exactly
 constexpr double kEntryError = 2e-9, kRowError = 0x1p-23;  // of the result
 constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
-// An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within this of the centre
+// An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within 117 of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
 // ln z, which is at most ln 2^18.  So an entry without a place, from a centre that is near that one, has no
 // mass on one side, and which of such entries comes first is of no account.
