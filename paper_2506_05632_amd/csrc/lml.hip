@@ -55,6 +55,25 @@ __device__ double block_sum(double v, double *scratch) {
   for (int w = 0; w < waves; ++w) r += scratch[w];  // a fixed order
   return r;
 }
+// The same of several values at a time, in place; `scratch` holds as many doubles per wavefront.
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N], double *scratch) {
+  const int waves = blockDim.x >> 6;
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v[n] += __shfl_xor(v[n], d);
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+    if ((threadIdx.x & 63) == 0) scratch[(threadIdx.x >> 6) * N + n] = v[n];
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] = 0.0;
+  for (int w = 0; w < waves; ++w)
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] += scratch[w * N + n];
+}
 __device__ double block_max(double v, double *scratch) {
   const int waves = blockDim.x >> 6;
 #pragma unroll
@@ -401,7 +420,8 @@ constexpr int kCellThreads = 1024;
 constexpr int kCells = 6144, kOuterCells = 384;
 constexpr uint32_t kNoCell = 0xFFFFu;  // of an entry that lacks mass on a side
 constexpr int kListed = 128;           // entries of a row whose sums are formed exactly
-constexpr double kEntryError = 2e-9, kRowError = 0x1p-23;  // of the result
+constexpr float kEntryError = 2e-9f;   // what cells may leave open of a result, whichever list size it is for: of one entry ...
+constexpr double kRowError = 0x1p-23;  // ... and of all
 constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
 // An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within 117 of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
@@ -561,10 +581,16 @@ __device__ __forceinline__ unsigned long long fixed_mass(double e) {
 // One workgroup per row, one per CU (the cells' masses fill its LDS).  Nothing is sorted or moved.  The inner sum of term j
 // over entries of other cells needs the masses before and behind j's cell only.  Over the other entries of its own cell,
 // with masses P and Q in all, the sum of max(q_i p_j, p_i q_j) lies between max(Q p_j, P q_j) and that plus a quarter of
-// P q_j times the cell's width in ln r (the maximum is convex in r_i), and is taken as if they lay evenly in it.  Where
-// that uncertainty times the entry's share of the result is more than kEntryError the entry's own sum is formed exactly by one more
+// P q_j times the cell's width in ln r (the maximum is convex in r_i), and is taken as if they lay evenly in it.  That
+// uncertainty d is a part g = d / D of the denominator D for K = 1, where the entry's term is t, and moves its term for K
+// by K f^2 t g, f = D / (D + (K - 1) p_j), which is up to K times as much: it is weighed by the largest of K f^2 / (the result
+// for K) over the list sizes asked for.  D / p_j is the sum of max(q_i, r_j p_i), which depends on r_j alone and grows with it, so
+// a weight belongs to a cell, taken at its right end or further right (1024 rows of 128 256, four sizes: 2.129 ms without weights,
+// 2.136 so, 2.175 from a table for every entry, 2.265 by the sizes for every entry; 512 x 8 192 151 us, 154).  Where t g times that is more than kEntryError the entry's own sum is formed exactly by one more
 // walk over the row's cell numbers (two large masses in one cell: a few rows in a hundred); a row whose uncertainties
-// sum to more than kRowError of the result is left to the sorting kernel.
+// sum to more than kRowError of a result is left to the sorting kernel.
+// A mass below 2^-46 of its row's largest is 0 in a cell's sum: a denominator is no less than the larger of p_j and q_j (the
+// maxima are over all of a row whose masses sum to 1), so 2^18 such masses are less than 2^-28 of it.
 // What bounds it: instruction issue in fp64 (two exponentials an entry and pass), the latency of LDS atomics and reads.
 // The row is read three times, and two bytes an entry are written and read.  1024 rows of 128 256, four sizes: 2.12 ms,
 // against 3.13 with entries moved to buckets of about 1000 and those ordered in LDS; 1024 x 32 000 0.63 : 0.87,
@@ -576,14 +602,16 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   __shared__ float4 s_bucket[kMaxBuckets + 1];  // left end, cells per unit of ln r, first cell, last cell
   __shared__ int s_low[kCells], s_high[kCells]; // the smallest and largest place in a cell
   __shared__ int s_split[kMaxBuckets + 1];      // bucket b holds the places from s_split[b] up to s_split[b + 1]
-  __shared__ double s_red[kCellThreads / 64];
+  __shared__ double s_red[5 * (kCellThreads / 64)];
   __shared__ unsigned long long s_redu[kCellThreads / 64];
   __shared__ int s_redi[kCellThreads / 64];
   __shared__ int s_listed, s_at[kListed], s_list_cell[kListed], s_order[kListed];  // entries whose sums are formed exactly
   __shared__ unsigned long long s_above[kListed], s_below[kListed];
   __shared__ double s_ratio[kListed];
   __shared__ uint32_t s_mark[kCells / 32];
-  __shared__ int s_far[2];
+  __shared__ int s_far;
+  __shared__ double s_about[kLmlMaxK];  // a list size's result, about
+  __shared__ float s_scale[kLmlMaxK];   // K over that
   int *s_sample = reinterpret_cast<int *>(s_p);  // (before the cells)
   static_assert(kSamples * sizeof(int) <= sizeof(s_p) && kSamples == 2 * kCellThreads, "sizes");
 
@@ -768,8 +796,8 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   const double norm_p = zp > 0.0 ? 1.0 / zp : 0.0, norm_q = zq > 0.0 ? 1.0 / zq : 0.0;
   const double first = uniform(block_sum(p_first, s_red) * norm_p);
   const double unit_p = 0x1p-45 * norm_p, unit_q = 0x1p-45 * norm_q;
+  constexpr int kEach = kCells / kCellThreads;
   {
-    constexpr int kEach = kCells / kCellThreads;
     unsigned long long all;
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
@@ -783,14 +811,52 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
     }
   }
   __syncthreads();
-  // about what the result for K = 1 will be, every cell taken as one entry: errors are measured against it
-  double about = 0.0;
-  for (int c = tid; c < kCells; c += kCellThreads) {
-    const double pc = (double)(s_p[c + 1] - s_p[c]) * unit_p, qc = (double)(s_q[c + 1] - s_q[c]) * unit_q;
-    const double base = (1.0 - (double)s_q[c] * unit_q) * pc + ((double)s_p[c] * unit_p + first) * qc;
-    if (pc > 0.0 && qc > 0.0 && base > 0.0) about += pc * qc / base;
+  // about what the results will be, the thread's cells taken as one entry: uncertainties are measured against them
+  const int my_cell = tid * kEach;
+  const unsigned long long my_p = s_p[my_cell + kEach], my_q = s_q[my_cell];
+  double about_1 = 0.0;
+#pragma unroll 1
+  for (int n0 = 0; n0 < p.n_k; n0 += 4) {
+    double about[4] = {0.0, 0.0, 0.0, 0.0};
+    const double pc = (double)(my_p - s_p[my_cell]) * unit_p, qc = (double)(s_q[my_cell + kEach] - my_q) * unit_q;
+    const double base = (1.0 - (double)my_q * unit_q) * pc + ((double)s_p[my_cell] * unit_p + first) * qc;
+    const bool shared = pc > 0.0 && qc > 0.0 && base > 0.0;
+    if (shared) add_quotients<2>(about, p, n0, pc * qc, base, 1.0, pc);
+    double sum[5] = {about[0], about[1], about[2], about[3], shared ? pc * qc * reciprocal(base) : 0.0};
+    block_sums(sum, s_red);
+    about_1 = uniform(sum[4]);
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      if (tid == 0 && n0 + n < p.n_k) { s_about[n0 + n] = sum[n]; s_scale[n0 + n] = (float)(p.kd[n0 + n] / sum[n]); }
   }
-  const float entry_error = (float)(kEntryError * uniform(block_sum(about, s_red)));
+  // (two sides that share next to nothing: whatever is open is resolved)
+  const bool some_shared = about_1 > 0x1p-90;
+  const float entry_error = some_shared ? kEntryError : 0.0f;
+  if (tid == 0) s_far = 0;
+  __syncthreads();
+  // in place of the places: a cell's width in ln r, and what its entries' uncertainties are weighed by (at the right
+  // end of the thread's cells)
+  {
+    int right = (int)0x80000000;
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) {
+      const int low = s_low[my_cell + e], high = s_high[my_cell + e];
+      right = max(right, high);
+      s_low[my_cell + e] = __float_as_int(high > low ? distance_of(high) - distance_of(low) : 0.0f);
+    }
+    const double r_0 = (PROBS ? top_p / top_q : 1.0) * zp * norm_q;  // q / p of an entry at distance 0
+    const double before = fma((double)my_p, unit_p, first), from = fmax(1.0 - (double)my_q * unit_q, 0.0);
+    const double d = fma(before, exp_of_negative((double)distance_of(right)) * r_0, from);  // D / p_j
+    const float u = (float)reciprocal(fmin(fmax(d, 1.0), 0x1p900));
+    float weight = some_shared ? 0.0f : 1.0f;
+    for (int n = 0; some_shared && n < p.n_k; ++n) {
+      const float f = __builtin_amdgcn_rcpf(fmaf((float)p.k[n] - 1.0f, u, 1.0f));
+      weight = fmaxf(weight, s_scale[n] * f * f);
+    }
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) s_high[my_cell + e] = __float_as_int(weight);
+  }
+  __syncthreads();
 
   // ---- third pass: the terms (list sizes four at a time)
   double tv = 0.0;
@@ -822,7 +888,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
           const double po = fmax((double)(long long)(s_p[cell + 1] - pb - fixed_mass(ep)), 0.0) * unit_p;
           const double qo = fmax((double)(long long)(qb - s_q[cell] - fixed_mass(eq)), 0.0) * unit_q;
           const double a = qo * pm, c = po * qm;
-          const float width = distance_of(s_high[cell]) - distance_of(s_low[cell]);
+          const float width = __int_as_float(s_low[cell]);
           const double rest = fma(fmax(1.0 - (double)qb * unit_q, 0.0), pm, fma((double)pb, unit_p, first) * qm) + pm * qm;
           double inside = fmax(a, c);
           const double base = rest + inside;
@@ -830,14 +896,14 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
           const double inv = reciprocal(base);
           const float cw = (float)(c * inv) * width, side = (float)((a - c) * inv);
           const float gap = fminf((float)(fmin(a, c) * inv), 0.25f * cw * (1.0f + width));
-          const float share = (float)(pm * qm * inv);
-          if (share * gap > entry_error) {
+          const float open = (float)(pm * qm * inv) * gap * __int_as_float(s_high[cell]);
+          if (open > entry_error) {
             if (n0 == 0) {
               const int pos = atomicAdd(&s_listed, 1);
               if (pos < kListed) { s_at[pos] = i + j; s_list_cell[pos] = (int)cell; }
             }
           } else {
-            if (n0 == 0) doubt += share * gap;
+            if (n0 == 0) doubt += open;
             if (width < 0.5f && 2.0f * fabsf(side) < cw) {
               const float t = 0.5f * cw + side;  // > 0
               inside = c + (double)(t * t / (2.0f * cw)) * base;
@@ -901,27 +967,24 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
         add_quotients<2>(sums, p, n0, pm * qm, fma(behind, pm, before * qm) + pm * qm, 1.0, pm);
       }
     }
-    double bound_0 = 0.0;
+    double bound[5] = {sums[0], sums[1], sums[2], sums[3], (double)doubt};
+    block_sums(bound, s_red);
+    double others[5] = {relaxed[0], relaxed[1], relaxed[2], relaxed[3], tv};
+    block_sums(others, s_red);
+    if (tid == 0) {
 #pragma unroll
-    for (int n = 0; n < 4; ++n)
-      if (n0 + n < p.n_k) {  // uniform
-        const double r = block_sum(sums[n], s_red);
-        if (n == 0) bound_0 = r;
-        if (tid == 0) p.bound[b_row * p.n_k + n0 + n] = r;
-        if (p.relaxed != nullptr) {
-          const double x = block_sum(relaxed[n], s_red);
-          if (tid == 0) p.relaxed[b_row * p.n_k + n0 + n] = x;
+      for (int n = 0; n < 4; ++n)
+        if (n0 + n < p.n_k) {
+          // (the doubt is relative to what each result was to be about)
+          if (bound[4] * s_about[n0 + n] > kRowError * bound[n]) s_far = 1;
+          p.bound[b_row * p.n_k + n0 + n] = bound[n];
+          if (p.relaxed != nullptr) p.relaxed[b_row * p.n_k + n0 + n] = others[n];
         }
-      }
-    if (n0 == 0) {
-      tv = block_sum(tv, s_red);
-      if (tid == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * tv;
-      const double d = block_sum((double)doubt, s_red);
-      if (tid == 0) s_far[0] = d > kRowError * bound_0 ? 1 : 0;
+      if (n0 == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * others[4];
     }
   }
   __syncthreads();
-  if (tid == 0) *flag_of(work, V) = s_listed > kListed || s_far[0] != 0 ? 1 : 0;
+  if (tid == 0) *flag_of(work, V) = s_listed > kListed || s_far != 0 ? 1 : 0;
 }
 
 }  // namespace

@@ -14,13 +14,13 @@ DEV = "cuda:0"
 KS = [1, 4, 5, 9, 16]
 
 
-def _check(draft, target, ws, kind="logits"):
-    gpu = llc.llc_lml_bound(draft, target, KS, kind=kind, workspace=ws)
+def _check(draft, target, ws, kind="logits", ks=KS):
+    gpu = llc.llc_lml_bound(draft, target, ks, kind=kind, workspace=ws)
     torch.cuda.synchronize()
-    ref = lml.lml_rows(draft.float().cpu().numpy(), target.float().cpu().numpy(), KS, kind=kind)
+    ref = lml.lml_rows(draft.float().cpu().numpy(), target.float().cpu().numpy(), ks, kind=kind)
     for name in ("bound", "relaxed", "tv"):
         np.testing.assert_allclose(gpu[name].cpu().numpy(), ref[name], rtol=2.0 ** -22, err_msg=name)
-    again = llc.llc_lml_bound(draft, target, KS, kind=kind, workspace=torch.zeros_like(ws))
+    again = llc.llc_lml_bound(draft, target, ks, kind=kind, workspace=torch.zeros_like(ws))
     for name in ("bound", "relaxed", "tv"):
         assert torch.equal(again[name], gpu[name]), name
 
@@ -60,3 +60,49 @@ def test_the_shortest_rows(V, dtype, kind):
         td, tq = (torch.exp(t.double() - t.double().amax(dim=1, keepdim=True)).float() for t in (td, tq))
     ws = torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV)
     _check(td.to(dtype), tq.to(dtype), ws, kind)
+
+
+def _uncertain_row(V, width, mass, g):
+    """Half of the entries have next to no mass and lie far to the right in ln(q/p); between them and the others, 200
+    entries of a few threads (so that the sample holds few of them) with one ratio and together `mass` of the
+    draft's and half of the target's, and at 0.5 `width` on either side of it in ln(q/p) one of them each: one cell whose order
+    is not known, and in which the entries do not lie evenly."""
+    p = torch.randn(V, generator=g, device=DEV, dtype=torch.float64)
+    q = p + torch.randn(V, generator=g, device=DEV, dtype=torch.float64)
+    far = torch.rand(V, generator=g, device=DEV) < 0.5
+    p[far] -= 70.0
+    q[far] -= 40.0
+    at = (torch.arange(25, device=DEV)[:, None] * 4096 + torch.arange(8, device=DEV)).flatten()
+    p_ln, q_ln = torch.log(p.exp().sum() * mass / 200), torch.log(q.exp().sum() / 200)
+    p[at] = p_ln
+    q[at] = q_ln + 1e-6 * torch.randn(200, generator=g, device=DEV, dtype=torch.float64)
+    q[at[0]] += 0.5 * width
+    q[at[1]] -= 0.5 * width
+    return p.float(), q.float()
+
+
+@pytest.mark.parametrize("ks", [[1, 4, 8, 16, 64], [64, 1], [1024, 64, 16, 8, 4, 2, 1], [1 << 20]])
+@pytest.mark.parametrize("swap", [False, True])
+def test_what_cells_leave_open_is_bounded_for_every_list_size(ks, swap):
+    # an error of a denominator counts up to K times as much for the sum of K as for that of 1, so rows that are certain
+    # enough for one list size are not for another, in whatever order they are asked for
+    g = torch.Generator(device=DEV).manual_seed(9)
+    V = 131072
+    rows = [_uncertain_row(V, width, mass, g) for width in (0.005, 0.02, 0.05) for mass in (0.0005, 0.002, 0.005)]
+    draft, target = (torch.stack(side) for side in zip(*rows))
+    if swap:
+        draft, target = target, draft
+    _check(draft, target, torch.zeros(24 * V * len(rows) + 256, dtype=torch.uint8, device=DEV), ks=ks)
+
+
+def test_masses_that_cells_do_not_see():
+    # all that the two sides share has less than 2^-46 of either row's largest: the cells' sums are 0 there
+    g = torch.Generator(device=DEV).manual_seed(10)
+    B, V = 3, 40000
+    draft = -40.0 + torch.randn(B, V, generator=g, device=DEV)
+    target = -40.0 + torch.randn(B, V, generator=g, device=DEV)
+    draft[:, 5], target[:, 5] = 0.0, -90.0
+    draft[:, 9], target[:, 9] = -90.0, 0.0
+    draft[1, 100:200], target[1, 100:200] = -0.5, -85.0
+    target[2, 300:900] = -20.0
+    _check(draft, target, torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV), ks=[1, 16, 1000])
