@@ -13,7 +13,7 @@
 //  cells, finely where a sample of the row has many entries or much mass; one pass adds every cell's masses up, as
 //  whole numbers in LDS, and the next takes the terms, for which only the order inside an entry's own cell is not
 //  known.  That is bounded per entry (see lml_cell_kernel); where it matters it is resolved exactly.
-//  by sorting (other rows, and a row that the cells do not resolve): four passes of a
+//  by sorting (other rows, and a row that the cells do not resolve, also when they are shared out again): four passes of a
 //  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses, rounded to fp32, travel with their
 //  key through two buffers in the workspace.
 //
@@ -409,6 +409,10 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
 // call, cells against sorting, 1, 256 and 1024 rows: fp32 4 000 entries 54 : 56, 60 : 66, 220 : 186; 6 144: 59 : 84,
 // 67 : 102, 249 : 296; 8 192: 68 : 101, 76 : 121, 283 : 356; 32 000: 138 : 272, 179 : 309, 646 : 867; bf16 4 000: 61 : 56, 64 : 64, 237 : 181; 6 144: 60 : 82, 70 : 96, 271 : 259; 8 192: 67 : 98,
 // 83 : 117, 309 : 319; 32 000: 141 : 335, 196 : 403, 718 : 1347).
+// Rows in doubt get a second attempt behind the first from kAgainMinV entries on: what cells leave open grows with the
+// entries that share one.  (Of twenty families of rows none had more than half of what is allowed at 50 257 entries, several more than
+// all of it from 152 064 on.  A launch that finds nothing to do is some 2 us; a row of 65 536 takes 230.)
+constexpr int kAgainMinV = 1 << 16;
 constexpr int kCellMinV = 6144, kCellMinVNarrow = 8192, kCellMaxV = 1 << 18;
 // The sample, and the buckets that its quantiles make.  Half of it are entries spread over the row, half the largest
 // that every two threads met on either side (those near enough the row's largest to count): where a row is masked by a finite
@@ -418,10 +422,12 @@ constexpr double kCounts = 0x1p-40;  // of the row's largest
 constexpr int kMaxBuckets = 255;
 constexpr int kCellThreads = 1024;
 constexpr int kCells = 6144, kOuterCells = 384;
+constexpr int kFewestCells = 8;        // of a bucket when they are shared out again
+constexpr int kInDoubt = 2;            // a row's flag: its uncertainties sum to too much
 constexpr uint32_t kNoCell = 0xFFFFu;  // of an entry that lacks mass on a side
 constexpr int kListed = 128;           // entries of a row whose sums are formed exactly
-constexpr float kEntryError = 2e-9f;   // what cells may leave open of a result, whichever list size it is for: of one entry ...
-constexpr double kRowError = 0x1p-23;  // ... and of all
+constexpr float kEntryError = 1e-9f;   // what cells may leave open of a result, whichever list size it is for: of one entry ...
+constexpr double kRowError = 0x1.8p-23;  // ... and of all
 constexpr float kFar = 512.0f;         // entries farther from the row's centre in ln r have no place
 // An entry with both masses above zero in fp32 (2^-150 or more: ln >= -104) lies within 117 of the centre
 // that the rows' largest entries make, in ln r: each mass is an entry's distance to its row's largest, less
@@ -580,15 +586,20 @@ __device__ __forceinline__ unsigned long long fixed_mass(double e) {
 
 // One workgroup per row, one per CU (the cells' masses fill its LDS).  Nothing is sorted or moved.  The inner sum of term j
 // over entries of other cells needs the masses before and behind j's cell only.  Over the other entries of its own cell,
-// with masses P and Q in all, the sum of max(q_i p_j, p_i q_j) lies between max(Q p_j, P q_j) and that plus a quarter of
-// P q_j times the cell's width in ln r (the maximum is convex in r_i), and is taken as if they lay evenly in it.  That
+// with masses P and Q in all, the sum of max(q_i p_j, p_i q_j) is P q_j times a mean of max(x_i, 1), x_i = r_i / r_j, weighed by
+// p_i.  That is convex in x: no less than the maximum at the mean 1 + s = (Q p_j) / (P q_j), and no more than the chord
+// over the cell there, which is (w - |s|)^2 / 4 w above it at most, wherever in the cell's width w (in x; below
+// w_l (1 + w_l) of the width in ln r, up to 1.5) j lies.  It is taken as if the others lay evenly in the cell.  That
 // uncertainty d is a part g = d / D of the denominator D for K = 1, where the entry's term is t, and moves its term for K
 // by K f^2 t g, f = D / (D + (K - 1) p_j), which is up to K times as much: it is weighed by the largest of K f^2 / (the result
 // for K) over the list sizes asked for.  D / p_j is the sum of max(q_i, r_j p_i), which depends on r_j alone and grows with it, so
 // a weight belongs to a cell, taken at its right end or further right (1024 rows of 128 256, four sizes: 2.129 ms without weights,
 // 2.136 so, 2.175 from a table for every entry, 2.265 by the sizes for every entry; 512 x 8 192 151 us, 154).  Where t g times that is more than kEntryError the entry's own sum is formed exactly by one more
 // walk over the row's cell numbers (two large masses in one cell: a few rows in a hundred); a row whose uncertainties
-// sum to more than kRowError of a result is left to the sorting kernel.
+// sum to more than kRowError of a result is done AGAIN by another launch, with cells shared out by where they were, and
+// left to the sorting kernel, which takes twice as long as both, if that is not enough.  (256 rows, one side flat, the other
+// normal times 3, us, before, when 0.25 w stood for (w - |s|)^2 / 4 w and 2^-23 for kRowError and nearly all were sorted, and now: 128 256
+// entries 2742, 1190, without a row in doubt 520; 152 064: 3362, 1389; 262 144: 5787, 2237.)
 // A mass below 2^-46 of its row's largest is 0 in a cell's sum: a denominator is no less than the larger of p_j and q_j (the
 // maxima are over all of a row whose masses sum to 1), so 2^18 such masses are less than 2^-28 of it.
 // What bounds it: instruction issue in fp64 (two exponentials an entry and pass), the latency of LDS atomics and reads.
@@ -596,7 +607,7 @@ __device__ __forceinline__ unsigned long long fixed_mass(double e) {
 // against 3.13 with entries moved to buckets of about 1000 and those ordered in LDS; 1024 x 32 000 0.63 : 0.87,
 // 512 x 152 064 bf16 1.37 : 1.94, one row 0.43 : 1.00, 64 x 262 144 0.96 : 2.11, eight sizes 512 rows 1.56 : 2.26.
 // All sums run in an order that does not depend on how the wavefronts interleave.
-template <typename E, bool PROBS>
+template <typename E, bool PROBS, bool AGAIN>
 __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlParams p) {
   __shared__ unsigned long long s_p[kCells + 1], s_q[kCells + 1];  // a cell's masses, then what lies before it
   __shared__ float4 s_bucket[kMaxBuckets + 1];  // left end, cells per unit of ln r, first cell, last cell
@@ -613,7 +624,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   __shared__ double s_about[kLmlMaxK];  // a list size's result, about
   __shared__ float s_scale[kLmlMaxK];   // K over that
   int *s_sample = reinterpret_cast<int *>(s_p);  // (before the cells)
-  static_assert(kSamples * sizeof(int) <= sizeof(s_p) && kSamples == 2 * kCellThreads, "sizes");
+  static_assert(kSamples * sizeof(int) <= sizeof(s_p) && kSamples == 2 * kCellThreads && kMaxBuckets * kFewestCells < kCells, "sizes");
 
   const int tid = threadIdx.x;
   const long long b_row = p.row0 + blockIdx.x;
@@ -621,6 +632,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   const E *prow = reinterpret_cast<const E *>(p.draft) + b_row * p.draft_stride_b;
   const E *qrow = reinterpret_cast<const E *>(p.target) + b_row * p.target_stride_b;
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
+  if (AGAIN && *flag_of(work, V) != kInDoubt) return;  // (uniform)
   unsigned short *ids = reinterpret_cast<unsigned short *>(work);
   const float none = PROBS ? 0.0f : -__builtin_huge_valf();
   const float ninf = -__builtin_huge_valf();
@@ -733,84 +745,106 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   pick_splitters();
   nb = uniform(nb);
   __syncthreads();
-  // cells: the outer buckets, which are the longest, get kOuterCells each, the others share the rest evenly
-  const int outer = nb > 2 ? kOuterCells : kCells / nb, inner = nb > 2 ? (kCells - 2 * kOuterCells) / (nb - 2) : 0;
-  const int last_first = kCells - outer;  // the last bucket's first cell
-  if (tid < nb) {
-    const float left = tid > 0 ? distance_of(s_split[tid]) : far_left;
-    const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : far_right;
-    // (two places can be farther apart than an int reaches; one more than a place is one)
-    const bool one_place = tid >= 1 && tid + 1 < nb && s_split[tid + 1] <= s_split[tid] + 1;
-    const int cells = tid == 0 || tid + 1 == nb ? outer : inner;
-    const int first = tid == 0 ? 0 : tid + 1 == nb ? last_first : outer + (tid - 1) * inner;
-    const float scale = one_place || !(right > left) ? 0.0f : (float)cells / (right - left);
-    s_bucket[tid] = make_float4(left, scale, (float)first, (float)(first + cells - 1));
-  }
   if (tid == 0) { s_split[0] = (int)0x80000000; s_listed = 0; }
   if (tid < kCells / 32) s_mark[tid] = 0u;
-  __syncthreads();
-  for (int c = tid; c <= kCells; c += kCellThreads) {
-    s_p[c] = 0ull;
-    s_q[c] = 0ull;
-    if (c < kCells) { s_low[c] = 0x7FFFFFFF; s_high[c] = (int)0x80000000; }
-  }
-  __syncthreads();
-
-  // ---- second pass: every entry's cell, the cells' masses, and the sums of all masses
-  double zp = 0.0, zq = 0.0, p_first = 0.0;
-  for (int i = tid * 4; i < V; i += kCellThreads * 4) {
-    const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
-    uint32_t packed[2] = {0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float xp = at(xp4, j), xq = at(xq4, j);
-      const double ep = relative(xp, top_p, per_p), eq = relative(xq, top_q, per_q);
-      zp += ep;
-      zq += eq;
-      uint32_t cell = kNoCell;
-      if (some && pl.mass(xp) && pl.mass(xq)) {
-        const float d = pl.distance(xp, xq);
-        if (fabsf(d) < kFar) {
-          const int place = place_of(d);
-          const float4 bu = s_bucket[nb > 1 ? bucket_of(s_split, nb, place) : 0];
-          cell = (uint32_t)(int)fminf(fmaxf((d - bu.x) * bu.y, 0.0f) + bu.z, bu.w);
-          atomicAdd(&s_p[cell], fixed_mass(ep));
-          atomicAdd(&s_q[cell], fixed_mass(eq));
-          atomicMin(&s_low[cell], place);
-          atomicMax(&s_high[cell], place);
-        }
-      }
-      // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
-      // p-mass to speak of)
-      if (cell == kNoCell) p_first += ep;
-      packed[j >> 1] |= cell << (16 * (j & 1));
-    }
-    if (i + 3 < V) {
-      *reinterpret_cast<uint2 *>(ids + i) = make_uint2(packed[0], packed[1]);
-    } else {
-      for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned short)(packed[j >> 1] >> (16 * (j & 1)));
-    }
-  }
-  zp = uniform(block_sum(zp, s_red));
-  zq = uniform(block_sum(zq, s_red));
-  const double norm_p = zp > 0.0 ? 1.0 / zp : 0.0, norm_q = zq > 0.0 ? 1.0 / zq : 0.0;
-  const double first = uniform(block_sum(p_first, s_red) * norm_p);
-  const double unit_p = 0x1p-45 * norm_p, unit_q = 0x1p-45 * norm_q;
+  // cells: the outer buckets, which are the longest, get kOuterCells each, the others share the rest evenly
+  int my_cells = 0;  // of bucket number `tid`
+  if (tid < nb) my_cells = nb <= 2 ? kCells / nb : tid == 0 || tid + 1 == nb ? kOuterCells : (kCells - 2 * kOuterCells) / (nb - 2);
+  double zp, zq, first, norm_p, norm_q, unit_p, unit_q;
   constexpr int kEach = kCells / kCellThreads;
-  {
-    unsigned long long all;
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      unsigned long long *m = side == 0 ? s_p : s_q, mine[kEach], sum = 0ull;
-#pragma unroll
-      for (int e = 0; e < kEach; ++e) { mine[e] = m[tid * kEach + e]; sum += mine[e]; }
-      unsigned long long before = block_prefix(sum, s_redu, &all);
-#pragma unroll
-      for (int e = 0; e < kEach; ++e) { m[tid * kEach + e] = before; before += mine[e]; }
-      if (tid == kCellThreads - 1) m[kCells] = before;
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    int in_all;
+    const int my_first = block_prefix(my_cells, s_redi, &in_all);
+    if (tid < nb) {
+      const float left = tid > 0 ? distance_of(s_split[tid]) : far_left;
+      const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : far_right;
+      // (two places can be farther apart than an int reaches; one more than a place is one)
+      const bool one_place = tid >= 1 && tid + 1 < nb && s_split[tid + 1] <= s_split[tid] + 1;
+      const float scale = one_place || !(right > left) ? 0.0f : (float)my_cells / (right - left);
+      s_bucket[tid] = make_float4(left, scale, (float)my_first, (float)(my_first + my_cells - 1));
     }
+    for (int c = tid; c <= kCells; c += kCellThreads) {
+      s_p[c] = 0ull;
+      s_q[c] = 0ull;
+      if (c < kCells) { s_low[c] = 0x7FFFFFFF; s_high[c] = (int)0x80000000; }
+    }
+    __syncthreads();
+
+    // ---- second pass: every entry's cell, the cells' masses, and the sums of all masses
+    double p_first = 0.0;
+    zp = zq = 0.0;
+    for (int i = tid * 4; i < V; i += kCellThreads * 4) {
+      const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+      uint32_t packed[2] = {0u, 0u};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float xp = at(xp4, j), xq = at(xq4, j);
+        const double ep = relative(xp, top_p, per_p), eq = relative(xq, top_q, per_q);
+        zp += ep;
+        zq += eq;
+        uint32_t cell = kNoCell;
+        if (some && pl.mass(xp) && pl.mass(xq)) {
+          const float d = pl.distance(xp, xq);
+          if (fabsf(d) < kFar) {
+            const int place = place_of(d);
+            const float4 bu = s_bucket[nb > 1 ? bucket_of(s_split, nb, place) : 0];
+            cell = (uint32_t)(int)fminf(fmaxf((d - bu.x) * bu.y, 0.0f) + bu.z, bu.w);
+            atomicAdd(&s_p[cell], fixed_mass(ep));
+            atomicAdd(&s_q[cell], fixed_mass(eq));
+            atomicMin(&s_low[cell], place);
+            atomicMax(&s_high[cell], place);
+          }
+        }
+        // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
+        // p-mass to speak of)
+        if (cell == kNoCell) p_first += ep;
+        packed[j >> 1] |= cell << (16 * (j & 1));
+      }
+      if (i + 3 < V) {
+        *reinterpret_cast<uint2 *>(ids + i) = make_uint2(packed[0], packed[1]);
+      } else {
+        for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned short)(packed[j >> 1] >> (16 * (j & 1)));
+      }
+    }
+    zp = uniform(block_sum(zp, s_red));
+    zq = uniform(block_sum(zq, s_red));
+    norm_p = zp > 0.0 ? 1.0 / zp : 0.0;
+    norm_q = zq > 0.0 ? 1.0 / zq : 0.0;
+    first = uniform(block_sum(p_first, s_red) * norm_p);
+    unit_p = 0x1p-45 * norm_p;
+    unit_q = 0x1p-45 * norm_q;
+    {
+      unsigned long long all;
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        unsigned long long *m = side == 0 ? s_p : s_q, mine[kEach], sum = 0ull;
+#pragma unroll
+        for (int e = 0; e < kEach; ++e) { mine[e] = m[tid * kEach + e]; sum += mine[e]; }
+        unsigned long long before = block_prefix(sum, s_redu, &all);
+#pragma unroll
+        for (int e = 0; e < kEach; ++e) { m[tid * kEach + e] = before; before += mine[e]; }
+        if (tid == kCellThreads - 1) m[kCells] = before;
+      }
+    }
+    __syncthreads();
+    if (!AGAIN || round == 1) break;
+    // cells where they are wanted: a bucket's uncertainty is about the sum of t^2 w over its cells, t a cell's term and w its
+    // width, and falls with the square of their number, so the sum over all buckets is least with numbers that go with
+    // the cube root of t^2 w times the present number squared
+    float wants = 0.0f;
+    if (tid < nb) {
+      for (int c = my_first; c < my_first + my_cells; ++c) {
+        const double pc = (double)(s_p[c + 1] - s_p[c]) * unit_p, qc = (double)(s_q[c + 1] - s_q[c]) * unit_q;
+        const double base = (1.0 - (double)s_q[c] * unit_q) * pc + ((double)s_p[c] * unit_p + first) * qc;
+        const float t = pc > 0.0 && qc > 0.0 && base > 0.0 ? (float)(pc * qc * reciprocal(base)) : 0.0f;
+        if (s_high[c] > s_low[c]) wants += t * t * (distance_of(s_high[c]) - distance_of(s_low[c]));
+      }
+      if (wants > 0.0f) wants = exp2f(log2f(wants * (float)my_cells * (float)my_cells) * (1.0f / 3.0f));
+    }
+    const float wanted = (float)block_sum((double)wants, s_red);
+    if (tid < nb && wanted > 0.0f) my_cells = kFewestCells + (int)((float)(kCells - 1 - nb * kFewestCells) * (wants / wanted));
   }
-  __syncthreads();
   // about what the results will be, the thread's cells taken as one entry: uncertainties are measured against them
   const int my_cell = tid * kEach;
   const unsigned long long my_p = s_p[my_cell + kEach], my_q = s_q[my_cell];
@@ -894,8 +928,9 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
           const double base = rest + inside;
           // relative to the denominator: in fp32, as small as they are
           const double inv = reciprocal(base);
-          const float cw = (float)(c * inv) * width, side = (float)((a - c) * inv);
-          const float gap = fminf((float)(fmin(a, c) * inv), 0.25f * cw * (1.0f + width));
+          const float cw = (float)(c * inv) * width, side = (float)((a - c) * inv), per_cw = __builtin_amdgcn_rcpf(fmaxf(cw, 1e-30f));
+          const float reach = fmaxf(fmaf(cw, width, cw) - fabsf(side), 0.0f);
+          const float gap = fminf((float)(fmin(a, c) * inv), width < 1.5f ? 0.25f * reach * reach * per_cw : 1.0f);
           const float open = (float)(pm * qm * inv) * gap * __int_as_float(s_high[cell]);
           if (open > entry_error) {
             if (n0 == 0) {
@@ -906,7 +941,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
             if (n0 == 0) doubt += open;
             if (width < 0.5f && 2.0f * fabsf(side) < cw) {
               const float t = 0.5f * cw + side;  // > 0
-              inside = c + (double)(t * t / (2.0f * cw)) * base;
+              inside = c + (double)(0.5f * t * t * per_cw) * base;
             }
             add_quotients<2>(sums, p, n0, pm * qm, rest + inside, 1.0, pm);
           }
@@ -984,7 +1019,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
     }
   }
   __syncthreads();
-  if (tid == 0) *flag_of(work, V) = s_listed > kListed || s_far != 0 ? 1 : 0;
+  if (tid == 0) *flag_of(work, V) = s_listed > kListed || (AGAIN && s_far != 0) ? 1 : s_far != 0 ? kInDoubt : 0;
 }
 
 }  // namespace
@@ -998,11 +1033,15 @@ hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
     const unsigned grid = (unsigned)(left < (long long)p.slots ? left : (long long)p.slots);
     const bool f32 = p.dtype == LLC_F32;
     if (cells) {
-#define LLC_LML(E, PROBS) hipLaunchKernelGGL((lml_cell_kernel<E, PROBS>), dim3(grid), dim3(kCellThreads), 0, s, p);
-      if (f32 && p.probs) { LLC_LML(float, true) }
-      else if (f32) { LLC_LML(float, false) }
-      else if (p.probs) { LLC_LML(uint16_t, true) }
-      else { LLC_LML(uint16_t, false) }
+#define LLC_LML(E, PROBS)                                                                                               \
+  {                                                                                                                     \
+    hipLaunchKernelGGL((lml_cell_kernel<E, PROBS, false>), dim3(grid), dim3(kCellThreads), 0, s, p);                    \
+    if (p.V >= kAgainMinV) hipLaunchKernelGGL((lml_cell_kernel<E, PROBS, true>), dim3(grid), dim3(kCellThreads), 0, s, p); \
+  }
+      if (f32 && p.probs) LLC_LML(float, true)
+      else if (f32) LLC_LML(float, false)
+      else if (p.probs) LLC_LML(uint16_t, true)
+      else LLC_LML(uint16_t, false)
 #undef LLC_LML
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
