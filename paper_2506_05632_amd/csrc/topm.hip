@@ -92,9 +92,10 @@ __device__ __forceinline__ void store_best(Race &r, const Best &v) {
 // What bounds it: the latency of its phases (reductions across lanes, the exact keys' logarithms), then
 // instruction issue.  Exact keys for all entries took more than half of all instructions; both halves of every
 // entry's word, two blocks for each draft, most of the rest: 1024 rows, K = 8, one list of 50, with keys 13.0 us, now
-// 10.9; lists of 256, own for each draft 36.1, 30.3, shared 28.4, 21.0.  (Fetching ahead of use, and a shorter
-// exponential for the normalisers, changed nothing.)
-template <bool PROBS, bool MANY>
+// 10.9; lists of 256, own for each draft 36.1, 30.3, shared 28.4, 21.0.  (Fetching every round's entries a
+// round ahead, beyond the first ones that are, and a shorter exponential for the normalisers, changed nothing.)
+// WHOLE: what is near by its upper half-word is looked at again with the whole word (see launch_topm).
+template <bool PROBS, bool MANY, bool WHOLE>
 __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   __shared__ double c_key[kCandidates];
   __shared__ int c_id[kCandidates], c_k[kCandidates];  // c_k: the draft, K more for a pool entry
@@ -165,10 +166,26 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   auto lower_tau = [&](float &tau, const float a) {
     tau = fminf(tau, unord32(__builtin_amdgcn_readlane(wave_min_to_last(ord32(a)), 63)));
   };
-  auto list = [&](const bool has, const int id, const float v, const uint32_t half, const int tag, const float low, const float tau) {
+  auto is_near = [&](const float a, const float tau) {
     // (far values: the fp32 product's rounding grows with them; beyond all measure every entry goes)
     const float band = kEps2 + (fabsf(tau) + 64.0f) * 0x1p-20f;
-    const bool near = low <= tau + band || !(fabsf(tau) < 1e30f);
+    return a <= tau + band || !(fabsf(tau) < 1e30f);
+  };
+  auto list = [&](const bool has, const int id, const float v, const uint32_t half, const float c, const int tag, const float low,
+                  float &tau) {
+    bool near = is_near(low, tau);
+    if (WHOLE && __ballot(has && near) != 0ull) {  // uniform
+      float a = inf, ell;
+      if (has && near && approx_log2_mass<PROBS>(v, c, ell)) {
+        const uint32_t k = (uint32_t)(tag >= K ? tag - K : tag);
+        uint32_t lo[4];
+        philox_block(row_lo, (uint32_t)id >> 2, row_hi, (k >> 1) | kLowBlock, p.seed_lo, p.seed_hi, lo);
+        const uint32_t lw = pick(lo, (uint32_t)id);
+        a = approx_log2_race_time((half << 16) | ((k & 1u) ? lw >> 16 : lw & 0xFFFFu)) - ell;
+      }
+      lower_tau(tau, a);
+      near = near && is_near(a, tau);
+    }
     if (has) ++evals;
     if (has && near) {
       const int pos = atomicAdd(&s_count, 1);
@@ -226,11 +243,11 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
         const uint32_t mine = (k & 1) ? halves >> 16 : halves & 0xFFFFu;
         const Bounds a = bounds(has, x.v, mine, c);
         lower_tau(tau[0], a.high);
-        list(has, x.id, x.v, mine, k, a.low, tau[0]);
+        list(has, x.id, x.v, mine, c, k, a.low, tau[0]);
         if (two) {  // (k is even)
           const Bounds o = bounds(has, x.v, halves >> 16, c);
           lower_tau(tau[1], o.high);
-          list(has, x.id, x.v, halves >> 16, k + 1, o.low, tau[1]);
+          list(has, x.id, x.v, halves >> 16, c, k + 1, o.low, tau[1]);
         }
       }
     }
@@ -248,8 +265,8 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
           const uint32_t halves = upper_of((uint32_t)x.id, (uint32_t)(k >> 1), row_lo, row_hi, p.seed_lo, p.seed_hi);
           const Bounds a = bounds(has, x.v, halves & 0xFFFFu, c), o = bounds(two, x.v, halves >> 16, c);
           lower_tau(tau, fminf(a.high, o.high));
-          list(has, x.id, x.v, halves & 0xFFFFu, K + k, a.low, tau);
-          list(two, x.id, x.v, halves >> 16, K + k + 1, o.low, tau);
+          list(has, x.id, x.v, halves & 0xFFFFu, c, K + k, a.low, tau);
+          list(two, x.id, x.v, halves >> 16, c, K + k + 1, o.low, tau);
         }
       }
       // ---- normalisers, only for reported keys (the argmins and near-ties need none): one wavefront per list
@@ -385,12 +402,24 @@ hipError_t launch_topm(hipStream_t s, const TopmParams &params) {
   // 1874 us, now 350; K = 256 in parts of 64 measured 182 against 166.)
   // (an even number: a pair of drafts is not divided)
   p.at_once = (int)(400.0 / (1.0 + std::log((double)((p.Md + 63) / 64)))) & ~1;
+  // Half-words tell race times apart by 2^-16 only, where the smallest of n is about 1 / n: a flat reduction leaves some n / 30 000 more
+  // candidates by them than by whole words (a list of 65 536 9.7 and not 7.3, a pool of 2^24 524 and not 42; values apart
+  // leave less).  Where that would fill the list, what is near is looked at again with the whole word, which would cost others 2
+  // to 8 %.  (Flat lists, 64 rows, ms, both halves of every word, half-words alone, now: 50 lists of 65 536 and as long a target's 22.0,
+  // 45.1, 17.8; K = 256, the target's of 65 536 46.0, 88.7, 27.9; K = 128, lists of 8 192, just beyond the line 5.56, 3.44, 3.71.)
+  const double at_a_time = p.K < p.at_once ? p.K : p.at_once, pairs = (double)p.K * p.Mt;
+  const double by_halves = at_a_time * (1.0 + std::log((p.Md + 63) / 64) + p.Md / 30000.0) +
+                           4.0 * (1.0 + std::log(std::ceil(pairs / 512.0))) + pairs / 30000.0;
+  const bool whole = by_halves > 440.0;  // (of 512: sums vary by twenty)
   // (four wavefronts a row: 1024 rows are resident at once; eight, with half as many rows resident, measured
   // 26.4 against 25.1 us a call at 1024 rows, K = 8, lists of 256)
   const unsigned lds = (unsigned)((p.K + 1) * sizeof(Race) + p.K * sizeof(double));
   const bool probs = p.kind == LLC_PROBS, many = p.K > p.at_once;
-  auto *kernel = probs ? (many ? topm_kernel<true, true> : topm_kernel<true, false>)
-                       : (many ? topm_kernel<false, true> : topm_kernel<false, false>);
+  auto *kernel = topm_kernel<false, false, false>;
+  if (probs) kernel = many ? (whole ? topm_kernel<true, true, true> : topm_kernel<true, true, false>)
+                           : (whole ? topm_kernel<true, false, true> : topm_kernel<true, false, false>);
+  else kernel = many ? (whole ? topm_kernel<false, true, true> : topm_kernel<false, true, false>)
+                     : (whole ? topm_kernel<false, false, true> : topm_kernel<false, false, false>);
   hipLaunchKernelGGL(kernel, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
   return hipGetLastError();
 }

@@ -97,3 +97,50 @@ def test_a_list_of_candidates_that_overflows_with_finite_keys(kind, K):
     ref = oracle_topm(*args, kind=kind, seed=5, temp_target=0.8, temp_draft=1.3)
     assert compare(out, ref) <= oracle_near_ties(ref)
     assert stats_dict(stats)["near_ties"] == oracle_near_ties(ref)
+
+
+def _long_lists(B, K, Md, Mt, scale, kind, own=False):
+    g = torch.Generator(device=DEV).manual_seed(Md + Mt)
+    ids = [torch.stack([torch.randperm(131072, generator=g, device=DEV)[:M] for _ in range(n)]).int().view(*shape, M)
+           for n, shape, M in ((B * K if own else B, (B, K) if own else (B,), Md), (B, (B,), Mt))]
+    val = [scale * torch.randn(i.shape, generator=g, device=DEV) for i in ids]
+    if kind == "probs":
+        val = [torch.exp(v) for v in val]
+    return ids[0], val[0], ids[1], val[1], K
+
+
+# (either side of where whole words are drawn for what is near by its half-word, by lists, by the pool, in parts)
+@pytest.mark.parametrize("K,Md,Mt", [(5, 65536, 16384), (40, 65536, 50), (50, 65536, 50), (200, 50, 50), (246, 50, 16384), (256, 50, 65536),
+                                     (300, 700, 4096), (120, 4096, 700)])
+@pytest.mark.parametrize("kind,scale", [("logits", 0.0), ("logits", 3.0), ("probs", 0.0), ("probs", 1.0)])
+def test_long_lists(K, Md, Mt, kind, scale):
+    args = _long_lists(2, K, Md, Mt, scale, kind)
+    stats = llc.new_stats(DEV)
+    out = llc.llc_couple_topm(*args, kind=kind, seed=7, want_keys=True, stats=stats)
+    torch.cuda.synchronize()
+    ref = oracle_topm(*args, kind=kind, seed=7)
+    assert compare(out, ref) <= oracle_near_ties(ref)
+    assert stats_dict(stats)["near_ties"] == oracle_near_ties(ref)
+    assert stats_dict(stats)["exact_evals"] == 2 * K * (Md + Mt)
+
+
+@pytest.mark.parametrize("K,Md,Mt,own", [(256, 50, 65536, False), (50, 65536, 65536, True)])
+def test_flat_long_lists_leave_few_candidates(K, Md, Mt, own):
+    # what overflows the list of candidates is evaluated in 64 bits, all of it, at several times the cost: flat lists must
+    # not (values far apart, with some hundred candidates less, show what a call takes otherwise)
+    def us(scale):
+        args = _long_lists(8, K, Md, Mt, scale, "logits", own)
+        llc.llc_couple_topm(*args, seed=7)
+        torch.cuda.synchronize()
+        taken = []
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            llc.llc_couple_topm(*args, seed=7)
+            b.record()
+            torch.cuda.synchronize()
+            taken.append(a.elapsed_time(b) * 1e3)
+        return min(taken)
+    flat, apart = us(0.0), us(100.0)
+    print(f"flat {flat:.0f} us, apart {apart:.0f} us")
+    assert flat < 1.4 * apart
