@@ -1,4 +1,8 @@
 """The output tensors that the binding makes in one step are what torch.empty gives."""
+import sys
+import threading
+import time
+
 import pytest
 import torch
 
@@ -27,3 +31,34 @@ def test_tensors_of_their_own():
     assert len({t.untyped_storage().data_ptr() for t in made.values() if t.numel()}) == 3
     with pytest.raises(RuntimeError):
         binding._empties(0, (torch.int32, -3))
+
+
+@pytest.mark.gpu
+def test_other_threads_run_while_the_tensors_are_allocated():
+    binding.load()
+    torch.cuda.empty_cache()
+    interval = sys.getswitchinterval()
+    ran, ready = [], threading.Event()
+
+    def other():
+        ready.set()
+        time.sleep(0.05)
+        ran.append(True)
+
+    try:
+        sys.setswitchinterval(1000.0)  # (nobody is made to give Python's lock up)
+        thread = threading.Thread(target=other)
+        thread.start()
+        ready.wait()
+        until = time.perf_counter() + 0.2
+        while time.perf_counter() < until:
+            pass
+        before = list(ran)  # (the other thread has waited for the lock for 0.15 s)
+        made = binding._empties(0, *[(torch.uint8, (1 << 30) + n) for n in range(7)])  # 0.4 ms each from the device
+        after = list(ran)
+    finally:
+        sys.setswitchinterval(interval)
+    thread.join()
+    assert before == [] and after == [True]
+    del made
+    torch.cuda.empty_cache()
