@@ -230,6 +230,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _new(device, specs: dict) -> dict:
     """Uninitialised tensors by name, from (dtype, size, ...) tuples."""
+    if torch._C._len_torch_function_stack() > 0:  # (a mode sees torch.empty only)
+        return {name: torch.empty(size, dtype=dtype, device=device) for name, (dtype, *size) in specs.items()}
     return dict(zip(specs, _empties(device.index, *specs.values())))
 
 

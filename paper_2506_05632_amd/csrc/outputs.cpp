@@ -3,6 +3,7 @@
 // 50: 15.5 -> 13.5 us a call).
 // They are what torch.empty gives: separate tensors from torch's allocator, through its dispatcher, with its errors, and
 // without Python's lock while they are allocated (the allocator may wait for the device, or for a thread that wants the lock).
+// (The binding calls torch.empty itself under a mode that overrides torch's functions, which sees nothing of this.)
 #include <Python.h>
 
 #include <ATen/ops/empty.h>

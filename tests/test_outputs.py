@@ -5,6 +5,7 @@ import time
 
 import pytest
 import torch
+from torch.overrides import TorchFunctionMode
 
 from paper_2506_05632_amd import binding
 
@@ -31,6 +32,27 @@ def test_tensors_of_their_own():
     assert len({t.untyped_storage().data_ptr() for t in made.values() if t.numel()}) == 3
     with pytest.raises(RuntimeError):
         binding._empties(0, (torch.int32, -3))
+
+
+class _OnTheHost(TorchFunctionMode):
+    def __init__(self):
+        super().__init__()
+        self.seen = []
+
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        kwargs = dict(kwargs or {})
+        if func is torch.empty:
+            self.seen.append((tuple(args[0]), kwargs.get("dtype"), kwargs.pop("device")))
+        return func(*args, **kwargs)
+
+
+def test_a_mode_that_overrides_functions_sees_the_outputs():
+    binding.load()
+    dev = torch.device("cuda:0")
+    with _OnTheHost() as mode:
+        made = binding._new(dev, {"a": (torch.int32, 5, 3), "b": (torch.float64,)})
+    assert mode.seen == [((5, 3), torch.int32, dev), ((), torch.float64, dev)]
+    assert made["a"].shape == (5, 3) and made["a"].dtype == torch.int32 and made["b"].shape == ()
 
 
 @pytest.mark.gpu
