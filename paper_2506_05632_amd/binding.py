@@ -5,13 +5,17 @@ memory and the current stream.  There is no CPU fallback: if the library is
 missing, `load()` raises.
 """
 import ctypes
+import importlib.util
 import os
+import sysconfig
 from typing import Optional
 
 import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libllc_hip.so")
+# makes the output tensors in one step; belongs to one torch and one Python (without it torch.empty makes them)
+OUTPUTS_PATH = os.path.join(HERE, f"_outputs-torch{torch.__version__}{sysconfig.get_config_var('EXT_SUFFIX')}")
 
 F32, BF16 = 0, 1
 LOGITS, PROBS, LOGW = 0, 1, 2
@@ -164,12 +168,14 @@ def load():
     global _lib, _empties
     if _lib is None:
         path = LIB_PATH
-        for needed in (path, os.path.join(os.path.dirname(os.path.abspath(__file__)), "_outputs.so")):
-            if not os.path.exists(needed):
-                raise RuntimeError(f"{needed} is missing: run `python -m paper_2506_05632_amd.build` "
-                                   "(there is no CPU fallback)")
-        from . import _outputs
-        _empties = _outputs.empties
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: run `python -m paper_2506_05632_amd.build` "
+                               "(there is no CPU fallback)")
+        if os.path.exists(OUTPUTS_PATH):
+            spec = importlib.util.spec_from_file_location(__package__ + "._outputs", OUTPUTS_PATH)
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+            _empties = module.empties
         lib = ctypes.CDLL(path)
         lib.llc_couple.argtypes = [ctypes.POINTER(CoupleArgs)]
         lib.llc_couple.restype = ctypes.c_int
@@ -230,7 +236,7 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _new(device, specs: dict) -> dict:
     """Uninitialised tensors by name, from (dtype, size, ...) tuples."""
-    if torch._C._len_torch_function_stack() > 0:  # (a mode sees torch.empty only)
+    if _empties is None or torch._C._len_torch_function_stack() > 0:  # (a mode sees torch.empty only)
         return {name: torch.empty(size, dtype=dtype, device=device) for name, (dtype, *size) in specs.items()}
     return dict(zip(specs, _empties(device.index, *specs.values())))
 

@@ -1,16 +1,18 @@
 """Build paper_2506_05632_amd/libllc_hip.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+import glob
 import os
 import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
+from .binding import OUTPUTS_PATH
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libllc_hip.so")
 PROBE_LIB = os.path.join(HERE, "libllc_probe.so")   # machine probes for bench.py --workload peaks
-OUTPUTS = os.path.join(HERE, "_outputs.so")          # the binding's output tensors (a Python module)
 SOURCES = ["api.hip", "static_scratch.hip", "finalize.hip", "topm.hip", "lml.hip", "scan_f32_shared.hip", "scan_f32_perk.hip",
            "scan_bf16_shared.hip", "scan_bf16_perk.hip", "scan_f32_shared_minf.hip", "scan_f32_perk_minf.hip",
            "scan_bf16_shared_minf.hip", "scan_bf16_perk_minf.hip"]
@@ -36,8 +38,10 @@ def _build_outputs(run):
     from torch.utils import cpp_extension
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    for other in glob.glob(os.path.join(HERE, "_outputs*.so")):  # (of another torch or Python)
+        os.remove(other)
     run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-         *("-isystem" + i for i in include), os.path.join(CSRC, "outputs.cpp"), "-o", OUTPUTS,
+         *("-isystem" + i for i in include), os.path.join(CSRC, "outputs.cpp"), "-o", OUTPUTS_PATH,
          "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"])
 
 
@@ -70,7 +74,7 @@ def build(force: bool = False, verbose: bool = False, extra_flags=()) -> str:
     if force or not os.path.exists(PROBE_LIB) or os.path.getmtime(PROBE_LIB) < os.path.getmtime(probe_src):
         run([hipcc, *FLAGS, *extra_flags, "-shared", probe_src, "-o", PROBE_LIB])
     outputs_src = os.path.join(CSRC, "outputs.cpp")
-    if force or not os.path.exists(OUTPUTS) or os.path.getmtime(OUTPUTS) < os.path.getmtime(outputs_src):
+    if force or not os.path.exists(OUTPUTS_PATH) or os.path.getmtime(OUTPUTS_PATH) < os.path.getmtime(outputs_src):
         _build_outputs(run)
     return LIB
 

@@ -1,5 +1,7 @@
 """The output tensors that the binding makes in one step are what torch.empty gives."""
+import os
 import sys
+import sysconfig
 import threading
 import time
 
@@ -53,6 +55,19 @@ def test_a_mode_that_overrides_functions_sees_the_outputs():
         made = binding._new(dev, {"a": (torch.int32, 5, 3), "b": (torch.float64,)})
     assert mode.seen == [((5, 3), torch.int32, dev), ((), torch.float64, dev)]
     assert made["a"].shape == (5, 3) and made["a"].dtype == torch.int32 and made["b"].shape == ()
+
+
+def test_the_module_belongs_to_this_torch_and_this_python(monkeypatch):
+    name = os.path.basename(binding.OUTPUTS_PATH)
+    assert torch.__version__ in name and name.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert os.path.exists(binding.OUTPUTS_PATH)
+    # one of another torch is not there under this name: the library loads, and torch.empty makes the tensors
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_empties", None)
+    monkeypatch.setattr(binding, "OUTPUTS_PATH", binding.OUTPUTS_PATH + ".other")
+    assert binding.load() is not None and binding._empties is None
+    made = binding._new(torch.device("cpu"), {"a": (torch.uint8, 4), "b": (torch.float32, 2, 0, 3)})
+    assert made["a"].shape == (4,) and made["b"].shape == (2, 0, 3) and made["a"].dtype == torch.uint8
 
 
 @pytest.mark.gpu
