@@ -1,7 +1,8 @@
-"""GPU parity of llc_lml_bound on rows long enough for its bucketed form (needs an MI355X).
+"""GPU parity of llc_lml_bound on rows long enough to go by cells of ln(q/p), which a sample shares out (needs an
+MI355X).
 
-Same oracle and same bound on the error as in test_gpu_lml.py: indices whose ratios agree to fp32
-precision may be swapped and the masses are rounded to fp32, everything else is fp64 on both sides; rtol
+Same oracle and same bound on the error as in test_gpu_lml.py: what cells leave open, or the order among
+ratios that agree to fp32 precision and masses rounded to fp32, everything else is fp64 on both sides; rtol
 1e-6."""
 import numpy as np
 import pytest
@@ -15,8 +16,9 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# (the ends of the range of either type, a tile of 4096 entries and one more, ragged tails)
-@pytest.mark.parametrize("V", [12287, 12288, 12289, 16384, 16385, 40959, 40961, 70003])
+# (the ends of the range of either type, a walk's 4096 entries and one more, ragged tails, the first length with a
+# second attempt; test_gpu_lml_cells.py has the ends more closely)
+@pytest.mark.parametrize("V", [6143, 6144, 8191, 8192, 8193, 16384, 16385, 40961, 65536, 70003])
 @pytest.mark.parametrize("kind", ["logits", "logw", "probs"])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_lengths_kinds_and_types(V, kind, dtype):
@@ -37,25 +39,34 @@ def test_lengths_kinds_and_types(V, kind, dtype):
 
 
 def _sampled(V):
-    """The positions of the kernel's sample of a row."""
-    j = np.arange(2048, dtype=np.uint64)
+    """The positions of the half of the kernel's sample that is spread over a row."""
+    j = np.arange(1024, dtype=np.uint64)
     jitter = (j * np.uint64(0x9E3779B9)) & np.uint64(0xFFFFFFFF)
-    return ((j * np.uint64(V) + ((jitter * np.uint64(V)) >> np.uint64(32))) >> np.uint64(11)).astype(np.int64)
+    return ((j * np.uint64(V) + ((jitter * np.uint64(V)) >> np.uint64(32))) >> np.uint64(10)).astype(np.int64)
+
+
+def _pair_of(V):
+    """Which two of the kernel's threads meet an entry; the other half of the sample is the largest entry of every pair."""
+    return torch.arange(V, device=DEV) // 8 % 512
 
 
 def test_a_row_whose_sample_misleads_is_sorted():
-    # everywhere but at the sample's positions the ratios crowd into a few quanta of 2^-22, so one bucket
-    # takes most of the row; the rows beside it are ordinary
+    # everywhere but at the sample's positions the ratios lie within 2e-5 of each other, beside all that the sample
+    # holds, so one cell takes most of the row: no entry leaves as much as 1e-9 of a result open, all together some
+    # 4e-6; the rows beside it are ordinary
     g = torch.Generator(device=DEV).manual_seed(1)
     B, V = 4, 20011
     tq = torch.randn(B, V, generator=g, device=DEV)
     td = tq + torch.randn(B, V, generator=g, device=DEV)
-    crowd = torch.full((V,), 0.1, device=DEV) + 2e-6 * torch.rand(V, generator=g, device=DEV)
-    at = torch.from_numpy(_sampled(V)).to(DEV)
-    crowd[at] = 3.0 * torch.randn(at.numel(), generator=g, device=DEV)
+    crowd = torch.full((V,), 0.1, device=DEV) + 2e-5 * torch.rand(V, generator=g, device=DEV)
+    # the draft's largest of every pair of threads, and the target's, all of which are as large: the pair's first entry
+    at = torch.cat([torch.from_numpy(_sampled(V)).to(DEV), 8 * torch.arange(512, device=DEV)])
+    crowd[at] = 0.2 + torch.randn(at.numel(), generator=g, device=DEV).abs()
     tq[2] = 0.0
     td[2] = crowd
-    check(td, tq, [1, 4])
+    ws = torch.zeros(24 * V * B + 256, dtype=torch.uint8, device=DEV)
+    check(td, tq, [1, 4], workspace=ws)
+    assert _left_to_sorting(ws, B, V) == [2]
 
 
 def test_results_do_not_depend_on_the_workspace_or_the_run():
@@ -102,7 +113,7 @@ def test_rows_masked_by_a_finite_value_and_very_sharp_rows(V, dtype, temp_draft,
     assert (gpu["bound"] <= 1 + 1e-9).all()
 
 
-@pytest.mark.parametrize("V", [12288, 40961])
+@pytest.mark.parametrize("V", [6144, 12288, 40961])
 @pytest.mark.parametrize("kind,temp", [("logw", 1.0), ("logits", 0.7)])
 def test_masses_of_every_size_down_to_nothing(V, kind, temp):
     # ln of either mass sweeps from 0 to -800, side by side and against each other, so that products and sums
@@ -126,30 +137,38 @@ def test_masses_of_every_size_down_to_nothing(V, kind, temp):
 
 
 def test_splitters_farther_apart_than_an_int():
-    # the sample sees entries at the two ends only (ln r = -400 and 400, one of them at 0), the rest of the row
-    # lies between them: one bucket of all the entries that matter
+    # nearly all of the sample has ln r = -400 or 400 and next to no mass, and no quantile falls between the two (1038
+    # entries, 64 quantiles, 16.2 entries apart: one is at the 503rd, the next at the 519th), where all that counts
+    # lies: some 270 entries of seven pairs of threads, of which the sample holds 14, at 14 ratios 0.5 apart.  Cells are 800 /
+    # 1792 wide there, so each ratio has one; the entries of a single cell would be too many to resolve.
     g = torch.Generator(device=DEV).manual_seed(3)
     V = 20011
-    td, tq = torch.zeros(2, V, device=DEV), 2.0 * torch.randn(2, V, generator=g, device=DEV)
+    td, tq = torch.full((2, V), float("-inf"), device=DEV), torch.full((2, V), float("-inf"), device=DEV)
+    pair = _pair_of(V)
+    heavy = pair < 7
+    td[:, heavy] = torch.round(64.0 * torch.randn(2, int(heavy.sum()), generator=g, device=DEV)) / 64.0
+    tq[:, heavy] = td[:, heavy] + (pair - 3.0 + 0.5 * (torch.arange(V, device=DEV) & 1))[heavy]
     at = torch.from_numpy(_sampled(V)).to(DEV)
-    tq[:, at] = 0.0
-    left = torch.arange(2048, device=DEV) % 64 < 32
-    tq[:, at[left]] = -400.0
-    td[:, at[~left]] = -400.0
-    td[:, at[1024]], tq[:, at[1024]] = 0.0, 0.0
-    check(td, tq, [1, 4])
-    check(tq, td, [1, 4])
+    at = at[torch.randperm(1024, generator=g, device=DEV)]
+    left, right = at[:504], at[504:]
+    td[:, left], tq[:, left] = -60.0, -460.0
+    td[:, right], tq[:, right] = -460.0, -60.0
+    ws = torch.zeros(24 * V * 2 + 256, dtype=torch.uint8, device=DEV)
+    for draft, target in ((td, tq), (tq, td)):
+        check(draft, target, [1, 4], workspace=ws)
+        assert _left_to_sorting(ws, 2, V) == []
 
 
 # (not probabilities 1e-7 apart: in fp32 most of those are the same, and the order among equal ratios is free,
-# which the masses' rounding makes worth up to 2^-23 of a pair's share)
+# which the sorted masses' rounding makes worth up to 2^-23 of a pair's share)
 @pytest.mark.parametrize("kind,width", [("logits", 1e-6), ("logits", 1e-7), ("probs", 1e-6)])
-def test_ratios_close_to_each_other_are_ordered_as_finely_as_by_sorting(kind, width):
-    # ratios within a few 1e-7 of each other, whose order fp32 still tells: the two forms (12 287 entries are
-    # sorted, 12 289 bucketed; the two more carry no mass) then sum the same masses in the same order, and
-    # differ by the rounding of fp64 sums and a rare mass that rounds the other way
+def test_ratios_close_to_each_other_are_told_apart(kind, width):
+    # ratios within a few 1e-7 of each other, whose order fp32 still tells, in both forms: 6143 entries are sorted, 6145 go
+    # by cells (the two more carry no mass).  Sorted masses are rounded to fp32.  A cell between splitters is some
+    # 1e-10 wide, and what is beyond the sample, a hundredth of the row on either side, is at most one cell of the whole
+    # width, which leaves 0.25 x 5e-6 x 1e-4 of a result open: 2e-10 (entries not told apart at all: 0.25 x 5e-6).
     g = torch.Generator(device=DEV).manual_seed(5)
-    B, V = 8, 12287
+    B, V = 8, 6143
     tq = -1.1 * torch.log(torch.rand(B, V, generator=g, device=DEV, dtype=torch.float64).argsort(dim=1) + 1.0)
     if kind == "probs":
         tq = torch.exp(tq).float()
@@ -157,20 +176,24 @@ def test_ratios_close_to_each_other_are_ordered_as_finely_as_by_sorting(kind, wi
     else:
         tq = (0.01 * tq).float()   # (so that fp32 logits can lie this close)
         td = (tq.double() + width * torch.randn(B, V, generator=g, device=DEV, dtype=torch.float64)).float()
-    none = torch.full((B, 2), 0.0 if kind == "probs" else float("-inf"), device=DEV)
+    ref = lml.lml_rows(td.cpu().numpy(), tq.cpu().numpy(), [1, 4], kind=kind)["bound"]
     by_sorting = llc.llc_lml_bound(td, tq, [1, 4], kind=kind)["bound"]
-    by_buckets = llc.llc_lml_bound(torch.cat([td, none], 1), torch.cat([tq, none], 1), [1, 4], kind=kind)["bound"]
-    torch.testing.assert_close(by_buckets, by_sorting, rtol=1e-10, atol=0)
+    np.testing.assert_allclose(by_sorting.cpu().numpy(), ref, rtol=2.0 ** -22)
+    none = torch.full((B, 2), 0.0 if kind == "probs" else float("-inf"), device=DEV)
+    ws = torch.zeros(24 * (V + 2) * B + 256, dtype=torch.uint8, device=DEV)
+    by_cells = llc.llc_lml_bound(torch.cat([td, none], 1), torch.cat([tq, none], 1), [1, 4], kind=kind, workspace=ws)["bound"]
+    assert _left_to_sorting(ws, B, V + 2) == []
+    np.testing.assert_allclose(by_cells.cpu().numpy(), ref, rtol=2e-9)
 
 
 def _left_to_sorting(ws, B, V):
-    """Which rows the bucketing kernel left to the sorting one: those have that kernel's second buffer of masses
+    """Which rows the cell kernel left to the sorting one: those have that kernel's second buffer of masses
     where the other writes a 0, behind 16 V bytes of the row's part of the workspace."""
     return [b for b in range(B) if ws[24 * V * b + 16 * V:24 * V * b + 16 * V + 4].view(torch.int32).item() != 0]
 
 
 @pytest.mark.parametrize("V,dtype", [(160000, torch.float32), (160001, torch.float32), (1 << 18, torch.float32), (1 << 18, torch.bfloat16)])
-def test_ordinary_rows_up_to_the_longest_are_bucketed(V, dtype):
+def test_ordinary_rows_up_to_the_longest_go_by_cells(V, dtype):
     g = torch.Generator(device=DEV).manual_seed(4)
     B = 48
     tq = -1.1 * torch.log(torch.rand(B, V, generator=g, device=DEV).argsort(dim=1) + 1.0)
@@ -186,7 +209,7 @@ def test_ordinary_rows_up_to_the_longest_are_bucketed(V, dtype):
 
 
 @pytest.mark.parametrize("kind,dtype", [("logits", torch.float32), ("probs", torch.float32), ("logits", torch.bfloat16)])
-def test_rows_of_ratios_shared_by_a_hundred_entries_are_bucketed(kind, dtype):
+def test_rows_of_ratios_shared_by_a_hundred_entries_go_by_cells(kind, dtype):
     # 1200 ratios: the sample holds most of them once, twice or three times, so quantiles fall inside such runs
     g = torch.Generator(device=DEV).manual_seed(6)
     B, V = 6, 128256
@@ -201,9 +224,9 @@ def test_rows_of_ratios_shared_by_a_hundred_entries_are_bucketed(kind, dtype):
 
 
 @pytest.mark.parametrize("V,dtype", [(12288, torch.float32), (20011, torch.float32), (70003, torch.float32), (41011, torch.bfloat16)])
-def test_groups_whose_cells_are_long(V, dtype):
-    # entries of a bucket that share a cell by the hundred: a crowd beside ratios far from it, at several
-    # distances, and values of few bits; groups of every size up to a full one are sorted whole
+def test_cells_of_hundreds_of_entries(V, dtype):
+    # entries that share a cell by the hundred: a crowd beside ratios far from it, at several distances, and values
+    # of few bits
     g = torch.Generator(device=DEV).manual_seed(V)
     B = 6
     tq = torch.randn(B, V, generator=g, device=DEV)
