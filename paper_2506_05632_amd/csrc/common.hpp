@@ -61,9 +61,6 @@ struct RowMap {
   __host__ __device__ long long target_off(long long b) const {
     return (b / inner_count) * target_outer + (b % inner_count) * target_inner;
   }
-  __host__ __device__ unsigned long long row_of(long long b) const {
-    return (unsigned long long)((b / inner_count) * row_outer + (b % inner_count) * row_inner);
-  }
 };
 
 struct FinalizeParams {
@@ -224,7 +221,7 @@ struct TopmParams {
 
 // Theorem 1's bound per row (diagnostics): one workgroup sums a row, by cells of ln(q/p) or by sorting.
 constexpr int kLmlMaxK = LLC_LML_MAX_K;
-constexpr int kLmlSlots = 512;  // (sorting runs two 512-thread workgroups on each of 256 CUs: more cannot be resident)
+constexpr int kLmlSlots = 512;  // (sorting runs two workgroups on each of 256 CUs, cells run one: more cannot be resident)
 struct LmlParams {
   long long B;
   int V;
