@@ -603,7 +603,7 @@ __device__ __forceinline__ unsigned long long fixed_mass(double e) {
 // A mass below 2^-46 of its row's largest is 0 in a cell's sum: a denominator is no less than the larger of p_j and q_j (the
 // maxima are over all of a row whose masses sum to 1), so 2^18 such masses are less than 2^-28 of it.
 // What bounds it: instruction issue in fp64 (two exponentials an entry and pass), the latency of LDS atomics and reads.
-// The row is read three times, and two bytes an entry are written and read.  1024 rows of 128 256, four sizes: 2.12 ms,
+// The row is read three times, and two bytes an entry are written and read.  1024 rows of 128 256, four sizes: 2.13 ms,
 // against 3.13 with entries moved to buckets of about 1000 and those ordered in LDS; 1024 x 32 000 0.63 : 0.87,
 // 512 x 152 064 bf16 1.37 : 1.94, one row 0.43 : 1.00, 64 x 262 144 0.96 : 2.11, eight sizes 512 rows 1.56 : 2.26.
 // All sums run in an order that does not depend on how the wavefronts interleave.
