@@ -89,13 +89,20 @@ __device__ __forceinline__ void store_best(Race &r, const Best &v) {
   r.second = ord64(v.sec);
 }
 
+enum Form {
+  kPairs,   // two drafts that share their blocks at a time, in the pool and, where all drafts have one list, there
+  kHalves,  // the same, and two wavefronts take a list, 64 entries each in turn
+  kSingle   // one draft at a time
+};
+
 // What bounds it: the latency of its phases (reductions across lanes, the exact keys' logarithms), then
 // instruction issue.  Exact keys for all entries took more than half of all instructions; both halves of every
 // entry's word, two blocks for each draft, most of the rest: 1024 rows, K = 8, one list of 50, with keys 13.0 us, now
 // 10.9; lists of 256, own for each draft 36.1, 30.3, shared 28.4, 21.0.  (Fetching every round's entries a
 // round ahead, beyond the first ones that are, and a shorter exponential for the normalisers, changed nothing.)
-// WHOLE: what is near by its upper half-word is looked at again with the whole word (see launch_topm).
-template <bool PROBS, bool MANY, bool WHOLE>
+// WHOLE: what is near by its upper half-word is looked at again with the whole word; FORM: how lists and the pool's
+// entries are shared out (both: see launch_topm).
+template <bool PROBS, bool MANY, bool WHOLE, int FORM>
 __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   __shared__ double c_key[kCandidates];
   __shared__ int c_id[kCandidates], c_k[kCandidates];  // c_k: the draft, K more for a pool entry
@@ -126,8 +133,12 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
 
   // The first entries of a wavefront's first list and of its share of the pool leave before anything is set up.
   // A wavefront takes a draft's list, or where all drafts have one list, a pair of drafts', which share their blocks.
-  const int step = one_list ? 2 : 1;
-  const unsigned pool_items = (unsigned)((K + 1) >> 1) * (unsigned)p.Mt;  // (draft pair, target entry); below 2^25
+  const int step = FORM != kSingle && one_list ? 2 : 1;  // drafts whose list a wavefront takes
+  const int my_list = FORM == kHalves ? wave >> 1 : wave;
+  const int e_first = FORM == kHalves ? __builtin_amdgcn_readfirstlane((wave & 1) * 64) : 0;
+  constexpr int kStepE = FORM == kHalves ? 128 : 64;
+  // ((draft pair or draft, target entry); below 2^25)
+  const unsigned pool_items = (unsigned)(FORM == kSingle ? K : (K + 1) >> 1) * (unsigned)p.Mt;
   struct Slot { int id; float v; };
   auto draft_slot = [&](const int k, const int e) {
     Slot x = {-1, 0.0f};
@@ -141,7 +152,7 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
   };
   Slot first_draft = {-1, 0.0f}, first_pool = {-1, 0.0f};
   if (!MANY) {
-    if (wave * step < K) first_draft = draft_slot(wave * step, lane);
+    if (my_list * step < K) first_draft = draft_slot(my_list * step, e_first + lane);
     first_pool = pool_slot((unsigned)((waves - 1 - wave) * 64 + lane));
   }
 
@@ -230,14 +241,14 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
     const int k1 = MANY ? min(k0 + p.at_once, K) : K;
     const bool last = !MANY || k1 == K;  // with the pool and the normalisers
     // ---- draft side: one wavefront per list, lanes over its entries
-    for (int k = k0 + wave * step; k < k1; k += waves * step) {
+    for (int k = k0 + (FORM == kHalves ? my_list : wave) * step; k < k1; k += waves * step) {
       const float T = draft_temp(k);
       const bool t_ok = T > 0.0f && T < inf;
-      const bool two = one_list && k + 1 < k1;  // uniform
+      const bool two = FORM != kSingle && one_list && k + 1 < k1;  // uniform
       const float c = kLog2e / T;
       float tau[2] = {inf, inf};
-      for (int e0 = 0; e0 < p.Md; e0 += 64) {
-        const Slot x = !MANY && e0 == 0 && k == wave * step ? first_draft : draft_slot(k, e0 + lane);
+      for (int e0 = e_first; e0 < p.Md; e0 += kStepE) {
+        const Slot x = !MANY && e0 == e_first && k == my_list * step ? first_draft : draft_slot(k, e0 + lane);
         const bool has = t_ok && has_mass(x.id, x.v, PROBS);
         const uint32_t halves = upper_of((uint32_t)x.id, (uint32_t)(k >> 1), row_lo, row_hi, p.seed_lo, p.seed_hi);
         const uint32_t mine = (k & 1) ? halves >> 16 : halves & 0xFFFFu;
@@ -260,9 +271,16 @@ __global__ void __launch_bounds__(kBlock, 4) topm_kernel(const TopmParams p) {
         for (unsigned i0 = (unsigned)(waves - 1 - wave) * 64; i0 < pool_items; i0 += (unsigned)nt) {
           const unsigned it = i0 + (unsigned)lane;
           const Slot x = !MANY && i0 < (unsigned)nt ? first_pool : pool_slot(it);
-          const int k = it < pool_items ? 2 * (int)(it / (unsigned)p.Mt) : 0;
+          const int k = it < pool_items ? (FORM == kSingle ? 1 : 2) * (int)(it / (unsigned)p.Mt) : 0;
           const bool has = has_mass(x.id, x.v, PROBS), two = has && k + 1 < K;
           const uint32_t halves = upper_of((uint32_t)x.id, (uint32_t)(k >> 1), row_lo, row_hi, p.seed_lo, p.seed_hi);
+          if (FORM == kSingle) {
+            const uint32_t mine = (k & 1) ? halves >> 16 : halves & 0xFFFFu;
+            const Bounds a = bounds(has, x.v, mine, c);
+            lower_tau(tau, a.high);
+            list(has, x.id, x.v, mine, c, K + k, a.low, tau);
+            continue;
+          }
           const Bounds a = bounds(has, x.v, halves & 0xFFFFu, c), o = bounds(two, x.v, halves >> 16, c);
           lower_tau(tau, fminf(a.high, o.high));
           list(has, x.id, x.v, halves & 0xFFFFu, c, K + k, a.low, tau);
@@ -415,11 +433,24 @@ hipError_t launch_topm(hipStream_t s, const TopmParams &params) {
   // 26.4 against 25.1 us a call at 1024 rows, K = 8, lists of 256)
   const unsigned lds = (unsigned)((p.K + 1) * sizeof(Race) + p.K * sizeof(double));
   const bool probs = p.kind == LLC_PROBS, many = p.K > p.at_once;
-  auto *kernel = topm_kernel<false, false, false>;
-  if (probs) kernel = many ? (whole ? topm_kernel<true, true, true> : topm_kernel<true, true, false>)
-                           : (whole ? topm_kernel<true, false, true> : topm_kernel<true, false, false>);
-  else kernel = many ? (whole ? topm_kernel<false, true, true> : topm_kernel<false, true, false>)
-                     : (whole ? topm_kernel<false, false, true> : topm_kernel<false, false, false>);
+  // Few drafts: pairs leave wavefronts idle, and a lone wavefront's second draft, or the other half of a long list, is what the
+  // row then waits for.  One draft at a time where there is a wavefront for every 64 (draft, entry) pairs, and for one
+  // draft, which has no other to share with; two wavefronts to a long list where there are two for every pair of drafts.
+  // Kernel us (whole words and a wavefront a list, pairs everywhere, now): K = 2, a list of 2000, 256 rows 25.7, 30.7, 19.2;
+  // K = 4, 660, 4 rows 19.2, 17.8, 13.6, 4096 rows 97.6, 76.2, 65.2; K = 3, 20, 4 rows 4.72, 5.25, 4.80; K = 1, 50, 4 rows 4.67, 4.92,
+  // 4.77.  (As run-time choices in one kernel they cost others 3 to 5 %; halves of a list of 50 are one half and nothing, K = 4
+  // 18.9 -> 23.0 at 4096 rows.)
+  constexpr int kWaves = kBlock / 64;
+  const bool one_list = p.draft_stride_k == 0 && p.temp_draft == nullptr;
+  const bool single = !whole && (p.K == 1 || (long long)p.K * ((p.Md + 63) / 64) + ((long long)p.K * p.Mt + 63) / 64 <= kWaves);
+  const bool halves = !whole && one_list && p.Md > 64 && (p.K + 1) / 2 * 2 <= kWaves;
+  auto *kernel = topm_kernel<false, false, false, kPairs>;
+  if (single) kernel = probs ? topm_kernel<true, false, false, kSingle> : topm_kernel<false, false, false, kSingle>;
+  else if (halves) kernel = probs ? topm_kernel<true, false, false, kHalves> : topm_kernel<false, false, false, kHalves>;
+  else if (probs) kernel = many ? (whole ? topm_kernel<true, true, true, kPairs> : topm_kernel<true, true, false, kPairs>)
+                                : (whole ? topm_kernel<true, false, true, kPairs> : topm_kernel<true, false, false, kPairs>);
+  else kernel = many ? (whole ? topm_kernel<false, true, true, kPairs> : topm_kernel<false, true, false, kPairs>)
+                     : (whole ? topm_kernel<false, false, true, kPairs> : topm_kernel<false, false, false, kPairs>);
   hipLaunchKernelGGL(kernel, dim3((unsigned)p.B), dim3(kBlock), lds, s, p);
   return hipGetLastError();
 }

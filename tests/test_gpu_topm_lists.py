@@ -124,6 +124,21 @@ def test_long_lists(K, Md, Mt, kind, scale):
     assert stats_dict(stats)["exact_evals"] == 2 * K * (Md + Mt)
 
 
+# (either side of where drafts are taken one at a time, and of where two wavefronts share a list)
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("Md,Mt", [(1, 1), (20, 42), (20, 43), (64, 64), (64, 65), (65, 1), (128, 64), (129, 500), (700, 50)])
+@pytest.mark.parametrize("own,kind", [(False, "logits"), (True, "logits"), (False, "probs")])
+def test_few_drafts(K, Md, Mt, own, kind):
+    args = _long_lists(6, K, Md, Mt, 1.0, kind, own)
+    stats = llc.new_stats(DEV)
+    out = llc.llc_couple_topm(*args, kind=kind, seed=11, want_keys=True, stats=stats)
+    torch.cuda.synchronize()
+    ref = oracle_topm(*args, kind=kind, seed=11)
+    assert compare(out, ref) <= oracle_near_ties(ref)
+    assert stats_dict(stats)["near_ties"] == oracle_near_ties(ref)
+    assert stats_dict(stats)["exact_evals"] == 6 * K * (Md + Mt)
+
+
 @pytest.mark.parametrize("K,Md,Mt,own", [(256, 50, 65536, False), (50, 65536, 65536, True)])
 def test_flat_long_lists_leave_few_candidates(K, Md, Mt, own):
     # what overflows the list of candidates is evaluated in 64 bits, all of it, at several times the cost: flat lists must
