@@ -598,8 +598,8 @@ __device__ __forceinline__ const ScanParams &fetch_params_again() {
 // waiting for the next tile's loads as well.  (One such build also returned wrong target-side
 // results, which the parity tests caught: the compiler had put the spill store of a value that
 // every lane needs into a stretch of code that runs with the exec mask narrowed to a few lanes.
-// The build's audit looks for that in the assembly of every kernel.)  They are allowed more
-// and take about 150: three workgroups per CU.
+// The build's audit looks for that in the assembly of every kernel.)  They are allowed more;
+// four drafts' take 121 in bf16, four workgroups per CU, and 133 in fp32, three.
 template <typename T, int KB, bool SHARED, bool PROBS, bool MASKED, bool LSE, bool MINF>
 __global__ void __launch_bounds__(lean_variant(SHARED, KB, LSE) ? kMaxThreads : kMaxThreads / 2, lean_variant(SHARED, KB, LSE) ? 4 : 2)
 scan_kernel(const ScanParams p) {
@@ -647,6 +647,15 @@ scan_kernel(const ScanParams p) {
   if (p.map.inner_count > 1) {
     b_outer = bid / (unsigned)p.map.inner_count;
     b_inner = bid - b_outer * (unsigned)p.map.inner_count;
+  }
+  // (the branches around the divisions left their results in vector registers, and with them the pointers of every
+  // draft's row, 8 to 26 registers: four drafts' bf16 variant with normalisers took 139 and three wavefronts a SIMD instead of
+  // 121 and four.  534 rows of 64, K = 12, keys: 45.9 us with divisions throughout, 50.6, now 42.0)
+  if (!SHARED) {
+    chunk = in_scalar_int(chunk);
+    kg = in_scalar_int(kg);
+    b_outer = (unsigned)in_scalar_int((int)b_outer);
+    b_inner = (unsigned)in_scalar_int((int)b_inner);
   }
   const int kbase = kg * KT;
   // same_race: every draft of the row uses the race times of draft 0 (the compression scheme's

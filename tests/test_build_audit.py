@@ -3,6 +3,10 @@
 One build of the scan kernel lost the target side's scale factor that way (see
 paper_2506_05632_amd/audit.py); the checker is pinned on small listings with and without the
 pattern, then run over the assembly of every source of the library as it is built."""
+import re
+
+import pytest
+
 from paper_2506_05632_amd import audit
 
 FAULTY = """
@@ -57,3 +61,16 @@ def test_the_checker_finds_the_pattern_and_only_the_pattern():
 def test_no_kernel_of_the_library_stores_a_spill_under_a_narrowed_exec_mask():
     bad = audit.audit()
     assert bad == {}, bad
+
+
+@pytest.fixture(scope="module")
+def registers(tmp_path_factory):
+    asm = audit.device_assembly("scan_bf16_perk.hip", str(tmp_path_factory.mktemp("asm")))
+    return {name: int(n) for name, n in re.findall(r"^ +\.name: +(_Z\S+)$.*?^ +\.vgpr_count: +(\d+)$", asm, re.M | re.S)}
+
+
+# (512 registers a SIMD lane in blocks of 8: 128 let four wavefronts run on a SIMD, 168 three)
+@pytest.mark.parametrize("kernel,most", [("BF16InELi2ELb0ELb0ELb0ELb1ELb0E", 128), ("BF16InELi4ELb0ELb0ELb0ELb0ELb0E", 168)])
+def test_rows_of_their_own_do_not_cost_the_scan_its_wavefronts(kernel, most, registers):
+    count = [n for name, n in registers.items() if kernel in name]
+    assert len(count) == 1 and count[0] <= most
