@@ -7,19 +7,21 @@
 //   sum_j K / sum_i ( max{q_i/q_j, p_i/p_j} + (K - 1) q_i/q_j ).
 // max{q_i/q_j, p_i/p_j} is q_i/q_j exactly when q_i/p_i >= q_j/p_j, so with the indices sorted by
 // r = q/p the inner sum is (the q-mass from j on)/q_j + (the p-mass before j)/p_j + (K-1) Q/q_j:
-// an order by r and running sums per row.  One workgroup does a whole row.  Two forms:
+// an order by r and running sums per row.  One workgroup does a whole row.  Three forms:
 //
-//  by cells (rows of 6144 to 2.6 10^5 entries, bf16 from 8192 on): nothing is ordered or moved.  ln r is divided into some 6000
-//  cells, finely where a sample of the row has many entries or much mass; one pass adds every cell's masses up, as
-//  whole numbers in LDS, and the next takes the terms, for which only the order inside an entry's own cell is not
-//  known.  That is bounded per entry (see lml_cell_kernel); where it matters it is resolved exactly.
-//  by sorting (other rows, and a row that the cells do not resolve, also when they are shared out again): four passes of a
+//  by cells' sums (rows of 6144 to 2.6 10^5 entries, bf16 from 8192 on): nothing is ordered or moved.  ln r is divided into some
+//  7000 cells, finely where a sample of the row has many entries or much mass; one pass adds up the masses of every cell's entries
+//  and how they are spread in it, as whole numbers in LDS, and a cell's terms follow from these sums (see lml_sum_kernel), but
+//  for what the order inside it is worth, which is bounded.
+//  by cells (a row whose cells leave too much open in all): a second pass takes the terms one by one, and entries for which the order in
+//  their cell matters are resolved exactly (see lml_cell_kernel).
+//  by sorting (other rows, and a row that the cells do not resolve either, also when they are shared out again): four passes of a
 //  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses, rounded to fp32, travel with their
 //  key through two buffers in the workspace.
 //
 // Indices whose r agree to fp32 precision may come out in either order, which together with the sorted masses' rounding
 // moves a result by a relative 2^-22 at most, and so does what the cells leave open (1024 rows of 128 256 come out
-// 2e-10 from the result in 64 bits, 5e-9 when sorted).
+// 3e-11 from the result in 64 bits by cells' sums, 1e-10 by cells, 5e-9 when sorted).
 // Entries without mass on one side follow the limits: p_j = 0 or q_j = 0 gives term j = 0; as a
 // summand i such an entry still counts with the mass it has on the other side.
 #include "common.hpp"
@@ -55,24 +57,76 @@ __device__ double block_sum(double v, double *scratch) {
   for (int w = 0; w < waves; ++w) r += scratch[w];  // a fixed order
   return r;
 }
+// What a lane gets of lane l ^ 1, l ^ 2, l ^ 3, 15 - l or 7 - l of its sixteen or eight, (l + 8) % 16, of the one N before in its sixteen, or of
+// the last lane of the sixteen or thirty-two before (lanes without such a one, and rows that ROWS leaves out, get 0), without a trip through LDS.
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kMirror16 = 0x140, kMirror8 = 0x141, kXor8 = 0x128, kBefore = 0x110, kLast16 = 0x142,
+              kLast32 = 0x143;
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int from_lane(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, true);
+}
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ unsigned long long from_lane(unsigned long long v) {
+  const uint32_t lo = (uint32_t)from_lane<CTRL, ROWS>((int)(uint32_t)v), hi = (uint32_t)from_lane<CTRL, ROWS>((int)(uint32_t)(v >> 32));
+  return ((unsigned long long)hi << 32) | lo;
+}
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double from_lane(double v) {
+  return __longlong_as_double((long long)from_lane<CTRL, ROWS>((unsigned long long)__double_as_longlong(v)));
+}
+__device__ __forceinline__ int of_lane(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ unsigned long long of_lane(unsigned long long v, int lane) {
+  const uint32_t lo = (uint32_t)of_lane((int)(uint32_t)v, lane), hi = (uint32_t)of_lane((int)(uint32_t)(v >> 32), lane);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ double of_lane(double v, int lane) {
+  return __longlong_as_double((long long)of_lane((unsigned long long)__double_as_longlong(v), lane));
+}
+// The sum over every sixteen lanes of a wavefront, all of which are active; every lane gets it.
+__device__ __forceinline__ double sum_of_16(double v) {
+  v += from_lane<kXor1>(v);
+  v += from_lane<kXor2>(v);
+  v += from_lane<kMirror8>(v);
+  v += from_lane<kMirror16>(v);
+  return v;
+}
+// ... and over the wavefront: lane 63 gets it.
+__device__ __forceinline__ double wave_sum(double v) {
+  v = sum_of_16(v);
+  v += from_lane<kLast16, 0xA>(v);
+  v += from_lane<kLast32, 0xC>(v);
+  return v;
+}
+// Inclusive prefix sums over the wavefront.
+template <typename N>
+__device__ __forceinline__ N prefix_of_16(N v) {
+  v += from_lane<kBefore + 1>(v);
+  v += from_lane<kBefore + 2>(v);
+  v += from_lane<kBefore + 4>(v);
+  v += from_lane<kBefore + 8>(v);
+  return v;
+}
+template <typename N>
+__device__ __forceinline__ N wave_prefix(N v) {
+  v = prefix_of_16(v);
+  v += from_lane<kLast16, 0xA>(v);
+  v += from_lane<kLast32, 0xC>(v);
+  return v;
+}
 // The same of several values at a time, in place; `scratch` holds as many doubles per wavefront.
 template <int N>
 __device__ __forceinline__ void block_sums(double (&v)[N], double *scratch) {
   const int waves = blockDim.x >> 6;
 #pragma unroll
-  for (int n = 0; n < N; ++n)
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v[n] += __shfl_xor(v[n], d);
+  for (int n = 0; n < N; ++n) v[n] = wave_sum(v[n]);
   __syncthreads();
 #pragma unroll
   for (int n = 0; n < N; ++n)
-    if ((threadIdx.x & 63) == 0) scratch[(threadIdx.x >> 6) * N + n] = v[n];
+    if ((threadIdx.x & 63) == 63) scratch[(threadIdx.x >> 6) * N + n] = v[n];
   __syncthreads();
+  const int lane = threadIdx.x & 63;  // (lane w fetches wavefront w's, of which there are sixteen at most)
 #pragma unroll
-  for (int n = 0; n < N; ++n) v[n] = 0.0;
-  for (int w = 0; w < waves; ++w)
-#pragma unroll
-    for (int n = 0; n < N; ++n) v[n] += scratch[w * N + n];
+  for (int n = 0; n < N; ++n) v[n] = of_lane(sum_of_16(lane < waves ? scratch[lane * N + n] : 0.0), 0);
 }
 __device__ double block_max(double v, double *scratch) {
   const int waves = blockDim.x >> 6;
@@ -405,13 +459,11 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
 
 // ---- the form by cells
 
-// The rows it takes.  Shorter ones are quicker sorted: two sorting workgroups share a CU, the cells fill its LDS (us a
-// call, cells against sorting, 1, 256 and 1024 rows: fp32 4 000 entries 54 : 56, 60 : 66, 220 : 186; 6 144: 59 : 84,
-// 67 : 102, 249 : 296; 8 192: 68 : 101, 76 : 121, 283 : 356; 32 000: 138 : 272, 179 : 309, 646 : 867; bf16 4 000: 61 : 56, 64 : 64, 237 : 181; 6 144: 60 : 82, 70 : 96, 271 : 259; 8 192: 67 : 98,
-// 83 : 117, 309 : 319; 32 000: 141 : 335, 196 : 403, 718 : 1347).
-// Rows in doubt get a second attempt behind the first from kAgainMinV entries on: what cells leave open grows with the
+// The rows that go by cells.  Shorter ones are sorted (us a call of four list sizes, cells' sums against sorting, 1, 64, 256 and 512 rows: fp32
+// 6144 entries 51 : 83, 53 : 86, 58 : 97, 108 : 140; bf16 8192: 52 : 96, 59 : 99, 63 : 112, 120 : 158; sorting 4096 fp32 entries takes 57, 58, 62, 89).
+// Rows in doubt get a second attempt after the first from kAgainMinV entries on: what cells leave open grows with the
 // entries that share one.  (Of twenty families of rows none had more than half of what is allowed at 50 257 entries, several more than
-// all of it from 152 064 on.  A launch that finds nothing to do is some 2 us; a row of 65 536 takes 230.)
+// all of it from 152 064 on.)
 constexpr int kAgainMinV = 1 << 16;
 constexpr int kCellMinV = 6144, kCellMinVNarrow = 8192, kCellMaxV = 1 << 18;
 // The sample, and the buckets that its quantiles make.  Half of it are entries spread over the row, half the largest
@@ -423,7 +475,6 @@ constexpr int kMaxBuckets = 255;
 constexpr int kCellThreads = 1024;
 constexpr int kCells = 6144, kOuterCells = 384;
 constexpr int kFewestCells = 8;        // of a bucket when they are shared out again
-constexpr int kInDoubt = 2;            // a row's flag: its uncertainties sum to too much
 constexpr uint32_t kNoCell = 0xFFFFu;  // of an entry that lacks mass on a side
 constexpr int kListed = 128;           // entries of a row whose sums are formed exactly
 constexpr float kEntryError = 1e-9f;   // what cells may leave open of a result, whichever list size it is for: of one entry ...
@@ -452,22 +503,14 @@ __device__ __forceinline__ float at(const float4 &v, int j) { return j == 0 ? v.
 template <typename N>
 __device__ __forceinline__ N block_prefix(N v, N *scratch, N *total) {
   const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-  N incl = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const N up = __shfl_up(incl, d);
-    if (lane >= d) incl += up;
-  }
+  const N incl = wave_prefix(v);
   __syncthreads();  // scratch may still be read from the previous call
   if (lane == 63) scratch[threadIdx.x >> 6] = incl;
   __syncthreads();
-  N before = N(0), sum = N(0);
-  for (int w = 0; w < waves; ++w) {
-    if (w == (int)(threadIdx.x >> 6)) before = sum;
-    sum += scratch[w];
-  }
-  *total = sum;
-  return before + incl - v;
+  const N own = lane < waves ? scratch[lane] : N(0), upto = prefix_of_16(own);  // (sixteen wavefronts at most)
+  *total = of_lane(upto, 15);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return of_lane(upto, wave) - of_lane(own, wave) + incl - v;
 }
 
 // A value that is the same in all lanes, held in scalar registers.
@@ -596,18 +639,18 @@ __device__ __forceinline__ unsigned long long fixed_mass(double e) {
 // a weight belongs to a cell, taken at its right end or further right (1024 rows of 128 256, four sizes: 2.129 ms without weights,
 // 2.136 so, 2.175 from a table for every entry, 2.265 by the sizes for every entry; 512 x 8 192 151 us, 154).  Where t g times that is more than kEntryError the entry's own sum is formed exactly by one more
 // walk over the row's cell numbers (two large masses in one cell: a few rows in a hundred); a row whose uncertainties
-// sum to more than kRowError of a result is done AGAIN by another launch, with cells shared out by where they were, and
+// sum to more than kRowError of a result gets a second attempt, with cells shared out by where they were, and is
 // left to the sorting kernel, which takes twice as long as both, if that is not enough.  (256 rows, one side flat, the other
 // normal times 3, us, before, when 0.25 w stood for (w - |s|)^2 / 4 w and 2^-23 for kRowError and nearly all were sorted, and now: 128 256
 // entries 2742, 1190, without a row in doubt 520; 152 064: 3362, 1389; 262 144: 5787, 2237.)
 // A mass below 2^-46 of its row's largest is 0 in a cell's sum: a denominator is no less than the larger of p_j and q_j (the
 // maxima are over all of a row whose masses sum to 1), so 2^18 such masses are less than 2^-28 of it.
-// What bounds it: instruction issue in fp64 (two exponentials an entry and pass), the latency of LDS atomics and reads.
-// The row is read three times, and two bytes an entry are written and read.  1024 rows of 128 256, four sizes: 2.13 ms,
+// It takes the rows that lml_sum_kernel marked.  What bounds it: instruction issue in fp64 (two exponentials an entry and pass), the latency of LDS atomics and reads.
+// The row is read three times, and two bytes an entry are written and read.  If it did every row, 1024 rows of 128 256, four sizes: 2.13 ms,
 // against 3.13 with entries moved to buckets of about 1000 and those ordered in LDS; 1024 x 32 000 0.63 : 0.87,
 // 512 x 152 064 bf16 1.37 : 1.94, one row 0.43 : 1.00, 64 x 262 144 0.96 : 2.11, eight sizes 512 rows 1.56 : 2.26.
 // All sums run in an order that does not depend on how the wavefronts interleave.
-template <typename E, bool PROBS, bool AGAIN>
+template <typename E, bool PROBS>
 __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlParams p) {
   __shared__ unsigned long long s_p[kCells + 1], s_q[kCells + 1];  // a cell's masses, then what lies before it
   __shared__ float4 s_bucket[kMaxBuckets + 1];  // left end, cells per unit of ln r, first cell, last cell
@@ -632,7 +675,13 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   const E *prow = reinterpret_cast<const E *>(p.draft) + b_row * p.draft_stride_b;
   const E *qrow = reinterpret_cast<const E *>(p.target) + b_row * p.target_stride_b;
   char *work = p.work + (size_t)blockIdx.x * 24u * (size_t)V;
-  if (AGAIN && *flag_of(work, V) != kInDoubt) return;  // (uniform)
+  {
+    const double done = p.bound[b_row * p.n_k];
+    if (done == done) {  // (uniform) the form by sums has done the row
+      if (tid == 0) *flag_of(work, V) = 0;
+      return;
+    }
+  }
   unsigned short *ids = reinterpret_cast<unsigned short *>(work);
   const float none = PROBS ? 0.0f : -__builtin_huge_valf();
   const float ninf = -__builtin_huge_valf();
@@ -745,313 +794,1068 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
   pick_splitters();
   nb = uniform(nb);
   __syncthreads();
-  if (tid == 0) { s_split[0] = (int)0x80000000; s_listed = 0; }
-  if (tid < kCells / 32) s_mark[tid] = 0u;
-  // cells: the outer buckets, which are the longest, get kOuterCells each, the others share the rest evenly
-  int my_cells = 0;  // of bucket number `tid`
-  if (tid < nb) my_cells = nb <= 2 ? kCells / nb : tid == 0 || tid + 1 == nb ? kOuterCells : (kCells - 2 * kOuterCells) / (nb - 2);
-  double zp, zq, first, norm_p, norm_q, unit_p, unit_q;
-  constexpr int kEach = kCells / kCellThreads;
+  if (tid == 0) s_split[0] = (int)0x80000000;
 #pragma unroll 1
-  for (int round = 0;; ++round) {
-    int in_all;
-    const int my_first = block_prefix(my_cells, s_redi, &in_all);
-    if (tid < nb) {
-      const float left = tid > 0 ? distance_of(s_split[tid]) : far_left;
-      const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : far_right;
-      // (two places can be farther apart than an int reaches; one more than a place is one)
-      const bool one_place = tid >= 1 && tid + 1 < nb && s_split[tid + 1] <= s_split[tid] + 1;
-      const float scale = one_place || !(right > left) ? 0.0f : (float)my_cells / (right - left);
-      s_bucket[tid] = make_float4(left, scale, (float)my_first, (float)(my_first + my_cells - 1));
+  for (int attempt = 0;; ++attempt) {
+    if (tid == 0) s_listed = 0;
+    if (tid < kCells / 32) s_mark[tid] = 0u;
+    // cells: the outer buckets, which are the longest, get kOuterCells each, the others share the rest evenly
+    int my_cells = 0;  // of bucket number `tid`
+    if (tid < nb) my_cells = nb <= 2 ? kCells / nb : tid == 0 || tid + 1 == nb ? kOuterCells : (kCells - 2 * kOuterCells) / (nb - 2);
+    double zp, zq, first, norm_p, norm_q, unit_p, unit_q;
+    constexpr int kEach = kCells / kCellThreads;
+  #pragma unroll 1
+    for (int round = 0;; ++round) {
+      int in_all;
+      const int my_first = block_prefix(my_cells, s_redi, &in_all);
+      if (tid < nb) {
+        const float left = tid > 0 ? distance_of(s_split[tid]) : far_left;
+        const float right = tid + 1 < nb ? distance_of(s_split[tid + 1]) : far_right;
+        // (two places can be farther apart than an int reaches; one more than a place is one)
+        const bool one_place = tid >= 1 && tid + 1 < nb && s_split[tid + 1] <= s_split[tid] + 1;
+        const float scale = one_place || !(right > left) ? 0.0f : (float)my_cells / (right - left);
+        s_bucket[tid] = make_float4(left, scale, (float)my_first, (float)(my_first + my_cells - 1));
+      }
+      for (int c = tid; c <= kCells; c += kCellThreads) {
+        s_p[c] = 0ull;
+        s_q[c] = 0ull;
+        if (c < kCells) { s_low[c] = 0x7FFFFFFF; s_high[c] = (int)0x80000000; }
+      }
+      __syncthreads();
+
+      // ---- second pass: every entry's cell, the cells' masses, and the sums of all masses
+      double p_first = 0.0;
+      zp = zq = 0.0;
+      for (int i = tid * 4; i < V; i += kCellThreads * 4) {
+        const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+        uint32_t packed[2] = {0u, 0u};
+  #pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float xp = at(xp4, j), xq = at(xq4, j);
+          const double ep = relative(xp, top_p, per_p), eq = relative(xq, top_q, per_q);
+          zp += ep;
+          zq += eq;
+          uint32_t cell = kNoCell;
+          if (some && pl.mass(xp) && pl.mass(xq)) {
+            const float d = pl.distance(xp, xq);
+            if (fabsf(d) < kFar) {
+              const int place = place_of(d);
+              const float4 bu = s_bucket[nb > 1 ? bucket_of(s_split, nb, place) : 0];
+              cell = (uint32_t)(int)fminf(fmaxf((d - bu.x) * bu.y, 0.0f) + bu.z, bu.w);
+              atomicAdd(&s_p[cell], fixed_mass(ep));
+              atomicAdd(&s_q[cell], fixed_mass(eq));
+              atomicMin(&s_low[cell], place);
+              atomicMax(&s_high[cell], place);
+            }
+          }
+          // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
+          // p-mass to speak of)
+          if (cell == kNoCell) p_first += ep;
+          packed[j >> 1] |= cell << (16 * (j & 1));
+        }
+        if (i + 3 < V) {
+          *reinterpret_cast<uint2 *>(ids + i) = make_uint2(packed[0], packed[1]);
+        } else {
+          for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned short)(packed[j >> 1] >> (16 * (j & 1)));
+        }
+      }
+      zp = uniform(block_sum(zp, s_red));
+      zq = uniform(block_sum(zq, s_red));
+      norm_p = zp > 0.0 ? 1.0 / zp : 0.0;
+      norm_q = zq > 0.0 ? 1.0 / zq : 0.0;
+      first = uniform(block_sum(p_first, s_red) * norm_p);
+      unit_p = 0x1p-45 * norm_p;
+      unit_q = 0x1p-45 * norm_q;
+      {
+        unsigned long long all;
+  #pragma unroll
+        for (int side = 0; side < 2; ++side) {
+          unsigned long long *m = side == 0 ? s_p : s_q, mine[kEach], sum = 0ull;
+  #pragma unroll
+          for (int e = 0; e < kEach; ++e) { mine[e] = m[tid * kEach + e]; sum += mine[e]; }
+          unsigned long long before = block_prefix(sum, s_redu, &all);
+  #pragma unroll
+          for (int e = 0; e < kEach; ++e) { m[tid * kEach + e] = before; before += mine[e]; }
+          if (tid == kCellThreads - 1) m[kCells] = before;
+        }
+      }
+      __syncthreads();
+      if (attempt == 0 || round == 1) break;
+      // cells where they are wanted: a bucket's uncertainty is about the sum of t^2 w over its cells, t a cell's term and w its
+      // width, and falls with the square of their number, so the sum over all buckets is least with numbers that go with
+      // the cube root of t^2 w times the present number squared
+      float wants = 0.0f;
+      if (tid < nb) {
+        for (int c = my_first; c < my_first + my_cells; ++c) {
+          const double pc = (double)(s_p[c + 1] - s_p[c]) * unit_p, qc = (double)(s_q[c + 1] - s_q[c]) * unit_q;
+          const double base = (1.0 - (double)s_q[c] * unit_q) * pc + ((double)s_p[c] * unit_p + first) * qc;
+          const float t = pc > 0.0 && qc > 0.0 && base > 0.0 ? (float)(pc * qc * reciprocal(base)) : 0.0f;
+          if (s_high[c] > s_low[c]) wants += t * t * (distance_of(s_high[c]) - distance_of(s_low[c]));
+        }
+        if (wants > 0.0f) wants = exp2f(log2f(wants * (float)my_cells * (float)my_cells) * (1.0f / 3.0f));
+      }
+      const float wanted = (float)block_sum((double)wants, s_red);
+      if (tid < nb && wanted > 0.0f) my_cells = kFewestCells + (int)((float)(kCells - 1 - nb * kFewestCells) * (wants / wanted));
     }
-    for (int c = tid; c <= kCells; c += kCellThreads) {
-      s_p[c] = 0ull;
-      s_q[c] = 0ull;
-      if (c < kCells) { s_low[c] = 0x7FFFFFFF; s_high[c] = (int)0x80000000; }
+    // about what the results will be, the thread's cells taken as one entry: uncertainties are measured against them
+    const int my_cell = tid * kEach;
+    const unsigned long long my_p = s_p[my_cell + kEach], my_q = s_q[my_cell];
+    double about_1 = 0.0;
+  #pragma unroll 1
+    for (int n0 = 0; n0 < p.n_k; n0 += 4) {
+      double about[4] = {0.0, 0.0, 0.0, 0.0};
+      const double pc = (double)(my_p - s_p[my_cell]) * unit_p, qc = (double)(s_q[my_cell + kEach] - my_q) * unit_q;
+      const double base = (1.0 - (double)my_q * unit_q) * pc + ((double)s_p[my_cell] * unit_p + first) * qc;
+      const bool shared = pc > 0.0 && qc > 0.0 && base > 0.0;
+      if (shared) add_quotients<2>(about, p, n0, pc * qc, base, 1.0, pc);
+      double sum[5] = {about[0], about[1], about[2], about[3], shared ? pc * qc * reciprocal(base) : 0.0};
+      block_sums(sum, s_red);
+      about_1 = uniform(sum[4]);
+  #pragma unroll
+      for (int n = 0; n < 4; ++n)
+        if (tid == 0 && n0 + n < p.n_k) { s_about[n0 + n] = sum[n]; s_scale[n0 + n] = (float)(p.kd[n0 + n] / sum[n]); }
+    }
+    // (two sides that share next to nothing: whatever is open is resolved)
+    const bool some_shared = about_1 > 0x1p-90;
+    const float entry_error = some_shared ? kEntryError : 0.0f;
+    if (tid == 0) s_far = 0;
+    __syncthreads();
+    // in place of the places: a cell's width in ln r, and what its entries' uncertainties are weighed by (at the right
+    // end of the thread's cells)
+    {
+      int right = (int)0x80000000;
+  #pragma unroll
+      for (int e = 0; e < kEach; ++e) {
+        const int low = s_low[my_cell + e], high = s_high[my_cell + e];
+        right = max(right, high);
+        s_low[my_cell + e] = __float_as_int(high > low ? distance_of(high) - distance_of(low) : 0.0f);
+      }
+      const double r_0 = (PROBS ? top_p / top_q : 1.0) * zp * norm_q;  // q / p of an entry at distance 0
+      const double before = fma((double)my_p, unit_p, first), from = fmax(1.0 - (double)my_q * unit_q, 0.0);
+      const double d = fma(before, exp_of_negative((double)distance_of(right)) * r_0, from);  // D / p_j
+      const float u = (float)reciprocal(fmin(fmax(d, 1.0), 0x1p900));
+      float weight = some_shared ? 0.0f : 1.0f;
+      for (int n = 0; some_shared && n < p.n_k; ++n) {
+        const float f = __builtin_amdgcn_rcpf(fmaf((float)p.k[n] - 1.0f, u, 1.0f));
+        weight = fmaxf(weight, s_scale[n] * f * f);
+      }
+  #pragma unroll
+      for (int e = 0; e < kEach; ++e) s_high[my_cell + e] = __float_as_int(weight);
     }
     __syncthreads();
 
-    // ---- second pass: every entry's cell, the cells' masses, and the sums of all masses
-    double p_first = 0.0;
-    zp = zq = 0.0;
+    // ---- third pass: the terms (list sizes four at a time)
+    double tv = 0.0;
+    float doubt = 0.0f;
+  #pragma unroll 1
+    for (int n0 = 0; n0 < p.n_k; n0 += 4) {
+      double sums[4] = {0.0, 0.0, 0.0, 0.0}, relaxed[4] = {0.0, 0.0, 0.0, 0.0};
+      // K pq / (base + (K - 1) pm) of one entry, base = D(r) p: numerator and denominator of K q / (D(r) + (K - 1) Q) times p
+  #pragma unroll 1
+      for (int i = tid * 4; i < V; i += kCellThreads * 4) {
+        const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
+        uint32_t cells[2] = {0u, 0u};
+        if (i + 3 < V) {
+          const uint2 c = *reinterpret_cast<const uint2 *>(ids + i);
+          cells[0] = c.x; cells[1] = c.y;
+        } else {
+          for (int j = 0; i + j < V; ++j) cells[j >> 1] |= (uint32_t)ids[i + j] << (16 * (j & 1));
+        }
+  #pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (i + j >= V) continue;
+          const double ep = relative(at(xp4, j), top_p, per_p), eq = relative(at(xq4, j), top_q, per_q);
+          double pm = ep * norm_p, qm = eq * norm_q;
+          if (n0 == 0) tv += fabs(pm - qm);
+          const uint32_t cell = (cells[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
+          if (cell != kNoCell && pm >= 0x1p-150 && qm >= 0x1p-150) {
+            const unsigned long long pb = s_p[cell], qb = s_q[cell + 1];
+            // what else is in the cell
+            const double po = fmax((double)(long long)(s_p[cell + 1] - pb - fixed_mass(ep)), 0.0) * unit_p;
+            const double qo = fmax((double)(long long)(qb - s_q[cell] - fixed_mass(eq)), 0.0) * unit_q;
+            const double a = qo * pm, c = po * qm;
+            const float width = __int_as_float(s_low[cell]);
+            const double rest = fma(fmax(1.0 - (double)qb * unit_q, 0.0), pm, fma((double)pb, unit_p, first) * qm) + pm * qm;
+            double inside = fmax(a, c);
+            const double base = rest + inside;
+            // relative to the denominator: in fp32, as small as they are
+            const double inv = reciprocal(base);
+            const float cw = (float)(c * inv) * width, side = (float)((a - c) * inv), per_cw = __builtin_amdgcn_rcpf(fmaxf(cw, 1e-30f));
+            const float reach = fmaxf(fmaf(cw, width, cw) - fabsf(side), 0.0f);
+            const float gap = fminf((float)(fmin(a, c) * inv), width < 1.5f ? 0.25f * reach * reach * per_cw : 1.0f);
+            const float open = (float)(pm * qm * inv) * gap * __int_as_float(s_high[cell]);
+            if (open > entry_error) {
+              if (n0 == 0) {
+                const int pos = atomicAdd(&s_listed, 1);
+                if (pos < kListed) { s_at[pos] = i + j; s_list_cell[pos] = (int)cell; }
+              }
+            } else {
+              if (n0 == 0) doubt += open;
+              if (width < 0.5f && 2.0f * fabsf(side) < cw) {
+                const float t = 0.5f * cw + side;  // > 0
+                inside = c + (double)(0.5f * t * t * per_cw) * base;
+              }
+              add_quotients<2>(sums, p, n0, pm * qm, rest + inside, 1.0, pm);
+            }
+          }
+          if (ep > 0.0 && eq > 0.0 && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
+            // (where the product nears the smallest numbers, both are taken relative to the larger one: its
+            // denominators, and their product, are then at least 1/4)
+            int scale = 0;
+            if (pm * qm < 0x1p-900) {
+              scale = __builtin_amdgcn_frexp_exp(fmax(pm, qm));
+              pm = __builtin_amdgcn_ldexp(pm, -scale);
+              qm = __builtin_amdgcn_ldexp(qm, -scale);
+            }
+            const double pq = __builtin_amdgcn_ldexp(pm * qm, scale);
+            if (pq > 0.0) add_quotients<2>(relaxed, p, n0, pq, qm, 0.0, pm);
+          }
+        }
+      }
+      __syncthreads();
+      const int listed = s_listed;
+      if (listed > kListed) break;  // (uniform) the row is the sorting kernel's
+      if (listed > 0) {
+        // ---- the listed entries' cells, entry by entry: what is above each in the order, and what below
+        if (n0 == 0) {
+          if (tid < listed) {
+            s_ratio[tid] = pl.log_ratio(elem<E>(prow, s_at[tid]), elem<E>(qrow, s_at[tid]));
+            s_above[tid] = 0ull;
+            s_below[tid] = 0ull;
+            atomicOr(&s_mark[s_list_cell[tid] >> 5], 1u << (s_list_cell[tid] & 31));
+          }
+          __syncthreads();
+          for (int i = tid; i < V; i += kCellThreads) {
+            const uint32_t cell = ids[i];
+            if (cell == kNoCell || !((s_mark[cell >> 5] >> (cell & 31u)) & 1u)) continue;
+            const float xp = elem<E>(prow, i), xq = elem<E>(qrow, i);
+            const double r = pl.log_ratio(xp, xq);
+            for (int l = 0; l < listed; ++l) {
+              if (s_list_cell[l] != (int)cell || s_at[l] == i) continue;
+              if (r >= s_ratio[l])
+                atomicAdd(&s_above[l], fixed_mass(relative(xq, top_q, per_q)));
+              else
+                atomicAdd(&s_below[l], fixed_mass(relative(xp, top_p, per_p)));
+            }
+          }
+          if (tid < listed) {
+            int before = 0;
+            for (int l = 0; l < listed; ++l) before += s_at[l] < s_at[tid] ? 1 : 0;
+            s_order[before] = tid;
+          }
+          __syncthreads();
+        }
+        if (tid < listed) {  // thread t takes the t-th in the row's order
+          const int from = s_order[tid];
+          const int i = s_at[from], cell = s_list_cell[from];
+          const double pm = relative(elem<E>(prow, i), top_p, per_p) * norm_p, qm = relative(elem<E>(qrow, i), top_q, per_q) * norm_q;
+          const double behind = fmax(1.0 - (double)s_q[cell + 1] * unit_q, 0.0) + (double)s_above[from] * unit_q;
+          const double before = fma((double)s_p[cell] + (double)s_below[from], unit_p, first);
+          add_quotients<2>(sums, p, n0, pm * qm, fma(behind, pm, before * qm) + pm * qm, 1.0, pm);
+        }
+      }
+      double bound[5] = {sums[0], sums[1], sums[2], sums[3], (double)doubt};
+      block_sums(bound, s_red);
+      double others[5] = {relaxed[0], relaxed[1], relaxed[2], relaxed[3], tv};
+      block_sums(others, s_red);
+      if (tid == 0) {
+  #pragma unroll
+        for (int n = 0; n < 4; ++n)
+          if (n0 + n < p.n_k) {
+            // (the doubt is relative to what each result was to be about)
+            if (bound[4] * s_about[n0 + n] > kRowError * bound[n]) s_far = 1;
+            p.bound[b_row * p.n_k + n0 + n] = bound[n];
+            if (p.relaxed != nullptr) p.relaxed[b_row * p.n_k + n0 + n] = others[n];
+          }
+        if (n0 == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * others[4];
+      }
+    }
+    __syncthreads();
+    const bool too_many = s_listed > kListed, in_doubt = s_far != 0;  // (uniform)
+    if (attempt == 0 && !too_many && in_doubt && V >= kAgainMinV) {
+      __syncthreads();  // s_listed and s_far have been read
+      continue;
+    }
+    if (tid == 0) *flag_of(work, V) = too_many || in_doubt ? 1 : 0;
+    break;
+  }
+}
+
+// ---- the form by cells' sums
+
+// A thread holds kSumEach cells.  Buckets: 127 quantiles' splitters, up to 128 of places that the sample holds often, and two
+// for every heavy entry.
+constexpr int kSumEach = 7, kSumCells = kSumEach * kCellThreads, kSumBuckets = 512;
+constexpr double kHeavy = 0x1p-9;     // of a side's mass: such an entry's place has a cell of its own
+constexpr float kSumFar = 740.0f;     // entries farther from the row's centre in log2 r have no place (kFar in ln r)
+constexpr float kBeyond = 6.0f;       // how far the outer buckets reach beyond the sample, in log2 r
+// What a row's cells may leave open of a result, of kRowError: as much as those of one side flat and the other normal times 3 do
+// (some 8e-13 an entry; Zipf-like rows a tenth of that or less).  More is no matter of chance but of a crowd in few cells.
+constexpr double kSumErrorLeast = 0.5, kSumErrorEach = 0x1p-17;
+constexpr double kShareAgain = 0x1p-18;  // what sharing the cells out again can mend
+constexpr float kWide = 0.5f;         // a cell this wide in ln r leaves its entries' whole terms open
+
+// 2^y for y <= 0 or so (what is below -1074 comes out as 0, NaN too) to about an ulp: y = n + f, |f| <= 1/2, and 2^f = 1 + f P(f)
+// with the P of degree 10 whose largest relative error on that range is least (1.8e-17; by Remez' exchange).
+__device__ __forceinline__ double exp2_of(double y) {
+  asm("v_max_f64 %0, %1, %2" : "=v"(y) : "v"(y), "s"(-1100.0));  // (fmax() takes one instruction more, to quiet a NaN that cannot be)
+  const double t = y + 0x1.8p52;        // (n in the lower half)
+  const double f = y - (t - 0x1.8p52);
+  double s = 0x1.c062ee76e864cp-32;
+  s = fma(s, f, 0x1.e605f90accdcbp-28);
+  s = fma(s, f, 0x1.b54167f262812p-24);
+  s = fma(s, f, 0x1.62bfd49f13823p-20);
+  s = fma(s, f, 0x1.ffcbee3aee4b9p-17);
+  s = fma(s, f, 0x1.4309130960facp-13);
+  s = fma(s, f, 0x1.5d87fe7bbbe3ep-10);
+  s = fma(s, f, 0x1.3b2ab6fba1e1cp-7);
+  s = fma(s, f, 0x1.c6b08d7048f31p-5);
+  s = fma(s, f, 0x1.ebfbdff82c598p-3);
+  s = fma(s, f, 0x1.62e42fefa39f3p-1);
+  s = fma(s, f, 1.0);
+  return __builtin_amdgcn_ldexp(s, (int)(uint32_t)__double_as_longlong(t));
+}
+
+// A mass relative to its row's largest as a whole number of `step` 2^-52ths, a power of two and no less than the mass.
+__device__ __forceinline__ unsigned long long whole_mass(double e, double step) {
+  const unsigned long long sum = (unsigned long long)__double_as_longlong(e + step);
+  const uint32_t hi = (uint32_t)(sum >> 32) - (uint32_t)((unsigned long long)__double_as_longlong(step) >> 32);  // (the lower half of `step` is 0)
+  return ((unsigned long long)hi << 32) | (uint32_t)sum;
+}
+// ... the least for masses that sum to z, which must stay below 2^63 (values of few bits are rounded alike, so that it is not chance
+// alone which keeps the rounding of their sums small: with 128 throughout, as fixed_mass has it, bf16 rows came out 2e-11 off, now 3e-12).
+__device__ __forceinline__ double step_for(double z) {
+  return fmax(__builtin_amdgcn_ldexp(1.0, __builtin_amdgcn_frexp_exp(z) - 11), 1.0);
+}
+
+// log2(e) / t, rounded once: of twice 53 bits of either factor.
+__device__ __forceinline__ double log2e_over(float t) {
+  const double hi = 0x1.71547652b82fep+0, lo = 0x1.777d0ffda0d24p-56;  // log2(e)
+  const double r = 1.0 / (double)t, rest = fma(-r, (double)t, 1.0) * r;  // 1 / t
+  return fma(r, hi, fma(r, lo, rest * hi));
+}
+
+// A side's masses relative to a reference entry.  Logits and log-weights: 2^(x per - off); probabilities: x per.
+template <bool PROBS>
+struct Masses {
+  double per, off;
+  __device__ __forceinline__ double log2_of(float x) const { return fma((double)x, per, -off); }
+  __device__ __forceinline__ double of(float x) const {
+    if (PROBS) return x > 0.0f && x < __builtin_huge_valf() ? (double)x * per : 0.0;
+    return exp2_of(log2_of(x));
+  }
+};
+
+// acc[n] += pq / (k[n] p + q) for 2 PAIRS list sizes: the relaxed sum's quotients less their factor k[n], by one reciprocal.
+// What has pq < 2^-400 (four denominators' product is far from the smallest numbers otherwise) adds less than k 2^-200 each
+// and is left out: a result below kLeastRelaxed is not this form's.
+constexpr double kLeastRelaxed = 0x1p-100;
+template <int PAIRS>
+__device__ __forceinline__ void add_relaxed(double (&acc)[4], const double *k, double pp, double q) {
+  const double pq = pp * q;
+  if (pq >= 0x1p-400) {
+    const double d0 = fma(k[0], pp, q), d1 = fma(k[1], pp, q), d01 = d0 * d1;
+    if (PAIRS == 1) {
+      const double r = pq * reciprocal(d01);
+      acc[0] = fma(r, d1, acc[0]);
+      acc[1] = fma(r, d0, acc[1]);
+    } else {
+      const double d2 = fma(k[2], pp, q), d3 = fma(k[3], pp, q), d23 = d2 * d3;
+      const double r = pq * reciprocal(d01 * d23), r01 = r * d23, r23 = r * d01;
+      acc[0] = fma(r01, d1, acc[0]);
+      acc[1] = fma(r01, d0, acc[1]);
+      acc[2] = fma(r23, d3, acc[2]);
+      acc[3] = fma(r23, d2, acc[3]);
+    }
+  }
+}
+
+// The place of a distance that is 0 or a multiple of 2^-36 below 2^11 in size takes 30 bits (the smallest such has the
+// bits 0x2D800000, the largest less than 0x45000000), in the same order.
+__device__ __forceinline__ int short_place(int place) {
+  return place > 0 ? place - 0x2D000000 : place < 0 ? place + 0x2D000000 : 0;
+}
+__device__ __forceinline__ int long_place(int v) { return v > 0 ? v + 0x2D000000 : v < 0 ? v - 0x2D000000 : 0; }
+
+// The largest of the four entries from `group` on, and where.
+template <typename E>
+__device__ __forceinline__ void largest_of_four(const E *row, int group, int V, float fill, float *best, int *at_best) {
+  const float4 x = four<E>(row, group, V, fill);
+  *best = -__builtin_huge_valf();
+  *at_best = group;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (at(x, j) > *best) { *best = at(x, j); *at_best = group + j; }
+}
+
+// A SIMD serves its wavefronts oldest first, so that the last of a workgroup goes through the end of its row alone.  Whoever
+// is behind one of these steps is served before those past it.
+struct Steps {
+  int left, at;
+  __device__ __forceinline__ explicit Steps(int V) : left((V + 4 * kCellThreads - 1) / (4 * kCellThreads)), at(left >> 1) {
+    __builtin_amdgcn_s_setprio(3);
+    level = 3;
+  }
+  __device__ __forceinline__ void next() {
+    if (left-- > at) return;
+    at >>= 2;
+    if (--level == 2) __builtin_amdgcn_s_setprio(2);
+    else if (level == 1) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+  }
+  __device__ __forceinline__ void done() { __builtin_amdgcn_s_setprio(0); }
+  int level;
+};
+
+// The kernel's parameters, fetched once more: held from its beginning they take scalar registers that its loops have not got.
+__device__ __forceinline__ const LmlParams &params_again() {
+  typedef const LmlParams __attribute__((address_space(4))) *kernarg;
+  uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));
+  return *(const LmlParams *)(kernarg)at;
+}
+
+// One workgroup per row, one per CU (the cells fill its LDS).  A term for K is K q_j / (F(r_j) + K - 1) with
+// F(r) = sum_i max(q_i, r p_i), a function of r_j = q_j / p_j alone, so what a cell of ln r adds to the result follows
+// from sums over its entries, and no entry is looked at again.  With P, Q a cell's masses, r = Q / P, r_j = r (1 + s_j), v the mean of s_j^2 (weighed by p)
+// and g the mean of |s_i - s_j|,
+//   sum_j K q_j / (F(r_j) + K - 1) = K Q / D (1 - x ((P' + P / 2) v + P g / 2) + x^2 (P' + P / 2)^2 v + third powers of s),
+// P' the p-mass and Q' the q-mass before and behind the cell, D = Q' + Q + r P' + K - 1, x = r / D.  P and Q are added up as whole numbers (whole_mass),
+// v comes from a third sum, of p u^2 with u an entry's place in its cell (the mean of u is known from Q / P), and g, for which the order
+// inside the cell would be needed, is taken as 4 v / w: right on average if the entries lie evenly in the cell's width w, whatever their
+// number and masses are.  It is no less than 2 v / w and no more than 2 sqrt(v / 3) (the mean difference of any masses with
+// that variance), so what a cell leaves open is known; an entry that is heavy on either side gets a cell without width (with others of its ratio),
+// for which nothing is open.  Rows whose cells leave more open in all than kSumErrorLeast and kSumErrorEach allow get one more pass with
+// cells shared out by where that was; what then still does, rows with +inf entries or without mass on a side, or whose results are so small that the rounding of
+// masses may count, are marked (a NaN in the place of their first result) and left to lml_cell_kernel, behind this one.
+// tv and the relaxed sums are taken in 64 bits, entry by entry, in the pass that makes the cells.
+// What bounds it: issue in fp64.  The row is read twice and nothing is written.  Two exponentials an entry and pass (15 instructions each), of some 45 in the
+// first pass and 110 in the second; of a row of 128 256 (220 us, four a CU in turn) those take 53 and 112 us, the sample and its order 17, the
+// cells 14, sums over the workgroup and their barriers the rest.  us a call, four list sizes, entries' terms taken one by one (lml_cell_kernel for
+// every row) and now: 1024 x 128 256 2135, 870; 512 x 152 064 bf16 1394, 720; 1024 x 32 000, two sizes, 645, 354; 256 x 50 257 bf16, one size, 272,
+// 152; one row of 128 256 423, 175; 64 x 8192 71, 56; 256 x 128 256, one side flat and the other normal times 3, 1187, 336, target masked by -10^9 but
+// for 50 297, 229, eight sizes 790, 319.  Rows whose two sides share next to nothing pay for an attempt in vain (256 x 128 256, bound 10^-4: 526, 885).
+// The bound's error against 64 bits, same inputs: 1.1e-10, 3e-11; T = 1: 3.3e-10, 1.5e-10; 152 064 bf16: 7e-12, 7e-13.
+template <typename E, bool PROBS>
+__global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParams p) {
+  __shared__ unsigned long long s_p[kSumCells + 1], s_q[kSumCells + 1];  // a cell's masses, then what lies before it
+  __shared__ uint32_t s_u2[kSumCells];         // sums of p (u - 1/2)^2 in 2^-31ths of the side's mass
+  __shared__ float4 s_bucket[kSumBuckets];     // left end, cells per unit of log2 r, first cell (its bits), largest place in the bucket in cells
+  __shared__ double s_per_left[kSumBuckets];   // 2^-(left end), for whole masses
+  __shared__ float s_split[2 * kSumBuckets];   // bucket b holds what lies from s_split[b] up to s_split[b + 1]
+  __shared__ unsigned short s_grid[kCellThreads];  // splitters to the left of each of 1024 equal parts of the range
+  __shared__ double s_red[8 * (kCellThreads / 64)];
+  __shared__ unsigned long long s_redu[kCellThreads / 64];
+  __shared__ int s_redi[kCellThreads / 64];
+  __shared__ double s_total[2];                // the sides' masses, relative to their largest
+  __shared__ double s_sizes[4];
+  __shared__ int s_single, s_most;             // buckets of a single place; splitters in one part of the range, at most
+  int *s_sample = reinterpret_cast<int *>(s_p);  // (before the cells)
+  static_assert(kCellMinV >= 4 * kCellThreads && kCellMinVNarrow >= 4 * kCellThreads, "every thread has four entries");
+  static_assert(kSumBuckets * (kFewestCells + 1) + 2 * kOuterCells < kSumCells, "too few cells");
+
+  const int tid = threadIdx.x;
+  const long long b_row = p.row0 + blockIdx.x;
+  const int V = p.V;
+  const E *prow = reinterpret_cast<const E *>(p.draft) + b_row * p.draft_stride_b;
+  const E *qrow = reinterpret_cast<const E *>(p.target) + b_row * p.target_stride_b;
+  const float none = PROBS ? 0.0f : -__builtin_huge_valf();
+  const float ninf = -__builtin_huge_valf(), pinf = __builtin_huge_valf();
+  auto leave = [&]() {
+    if (tid == 0) p.bound[b_row * p.n_k] = __builtin_nan("");
+  };
+
+  Placer<PROBS> pl;
+  pl.itp = 1.0 / (double)p.temp_draft;
+  pl.itq = 1.0 / (double)p.temp_target;
+  pl.center = 0.0;
+
+  // ---- first pass: the sides' sums and largest entries.  Masses are taken relative to the largest of the first
+  // 64 entries, which serves unless that is so far below the row's largest that the sum overflows
+  Masses<PROBS> mp, mq;
+  mp.per = PROBS ? 1.0 : log2e_over(p.temp_draft);
+  mq.per = PROBS ? 1.0 : log2e_over(p.temp_target);
+  double zp, zq;
+  float own_p, own_q;  // the largest entry that this thread met
+  int at_p, at_q;
+  float top_p, top_q;
+  {
+    const int lane = tid & 63;
+    top_p = elem<E>(prow, lane);
+    top_q = elem<E>(qrow, lane);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      top_p = fmaxf(top_p, __shfl_xor(top_p, d));
+      top_q = fmaxf(top_q, __shfl_xor(top_q, d));
+    }
+  }
+#pragma unroll 1
+  for (int attempt = 0;; ++attempt) {
+    mp.off = uniform(fabsf(top_p) < pinf ? (double)top_p * mp.per : 0.0);
+    mq.off = uniform(fabsf(top_q) < pinf ? (double)top_q * mq.per : 0.0);
+    double sum_p = 0.0, sum_q = 0.0, best_p = -__builtin_huge_val(), best_q = best_p;
+    at_p = at_q = tid * 4;
+    Steps stage(V);
+    float4 next_p = four<E>(prow, tid * 4, V, none), next_q = four<E>(qrow, tid * 4, V, none);
+#pragma unroll 1
     for (int i = tid * 4; i < V; i += kCellThreads * 4) {
-      const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
-      uint32_t packed[2] = {0u, 0u};
+      stage.next();
+      const float4 xp4 = next_p, xq4 = next_q;
+      if (i + kCellThreads * 4 < V) {
+        next_p = four<E>(prow, i + kCellThreads * 4, V, none);
+        next_q = four<E>(qrow, i + kCellThreads * 4, V, none);
+      }
+      double yp[4], yq[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const float xp = at(xp4, j), xq = at(xq4, j);
-        const double ep = relative(xp, top_p, per_p), eq = relative(xq, top_q, per_q);
-        zp += ep;
-        zq += eq;
-        uint32_t cell = kNoCell;
-        if (some && pl.mass(xp) && pl.mass(xq)) {
-          const float d = pl.distance(xp, xq);
-          if (fabsf(d) < kFar) {
-            const int place = place_of(d);
-            const float4 bu = s_bucket[nb > 1 ? bucket_of(s_split, nb, place) : 0];
-            cell = (uint32_t)(int)fminf(fmaxf((d - bu.x) * bu.y, 0.0f) + bu.z, bu.w);
-            atomicAdd(&s_p[cell], fixed_mass(ep));
-            atomicAdd(&s_q[cell], fixed_mass(eq));
-            atomicMin(&s_low[cell], place);
-            atomicMax(&s_high[cell], place);
+        yp[j] = PROBS ? mp.of(xp) : mp.log2_of(xp);
+        yq[j] = PROBS ? mq.of(xq) : mq.log2_of(xq);
+        sum_p += PROBS ? yp[j] : exp2_of(yp[j]);
+        sum_q += PROBS ? yq[j] : exp2_of(yq[j]);
+      }
+      const double gp = fmax(fmax(yp[0], yp[1]), fmax(yp[2], yp[3])), gq = fmax(fmax(yq[0], yq[1]), fmax(yq[2], yq[3]));
+      if (gp > best_p) { best_p = gp; at_p = i; }
+      if (gq > best_q) { best_q = gq; at_q = i; }
+    }
+    stage.done();
+    largest_of_four<E>(prow, at_p, V, none, &own_p, &at_p);
+    largest_of_four<E>(qrow, at_q, V, none, &own_q, &at_q);
+    {
+      // the two sums and the two largest entries over the workgroup
+      const int lane = tid & 63;
+      float wave_p = own_p, wave_q = own_q;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) {
+        wave_p = fmaxf(wave_p, __shfl_xor(wave_p, d));
+        wave_q = fmaxf(wave_q, __shfl_xor(wave_q, d));
+      }
+      sum_p = wave_sum(sum_p);
+      sum_q = wave_sum(sum_q);
+      __syncthreads();  // (s_red may still be read from the attempt before)
+      if (lane == 63) {
+        double *mine = s_red + (tid >> 6) * 4;
+        mine[0] = sum_p; mine[1] = sum_q; mine[2] = (double)wave_p; mine[3] = (double)wave_q;
+      }
+      __syncthreads();
+      const double *theirs = s_red + (lane & 15) * 4;
+      zp = of_lane(sum_of_16(theirs[0]), 0);
+      zq = of_lane(sum_of_16(theirs[1]), 0);
+      float most_p = (float)theirs[2], most_q = (float)theirs[3];
+#pragma unroll
+      for (int d = 8; d >= 1; d >>= 1) {
+        most_p = fmaxf(most_p, __shfl_xor(most_p, d));
+        most_q = fmaxf(most_q, __shfl_xor(most_q, d));
+      }
+      top_p = uniform(most_p);
+      top_q = uniform(most_q);
+    }
+    if (!(fabsf(top_p) < pinf && fabsf(top_q) < pinf) || (PROBS && !(top_p > 0.0f && top_q > 0.0f))) {  // (uniform)
+      leave();
+      return;
+    }
+    if (zp >= 0x1p-300 && zp < 0x1p1000 && zq >= 0x1p-300 && zq < 0x1p1000) break;
+    if (attempt == 1) {  // (uniform) a NaN among the sums: an entry of +inf
+      leave();
+      return;
+    }
+  }
+  if (PROBS) {
+    mp.per = uniform(1.0 / (double)top_p);
+    mq.per = uniform(1.0 / (double)top_q);
+    zp *= mp.per;
+    zq *= mq.per;
+    pl.center = uniform(pl.log_ratio(top_p, top_q));
+  } else {
+    const double off_p = (double)top_p * mp.per, off_q = (double)top_q * mq.per;
+    zp *= exp2_of(mp.off - off_p);
+    zq *= exp2_of(mq.off - off_q);
+    mp.off = uniform(off_p);
+    mq.off = uniform(off_q);
+  }
+  if (tid < 4) s_sizes[tid] = p.kd[tid];
+  if (tid == 0) { s_total[0] = zp; s_total[1] = zq; }  // (registers are scarce in the second pass)
+  // log2 r of an entry less the row's centre, where both its masses are the largest ones' (rounded to 2^-36 first: equal
+  // ratios of different entries differ by fp64's rounding)
+  auto distance = [&](const float xp, const float xq, const double yp, const double yq) {
+    constexpr double kStep = 0x1.8p16;
+    if (!PROBS) return (float)(((yq - yp) + kStep) - kStep);
+    const double d = (pl.log_ratio(xp, xq) - pl.center) * 1.4426950408889634;
+    return pl.mass(xp) && pl.mass(xq) ? (float)((d + kStep) - kStep) : __builtin_nanf("");
+  };
+
+  // ---- splitters: the quantiles of a sample, half of it spread over the row, half the largest entry of every thread on one
+  // side or the other (of a pair's two the even thread answers for the target; where the smaller of these is heavy
+  // it takes the place of a spread entry), the places it holds several times, and those of heavy entries
+  int nb = 1;
+  float far_left = -kSumFar, far_right = kSumFar;
+  {
+    constexpr int kPer = 2, kMany = 32;
+    static_assert(kSamples == kPer * kCellThreads && kSamples * sizeof(int) <= sizeof(s_p), "a sample of two entries a thread");
+    const bool odd = (tid & 1) != 0;
+    float own = odd ? own_p : own_q, lost = __shfl_xor(odd ? own_q : own_p, 1);
+    int at_own = odd ? at_p : at_q, at_lost = __shfl_xor(odd ? at_q : at_p, 1);
+    if (lost > own) {
+      const float x = own; own = lost; lost = x;
+      const int a = at_own; at_own = at_lost; at_lost = a;
+    }
+    int valid = 0, n_valid;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const float largest = e == 0 ? lost : own;
+      const double m = odd ? mp.of(largest) : mq.of(largest);
+      const bool heavy = m >= kHeavy * (odd ? zp : zq);
+      int i = e == 0 ? at_lost : at_own;
+      bool counts = true;
+      if (e == 0 && !heavy) {
+        const unsigned j = (unsigned)tid, jitter = j * 0x9E3779B9u;
+        i = (int)(((unsigned long long)j * (unsigned)V + (((unsigned long long)jitter * (unsigned)V) >> 32)) / kSpread);
+      } else {
+        counts = m >= kCounts;
+      }
+      const float xp = elem<E>(prow, i), xq = elem<E>(qrow, i);
+      const float d = distance(xp, xq, mp.log2_of(xp), mq.log2_of(xq));
+      const bool has_place = counts && fabsf(d) < kSumFar;
+      s_sample[e * kCellThreads + tid] = has_place ? 2 * short_place(place_of(d)) + (heavy ? 1 : 0) : 0x7FFFFFFF;
+      valid += has_place ? 1 : 0;
+    }
+    block_prefix(valid, s_redi, &n_valid);
+    // sorted: a wavefront holds 128 entries, lane l the l-th and the (64 + l)-th, and exchanges them between lanes (66 rounds
+    // through LDS took 12 us of a row's 240, so 6)
+    {
+      const int base = (tid >> 6) * 128 + (tid & 63);
+      int x[kPer];
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) x[e] = s_sample[base + 64 * e];
+#pragma unroll 1
+      for (int size = 2; size <= kSamples; size <<= 1) {
+        if (size >= 256) {
+#pragma unroll
+          for (int e = 0; e < kPer; ++e) s_sample[base + 64 * e] = x[e];
+#pragma unroll 1
+          for (int stride = size >> 1; stride >= 128; stride >>= 1) {
+            __syncthreads();
+            const int lo = 2 * tid - (tid & (stride - 1)), hi = lo + stride;
+            const int a = s_sample[lo], b = s_sample[hi];
+            if ((a > b) == ((lo & size) == 0)) { s_sample[lo] = b; s_sample[hi] = a; }
+          }
+          __syncthreads();
+#pragma unroll
+          for (int e = 0; e < kPer; ++e) x[e] = s_sample[base + 64 * e];
+        }
+        if (size >= 128) {
+          const int lo = min(x[0], x[1]), hi = max(x[0], x[1]);
+          const bool up = (base & size) == 0;
+          x[0] = up ? lo : hi;
+          x[1] = up ? hi : lo;
+        }
+#pragma unroll
+        for (int stride = 32; stride >= 1; stride >>= 1)
+          if (stride < size) {  // (uniform)
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+              int other;
+              switch (stride) {
+                case 1: other = from_lane<kXor1>(x[e]); break;
+                case 2: other = from_lane<kXor2>(x[e]); break;
+                case 4: other = from_lane<kXor3>(from_lane<kMirror8>(x[e])); break;
+                case 8: other = from_lane<kXor8>(x[e]); break;
+                case 16: other = __builtin_amdgcn_ds_swizzle(x[e], 0x401F); break;
+                default: other = __shfl_xor(x[e], stride); break;
+              }
+              const bool up = ((base + 64 * e) & size) == 0, lower = (tid & stride) == 0;
+              x[e] = up == lower ? min(x[e], other) : max(x[e], other);
+            }
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) s_sample[base + 64 * e] = x[e];
+    }
+    __syncthreads();
+    if (n_valid > 0) {  // (uniform)
+      const int want = max(1, min(kQuantiles, n_valid / 16));
+      // `many` equal places or more are two splitters (the place is a bucket), and so is a heavy entry's; others
+      // are one, if a quantile falls into them.  As many of them as there are buckets; heavy ones go last
+      int emit[kPer], total, before = 0;
+#pragma unroll 1
+      for (int many = 4; many <= 2 * kMany; many *= 2) {
+        int mine = 0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+          const int j = tid * kPer + e, v = s_sample[j] >> 1, run = min(many, kMany);
+          emit[e] = 0;
+          if (j < n_valid && (j == 0 || (s_sample[j - 1] >> 1) != v)) {
+            int last = j;
+            while (last + 1 < n_valid && last + 1 < j + run && (s_sample[last + 1] >> 1) == v) ++last;
+            if (last + 1 == j + run || (many <= kMany && (s_sample[last] & 1) != 0)) emit[e] = 2;
+            else if (j > 0 && (unsigned)(last * want) / (unsigned)n_valid != (unsigned)((j - 1) * want) / (unsigned)n_valid) emit[e] = 1;
+          }
+          mine += emit[e];
+        }
+        before = block_prefix(mine, s_redi, &total);
+        if (total < kSumBuckets) break;  // uniform
+      }
+      nb = 1 + min(total, kSumBuckets - 1);
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int v = long_place(s_sample[tid * kPer + e] >> 1);
+        for (int c = 0; c < emit[e]; ++c, ++before)
+          if (1 + before < nb) s_split[1 + before] = distance_of(v + c);
+      }
+      far_left = uniform(distance_of(long_place(s_sample[0] >> 1)) - kBeyond);
+      far_right = uniform(distance_of(long_place(s_sample[n_valid - 1] >> 1)) + kBeyond);
+    }
+  }
+  nb = uniform(nb);
+  if (tid == 0) { s_single = 0; s_most = 0; }
+  for (int b = tid; b < 2 * kSumBuckets; b += kCellThreads)
+    if (b == 0 || b >= nb) s_split[b] = b == 0 ? ninf : pinf;
+  __syncthreads();
+  // an entry's bucket is looked for among the splitters that share its part of the range
+  const float grid_per = uniform((float)kCellThreads / (far_right - far_left));
+  auto part_of = [&](const float d) {
+    return (int)__builtin_amdgcn_fmed3f((d - far_left) * grid_per, 0.0f, (float)(kCellThreads - 1));
+  };
+  bool one_place = false;
+  if (tid >= 1 && tid + 1 < nb) one_place = place_of(s_split[tid + 1]) <= place_of(s_split[tid]) + 1;
+  {
+    int b = 0;  // splitters in the parts before this thread's
+#pragma unroll 1
+    for (int step = kSumBuckets / 2; step >= 1; step >>= 1)
+      if (b + step < nb && part_of(s_split[b + step]) < tid) b += step;
+    s_grid[tid] = (unsigned short)b;
+    const unsigned long long singles = __ballot(one_place);
+    if ((tid & 63) == 0 && singles != 0ull) atomicAdd(&s_single, __popcll(singles));
+    __syncthreads();
+    const int here = (tid + 1 < kCellThreads ? (int)s_grid[tid + 1] : nb - 1) - b;
+    int most = here;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) most = max(most, __shfl_xor(most, d));
+    if ((tid & 63) == 0) atomicMax(&s_most, most);
+    __syncthreads();
+  }
+  const int most = uniform(s_most), n_single = uniform(s_single), steps = most > 0 ? 32 - __builtin_clz(most) : 0;
+  // cells: the outer buckets get kOuterCells each, a single place has one, the others share the rest evenly
+  int my_cells = 0;  // of bucket number `tid`
+  if (tid < nb)
+    my_cells = nb <= 2 ? kSumCells / nb : one_place ? 1 : tid == 0 || tid + 1 == nb ? kOuterCells :
+               (kSumCells - 2 * kOuterCells - n_single) / (nb - 2 - n_single);
+
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    const double step_p = uniform(step_for(s_total[0])), step_q = uniform(step_for(s_total[1]));
+    int in_all;
+    const int my_first = block_prefix(my_cells, s_redi, &in_all);
+    if (tid < nb) {
+      const float left = tid > 0 ? s_split[tid] : far_left, right = tid + 1 < nb ? s_split[tid + 1] : far_right;
+      const float per = one_place || !(right > left) ? 0.0f : (float)my_cells / (right - left);
+      s_per_left[tid] = exp2_of(-(double)left) * (step_q / step_p);
+      s_bucket[tid] = make_float4(left, per, __int_as_float(my_first), __int_as_float(__float_as_int((float)my_cells) - 1));
+    }
+    for (int c = tid; c <= kSumCells; c += kCellThreads) {
+      s_p[c] = 0ull;
+      s_q[c] = 0ull;
+      if (c < kSumCells) s_u2[c] = 0u;
+    }
+    __syncthreads();
+
+    // ---- second pass: the cells' sums, tv and the relaxed sums
+    const double rho = uniform(s_total[1] / s_total[0]);  // p relative to the target's largest mass (1 where the sides are alike)
+    const float to_u2 = uniform((float)(0x1p31 / s_total[0]));
+    double tv = 0.0, p_first = 0.0, relaxed[4] = {0.0, 0.0, 0.0, 0.0};
+    const bool first_round = round == 0, four_sizes = p.n_k > 2, want_relaxed = first_round && p.relaxed != nullptr;
+    float4 next_p = four<E>(prow, tid * 4, V, none), next_q = four<E>(qrow, tid * 4, V, none);
+    Steps stage(V);
+#pragma unroll 1
+    for (int i = tid * 4; i < V; i += kCellThreads * 4) {
+      stage.next();
+      const float4 xp4 = next_p, xq4 = next_q;
+      if (i + kCellThreads * 4 < V) {
+        next_p = four<E>(prow, i + kCellThreads * 4, V, none);
+        next_q = four<E>(qrow, i + kCellThreads * 4, V, none);
+      }
+      double ep[4], eq[4];
+      float d[4];
+      int b[4];
+      // (the four entries side by side: their look-ups are chains of reads from LDS)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float xp = at(xp4, j), xq = at(xq4, j);
+        double yp = 0.0, yq = 0.0;
+        if (PROBS) {
+          ep[j] = mp.of(xp);
+          eq[j] = mq.of(xq);
+        } else {
+          yp = mp.log2_of(xp);
+          yq = mq.log2_of(xq);
+          ep[j] = exp2_of(yp);
+          eq[j] = exp2_of(yq);
+        }
+        d[j] = distance(xp, xq, yp, yq);
+        b[j] = s_grid[part_of(fabsf(d[j]) < kSumFar ? d[j] : 0.0f)];
+      }
+#pragma unroll 1
+      for (int step = (1 << steps) >> 1; step >= 1; step >>= 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j] += s_split[b[j] + step] <= d[j] ? step : 0;
+      }
+      float4 bu[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bu[j] = s_bucket[b[j]];
+      // (all four before the first is used, not each where it is)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(bu[j].x), "+v"(bu[j].y), "+v"(bu[j].z), "+v"(bu[j].w));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (fabsf(d[j]) < kSumFar) {
+          const float t = __builtin_amdgcn_fmed3f((d[j] - bu[j].x) * bu[j].y, 0.0f, bu[j].w);
+          const int cell = (int)t + __float_as_int(bu[j].z);
+          const float u = __builtin_amdgcn_fractf(t) - 0.5f;
+          atomicAdd(&s_p[cell], whole_mass(ep[j], step_p));
+          atomicAdd(&s_q[cell], whole_mass(eq[j], step_q));
+          atomicAdd(&s_u2[cell], (uint32_t)fmaf((float)ep[j] * to_u2, u * u, 0.5f));
+        } else {
+          // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
+          // p-mass to speak of)
+          p_first += ep[j];
+        }
+      }
+      if (first_round) {
+        // (fetched here each time: there are no registers to hold them, of either kind)
+        int from = 0;
+        asm volatile("" : "+v"(from));
+        const double k[4] = {s_sizes[from], s_sizes[from + 1], s_sizes[from + 2], s_sizes[from + 3]};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double pp = ep[j] * rho;
+          tv += fabs(pp - eq[j]);
+          if (want_relaxed) {
+            if (four_sizes) add_relaxed<2>(relaxed, k, pp, eq[j]);
+            else add_relaxed<1>(relaxed, k, pp, eq[j]);
           }
         }
-        // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
-        // p-mass to speak of)
-        if (cell == kNoCell) p_first += ep;
-        packed[j >> 1] |= cell << (16 * (j & 1));
-      }
-      if (i + 3 < V) {
-        *reinterpret_cast<uint2 *>(ids + i) = make_uint2(packed[0], packed[1]);
-      } else {
-        for (int j = 0; i + j < V; ++j) ids[i + j] = (unsigned short)(packed[j >> 1] >> (16 * (j & 1)));
       }
     }
-    zp = uniform(block_sum(zp, s_red));
-    zq = uniform(block_sum(zq, s_red));
-    norm_p = zp > 0.0 ? 1.0 / zp : 0.0;
-    norm_q = zq > 0.0 ? 1.0 / zq : 0.0;
-    first = uniform(block_sum(p_first, s_red) * norm_p);
-    unit_p = 0x1p-45 * norm_p;
-    unit_q = 0x1p-45 * norm_q;
+    stage.done();
+    const LmlParams &again = params_again();
+    const double norm_p = 1.0 / s_total[0], norm_q = 1.0 / s_total[1], unit_p = 0x1p-52 * step_p * norm_p,
+                 unit_q = 0x1p-52 * step_q * norm_q;
+    bool bad = false;
+    {
+      double sums[6] = {p_first, tv, relaxed[0], relaxed[1], relaxed[2], relaxed[3]};
+      block_sums(sums, s_red);
+      p_first = uniform(sums[0]);
+      if (first_round) {
+        if (tid == 0 && again.tv != nullptr) again.tv[b_row] = 0.5 * sums[1] * norm_q;
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+          if (want_relaxed && n < again.n_k) {
+            const double r = again.kd[n] * sums[2 + n] * norm_q;
+            if (!(r >= kLeastRelaxed)) bad = true;
+            if (tid == 0) again.relaxed[b_row * again.n_k + n] = r;
+          }
+      }
+    }
+    if (bad) {  // (uniform)
+      leave();
+      return;
+    }
+    const double first = p_first * norm_p;
     {
       unsigned long long all;
 #pragma unroll
       for (int side = 0; side < 2; ++side) {
-        unsigned long long *m = side == 0 ? s_p : s_q, mine[kEach], sum = 0ull;
+        unsigned long long *m = side == 0 ? s_p : s_q, mine[kSumEach], sum = 0ull;
 #pragma unroll
-        for (int e = 0; e < kEach; ++e) { mine[e] = m[tid * kEach + e]; sum += mine[e]; }
+        for (int e = 0; e < kSumEach; ++e) { mine[e] = m[tid * kSumEach + e]; sum += mine[e]; }
         unsigned long long before = block_prefix(sum, s_redu, &all);
 #pragma unroll
-        for (int e = 0; e < kEach; ++e) { m[tid * kEach + e] = before; before += mine[e]; }
-        if (tid == kCellThreads - 1) m[kCells] = before;
+        for (int e = 0; e < kSumEach; ++e) { m[tid * kSumEach + e] = before; before += mine[e]; }
+        if (tid == kCellThreads - 1) m[kSumCells] = before;
       }
     }
     __syncthreads();
-    if (!AGAIN || round == 1) break;
-    // cells where they are wanted: a bucket's uncertainty is about the sum of t^2 w over its cells, t a cell's term and w its
-    // width, and falls with the square of their number, so the sum over all buckets is least with numbers that go with
-    // the cube root of t^2 w times the present number squared
-    float wants = 0.0f;
-    if (tid < nb) {
-      for (int c = my_first; c < my_first + my_cells; ++c) {
-        const double pc = (double)(s_p[c + 1] - s_p[c]) * unit_p, qc = (double)(s_q[c + 1] - s_q[c]) * unit_q;
-        const double base = (1.0 - (double)s_q[c] * unit_q) * pc + ((double)s_p[c] * unit_p + first) * qc;
-        const float t = pc > 0.0 && qc > 0.0 && base > 0.0 ? (float)(pc * qc * reciprocal(base)) : 0.0f;
-        if (s_high[c] > s_low[c]) wants += t * t * (distance_of(s_high[c]) - distance_of(s_low[c]));
+
+    // ---- the cells' terms, list sizes four at a time
+    // what rounding may have done to the masses before and behind a cell (four deviations of such a sum), and in all
+    const float slip = 2.0f * sqrtf((float)V), slip_p = slip * (float)unit_p, slip_q = slip * (float)unit_q;
+    const double lost_p = 0.5 * unit_p * (double)V, lost_q = 0.5 * unit_q * (double)V;
+    const double may_be_open = fmin(fmax((double)V * kSumErrorEach, kSumErrorLeast), 1.0) * kRowError;
+    bool open = false;
+    double worst = 0.0;  // the largest doubt of a result, relative to it
+#pragma unroll 1
+    for (int n0 = 0; n0 < again.n_k; n0 += 4) {
+      // per list size and without its factor K: terms as if nothing were spread, what spread takes from them, what is open
+      double whole[4] = {0.0, 0.0, 0.0, 0.0};
+      float taken[4] = {0.0f, 0.0f, 0.0f, 0.0f}, left_open[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      int c = tid * kSumEach, b = 0;  // the cell at hand and its bucket
+#pragma unroll 1
+      for (int step = kSumBuckets / 2; step >= 1; step >>= 1)
+        if (b + step < nb && __float_as_int(s_bucket[b + step].z) <= c) b += step;
+      unsigned long long here_p = s_p[c], here_q = s_q[c];
+      double sum_p = (double)here_p, sum_q = (double)here_q;  // up to the cell
+#pragma unroll 1
+      for (const int end = c + kSumEach; c < end; ++c) {
+        while (b + 1 < nb && __float_as_int(s_bucket[b + 1].z) <= c) ++b;
+        const float4 bu = s_bucket[b];
+        const unsigned long long next_p = s_p[c + 1], next_q = s_q[c + 1];
+        const double raw_p = (double)(next_p - here_p), raw_q = (double)(next_q - here_q);
+        here_p = next_p;
+        here_q = next_q;
+        const double P = raw_p * unit_p, Q = raw_q * unit_q, before = fma(sum_p, unit_p, first);
+        sum_p += raw_p;
+        sum_q += raw_q;
+        const double behind = fmax(fma(-unit_q, sum_q, 1.0), 0.0);
+        float doubt = 0.0f;
+        if (raw_p > 0.0 && raw_q > 0.0) {
+          float v = 0.0f, half_g = 0.0f, half_g_open = 0.0f, v_open = 0.0f;
+          bool wide = false;
+          const float fp = (float)P, per_p = __builtin_amdgcn_rcpf(fp);
+          if (bu.y > 0.0f) {
+            const int place = c - __float_as_int(bu.z);
+            const float w = 0.69314718f * __builtin_amdgcn_rcpf(bu.y);  // (in ln r)
+            wide = w > kWide || (b == 0 && place == 0) || (b + 1 == nb && place == (int)bu.w);  // (or an end: what lies beyond it is in it)
+            // log2 of the mean ratio less the bucket's left end, in cells: ln(1 + t) = 2 artanh(t / (2 + t)) for small t
+            const double ratio = raw_q * reciprocal(raw_p) * s_per_left[b];
+            const float t = (float)(ratio - 1.0), z = t * __builtin_amdgcn_rcpf(2.0f + t), zz = z * z;
+            const float small = z * fmaf(zz, fmaf(zz, fmaf(zz, 2.8853901f / 7.0f, 2.8853901f / 5.0f), 2.8853901f / 3.0f), 2.8853901f);
+            const float m = (t < 0.4f ? small : __builtin_amdgcn_logf((float)ratio)) * bu.y - (float)place;
+            const float u2 = (float)s_u2[c] * 0x1p-31f * per_p;
+            float var, mean = m;
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {  // the logarithm of the mean ratio is half a variance above the mean place
+              var = fminf(fmaxf(u2 - (mean - 0.5f) * (mean - 0.5f), 0.0f), 0.25f);
+              mean = fminf(fmaxf(m - 0.5f * w * var, 0.0f), 1.0f);
+            }
+            var = fminf(fmaxf(u2 - (mean - 0.5f) * (mean - 0.5f), 0.0f), mean * (1.0f - mean));
+            const float var_open = fmaf(0.02f * w, w, var);  // (and a third power more)
+            v = var * w * w;
+            v_open = 0.25f * fminf(w, 1.0f) * var_open * w * w;
+            half_g = 2.0f * var * w;
+            half_g_open = w * fmaxf(var_open, __builtin_amdgcn_sqrtf(var_open * (1.0f / 3.0f)) - 2.0f * var);
+          }
+          const double half = fma(0.5, P, before), base = fma(behind + Q, P, Q * before);
+          const float half_per_p = (float)half * per_p, slips = slip_p * __builtin_amdgcn_rcpf((float)half);
+          double den[4];
+#pragma unroll
+          for (int n = 0; n < 4; ++n) den[n] = fma(again.kd[n0 + n] - 1.0, P, base);
+          const double d01 = den[0] * den[1], d23 = den[2] * den[3], all = P * Q * reciprocal(d01 * d23);
+          const double r01 = all * d23, r23 = all * d01;
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            const double term = (n < 2 ? r01 : r23) * den[n ^ 1];  // P x
+            whole[n] += term;
+            const float xp = (float)term, xh = xp * half_per_p;    // x times P, and times P' + P / 2
+            taken[n] = fmaf(xp, fmaf(xp, half_g, xh * v * (1.0f - xh)), taken[n]);
+            const float left = wide ? xp : xp * fmaf(xp, half_g_open, v_open);
+            left_open[n] += fmaf(xp, fmaf(xh, slips, slip_q), left);
+            doubt += left * (float)again.kd[n0 + n];
+          }
+        } else if (raw_q > 0.0) {
+          // no p-mass that its sum would show: K q / (F + K - 1), where F is no less than 1 or than r times the p-mass before
+          const float most = (float)lost_p * __builtin_amdgcn_rcpf(fmaxf((float)before, 0x1p-60f));
+#pragma unroll
+          for (int n = 0; n < 4; ++n) left_open[n] += fminf((float)Q * __builtin_amdgcn_rcpf((float)again.kd[n0 + n]), most);
+        }
+        if (n0 + 4 >= again.n_k) s_u2[c] = __float_as_uint(doubt);  // (for sharing the cells out again)
       }
+      double sums[8];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        sums[n] = (whole[n] - (double)taken[n]) * again.kd[n0 + n];
+        sums[4 + n] = (double)left_open[n] * again.kd[n0 + n];
+      }
+      block_sums(sums, s_red);
+#pragma unroll
+      for (int n = 0; n < 4; ++n)
+        if (n0 + n < again.n_k) {
+          const double left = sums[4 + n] + lost_q;
+          if (!(left <= may_be_open * sums[n])) open = true;
+          worst = fmax(worst, sums[n] > 0.0 ? left / sums[n] : 1.0);
+          if (tid == 0) again.bound[b_row * again.n_k + n0 + n] = sums[n];
+        }
+    }
+    if (!open) break;  // (uniform)
+    // (a shorter row with little too much is quicker left to the other form, which looks at its entries one by one)
+    if (round == 1 || !(worst <= kShareAgain) || (V < kAgainMinV && worst <= kRowError)) {
+      leave();
+      return;
+    }
+    // cells where they are wanted: what a bucket leaves open falls with the square of the number of its cells, so the sum over all
+    // buckets is least with numbers that go with the cube root of that times the present number squared; no fewer than keep
+    // its cells narrow, up to a point
+    float wants = 0.0f;
+    int fewest = 0;
+    if (tid < nb && !one_place) {
+      const float width = (tid + 1 < nb ? s_split[tid + 1] : far_right) - (tid > 0 ? s_split[tid] : far_left);
+      fewest = min(max((int)(width * (2.0f * 0.69314718f / kWide)), kFewestCells), my_cells);
+      for (int c = my_first; c < my_first + my_cells; ++c) wants += __uint_as_float(s_u2[c]);
       if (wants > 0.0f) wants = exp2f(log2f(wants * (float)my_cells * (float)my_cells) * (1.0f / 3.0f));
     }
     const float wanted = (float)block_sum((double)wants, s_red);
-    if (tid < nb && wanted > 0.0f) my_cells = kFewestCells + (int)((float)(kCells - 1 - nb * kFewestCells) * (wants / wanted));
+    int all_fewest;
+    block_prefix(fewest, s_redi, &all_fewest);
+    if (tid < nb && !one_place && wanted > 0.0f)
+      my_cells = fewest + (int)((float)(kSumCells - 1 - n_single - all_fewest) * (wants / wanted));
   }
-  // about what the results will be, the thread's cells taken as one entry: uncertainties are measured against them
-  const int my_cell = tid * kEach;
-  const unsigned long long my_p = s_p[my_cell + kEach], my_q = s_q[my_cell];
-  double about_1 = 0.0;
+  // ---- the relaxed sums of the fifth list size on: one more pass
 #pragma unroll 1
-  for (int n0 = 0; n0 < p.n_k; n0 += 4) {
-    double about[4] = {0.0, 0.0, 0.0, 0.0};
-    const double pc = (double)(my_p - s_p[my_cell]) * unit_p, qc = (double)(s_q[my_cell + kEach] - my_q) * unit_q;
-    const double base = (1.0 - (double)my_q * unit_q) * pc + ((double)s_p[my_cell] * unit_p + first) * qc;
-    const bool shared = pc > 0.0 && qc > 0.0 && base > 0.0;
-    if (shared) add_quotients<2>(about, p, n0, pc * qc, base, 1.0, pc);
-    double sum[5] = {about[0], about[1], about[2], about[3], shared ? pc * qc * reciprocal(base) : 0.0};
-    block_sums(sum, s_red);
-    about_1 = uniform(sum[4]);
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-      if (tid == 0 && n0 + n < p.n_k) { s_about[n0 + n] = sum[n]; s_scale[n0 + n] = (float)(p.kd[n0 + n] / sum[n]); }
-  }
-  // (two sides that share next to nothing: whatever is open is resolved)
-  const bool some_shared = about_1 > 0x1p-90;
-  const float entry_error = some_shared ? kEntryError : 0.0f;
-  if (tid == 0) s_far = 0;
-  __syncthreads();
-  // in place of the places: a cell's width in ln r, and what its entries' uncertainties are weighed by (at the right
-  // end of the thread's cells)
-  {
-    int right = (int)0x80000000;
-#pragma unroll
-    for (int e = 0; e < kEach; ++e) {
-      const int low = s_low[my_cell + e], high = s_high[my_cell + e];
-      right = max(right, high);
-      s_low[my_cell + e] = __float_as_int(high > low ? distance_of(high) - distance_of(low) : 0.0f);
-    }
-    const double r_0 = (PROBS ? top_p / top_q : 1.0) * zp * norm_q;  // q / p of an entry at distance 0
-    const double before = fma((double)my_p, unit_p, first), from = fmax(1.0 - (double)my_q * unit_q, 0.0);
-    const double d = fma(before, exp_of_negative((double)distance_of(right)) * r_0, from);  // D / p_j
-    const float u = (float)reciprocal(fmin(fmax(d, 1.0), 0x1p900));
-    float weight = some_shared ? 0.0f : 1.0f;
-    for (int n = 0; some_shared && n < p.n_k; ++n) {
-      const float f = __builtin_amdgcn_rcpf(fmaf((float)p.k[n] - 1.0f, u, 1.0f));
-      weight = fmaxf(weight, s_scale[n] * f * f);
-    }
-#pragma unroll
-    for (int e = 0; e < kEach; ++e) s_high[my_cell + e] = __float_as_int(weight);
-  }
-  __syncthreads();
-
-  // ---- third pass: the terms (list sizes four at a time)
-  double tv = 0.0;
-  float doubt = 0.0f;
-#pragma unroll 1
-  for (int n0 = 0; n0 < p.n_k; n0 += 4) {
-    double sums[4] = {0.0, 0.0, 0.0, 0.0}, relaxed[4] = {0.0, 0.0, 0.0, 0.0};
-    // K pq / (base + (K - 1) pm) of one entry, base = D(r) p: numerator and denominator of K q / (D(r) + (K - 1) Q) times p
+  for (int n0 = 4; n0 < p.n_k && p.relaxed != nullptr; n0 += 4) {
+    const double rho = s_total[1] / s_total[0], norm_q = 1.0 / s_total[1];
+    double relaxed[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
     for (int i = tid * 4; i < V; i += kCellThreads * 4) {
       const float4 xp4 = four<E>(prow, i, V, none), xq4 = four<E>(qrow, i, V, none);
-      uint32_t cells[2] = {0u, 0u};
-      if (i + 3 < V) {
-        const uint2 c = *reinterpret_cast<const uint2 *>(ids + i);
-        cells[0] = c.x; cells[1] = c.y;
-      } else {
-        for (int j = 0; i + j < V; ++j) cells[j >> 1] |= (uint32_t)ids[i + j] << (16 * (j & 1));
-      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (i + j >= V) continue;
-        const double ep = relative(at(xp4, j), top_p, per_p), eq = relative(at(xq4, j), top_q, per_q);
-        double pm = ep * norm_p, qm = eq * norm_q;
-        if (n0 == 0) tv += fabs(pm - qm);
-        const uint32_t cell = (cells[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-        if (cell != kNoCell && pm >= 0x1p-150 && qm >= 0x1p-150) {
-          const unsigned long long pb = s_p[cell], qb = s_q[cell + 1];
-          // what else is in the cell
-          const double po = fmax((double)(long long)(s_p[cell + 1] - pb - fixed_mass(ep)), 0.0) * unit_p;
-          const double qo = fmax((double)(long long)(qb - s_q[cell] - fixed_mass(eq)), 0.0) * unit_q;
-          const double a = qo * pm, c = po * qm;
-          const float width = __int_as_float(s_low[cell]);
-          const double rest = fma(fmax(1.0 - (double)qb * unit_q, 0.0), pm, fma((double)pb, unit_p, first) * qm) + pm * qm;
-          double inside = fmax(a, c);
-          const double base = rest + inside;
-          // relative to the denominator: in fp32, as small as they are
-          const double inv = reciprocal(base);
-          const float cw = (float)(c * inv) * width, side = (float)((a - c) * inv), per_cw = __builtin_amdgcn_rcpf(fmaxf(cw, 1e-30f));
-          const float reach = fmaxf(fmaf(cw, width, cw) - fabsf(side), 0.0f);
-          const float gap = fminf((float)(fmin(a, c) * inv), width < 1.5f ? 0.25f * reach * reach * per_cw : 1.0f);
-          const float open = (float)(pm * qm * inv) * gap * __int_as_float(s_high[cell]);
-          if (open > entry_error) {
-            if (n0 == 0) {
-              const int pos = atomicAdd(&s_listed, 1);
-              if (pos < kListed) { s_at[pos] = i + j; s_list_cell[pos] = (int)cell; }
-            }
-          } else {
-            if (n0 == 0) doubt += open;
-            if (width < 0.5f && 2.0f * fabsf(side) < cw) {
-              const float t = 0.5f * cw + side;  // > 0
-              inside = c + (double)(0.5f * t * t * per_cw) * base;
-            }
-            add_quotients<2>(sums, p, n0, pm * qm, rest + inside, 1.0, pm);
-          }
-        }
-        if (ep > 0.0 && eq > 0.0 && p.relaxed != nullptr) {  // q / (1 + q / (K p)) = K p q / (K p + q)
-          // (where the product nears the smallest numbers, both are taken relative to the larger one: its
-          // denominators, and their product, are then at least 1/4)
-          int scale = 0;
-          if (pm * qm < 0x1p-900) {
-            scale = __builtin_amdgcn_frexp_exp(fmax(pm, qm));
-            pm = __builtin_amdgcn_ldexp(pm, -scale);
-            qm = __builtin_amdgcn_ldexp(qm, -scale);
-          }
-          const double pq = __builtin_amdgcn_ldexp(pm * qm, scale);
-          if (pq > 0.0) add_quotients<2>(relaxed, p, n0, pq, qm, 0.0, pm);
-        }
+        const double pp = mp.of(at(xp4, j)) * rho, eq = mq.of(at(xq4, j));
+        add_relaxed<2>(relaxed, p.kd + n0, pp, eq);
       }
     }
-    __syncthreads();
-    const int listed = s_listed;
-    if (listed > kListed) break;  // (uniform) the row is the sorting kernel's
-    if (listed > 0) {
-      // ---- the listed entries' cells, entry by entry: what is above each in the order, and what below
-      if (n0 == 0) {
-        if (tid < listed) {
-          s_ratio[tid] = pl.log_ratio(elem<E>(prow, s_at[tid]), elem<E>(qrow, s_at[tid]));
-          s_above[tid] = 0ull;
-          s_below[tid] = 0ull;
-          atomicOr(&s_mark[s_list_cell[tid] >> 5], 1u << (s_list_cell[tid] & 31));
-        }
-        __syncthreads();
-        for (int i = tid; i < V; i += kCellThreads) {
-          const uint32_t cell = ids[i];
-          if (cell == kNoCell || !((s_mark[cell >> 5] >> (cell & 31u)) & 1u)) continue;
-          const float xp = elem<E>(prow, i), xq = elem<E>(qrow, i);
-          const double r = pl.log_ratio(xp, xq);
-          for (int l = 0; l < listed; ++l) {
-            if (s_list_cell[l] != (int)cell || s_at[l] == i) continue;
-            if (r >= s_ratio[l])
-              atomicAdd(&s_above[l], fixed_mass(relative(xq, top_q, per_q)));
-            else
-              atomicAdd(&s_below[l], fixed_mass(relative(xp, top_p, per_p)));
-          }
-        }
-        if (tid < listed) {
-          int before = 0;
-          for (int l = 0; l < listed; ++l) before += s_at[l] < s_at[tid] ? 1 : 0;
-          s_order[before] = tid;
-        }
-        __syncthreads();
-      }
-      if (tid < listed) {  // thread t takes the t-th in the row's order
-        const int from = s_order[tid];
-        const int i = s_at[from], cell = s_list_cell[from];
-        const double pm = relative(elem<E>(prow, i), top_p, per_p) * norm_p, qm = relative(elem<E>(qrow, i), top_q, per_q) * norm_q;
-        const double behind = fmax(1.0 - (double)s_q[cell + 1] * unit_q, 0.0) + (double)s_above[from] * unit_q;
-        const double before = fma((double)s_p[cell] + (double)s_below[from], unit_p, first);
-        add_quotients<2>(sums, p, n0, pm * qm, fma(behind, pm, before * qm) + pm * qm, 1.0, pm);
-      }
-    }
-    double bound[5] = {sums[0], sums[1], sums[2], sums[3], (double)doubt};
-    block_sums(bound, s_red);
-    double others[5] = {relaxed[0], relaxed[1], relaxed[2], relaxed[3], tv};
-    block_sums(others, s_red);
-    if (tid == 0) {
+    block_sums(relaxed, s_red);
+    bool bad = false;
 #pragma unroll
-      for (int n = 0; n < 4; ++n)
-        if (n0 + n < p.n_k) {
-          // (the doubt is relative to what each result was to be about)
-          if (bound[4] * s_about[n0 + n] > kRowError * bound[n]) s_far = 1;
-          p.bound[b_row * p.n_k + n0 + n] = bound[n];
-          if (p.relaxed != nullptr) p.relaxed[b_row * p.n_k + n0 + n] = others[n];
-        }
-      if (n0 == 0 && p.tv != nullptr) p.tv[b_row] = 0.5 * others[4];
-    }
+    for (int n = 0; n < 4; ++n)
+      if (n0 + n < p.n_k) {
+        const double r = p.kd[n0 + n] * relaxed[n] * norm_q;
+        if (!(r >= kLeastRelaxed)) bad = true;
+        if (tid == 0) p.relaxed[b_row * p.n_k + n0 + n] = r;
+      }
+    if (bad) leave();
   }
-  __syncthreads();
-  if (tid == 0) *flag_of(work, V) = s_listed > kListed || (AGAIN && s_far != 0) ? 1 : s_far != 0 ? kInDoubt : 0;
 }
 
 }  // namespace
 
 hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
   LmlParams p = params;
-  const bool cells = p.V >= (p.dtype == LLC_F32 ? kCellMinV : kCellMinVNarrow) && p.V <= kCellMaxV;
+  const bool f32 = p.dtype == LLC_F32;
+  const bool cells = p.V >= (f32 ? kCellMinV : kCellMinVNarrow) && p.V <= kCellMaxV;
   p.only_flagged = cells ? 1 : 0;
+#define LLC_LML(KERNEL, ROWS)                                                                            \
+  {                                                                                                      \
+    if (f32 && p.probs) hipLaunchKernelGGL((KERNEL<float, true>), dim3(ROWS), dim3(kCellThreads), 0, s, p);        \
+    else if (f32) hipLaunchKernelGGL((KERNEL<float, false>), dim3(ROWS), dim3(kCellThreads), 0, s, p);             \
+    else if (p.probs) hipLaunchKernelGGL((KERNEL<uint16_t, true>), dim3(ROWS), dim3(kCellThreads), 0, s, p);       \
+    else hipLaunchKernelGGL((KERNEL<uint16_t, false>), dim3(ROWS), dim3(kCellThreads), 0, s, p);                   \
+    const hipError_t e = hipGetLastError();                                                              \
+    if (e != hipSuccess) return e;                                                                       \
+  }
+  // (no workspace: as many rows as a launch may have threads for)
+  constexpr long long kMostRows = 1 << 21;
+  for (p.row0 = 0; cells && p.row0 < p.B; p.row0 += kMostRows)
+    LLC_LML(lml_sum_kernel, (unsigned)(p.B - p.row0 < kMostRows ? p.B - p.row0 : kMostRows))
   for (p.row0 = 0; p.row0 < p.B; p.row0 += p.slots) {
     const long long left = p.B - p.row0;
     const unsigned grid = (unsigned)(left < (long long)p.slots ? left : (long long)p.slots);
-    const bool f32 = p.dtype == LLC_F32;
-    if (cells) {
-#define LLC_LML(E, PROBS)                                                                                               \
-  {                                                                                                                     \
-    hipLaunchKernelGGL((lml_cell_kernel<E, PROBS, false>), dim3(grid), dim3(kCellThreads), 0, s, p);                    \
-    if (p.V >= kAgainMinV) hipLaunchKernelGGL((lml_cell_kernel<E, PROBS, true>), dim3(grid), dim3(kCellThreads), 0, s, p); \
-  }
-      if (f32 && p.probs) LLC_LML(float, true)
-      else if (f32) LLC_LML(float, false)
-      else if (p.probs) LLC_LML(uint16_t, true)
-      else LLC_LML(uint16_t, false)
-#undef LLC_LML
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    // (behind the cell kernel: the rows that it left, as a rule none)
+    // (the rows that the form by sums left, as a rule none, and behind it those that this one left)
+    if (cells) LLC_LML(lml_cell_kernel, grid)
     if (f32) hipLaunchKernelGGL(lml_sort_kernel<float>, dim3(grid), dim3(kThreads), 0, s, p);
     else hipLaunchKernelGGL(lml_sort_kernel<uint16_t>, dim3(grid), dim3(kThreads), 0, s, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+#undef LLC_LML
   return hipSuccess;
 }
 
