@@ -138,6 +138,7 @@ struct ScanJob {
   bool same_race = false;   // every draft uses draft 0's race times
   bool min_first = false;   // the race times of an index are drawn through their minimum
   bool force_perk = false;  // every draft has its own row even if draft_stride_k == 0
+  int n_each = 1;           // rows, draft_stride_k apart, that each price all drafts (shared-proposal layout; with need_lse only)
   const uint8_t *bins = nullptr;  // binned candidates: mask of the draft rows (see ScanParams)
   long long bins_stride_b = 0;
   const int32_t *bin_of = nullptr;
@@ -179,7 +180,7 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   if (((uintptr_t)j.draft % esize) != 0 || ((uintptr_t)j.target % esize) != 0) return LLC_E_ALIGN;
 
   const float *temp_draft = logits ? j.temp_draft : nullptr;
-  const bool shared = j.draft_stride_k == 0 && temp_draft == nullptr && !j.force_perk;
+  const bool shared = (j.draft_stride_k == 0 || j.n_each > 1) && temp_draft == nullptr && !j.force_perk;
 
   Plan &pl = out->pl;
   pl.kt = j.k_tile != 0 ? (j.k_tile == 1 ? 2 : j.k_tile) : auto_ktile(j.K, shared, j.min_first);
@@ -190,14 +191,22 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   pl.threads = kBlock;
   int want = j.v_chunks;
   if (want == 0)  // (min-first: a staging area and a queue per wavefront, within 64 KB of LDS)
-    auto_shape(j.B * pl.n_kgroups, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, lean, &pl.threads, &want);
+    auto_shape(j.B * j.n_each * pl.n_kgroups, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, lean, &pl.threads, &want);
   plan_chunks(G, pl.threads, want, &pl.n_chunks, &pl.groups_per_chunk);
-  out->blocks = j.B * pl.n_kgroups * pl.n_chunks;
+  out->blocks = j.B * j.n_each * pl.n_kgroups * pl.n_chunks;
   // (a launch takes fewer than 2^32 threads in all)
   if (out->blocks > kMaxBlocks) return LLC_E_SHAPE;
-  out->lay = layout_for(j.B, j.K, pl.n_kgroups, pl.n_chunks);
+  out->lay = layout_for(j.B * j.n_each, j.K, pl.n_kgroups, pl.n_chunks);
   out->shared = shared;
   return LLC_OK;
+}
+
+// The same plan with no more than `chunks` of them.
+void fewer_chunks(const ScanJob &j, ScanPlan *sp, int chunks) {
+  Plan &pl = sp->pl;
+  plan_chunks((j.V + 3) / 4, pl.threads, chunks, &pl.n_chunks, &pl.groups_per_chunk);
+  sp->blocks = j.B * j.n_each * pl.n_kgroups * pl.n_chunks;
+  sp->lay = layout_for(j.B * j.n_each, j.K, pl.n_kgroups, pl.n_chunks);
 }
 
 // Where the caller's own region starts, and what the whole call needs.
@@ -278,7 +287,7 @@ int launch_scan_job(const ScanJob &j, const ScanPlan &plan, Partials *partials, 
   sp.draft_row_off = j.draft_row_off;
   sp.draft = j.draft; sp.target = j.target;
   sp.map = j.map; sp.draft_stride_k = j.draft_stride_k;
-  sp.B = j.B; sp.K = (int)j.K; sp.V = (int)j.V;
+  sp.B = j.B; sp.n_each = j.n_each; sp.K = (int)j.K; sp.V = (int)j.V;
   sp.n_chunks = pl.n_chunks; sp.groups_per_chunk = pl.groups_per_chunk; sp.n_kgroups = pl.n_kgroups;
   sp.seed_lo = (unsigned)j.seed; sp.seed_hi = (unsigned)(j.seed >> 32);
   sp.row_offset = j.row_offset;
@@ -644,6 +653,16 @@ size_t llc_verify_workspace_size(int64_t S, int64_t L, int64_t K, int64_t V) {
   return (all > one ? all : one) + verify_extra(S, B, K).total;
 }
 
+// The strong form's loop knows only at a position which row prices the dropped drafts, so that every position after the first is
+// one more scan and a step, which wait for each other: some 15 us a position.  Scanning all K rows of every position for all K drafts at
+// once instead is the generator's work K times over, but one launch, or two.  It pays while that work is less than the waiting, some 0.13 us
+// a million race times, or, drawn min-first, indices times 4 (us a call, loop and at once: 16 sequences x 5 positions x 4 drafts x 32 000 bf16
+// 102, 39; 1 x 9 x 8 x 128 256 105, 52; 64 x 5 x 4 x 32 000 126, 89; 128 x 5 x 4 x 32 000 142, 135; beyond the line 16 x 8 x 8 x 128 256 219, 209, 64 x 8 x 8 x 32 000
+// 235, 267, 128 x 8 x 8 x 128 256 689, 1508; min-first 64 x 8 x 8 x 32 000 269, 198, 128 x 8 x 8 x 128 256 748, 895).
+static bool pairs_pay(long long S, long long L, long long K, long long V, bool min_first) {
+  return (double)(S * (L + 1) * K) * (double)V * (double)(min_first ? 4 : K) <= 1.15e8 * (double)L;
+}
+
 int llc_verify(const llc_verify_args *a) {
   if (a == nullptr) return LLC_E_NULL;
   if (a->S < 0 || a->L < 0 || a->L > (1 << 20) || a->K > 64) return LLC_E_SHAPE;
@@ -711,6 +730,46 @@ int llc_verify(const llc_verify_args *a) {
   }
   if (!workspace_ok(j, plan_all)) return LLC_E_WORKSPACE;
   if (dry) return LLC_OK;
+
+  // (partial argmins are those of the one-shot scan, counters count it; a launch shape asked for is that scan's)
+  if (strong && a->L > 0 && a->K > 1 && a->stats == nullptr && a->Yk == nullptr && a->keyYk == nullptr && j.flags == 0 &&
+      a->v_chunks == 0 && a->k_tile == 0 && pairs_pay(a->S, a->L, a->K, a->V, j.min_first)) {
+    ScanJob w = j;
+    w.n_each = (int)a->K;
+    w.force_perk = false;
+    w.lse_in_extra = (size_t)-1;
+    w.extra_at = (size_t)-1;
+    ScanPlan plan;
+    const size_t n = (size_t)(B * a->K * a->K), keys = align256(n * sizeof(double)), all = keys + align256(n * sizeof(int32_t));
+    bool fits = plan_scan(w, &plan) == LLC_OK;
+    // (the workspace is sized for the loop: as many chunks as it holds)
+    while (fits && plan.lay.total + all > a->workspace_bytes) {
+      fits = plan.pl.n_chunks > 1;
+      if (fits) fewer_chunks(w, &plan, plan.pl.n_chunks - 1);
+    }
+    if (fits) {
+      char *at = (char *)a->workspace + plan.lay.total;
+      FinalizeParams fp;
+      std::memset(&fp, 0, sizeof(fp));
+      fp.B = B * a->K; fp.K = (int)a->K; fp.n_chunks = plan.pl.n_chunks; fp.n_kgroups = plan.pl.n_kgroups;
+      fp.log_kind = 1; fp.need_norm = 1;
+      fp.X = (int32_t *)(at + keys); fp.log_keyX = (double *)at;
+      w.fin = &fp;
+      Partials part;
+      bool finished = false;
+      rc = launch_scan_job(w, plan, &part, nullptr, &finished);
+      if (rc != LLC_OK) return rc;
+      fp.in = part;
+      hipStream_t st = (hipStream_t)a->stream;
+      if (!finished && launch_finalize(st, fp) != hipSuccess) return LLC_E_LAUNCH;
+      StrongParams sp;
+      sp.S = a->S; sp.L = (int)a->L; sp.K = (int)a->K;
+      sp.cand = fp.X; sp.cand_key = fp.log_keyX;
+      sp.tokens = a->tokens; sp.tok_stride_s = a->tok_stride_s; sp.tok_stride_j = a->tok_stride_j;
+      sp.Y = a->Y; sp.n_out = a->n_out; sp.active = a->active; sp.keyY = a->keyY;
+      return launch_strong(st, sp) == hipSuccess ? LLC_OK : LLC_E_LAUNCH;
+    }
+  }
 
   const Plan pl = plan_all.pl;
   char *extra = (char *)a->workspace + extra_offset(j, plan_all);

@@ -101,6 +101,7 @@ struct ScanParams {
   RowMap map;
   long long draft_stride_k;  // elements
   long long B;
+  int n_each;            // rows (draft_stride_k apart) that each price all K drafts: B x n_each rows of results; else 1
   int K, V;
   int threads;           // of a workgroup
   int finish;            // a row is one workgroup, which also takes the finalize step (fin)
@@ -197,6 +198,20 @@ struct StrongStepParams {
   llc_stats *stats;          // optional: near_ties of the emitted positions
 };
 
+// The same loop where every position's K rows have been scanned for all K drafts at once.
+struct StrongParams {
+  long long S;
+  int L, K;
+  const int32_t *cand;       // [S][L+1][K][K] argmin of draft (last) priced with a row
+  const double *cand_key;    // [S][L+1][K][K] ln of their normalised keys
+  const int32_t *tokens;
+  long long tok_stride_s, tok_stride_j;
+  int32_t *Y;                // [S][L+1]
+  int32_t *n_out;            // [S]
+  uint8_t *active;           // [S][K] optional
+  float *keyY;               // [S][L+1] optional
+};
+
 // Algorithm 1 on candidate lists: one workgroup per row, exact keys for the entries an fp32 key lets through.
 struct TopmParams {
   long long B;
@@ -262,6 +277,7 @@ hipError_t launch_finalize(hipStream_t s, const FinalizeParams &p);
 hipError_t launch_lse(hipStream_t s, const LseParams &p);
 hipError_t launch_verify(hipStream_t s, const VerifyParams &p);
 hipError_t launch_strong_step(hipStream_t s, const StrongStepParams &p);
+hipError_t launch_strong(hipStream_t s, const StrongParams &p);
 hipError_t launch_topm(hipStream_t s, const TopmParams &p);
 hipError_t launch_lml(hipStream_t s, const LmlParams &p);
 

@@ -388,6 +388,51 @@ __global__ void __launch_bounds__(64) strong_step_kernel(const StrongStepParams 
   if (!more && p.active != nullptr && lane < K) p.active[s * K + lane] = viable ? 1 : 0;
 }
 
+// The whole loop in its strong form, one wavefront per sequence, lane k holds draft k, where every row's candidates of
+// all drafts are known.  Bound by latency: a position is a trip to memory, for the row that the position before leaves, and a reduction over
+// the lanes.  (See pairs_pay in api.hip for what it replaces, and where.)
+__global__ void __launch_bounds__(64) strong_kernel(const StrongParams p) {
+  const long long s = blockIdx.x;
+  const int lane = threadIdx.x;
+  const int L = p.L, K = p.K;
+  int32_t *Y = p.Y + s * (L + 1);
+  float *keyY = p.keyY != nullptr ? p.keyY + s * (L + 1) : nullptr;
+  const bool here = lane < K;
+  bool viable = here;
+  int n = 0;
+  for (bool more = true; more; ++n) {
+    const int j = n;
+    const unsigned long long mask = __ballot(viable);
+    const int row = viable ? lane : __ffsll((long long)mask) - 1;  // a dropped draft is priced with the first viable one's row
+    const long long at = ((s * (L + 1) + j) * K + row) * K + lane;
+    const int tok = here && j < L ? p.tokens[s * p.tok_stride_s + (long long)j * p.tok_stride_j + lane] : -2;
+    const int idx = here ? p.cand[at] : -1;
+    double bkey = idx >= 0 ? p.cand_key[at] : __builtin_huge_val();
+    int bidx = idx, bk = lane;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      const double okey = __shfl_xor(bkey, d);
+      const int oidx = __shfl_xor(bidx, d), ok = __shfl_xor(bk, d);
+      if (beats(okey, oidx, ok, bkey, bidx, bk)) { bkey = okey; bidx = oidx; bk = ok; }
+    }
+    if (lane == 0) {
+      Y[j] = bidx;
+      if (keyY != nullptr) keyY[j] = bidx >= 0 ? (float)exp(bkey) : __builtin_huge_valf();
+    }
+    more = j < L;
+    if (more) {
+      viable = viable && tok == bidx;
+      more = __ballot(viable) != 0ull;
+    }
+  }
+  for (int j = n + lane; j <= L; j += 64) {
+    Y[j] = -1;
+    if (keyY != nullptr) keyY[j] = __builtin_huge_valf();
+  }
+  if (lane == 0) p.n_out[s] = n;
+  if (p.active != nullptr && here) p.active[s * K + lane] = viable ? 1 : 0;
+}
+
 }  // namespace
 
 hipError_t launch_verify(hipStream_t s, const VerifyParams &p) {
@@ -399,6 +444,12 @@ hipError_t launch_verify(hipStream_t s, const VerifyParams &p) {
 hipError_t launch_strong_step(hipStream_t s, const StrongStepParams &p) {
   if (p.S == 0) return hipSuccess;
   hipLaunchKernelGGL(strong_step_kernel, dim3((unsigned)p.S), dim3(64), 0, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_strong(hipStream_t s, const StrongParams &p) {
+  if (p.S == 0) return hipSuccess;
+  hipLaunchKernelGGL(strong_kernel, dim3((unsigned)p.S), dim3(64), 0, s, p);
   return hipGetLastError();
 }
 

@@ -641,7 +641,17 @@ scan_kernel(const ScanParams p) {
     kg = (int)(bid % (unsigned)p.n_kgroups);
     bid /= (unsigned)p.n_kgroups;
   }
+  // Every row of K prices all K drafts (the strong verification of few sequences): a place in the batch is that many rows
+  // of the results, each read for itself.
+  constexpr bool kEach = SHARED && LSE;
+  int each = 0;
+  if (kEach && p.n_each > 1) {
+    each = (int)(bid % (unsigned)p.n_each);
+    bid /= (unsigned)p.n_each;
+  }
   const long long b = (long long)bid;
+  const unsigned b_results = kEach ? bid * (unsigned)p.n_each + (unsigned)each : bid;
+  const long long b_out = (long long)b_results;  // the row of the results (a launch has fewer than 2^24 workgroups)
   // (a row's place in its tensors: b = outer * inner_count + inner, see RowMap)
   unsigned b_outer = bid, b_inner = 0;
   if (p.map.inner_count > 1) {
@@ -675,6 +685,7 @@ scan_kernel(const ScanParams p) {
 
   const elem *trow = reinterpret_cast<const elem *>(p.target) + (b_outer * p.map.target_outer + b_inner * p.map.target_inner);
   const elem *drow0 = reinterpret_cast<const elem *>(p.draft) + (b_outer * p.map.draft_outer + b_inner * p.map.draft_inner);
+  if (kEach) drow0 += each * p.draft_stride_k;
   if (p.draft_row_off != nullptr) {
     const long long off = p.draft_row_off[b];
     if (off < 0) {
@@ -1554,7 +1565,7 @@ scan_kernel(const ScanParams p) {
     if (tid <= KT && slot_used) {
       const long long slot = tid < KT ? kbase + tid : q.K;
       if (q.finish) s.share[tid] = share;
-      else q.lse_part[(b * (q.K + 1) + slot) * q.n_chunks + chunk] = share;
+      else q.lse_part[(b_out * (q.K + 1) + slot) * q.n_chunks + chunk] = share;
     }
   }
 
@@ -1570,11 +1581,11 @@ scan_kernel(const ScanParams p) {
         m.sec = unord64(s.second[min(slot, KT)]);
         m.norm = 0.0;
         if (formed) m.norm = s.share[min(slot, KT)];
-        else if (q.fin.need_norm && k <= q.K) m.norm = q.out.lse[b * (q.K + 1) + k];
+        else if (q.fin.need_norm && k <= q.K) m.norm = q.out.lse[b_out * (q.K + 1) + k];
         return m;
       };
       const Merged pool = outcome(KT, q.K, LSE && lse_target);
-      finish_row(q.fin, b, tid, 1, pool, [&](const int k) { return outcome(k < q.K ? k : KT + 1, k, LSE && k < q.K); });
+      finish_row(q.fin, b_out, tid, 1, pool, [&](const int k) { return outcome(k < q.K ? k : KT + 1, k, LSE && k < q.K); });
     }
   } else if (tid <= KT) {
     const bool has = s.where[tid] != ~0ull;
@@ -1583,13 +1594,13 @@ scan_kernel(const ScanParams p) {
     if (tid < KT) {
       const int k = kbase + tid;
       if (k < q.K) {
-        const long long o = (b * q.K + k) * q.n_chunks + chunk;
+        const long long o = (b_out * q.K + k) * q.n_chunks + chunk;
         q.out.keyX[o] = key;
         q.out.idxX[o] = idx;
         q.out.secX[o] = unord64(s.second[tid]);
       }
     } else {
-      const long long o = (b * q.n_kgroups + kg) * q.n_chunks + chunk;
+      const long long o = (b_out * q.n_kgroups + kg) * q.n_chunks + chunk;
       q.out.keyY[o] = key;
       q.out.idxY[o] = idx;
       q.out.kY[o] = has ? (int)(uint32_t)s.where[tid] : -1;
