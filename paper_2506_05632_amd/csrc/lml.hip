@@ -1093,6 +1093,7 @@ constexpr float kBeyond = 6.0f;       // how far the outer buckets reach beyond 
 // (some 8e-13 an entry; Zipf-like rows a tenth of that or less).  More is no matter of chance but of a crowd in few cells.
 constexpr double kSumErrorLeast = 0.5, kSumErrorEach = 0x1p-17;
 constexpr double kShareAgain = 0x1p-18;  // what sharing the cells out again can mend
+constexpr float kLaneStep = 0x1p40f;  // (a distance is a multiple of 2^-36)
 constexpr float kWide = 0.5f;         // a cell this wide in ln r leaves its entries' whole terms open
 
 // 2^y for y <= 0 or so (what is below -1074 comes out as 0, NaN too) to about an ulp: y = n + f, |f| <= 1/2, and 2^f = 1 + f P(f)
@@ -1232,8 +1233,8 @@ __device__ __forceinline__ const LmlParams &params_again() {
 // What bounds it: issue in fp64.  The row is read twice and nothing is written.  Two exponentials an entry and pass (15 instructions each), of some 45 in the
 // first pass and 110 in the second; of a row of 128 256 (220 us, four a CU in turn) those take 53 and 112 us, the sample and its order 17, the
 // cells 14, sums over the workgroup and their barriers the rest.  us a call, four list sizes, entries' terms taken one by one (lml_cell_kernel for
-// every row) and now: 1024 x 128 256 2135, 870; 512 x 152 064 bf16 1394, 720; 1024 x 32 000, two sizes, 645, 354; 256 x 50 257 bf16, one size, 272,
-// 152; one row of 128 256 423, 175; 64 x 8192 71, 56; 256 x 128 256, one side flat and the other normal times 3, 1187, 336, target masked by -10^9 but
+// every row) and now: 1024 x 128 256 2135, 870; 512 x 152 064 bf16 1394, 534; 1024 x 32 000, two sizes, 645, 354; 256 x 50 257 bf16, one size, 272,
+// 127; one row of 128 256 423, 175; 64 x 8192 71, 56; 256 x 128 256, one side flat and the other normal times 3, 1187, 336, target masked by -10^9 but
 // for 50 297, 229, eight sizes 790, 319.  Rows whose two sides share next to nothing pay for an attempt in vain (256 x 128 256, bound 10^-4: 526, 885).
 // The bound's error against 64 bits, same inputs: 1.1e-10, 3e-11; T = 1: 3.3e-10, 1.5e-10; 152 064 bf16: 7e-12, 7e-13.
 template <typename E, bool PROBS>
@@ -1249,10 +1250,10 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   __shared__ int s_redi[kCellThreads / 64];
   __shared__ double s_total[2];                // the sides' masses, relative to their largest
   __shared__ double s_sizes[4];
-  __shared__ int s_single, s_most;             // buckets of a single place; splitters in one part of the range, at most
+  __shared__ int s_single, s_shared, s_most;   // buckets of a single place, and of one with several cells; splitters in one part of the range, at most
   int *s_sample = reinterpret_cast<int *>(s_p);  // (before the cells)
   static_assert(kCellMinV >= 4 * kCellThreads && kCellMinVNarrow >= 4 * kCellThreads, "every thread has four entries");
-  static_assert(kSumBuckets * (kFewestCells + 1) + 2 * kOuterCells < kSumCells, "too few cells");
+  static_assert(kSumBuckets * (kFewestCells + 1) + 2 * kOuterCells + kSumCells / 14 < kSumCells, "too few cells");
 
   const int tid = threadIdx.x;
   const long long b_row = p.row0 + blockIdx.x;
@@ -1477,6 +1478,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
       // `many` equal places or more are two splitters (the place is a bucket), and so is a heavy entry's; others
       // are one, if a quantile falls into them.  As many of them as there are buckets; heavy ones go last
       int emit[kPer], total, before = 0;
+      bool tied[kPer];
 #pragma unroll 1
       for (int many = 4; many <= 2 * kMany; many *= 2) {
         int mine = 0;
@@ -1484,10 +1486,12 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
         for (int e = 0; e < kPer; ++e) {
           const int j = tid * kPer + e, v = s_sample[j] >> 1, run = min(many, kMany);
           emit[e] = 0;
+          tied[e] = false;
           if (j < n_valid && (j == 0 || (s_sample[j - 1] >> 1) != v)) {
             int last = j;
             while (last + 1 < n_valid && last + 1 < j + run && (s_sample[last + 1] >> 1) == v) ++last;
-            if (last + 1 == j + run || (many <= kMany && (s_sample[last] & 1) != 0)) emit[e] = 2;
+            tied[e] = last + 1 == j + run;
+            if (tied[e] || (many <= kMany && (s_sample[last] & 1) != 0)) emit[e] = 2;
             else if (j > 0 && (unsigned)(last * want) / (unsigned)n_valid != (unsigned)((j - 1) * want) / (unsigned)n_valid) emit[e] = 1;
           }
           mine += emit[e];
@@ -1500,14 +1504,17 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
       for (int e = 0; e < kPer; ++e) {
         const int v = long_place(s_sample[tid * kPer + e] >> 1);
         for (int c = 0; c < emit[e]; ++c, ++before)
-          if (1 + before < nb) s_split[1 + before] = distance_of(v + c);
+          if (1 + before < nb) {
+            s_split[1 + before] = distance_of(v + c);
+            s_per_left[1 + before] = tied[e] && c == 0 ? 1.0 : 0.0;  // (on its way to the bucket's thread)
+          }
       }
       far_left = uniform(distance_of(long_place(s_sample[0] >> 1)) - kBeyond);
       far_right = uniform(distance_of(long_place(s_sample[n_valid - 1] >> 1)) + kBeyond);
     }
   }
   nb = uniform(nb);
-  if (tid == 0) { s_single = 0; s_most = 0; }
+  if (tid == 0) { s_single = 0; s_shared = 0; s_most = 0; s_per_left[0] = 0.0; }
   for (int b = tid; b < 2 * kSumBuckets; b += kCellThreads)
     if (b == 0 || b >= nb) s_split[b] = b == 0 ? ninf : pinf;
   __syncthreads();
@@ -1516,16 +1523,22 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   auto part_of = [&](const float d) {
     return (int)__builtin_amdgcn_fmed3f((d - far_left) * grid_per, 0.0f, (float)(kCellThreads - 1));
   };
-  bool one_place = false;
-  if (tid >= 1 && tid + 1 < nb) one_place = place_of(s_split[tid + 1]) <= place_of(s_split[tid]) + 1;
+  bool one_place = false, shared_place = false;
+  if (tid >= 1 && tid + 1 < nb) {
+    one_place = place_of(s_split[tid + 1]) <= place_of(s_split[tid]) + 1;
+    shared_place = one_place && s_per_left[tid] != 0.0;
+  }
   {
     int b = 0;  // splitters in the parts before this thread's
 #pragma unroll 1
     for (int step = kSumBuckets / 2; step >= 1; step >>= 1)
       if (b + step < nb && part_of(s_split[b + step]) < tid) b += step;
     s_grid[tid] = (unsigned short)b;
-    const unsigned long long singles = __ballot(one_place);
-    if ((tid & 63) == 0 && singles != 0ull) atomicAdd(&s_single, __popcll(singles));
+    const unsigned long long singles = __ballot(one_place), shared = __ballot(shared_place);
+    if ((tid & 63) == 0 && singles != 0ull) {
+      atomicAdd(&s_single, __popcll(singles));
+      atomicAdd(&s_shared, __popcll(shared));
+    }
     __syncthreads();
     const int here = (tid + 1 < kCellThreads ? (int)s_grid[tid + 1] : nb - 1) - b;
     int most = here;
@@ -1534,12 +1547,18 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
     if ((tid & 63) == 0) atomicMax(&s_most, most);
     __syncthreads();
   }
-  const int most = uniform(s_most), n_single = uniform(s_single), steps = most > 0 ? 32 - __builtin_clz(most) : 0;
-  // cells: the outer buckets get kOuterCells each, a single place has one, the others share the rest evenly
+  const int most = uniform(s_most), n_single = uniform(s_single), n_shared = uniform(s_shared), steps = most > 0 ? 32 - __builtin_clz(most) : 0;
+  // cells: the outer buckets get kOuterCells each, a single place has one, the others share the rest evenly.  A place that the
+  // sample holds often has as many as there is room for, which its entries take by their lane: additions to one address wait for each
+  // other (512 x 152 064 bf16, whose bulk has some fifty ratios, 736 us with one cell a place, 534; 512 x 128 256 bf16, T = 0.7, 634, 467)
+  int copies = 8;
+  while (n_shared * copies > kSumCells / 14) copies >>= 1;
+  copies = max(copies, 1);
+  const int single_cells = n_single + n_shared * (copies - 1);
   int my_cells = 0;  // of bucket number `tid`
   if (tid < nb)
-    my_cells = nb <= 2 ? kSumCells / nb : one_place ? 1 : tid == 0 || tid + 1 == nb ? kOuterCells :
-               (kSumCells - 2 * kOuterCells - n_single) / (nb - 2 - n_single);
+    my_cells = nb <= 2 ? kSumCells / nb : one_place ? (shared_place ? copies : 1) : tid == 0 || tid + 1 == nb ? kOuterCells :
+               (kSumCells - 2 * kOuterCells - single_cells) / (nb - 2 - n_single);
 
 #pragma unroll 1
   for (int round = 0;; ++round) {
@@ -1548,7 +1567,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
     const int my_first = block_prefix(my_cells, s_redi, &in_all);
     if (tid < nb) {
       const float left = tid > 0 ? s_split[tid] : far_left, right = tid + 1 < nb ? s_split[tid + 1] : far_right;
-      const float per = one_place || !(right > left) ? 0.0f : (float)my_cells / (right - left);
+      const float per = one_place ? -kLaneStep : right > left ? (float)my_cells / (right - left) : 0.0f;
       s_per_left[tid] = exp2_of(-(double)left) * (step_q / step_p);
       s_bucket[tid] = make_float4(left, per, __int_as_float(my_first), __int_as_float(__float_as_int((float)my_cells) - 1));
     }
@@ -1563,6 +1582,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
     const double rho = uniform(s_total[1] / s_total[0]);  // p relative to the target's largest mass (1 where the sides are alike)
     const float to_u2 = uniform((float)(0x1p31 / s_total[0]));
     double tv = 0.0, p_first = 0.0, relaxed[4] = {0.0, 0.0, 0.0, 0.0};
+    const float lane_step = (float)(tid & (copies - 1)) * (1.0f / kLaneStep);  // (nothing to a distance, a cell where a place has several)
     const bool first_round = round == 0, four_sizes = p.n_k > 2, want_relaxed = first_round && p.relaxed != nullptr;
     float4 next_p = four<E>(prow, tid * 4, V, none), next_q = four<E>(qrow, tid * 4, V, none);
     Steps stage(V);
@@ -1608,7 +1628,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (fabsf(d[j]) < kSumFar) {
-          const float t = __builtin_amdgcn_fmed3f((d[j] - bu[j].x) * bu[j].y, 0.0f, bu[j].w);
+          const float t = __builtin_amdgcn_fmed3f(((d[j] - bu[j].x) - lane_step) * bu[j].y, 0.0f, bu[j].w);
           const int cell = (int)t + __float_as_int(bu[j].z);
           const float u = __builtin_amdgcn_fractf(t) - 0.5f;
           atomicAdd(&s_p[cell], whole_mass(ep[j], step_p));
@@ -1796,7 +1816,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
     int all_fewest;
     block_prefix(fewest, s_redi, &all_fewest);
     if (tid < nb && !one_place && wanted > 0.0f)
-      my_cells = fewest + (int)((float)(kSumCells - 1 - n_single - all_fewest) * (wants / wanted));
+      my_cells = fewest + (int)((float)(kSumCells - 1 - single_cells - all_fewest) * (wants / wanted));
   }
   // ---- the relaxed sums of the fifth list size on: one more pass
 #pragma unroll 1

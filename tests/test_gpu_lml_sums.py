@@ -100,3 +100,18 @@ def test_cells_are_shared_out_again(V, kind):
     for draft, target in ((wide, flat), (flat, wide)):
         ws = _check(draft, target, [1, 8], kind)
         assert _left_to_sorting(ws, 4, V) == []
+
+
+@pytest.mark.parametrize("ratios", [1, 5, 40, 130, 300])
+@pytest.mark.parametrize("V", [8192, 40001])
+def test_ratios_shared_by_many_entries(ratios, V):
+    # whole cells of one ratio, which have one cell each or up to eight (sums are exact but for the masses' rounding), beside
+    # entries spread between them
+    g = torch.Generator(device=DEV).manual_seed(ratios)
+    tq = torch.randn(3, V, generator=g, device=DEV)
+    td = tq + 0.125 * torch.randint(-ratios // 2, ratios - ratios // 2, (3, V), generator=g, device=DEV)
+    td[1, ::3] += 0.01 * torch.randn(td[1, ::3].numel(), generator=g, device=DEV)
+    td[2, :40] = tq[2, :40] + 3.0   # heavy ones among them
+    tq[2, :40] += 8.0
+    _check(td, tq, [1, 4])
+    _check(td.bfloat16(), tq.bfloat16(), [1, 4])
