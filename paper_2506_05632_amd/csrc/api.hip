@@ -49,7 +49,7 @@ void plan_chunks(long long G, int threads, int want, int *n_chunks, int *groups_
 // keys 95 -> 73; 512 x 128 256, K = 8, min-first, with keys 127 -> 114; 64 x 128 256 60 -> 37;
 // 1 x 128 256 32 -> 26; 4 x 32 000 29 -> 21.  From 513 rows on a workgroup of 256 is the better one
 // (700 rows: 163 against 185 with 512 threads; 1024: 218 against 220, 242 with 1024).
-void auto_shape(long long rows, long long G, int most_threads, bool lean, int *threads, int *chunks) {
+void auto_shape(long long rows, long long G, int most_threads, bool lean, bool fine, int *threads, int *chunks) {
   // (the others run one workgroup of 512 per CU)
   const long long room = lean ? 1LL << 18 : 1LL << 17;
   *threads = kBlock;
@@ -58,10 +58,28 @@ void auto_shape(long long rows, long long G, int most_threads, bool lean, int *t
   // (two tiles a chunk up to eight chunks, four beyond: more chunks also make the finalize launch longer;
   // 16 rows x 128 256, min-first with keys: 36 us with 8 to 16 chunks, 45 with 31)
   const long long tiles = (G + *threads - 1) / *threads;
-  const long long most = tiles / 2 < 8 ? tiles / 2 : tiles / 4 < 8 ? 8 : tiles / 4;
+  // (`fine`: an odd tile is a chunk of its own rather than a third one everywhere, from five tiles on)
+  const long long half = fine && tiles >= 5 ? (tiles + 1) / 2 : tiles / 2;
+  const long long most = half < 8 ? half : tiles / 4 < 8 ? 8 : tiles / 4;
   if (c > most) c = most;
   if (c < 1) c = 1;
   *chunks = (int)(c > kMaxChunks ? kMaxChunks : c);
+}
+
+// A better shape for few rows, where the time is the latency of a workgroup's phases: those of 512 threads, at most one to
+// a CU, with a tile each as far as 16 to a row go (a wavefront then shares its SIMD with one other).  For at most four drafts a pass, drawn
+// one word at a time and without normalisers: the others' phases are longer and do not pay for being more (K = 8, or with keys: 0.9 to 1.1).
+// A pool needs rows of a dozen tiles to pay.  us a call, before and now: 4 x 32 000, K = 4, bf16 17.0, 15.0; 1 x 50 257 17.3, 15.8; 16 x 24 000
+// 17.6, 15.9; drafts alone, own rows, 16 x 32 000 16.9, 13.8; 6 x 12 000 15.7, 13.3; 16 x 80 000 18.4, 16.4.
+void fine_shape(long long rows, long long G, bool with_pool, int *threads, int *chunks) {
+  constexpr int kThreads = 512, kCus = 256, kMost = 16;
+  const long long tiles = (G + kThreads - 1) / kThreads;
+  long long c = rows > 0 ? kCus / rows : 0;
+  if (c > kMost) c = kMost;
+  if (c > tiles) c = tiles;
+  if (c < 3 || c < (tiles < 8 ? tiles : 8) || (with_pool && tiles < 12)) return;
+  *threads = kThreads;
+  *chunks = (int)c;
 }
 
 struct Layout {
@@ -189,14 +207,22 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   const bool masked = j.bins != nullptr || j.no_draft || j.same_race;
   const bool lean = lean_variant(shared, pl.kt / 2, j.need_lse && j.kind != LLC_PROBS && !masked);
   pl.threads = kBlock;
+  const long long rows = j.B * j.n_each * pl.n_kgroups;
   int want = j.v_chunks;
-  if (want == 0)  // (min-first: a staging area and a queue per wavefront, within 64 KB of LDS)
-    auto_shape(j.B * j.n_each * pl.n_kgroups, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, lean, &pl.threads, &want);
-  plan_chunks(G, pl.threads, want, &pl.n_chunks, &pl.groups_per_chunk);
-  out->blocks = j.B * j.n_each * pl.n_kgroups * pl.n_chunks;
-  // (a launch takes fewer than 2^32 threads in all)
-  if (out->blocks > kMaxBlocks) return LLC_E_SHAPE;
-  out->lay = layout_for(j.B * j.n_each, j.K, pl.n_kgroups, pl.n_chunks);
+  bool fine = want == 0;
+  if (fine && lean && pl.kt <= 4 && !j.min_first && !masked && !(j.need_lse && j.kind != LLC_PROBS))
+    fine_shape(rows, G, !j.no_pool, &pl.threads, &want);
+  for (;; fine = false, want = 0) {
+    if (want == 0)  // (min-first: a staging area and a queue per wavefront, within 64 KB of LDS)
+      auto_shape(rows, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, lean, fine, &pl.threads, &want);
+    plan_chunks(G, pl.threads, want, &pl.n_chunks, &pl.groups_per_chunk);
+    out->blocks = rows * pl.n_chunks;
+    // (a launch takes fewer than 2^32 threads in all)
+    if (out->blocks > kMaxBlocks) return LLC_E_SHAPE;
+    out->lay = layout_for(j.B * j.n_each, j.K, pl.n_kgroups, pl.n_chunks);
+    // (more chunks need more workspace: one that holds the other shape only gets that)
+    if (!fine || out->lay.total + j.extra_bytes <= j.workspace_bytes) break;
+  }
   out->shared = shared;
   return LLC_OK;
 }
@@ -435,7 +461,7 @@ size_t llc_couple_workspace_size(int64_t B, int64_t K, int64_t V) {
   // worst case over k_tile (one draft per group) and over v_chunks up to the planned floor
   const long long G = (V + 3) / 4;
   int nc, gpc, threads, want;
-  auto_shape(B, G, kMaxThreads / 2, true, &threads, &want);
+  auto_shape(B, G, kMaxThreads / 2, true, false, &threads, &want);
   if (want < kPlannedChunkFloor) want = kPlannedChunkFloor;
   plan_chunks(G, kBlock, want, &nc, &gpc);
   return layout_for(B, K, K, nc).total + 256;
@@ -721,11 +747,12 @@ int llc_verify(const llc_verify_args *a) {
     q.need_lse = false;                   // the rows' normalisers are known from the one-shot scan
     q.lse_in_extra = (size_t)-1;
     q.stats = nullptr; q.ev_begin = nullptr; q.ev_end = nullptr;
-    q.extra_bytes = 0;
+    q.extra_bytes = ex.total;  // (what has to fit behind it)
     q.draft = (const char *)a->target + (size_t)a->stride_j * esize;  // position 1 stands for all
     q.target = q.draft;
     rc = plan_scan(q, &plan_one);
     if (rc != LLC_OK) return rc;
+    q.extra_bytes = 0;
     if (plan_one.lay.total > plan_all.lay.total) j.extra_at = plan_one.lay.total;
   }
   if (!workspace_ok(j, plan_all)) return LLC_E_WORKSPACE;
