@@ -1102,8 +1102,7 @@ __device__ __forceinline__ double exp2_of(double y) {
   asm("v_max_f64 %0, %1, %2" : "=v"(y) : "v"(y), "s"(-1100.0));  // (fmax() takes one instruction more, to quiet a NaN that cannot be)
   const double t = y + 0x1.8p52;        // (n in the lower half)
   const double f = y - (t - 0x1.8p52);
-  double s = 0x1.c062ee76e864cp-32;
-  s = fma(s, f, 0x1.e605f90accdcbp-28);
+  double s = fma(0x1.c062ee76e864cp-32, f, 0x1.e605f90accdcbp-28);
   s = fma(s, f, 0x1.b54167f262812p-24);
   s = fma(s, f, 0x1.62bfd49f13823p-20);
   s = fma(s, f, 0x1.ffcbee3aee4b9p-17);
@@ -1120,7 +1119,8 @@ __device__ __forceinline__ double exp2_of(double y) {
 // A mass relative to its row's largest as a whole number of `step` 2^-52ths, a power of two and no less than the mass.
 __device__ __forceinline__ unsigned long long whole_mass(double e, double step) {
   const unsigned long long sum = (unsigned long long)__double_as_longlong(e + step);
-  const uint32_t hi = (uint32_t)(sum >> 32) - (uint32_t)((unsigned long long)__double_as_longlong(step) >> 32);  // (the lower half of `step` is 0)
+  uint32_t hi = (uint32_t)(sum >> 32);  // (the lower half of `step` is 0; written as a difference it becomes one of 64 bits again)
+  asm("v_subrev_u32 %0, %1, %0" : "+v"(hi) : "s"((uint32_t)((unsigned long long)__double_as_longlong(step) >> 32)));
   return ((unsigned long long)hi << 32) | (uint32_t)sum;
 }
 // ... the least for masses that sum to z, which must stay below 2^63 (values of few bits are rounded alike, so that it is not chance
@@ -1231,10 +1231,10 @@ __device__ __forceinline__ const LmlParams &params_again() {
 // masses may count, are marked (a NaN in the place of their first result) and left to lml_cell_kernel, behind this one.
 // tv and the relaxed sums are taken in 64 bits, entry by entry, in the pass that makes the cells.
 // What bounds it: issue in fp64.  The row is read twice and nothing is written.  Two exponentials an entry and pass (15 instructions each), of some 45 in the
-// first pass and 110 in the second; of a row of 128 256 (220 us, four a CU in turn) those take 53 and 112 us, the sample and its order 17, the
+// first pass and 110 in the second; of a row of 128 256 (220 us, four a CU in turn) those take 53 and 108 us, the sample and its order 17, the
 // cells 14, sums over the workgroup and their barriers the rest.  us a call, four list sizes, entries' terms taken one by one (lml_cell_kernel for
-// every row) and now: 1024 x 128 256 2135, 870; 512 x 152 064 bf16 1394, 534; 1024 x 32 000, two sizes, 645, 354; 256 x 50 257 bf16, one size, 272,
-// 127; one row of 128 256 423, 175; 64 x 8192 71, 56; 256 x 128 256, one side flat and the other normal times 3, 1187, 336, target masked by -10^9 but
+// every row) and now: 1024 x 128 256 2135, 875; 512 x 152 064 bf16 1394, 507; 1024 x 32 000, two sizes, 645, 366; 256 x 50 257 bf16, one size, 272,
+// 115; one row of 128 256 423, 170; 64 x 8192 71, 56; 256 x 128 256, one side flat and the other normal times 3, 1187, 336, target masked by -10^9 but
 // for 50 297, 229, eight sizes 790, 319.  Rows whose two sides share next to nothing pay for an attempt in vain (256 x 128 256, bound 10^-4: 526, 885).
 // The bound's error against 64 bits, same inputs: 1.1e-10, 3e-11; T = 1: 3.3e-10, 1.5e-10; 152 064 bf16: 7e-12, 7e-13.
 template <typename E, bool PROBS>
@@ -1550,7 +1550,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   const int most = uniform(s_most), n_single = uniform(s_single), n_shared = uniform(s_shared), steps = most > 0 ? 32 - __builtin_clz(most) : 0;
   // cells: the outer buckets get kOuterCells each, a single place has one, the others share the rest evenly.  A place that the
   // sample holds often has as many as there is room for, which its entries take by their lane: additions to one address wait for each
-  // other (512 x 152 064 bf16, whose bulk has some fifty ratios, 736 us with one cell a place, 534; 512 x 128 256 bf16, T = 0.7, 634, 467)
+  // other (512 x 152 064 bf16, whose bulk has some fifty ratios, 736 us with one cell a place, 518; 512 x 128 256 bf16, T = 0.7, 634, 467)
   int copies = 8;
   while (n_shared * copies > kSumCells / 14) copies >>= 1;
   copies = max(copies, 1);
@@ -1647,12 +1647,15 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
         const double k[4] = {s_sizes[from], s_sizes[from + 1], s_sizes[from + 2], s_sizes[from + 3]};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const double pp = ep[j] * rho;
-          tv += fabs(pp - eq[j]);
-          if (want_relaxed) {
-            if (four_sizes) add_relaxed<2>(relaxed, k, pp, eq[j]);
-            else add_relaxed<1>(relaxed, k, pp, eq[j]);
-          }
+          ep[j] *= rho;
+          tv += fabs(ep[j] - eq[j]);
+        }
+        if (want_relaxed && four_sizes) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) add_relaxed<2>(relaxed, k, ep[j], eq[j]);
+        } else if (want_relaxed) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) add_relaxed<1>(relaxed, k, ep[j], eq[j]);
         }
       }
     }
