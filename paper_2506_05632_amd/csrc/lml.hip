@@ -7,7 +7,7 @@
 //   sum_j K / sum_i ( max{q_i/q_j, p_i/p_j} + (K - 1) q_i/q_j ).
 // max{q_i/q_j, p_i/p_j} is q_i/q_j exactly when q_i/p_i >= q_j/p_j, so with the indices sorted by
 // r = q/p the inner sum is (the q-mass from j on)/q_j + (the p-mass before j)/p_j + (K-1) Q/q_j:
-// an order by r and running sums per row.  One workgroup does a whole row.  Three forms:
+// an order by r and running sums per row.  One workgroup does a whole row.  Four forms:
 //
 //  by cells' sums (rows of 6144 to 2.6 10^5 entries, bf16 from 8192 on): nothing is ordered or moved.  ln r is divided into some
 //  7000 cells, finely where a sample of the row has many entries or much mass; one pass adds up the masses of every cell's entries
@@ -15,9 +15,10 @@
 //  for what the order inside it is worth, which is bounded.
 //  by cells (a row whose cells leave too much open in all): a second pass takes the terms one by one, and entries for which the order in
 //  their cell matters are resolved exactly (see lml_cell_kernel).
-//  by sorting (other rows, and a row that the cells do not resolve either, also when they are shared out again): four passes of a
-//  stable 8-bit radix sort on the fp32 image of ln r, in which the two masses, rounded to fp32, travel with their
-//  key through two buffers in the workspace.
+//  by sorting in LDS (shorter rows): four passes of a stable 8-bit radix sort on the fp32 image of ln r; masses rounded to fp32
+//  (see lml_short_kernel).
+//  by sorting (longer rows, and a row that the cells do not resolve either, also when they are shared out again): the same, the
+//  masses travelling with their key through two buffers in the workspace.
 //
 // Indices whose r agree to fp32 precision may come out in either order, which together with the sorted masses' rounding
 // moves a result by a relative 2^-22 at most, and so does what the cells leave open (1024 rows of 128 256 come out
@@ -459,8 +460,9 @@ __global__ void __launch_bounds__(kThreads) lml_sort_kernel(const LmlParams p) {
 
 // ---- the form by cells
 
-// The rows that go by cells.  Shorter ones are sorted (us a call of four list sizes, cells' sums against sorting, 1, 64, 256 and 512 rows: fp32
-// 6144 entries 51 : 83, 53 : 86, 58 : 97, 108 : 140; bf16 8192: 52 : 96, 59 : 99, 63 : 112, 120 : 158; sorting 4096 fp32 entries takes 57, 58, 62, 89).
+// The rows that go by cells.  Shorter ones are sorted, in LDS.  Where the line lies that is the faster way still (us a call of four list sizes, cells'
+// sums against it, 1, 64 and 512 rows: fp32 6000 entries 51 : 40, 53 : 42, 108 : 82; bf16 8191: 52 : 48, 59 : 48, 120 : 97), but
+// it rounds masses to fp32: a result is some 5e-9 off, by sums 3e-11, and longer rows keep that.
 // Rows in doubt get a second attempt after the first from kAgainMinV entries on: what cells leave open grows with the
 // entries that share one.  (Of twenty families of rows none had more than half of what is allowed at 50 257 entries, several more than
 // all of it from 152 064 on.)
@@ -1848,12 +1850,269 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   }
 }
 
+// ---- rows that fit into LDS, sorted there
+
+constexpr int kShortThreads = 1024, kShortWaves = kShortThreads / 64;
+constexpr int kCountRow = 260;  // a wavefront's 256 counters and some: four wavefronts' counters of a digit lie in different banks
+
+// Rows too short for the forms by cells, up to ROUNDS * 1024 entries, one workgroup each; a thread holds an entry of every 1024.  The
+// same sort as lml_sort_kernel's, but nothing passes through memory: an entry is its key and its index, eight bytes that go
+// from LDS to registers and back in each of the four passes, and the masses stay where they are.
+// What bounds it: issue (some 60 instructions an entry and pass to find the lanes with its digit, an exponential and side) and, in the
+// shortest rows, the chain of four passes with four barriers each.  Two workgroups of up to 4 rounds fit on a CU (64 registers, 75 KB).
+// us a call of four list sizes, through memory (lml_sort_kernel, 512 threads) and here, 1, 64, 512 and 4096 rows: fp32 1000 entries 33, 34, 47, 371 and
+// 16, 16, 26, 161; 2000: 39, 40, 58, 456 and 20, 21, 34, 220; 4096: 56, 57, 90, 708 and 29, 30, 50, 338; 6000: 83, 85, 140, 1121 and
+// 40, 42, 82, 634; bf16 8191: 96, 100, 158, 1261 and 48, 48, 97, 780.  Errors against 64 bits are the same.
+template <typename E, int ROUNDS>
+__global__ void __launch_bounds__(kShortThreads, ROUNDS <= 4 ? 8 : 4) lml_short_kernel(const LmlParams p) {
+  constexpr int kEntries = ROUNDS * kShortThreads;
+  __shared__ unsigned long long s_row[kEntries];  // key, index
+  __shared__ float2 s_mass[kEntries];
+  __shared__ unsigned short s_cnt[kShortWaves][kCountRow];  // per wavefront and digit: counts, then starts
+  __shared__ double s_out[2 * kLmlMaxK + 1][kShortWaves];   // bounds, relaxed sums, tv: the wavefronts' shares
+  __shared__ double s_red[2 * kShortWaves], s_seg[2][kShortWaves];
+  __shared__ float s_top[2][kShortWaves];
+  __shared__ int s_tot[kShortWaves];
+  static_assert(kShortWaves == 16, "a lane of sixteen for every wavefront");
+
+  const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
+  const long long b = p.row0 + blockIdx.x;
+  const int V = p.V, rounds = (V + kShortThreads - 1) / kShortThreads;
+  const float finf = __builtin_huge_valf();
+  const double ninf = -__builtin_huge_val();
+  float x[ROUNDS], y[ROUNDS];
+  {
+    const E *prow = reinterpret_cast<const E *>(p.draft) + b * p.draft_stride_b;
+    const E *qrow = reinterpret_cast<const E *>(p.target) + b * p.target_stride_b;
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e) {
+      const int i = e * kShortThreads + tid;  // (behind the row: no mass)
+      x[e] = i < V ? elem<E>(prow, i) : __builtin_nanf("");
+      y[e] = i < V ? elem<E>(qrow, i) : __builtin_nanf("");
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s_cnt[wv][q * 64 + lane] = 0;
+
+  // ---- the two sides' largest finite values and masses
+  Side sp, sq;
+  sp.probs = sq.probs = p.probs;
+  sp.inv_t = 1.0 / (double)p.temp_draft;
+  sq.inv_t = 1.0 / (double)p.temp_target;
+  sp.m = sq.m = ninf;
+  if (!p.probs) {
+    float top_p = -finf, top_q = -finf;
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e) {
+      if (x[e] < finf) top_p = fmaxf(top_p, x[e]);
+      if (y[e] < finf) top_q = fmaxf(top_q, y[e]);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      top_p = fmaxf(top_p, __shfl_xor(top_p, d));
+      top_q = fmaxf(top_q, __shfl_xor(top_q, d));
+    }
+    if (lane == 0) { s_top[0][wv] = top_p; s_top[1][wv] = top_q; }
+    __syncthreads();
+    top_p = s_top[0][lane & 15];
+    top_q = s_top[1][lane & 15];
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) {
+      top_p = fmaxf(top_p, __shfl_xor(top_p, d));
+      top_q = fmaxf(top_q, __shfl_xor(top_q, d));
+    }
+    sp.m = (double)uniform(top_p);
+    sq.m = (double)uniform(top_q);
+  }
+  // (masses, relative to the largest at first; kept: an exponential takes longer than all else about an entry)
+  double pm[ROUNDS], qm[ROUNDS], z[2] = {0.0, 0.0};
+  auto mass_of = [&](const Side &side, float v) {
+    if (p.probs) return v > 0.0f && v < finf ? (double)v : 0.0;
+    return v < finf && v > -finf ? exp(((double)v - side.m) * side.inv_t) : 0.0;
+  };
+#pragma unroll
+  for (int e = 0; e < ROUNDS; ++e) {
+    pm[e] = qm[e] = 0.0;
+    if (e < rounds) {
+      pm[e] = mass_of(sp, x[e]);
+      qm[e] = mass_of(sq, y[e]);
+      z[0] += pm[e];
+      z[1] += qm[e];
+    }
+  }
+  block_sums(z, s_red);
+  sp.ln_z = log(z[0]);
+  sq.ln_z = log(z[1]);
+  const double norm_p = z[0] > 0.0 ? 1.0 / z[0] : 0.0, norm_q = z[1] > 0.0 ? 1.0 / z[1] : 0.0;
+
+  // ---- keys and masses, and the sums that need no order
+  double tv = 0.0;
+#pragma unroll
+  for (int e = 0; e < ROUNDS; ++e)
+    if (e < rounds) {
+#pragma clang fp contract(off)  // (equal masses differ by 0)
+      const int i = e * kShortThreads + tid;
+      const double lp = sp.log_mass(x[e]), lq = sq.log_mass(y[e]);
+      const bool hp = lp > ninf, hq = lq > ninf;
+      float lr = -finf;             // no target mass (or none at all): sorts first
+      if (hq) lr = hp ? (float)(lq - lp) : finf;
+      pm[e] *= norm_p;
+      qm[e] *= norm_q;
+      tv += fabs(pm[e] - qm[e]);
+      s_row[i] = ((unsigned long long)sort_key(lr) << 32) | (uint32_t)i;
+      s_mass[i] = make_float2((float)pm[e], (float)qm[e]);
+    }
+  tv = wave_sum(tv);
+  if (lane == 63) s_out[2 * kLmlMaxK][wv] = tv;
+#pragma unroll 1
+  for (int kk = 0; kk < p.n_k; ++kk) {
+    const double K = p.kd[kk];
+    double sum = 0.0;  // of q / (1 + q / (K p)) with one division
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e)
+      if (e < rounds) {
+        const double kp = K * pm[e], kpq = kp * qm[e];
+        if (kpq > 0.0) sum += kpq / (kp + qm[e]);
+      }
+    sum = wave_sum(sum);
+    if (lane == 63) s_out[kLmlMaxK + kk][wv] = sum;
+  }
+  __syncthreads();
+
+  // ---- stable radix sort, 8 bits a pass; wavefront w holds the w-th part of the row, `rounds` times 64 entries
+  const int from = wv * 64 * rounds + lane;
+#pragma unroll 1
+  for (int shift = 32; shift < 64; shift += 8) {
+    unsigned long long entry[ROUNDS];
+    int where[ROUNDS];  // digit, and rank among the wavefront's entries of it
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e)
+      if (e < rounds) entry[e] = s_row[from + e * 64];
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e)
+      if (e < rounds) {
+        const uint32_t d = (uint32_t)(entry[e] >> shift) & 255u;
+        uint32_t peers_lo = ~0u, peers_hi = ~0u;  // lanes with the same digit: bit by bit, keep those whose bit is like mine
+#pragma unroll
+        for (int bit = 0; bit < 8; ++bit) {
+          const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, bit, 1);  // all ones if the bit is set
+          const unsigned long long have = __ballot(mine != 0u);
+          peers_lo &= ~((uint32_t)have ^ mine);
+          peers_hi &= ~((uint32_t)(have >> 32) ^ mine);
+        }
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0u));
+        const int seen = s_cnt[wv][d];
+        if (rank == 0) s_cnt[wv][d] = (unsigned short)(seen + __popc(peers_lo) + __popc(peers_hi));
+        where[e] = seen + rank;
+        __builtin_amdgcn_wave_barrier();
+      }
+    __syncthreads();
+    {
+      // four wavefronts' counters of a digit a thread, in the order of digits and wavefronts: what is before each
+      const int d = tid >> 2, w0 = (tid & 3) * 4;
+      int c[4], sum = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        c[j] = sum;
+        sum += s_cnt[w0 + j][d];
+      }
+      const int incl = wave_prefix(sum);
+      if (lane == 63) s_tot[wv] = incl;
+      __syncthreads();
+      const int before = of_lane(prefix_of_16((lane & 15) < wv ? s_tot[lane & 15] : 0), 15) + incl - sum;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s_cnt[w0 + j][d] = (unsigned short)(before + c[j]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e)
+      if (e < rounds) s_row[s_cnt[wv][(uint32_t)(entry[e] >> shift) & 255u] + where[e]] = entry[e];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s_cnt[wv][q * 64 + lane] = 0;  // (this wavefront's only, until the next pass's first barrier)
+    __syncthreads();
+  }
+
+  // ---- running sums over the sorted order: every wavefront's part, then each walks its own with those before it as the carry
+  float2 mass[ROUNDS];
+  double all_p = 0.0, all_q = 0.0;
+#pragma unroll
+  for (int e = 0; e < ROUNDS; ++e) {
+    mass[e] = make_float2(0.0f, 0.0f);
+    if (e < rounds) mass[e] = s_mass[(uint32_t)s_row[from + e * 64]];
+    all_p += (double)mass[e].x;
+    all_q += (double)mass[e].y;
+  }
+  all_p = wave_sum(all_p);
+  all_q = wave_sum(all_q);
+  if (lane == 63) { s_seg[0][wv] = all_p; s_seg[1][wv] = all_q; }
+  __syncthreads();
+  const double upto_p = prefix_of_16(s_seg[0][lane & 15]), upto_q = prefix_of_16(s_seg[1][lane & 15]);
+  const double q_total = of_lane(upto_q, 15);
+  double p_before = wv > 0 ? of_lane(upto_p, wv - 1) : 0.0, q_before = wv > 0 ? of_lane(upto_q, wv - 1) : 0.0;
+  double common[ROUNDS];  // q_suf/q_j + p_pre/p_j, times q_j
+#pragma unroll
+  for (int e = 0; e < ROUNDS; ++e) {
+    common[e] = 0.0;
+    if (e < rounds) {
+      const double pj = (double)mass[e].x, qj = (double)mass[e].y;
+      const double pin = wave_prefix(pj), qin = wave_prefix(qj);  // inclusive sums over the lanes
+      if (pj > 0.0 && qj > 0.0)
+        common[e] = (q_total - (q_before + (qin - qj))) + (p_before + (pin - pj)) * (qj / pj);
+      else
+        mass[e].y = 0.0f;
+      p_before += of_lane(pin, 63);
+      q_before += of_lane(qin, 63);
+    }
+  }
+#pragma unroll 1
+  for (int kk = 0; kk < p.n_k; ++kk) {
+    const double K = p.kd[kk];
+    double sum = 0.0;
+#pragma unroll
+    for (int e = 0; e < ROUNDS; ++e)
+      if (e < rounds && mass[e].y > 0.0f) sum += K * (double)mass[e].y / (common[e] + (K - 1.0) * q_total);
+    sum = wave_sum(sum);
+    if (lane == 63) s_out[kk][wv] = sum;
+  }
+  __syncthreads();
+  // sixteen lanes a result
+  const int result = tid >> 4, kk = result < kLmlMaxK ? result : result - kLmlMaxK;
+  if (wv * 4 > 2 * kLmlMaxK) return;  // (whole wavefronts)
+  const double sum = sum_of_16(s_out[min(result, 2 * kLmlMaxK)][tid & 15]);
+  if ((tid & 15) != 0 || result > 2 * kLmlMaxK) return;
+  if (result == 2 * kLmlMaxK) {
+    if (p.tv != nullptr) p.tv[b] = 0.5 * sum;
+  } else if (kk < p.n_k) {
+    if (result < kLmlMaxK) p.bound[b * p.n_k + kk] = sum;
+    else if (p.relaxed != nullptr) p.relaxed[b * p.n_k + kk] = sum;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
   LmlParams p = params;
   const bool f32 = p.dtype == LLC_F32;
   const bool cells = p.V >= (f32 ? kCellMinV : kCellMinVNarrow) && p.V <= kCellMaxV;
+  // (no workspace: as many rows as a launch may have threads for)
+  constexpr long long kMostRows = 1 << 21;
+  if (!cells && p.V <= 8 * kShortThreads) {
+    static_assert(kCellMinV <= 8 * kShortThreads && kCellMinVNarrow <= 8 * kShortThreads, "shorter rows fit into LDS");
+    for (p.row0 = 0; p.row0 < p.B; p.row0 += kMostRows) {
+      const dim3 grid((unsigned)(p.B - p.row0 < kMostRows ? p.B - p.row0 : kMostRows)), block(kShortThreads);
+      if (p.V <= 4 * kShortThreads) {
+        if (f32) hipLaunchKernelGGL((lml_short_kernel<float, 4>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((lml_short_kernel<uint16_t, 4>), grid, block, 0, s, p);
+      } else {
+        if (f32) hipLaunchKernelGGL((lml_short_kernel<float, 8>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((lml_short_kernel<uint16_t, 8>), grid, block, 0, s, p);
+      }
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   p.only_flagged = cells ? 1 : 0;
 #define LLC_LML(KERNEL, ROWS)                                                                            \
   {                                                                                                      \
@@ -1864,8 +2123,6 @@ hipError_t launch_lml(hipStream_t s, const LmlParams &params) {
     const hipError_t e = hipGetLastError();                                                              \
     if (e != hipSuccess) return e;                                                                       \
   }
-  // (no workspace: as many rows as a launch may have threads for)
-  constexpr long long kMostRows = 1 << 21;
   for (p.row0 = 0; cells && p.row0 < p.B; p.row0 += kMostRows)
     LLC_LML(lml_sum_kernel, (unsigned)(p.B - p.row0 < kMostRows ? p.B - p.row0 : kMostRows))
   for (p.row0 = 0; p.row0 < p.B; p.row0 += p.slots) {
