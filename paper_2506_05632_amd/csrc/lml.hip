@@ -1232,7 +1232,7 @@ __device__ __forceinline__ const LmlParams &params_again() {
 // cells shared out by where that was; what then still does, rows with +inf entries or without mass on a side, or whose results are so small that the rounding of
 // masses may count, are marked (a NaN in the place of their first result) and left to lml_cell_kernel, behind this one.
 // tv and the relaxed sums are taken in 64 bits, entry by entry, in the pass that makes the cells.
-// What bounds it: issue in fp64.  The row is read twice and nothing is written.  Two exponentials an entry and pass (15 instructions each), of some 45 in the
+// What bounds it: issue in fp64 (0.83 of the slots; 200 instructions an entry in all).  The row is read twice.  Two exponentials an entry and pass (15 instructions each), of some 45 in the
 // first pass and 110 in the second; of a row of 128 256 (220 us, four a CU in turn) those take 53 and 108 us, the sample and its order 17, the
 // cells 14, sums over the workgroup and their barriers the rest.  us a call, four list sizes, entries' terms taken one by one (lml_cell_kernel for
 // every row) and now: 1024 x 128 256 2135, 875; 512 x 152 064 bf16 1394, 507; 1024 x 32 000, two sizes, 645, 366; 256 x 50 257 bf16, one size, 272,
