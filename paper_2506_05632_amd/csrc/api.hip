@@ -82,6 +82,36 @@ void fine_shape(long long rows, long long G, bool with_pool, int *threads, int *
   *chunks = (int)c;
 }
 
+// Workgroups of 256 threads that a CU holds: of fp32 rows of their own with normalisers, four drafts a pass, three (133 registers).
+int to_a_cu(bool f32, int kt, bool own, bool lse) { return own && lse && f32 && kt == 4 ? 3 : 4; }
+
+// A better shape for (row, draft group) pairs of which workgroups as large as a CU takes would leave many CUs half idle: as many chunks
+// of 256 threads as the chip holds at a time.  us a call, before and now: own rows with keys, 270 to 341 pairs, K = 4, bf16 50 257
+// entries 110 to 113, 88; 128 256 251 to 263, 175 to 187; fp32 32 000 78 to 81, 70 to 73; 128 256 276 to 287, 232 to 257; 140 x 128 256 bf16 157,
+// 127, fp32 172, 145.  A chunk pays its own warm-up and exact step, and the call a finalize launch, so rows have to be long enough: 48 tiles for
+// four drafts a pass without keys (300 x 32 000 fp32 38, 40; 50 257 64, 57; 128 256 162, 142), 120 for two (50 257 35, 38; 128 256 96, 90), for a
+// shared proposal (K = 8 with keys 300 x 50 257 69, 79; 128 256 128, 119; 152 064 145, 130; min-first without keys 257 x 128 256 63, 66)
+// and for pairs that get 512 threads and a CU anyway (170 x 32 000 bf16 with keys 58, 59; 200 x 128 256 160, 139).
+void filled_shape(long long rows, long long G, bool f32, int kt, bool own, bool lse, int *threads, int *chunks) {
+  constexpr int kCus = 256;
+  if (rows <= kCus / 2 || (own && kt > 4)) return;
+  const int slots = to_a_cu(f32, kt, own, lse);
+  const long long c = kCus * slots / rows;
+  int least_tiles = 120, least = 3;
+  if (rows <= kCus) {
+    if (!(own && lse)) return;
+    least = 4;
+  } else if (slots == 3) {
+    least_tiles = 30;
+    least = 2;
+  } else if (own && (lse || kt == 4)) {
+    least_tiles = 48;
+  }
+  if (c < least || (G + kBlock - 1) / kBlock < least_tiles) return;
+  *threads = kBlock;
+  *chunks = (int)c;
+}
+
 struct Layout {
   size_t keyX, idxX, keyY, idxY, kY, secX, secY, lse, lse_part, total;
 };
@@ -212,9 +242,15 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   bool fine = want == 0;
   if (fine && lean && pl.kt <= 4 && !j.min_first && !masked && !(j.need_lse && j.kind != LLC_PROBS))
     fine_shape(rows, G, !j.no_pool, &pl.threads, &want);
+  const bool lse = j.need_lse && j.kind != LLC_PROBS, f32 = j.dtype == LLC_F32;
+  if (fine && want == 0 && !masked && (!j.min_first || (shared && lse)))
+    filled_shape(rows, G, f32, pl.kt, !shared, lse, &pl.threads, &want);
+  // (own rows with normalisers that fit four wavefronts to a SIMD: two workgroups of 512 threads to a CU where there are as many; us a
+  // call with 256 threads and so, K = 4: 400 x 32 000 bf16 82, 69; 512 x 128 256 277, 225; K = 2: fp32 400 x 50 257 90, 77)
+  const bool roomy = lean || (!shared && lse && !masked && !j.min_first && rows > 256 && pl.kt <= 4 && to_a_cu(f32, pl.kt, true, true) == 4);
   for (;; fine = false, want = 0) {
     if (want == 0)  // (min-first: a staging area and a queue per wavefront, within 64 KB of LDS)
-      auto_shape(rows, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, lean, fine, &pl.threads, &want);
+      auto_shape(rows, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, roomy, fine, &pl.threads, &want);
     plan_chunks(G, pl.threads, want, &pl.n_chunks, &pl.groups_per_chunk);
     out->blocks = rows * pl.n_chunks;
     // (a launch takes fewer than 2^32 threads in all)

@@ -31,3 +31,13 @@ def _layout(B, K, groups, chunks):
 @pytest.mark.parametrize("B,K,V,groups,chunks", [(4, 4, 32000, 1, 4), (1, 2, 24576, 1, 3), (16, 3, 40001, 1, 5), (2, 8, 50257, 1, 5), (3, 6, 45056, 1, 4)])
 def test_the_least_workspace_is_what_it_was(B, K, V, groups, chunks):
     assert _least(B=B, K=K, V=V, draft_stride_b=V, target_stride_b=V) == _layout(B, K, groups, chunks)
+
+
+# rows for which chunks of 256 threads fill the chip better: the least workspace is that of one chunk a row
+@pytest.mark.parametrize("own,kw", [(True, dict(B=300, K=4, V=50257, keyX=0x3000, keyY=0x3000)), (True, dict(B=140, K=4, V=128256, keyX=0x3000, keyY=0x3000)),
+                                    (True, dict(B=341, K=4, V=50257)), (False, dict(B=257, K=8, V=128256)), (False, dict(B=300, K=6, V=152064))])
+@pytest.mark.parametrize("dtype", [binding.F32, binding.BF16])
+def test_a_workspace_for_one_chunk_a_row_is_enough(own, kw, dtype):
+    B, K, V = kw["B"], kw["K"], kw["V"]
+    strides = dict(draft_stride_b=K * V if own else V, draft_stride_k=V if own else 0, target_stride_b=V)
+    assert _least(dtype=dtype, **strides, **kw) == _layout(B, K, 1, 1)
