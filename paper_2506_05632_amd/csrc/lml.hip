@@ -26,6 +26,7 @@
 // Entries without mass on one side follow the limits: p_j = 0 or q_j = 0 gives term j = 0; as a
 // summand i such an entry still counts with the mass it has on the other side.
 #include "common.hpp"
+#include "lml_search.hpp"
 
 #include <type_traits>
 
@@ -1087,7 +1088,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_cell_kernel(const LmlPara
 
 // A thread holds kSumEach cells.  Buckets: 127 quantiles' splitters, up to 128 of places that the sample holds often, and two
 // for every heavy entry.
-constexpr int kSumEach = 7, kSumCells = kSumEach * kCellThreads, kSumBuckets = 512;
+constexpr int kSumEach = 7, kSumCells = kSumEach * kCellThreads;
 constexpr double kHeavy = 0x1p-9;     // of a side's mass: such an entry's place has a cell of its own
 constexpr float kSumFar = 740.0f;     // entries farther from the row's centre in log2 r have no place (kFar in ln r)
 constexpr float kBeyond = 6.0f;       // how far the outer buckets reach beyond the sample, in log2 r
@@ -1518,7 +1519,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   nb = uniform(nb);
   if (tid == 0) { s_single = 0; s_shared = 0; s_most = 0; s_per_left[0] = 0.0; }
   for (int b = tid; b < 2 * kSumBuckets; b += kCellThreads)
-    if (b == 0 || b >= nb) s_split[b] = b == 0 ? ninf : pinf;
+    if (b == 0 || b >= nb) s_split[b] = b == 0 ? ninf : kNoSplitter;
   __syncthreads();
   // an entry's bucket is looked for among the splitters that share its part of the range
   const float grid_per = uniform((float)kCellThreads / (far_right - far_left));
@@ -1616,11 +1617,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
         d[j] = distance(xp, xq, yp, yq);
         b[j] = s_grid[part_of(fabsf(d[j]) < kSumFar ? d[j] : 0.0f)];
       }
-#pragma unroll 1
-      for (int step = (1 << steps) >> 1; step >= 1; step >>= 1) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] += s_split[b[j] + step] <= d[j] ? step : 0;
-      }
+      find_buckets(s_split, steps, d, b);
       float4 bu[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) bu[j] = s_bucket[b[j]];
