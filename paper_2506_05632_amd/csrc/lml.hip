@@ -1097,6 +1097,9 @@ constexpr float kBeyond = 6.0f;       // how far the outer buckets reach beyond 
 constexpr double kSumErrorLeast = 0.5, kSumErrorEach = 0x1p-17;
 constexpr double kShareAgain = 0x1p-18;  // what sharing the cells out again can mend
 constexpr float kLaneStep = 0x1p40f;  // (a distance is a multiple of 2^-36)
+constexpr double kU2Units = 0x1p35;   // of a side's mass in a cell's sum of p u (1 - u), which is no more than a quarter of the cell's, so that ...
+constexpr float kU2Most = 0x1.fp-2f;  // ... it has 32 bits in a cell with less than this (and 2^18 entries): one with more is not known
+constexpr uint32_t kDitherStep = 0x9E3779B9u;  // (2^32 over the golden ratio: its multiples are spread evenly)
 constexpr float kWide = 0.5f;         // a cell this wide in ln r leaves its entries' whole terms open
 
 // 2^y for y <= 0 or so (what is below -1074 comes out as 0, NaN too) to about an ulp: y = n + f, |f| <= 1/2, and 2^f = 1 + f P(f)
@@ -1117,6 +1120,13 @@ __device__ __forceinline__ double exp2_of(double y) {
   s = fma(s, f, 0x1.62e42fefa39f3p-1);
   s = fma(s, f, 1.0);
   return __builtin_amdgcn_ldexp(s, (int)(uint32_t)__double_as_longlong(t));
+}
+
+// x >= 0 as a whole number, the largest of 32 bits if it is larger.
+__device__ __forceinline__ uint32_t saturated(float x) {
+  uint32_t n;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(n) : "v"(x));
+  return n;
 }
 
 // A mass relative to its row's largest as a whole number of `step` 2^-52ths, a power of two and no less than the mass.
@@ -1225,7 +1235,9 @@ __device__ __forceinline__ const LmlParams &params_again() {
 // and g the mean of |s_i - s_j|,
 //   sum_j K q_j / (F(r_j) + K - 1) = K Q / D (1 - x ((P' + P / 2) v + P g / 2) + x^2 (P' + P / 2)^2 v + third powers of s),
 // P' the p-mass and Q' the q-mass before and behind the cell, D = Q' + Q + r P' + K - 1, x = r / D.  P and Q are added up as whole numbers (whole_mass),
-// v comes from a third sum, of p u^2 with u an entry's place in its cell (the mean of u is known from Q / P), and g, for which the order
+// v comes from a third sum, of p u (1 - u) with u an entry's place in its cell (the mean of u is known from Q / P), whose shares are rounded to 2^-35ths of the
+// row's mass, up or down by the entry's place in the row: right on average, and what that may be off by in a cell counts as open.  (Rounded to the nearest of 2^-31ths the shares of
+// light entries were all nothing, which looked like a cell without spread: rows whose sides share light entries only came out up to 16 x 2^-22 off, now 0.12 x 2^-22.)  And g, for which the order
 // inside the cell would be needed, is taken as 4 v / w: right on average if the entries lie evenly in the cell's width w, whatever their
 // number and masses are.  It is no less than 2 v / w and no more than 2 sqrt(v / 3) (the mean difference of any masses with
 // that variance), so what a cell leaves open is known; an entry that is heavy on either side gets a cell without width (with others of its ratio),
@@ -1243,7 +1255,7 @@ __device__ __forceinline__ const LmlParams &params_again() {
 template <typename E, bool PROBS>
 __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParams p) {
   __shared__ unsigned long long s_p[kSumCells + 1], s_q[kSumCells + 1];  // a cell's masses, then what lies before it
-  __shared__ uint32_t s_u2[kSumCells];         // sums of p (u - 1/2)^2 in 2^-31ths of the side's mass
+  __shared__ uint32_t s_u2[kSumCells];         // sums of p u (1 - u) in 2^-35ths of the side's mass, u an entry's place in its cell
   __shared__ float4 s_bucket[kSumBuckets];     // left end, cells per unit of log2 r, first cell (its bits), largest place in the bucket in cells
   __shared__ double s_per_left[kSumBuckets];   // 2^-(left end), for whole masses
   __shared__ float s_split[2 * kSumBuckets];   // bucket b holds what lies from s_split[b] up to s_split[b + 1]
@@ -1583,11 +1595,12 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
 
     // ---- second pass: the cells' sums, tv and the relaxed sums
     const double rho = uniform(s_total[1] / s_total[0]);  // p relative to the target's largest mass (1 where the sides are alike)
-    const float to_u2 = uniform((float)(0x1p31 / s_total[0]));
+    const float to_u2 = uniform((float)(kU2Units / s_total[0]));
     double tv = 0.0, p_first = 0.0, relaxed[4] = {0.0, 0.0, 0.0, 0.0};
     const float lane_step = (float)(tid & (copies - 1)) * (1.0f / kLaneStep);  // (nothing to a distance, a cell where a place has several)
     const bool first_round = round == 0, four_sizes = p.n_k > 2, want_relaxed = first_round && p.relaxed != nullptr;
     float4 next_p = four<E>(prow, tid * 4, V, none), next_q = four<E>(qrow, tid * 4, V, none);
+    uint32_t dither = (uint32_t)tid * kDitherStep;
     Steps stage(V);
 #pragma unroll 1
     for (int i = tid * 4; i < V; i += kCellThreads * 4) {
@@ -1597,6 +1610,10 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
         next_p = four<E>(prow, i + kCellThreads * 4, V, none);
         next_q = four<E>(qrow, i + kCellThreads * 4, V, none);
       }
+      // (what an entry's share of the third sum is rounded up or down by, so that sums are right on average: a number from 0 to 1 that belongs
+      // to its place in the row, and for its neighbour what is left to 1)
+      dither += (uint32_t)kCellThreads * kDitherStep;
+      const float up = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, dither, 9));  // from 1 to 2
       double ep[4], eq[4];
       float d[4];
       int b[4];
@@ -1629,10 +1646,10 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
         if (fabsf(d[j]) < kSumFar) {
           const float t = __builtin_amdgcn_fmed3f(((d[j] - bu[j].x) - lane_step) * bu[j].y, 0.0f, bu[j].w);
           const int cell = (int)t + __float_as_int(bu[j].z);
-          const float u = __builtin_amdgcn_fractf(t) - 0.5f;
+          const float u = __builtin_amdgcn_fractf(t);
           atomicAdd(&s_p[cell], whole_mass(ep[j], step_p));
           atomicAdd(&s_q[cell], whole_mass(eq[j], step_q));
-          atomicAdd(&s_u2[cell], (uint32_t)fmaf((float)ep[j] * to_u2, u * u, 0.5f));
+          atomicAdd(&s_u2[cell], saturated(fmaf((float)ep[j] * to_u2, fmaf(-u, u, u), (j & 1) != 0 ? 2.0f - up : up - 1.0f)));
         } else {
           // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
           // p-mass to speak of)
@@ -1742,22 +1759,25 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
             const float t = (float)(ratio - 1.0), z = t * __builtin_amdgcn_rcpf(2.0f + t), zz = z * z;
             const float small = z * fmaf(zz, fmaf(zz, fmaf(zz, 2.8853901f / 7.0f, 2.8853901f / 5.0f), 2.8853901f / 3.0f), 2.8853901f);
             const float m = (t < 0.4f ? small : __builtin_amdgcn_logf((float)ratio)) * bu.y - (float)place;
-            const float u2 = (float)s_u2[c] * 0x1p-31f * per_p;
+            const float within = (float)s_u2[c] * (float)(1.0 / kU2Units) * per_p;  // the mean of u (1 - u): u's variance is this below mean (1 - mean)
+            // what rounding may have done to it: an entry's has a variance of no more than a quarter, nor more than what it adds.  Two deviations as if the
+            // cell had all of the row's entries, which is four or more of the sum over the cells unless one of them has nearly all
+            const float slip_var = fp < kU2Most ? fminf((float)(1.0 / kU2Units) * __builtin_amdgcn_sqrtf(fminf((float)V, (float)kU2Units * fp)) * per_p, 0.25f) : 0.25f;
             float var, mean = m;
 #pragma unroll
             for (int it = 0; it < 2; ++it) {  // the logarithm of the mean ratio is half a variance above the mean place
-              var = fminf(fmaxf(u2 - (mean - 0.5f) * (mean - 0.5f), 0.0f), 0.25f);
+              var = fmaxf(fmaf(-mean, mean, mean) - within, 0.0f);
               mean = fminf(fmaxf(m - 0.5f * w * var, 0.0f), 1.0f);
             }
-            var = fminf(fmaxf(u2 - (mean - 0.5f) * (mean - 0.5f), 0.0f), mean * (1.0f - mean));
-            const float var_open = fmaf(0.02f * w, w, var);  // (and a third power more)
+            var = fmaxf(fmaf(-mean, mean, mean) - within, 0.0f);
+            const float var_open = fmaf(0.02f * w, w, var + slip_var);  // (and a third power more)
             v = var * w * w;
-            v_open = 0.25f * fminf(w, 1.0f) * var_open * w * w;
+            v_open = fmaf(0.25f * fminf(w, 1.0f), var_open, slip_var) * w * w;
             half_g = 2.0f * var * w;
             half_g_open = w * fmaxf(var_open, __builtin_amdgcn_sqrtf(var_open * (1.0f / 3.0f)) - 2.0f * var);
           }
           const double half = fma(0.5, P, before), base = fma(behind + Q, P, Q * before);
-          const float half_per_p = (float)half * per_p, slips = slip_p * __builtin_amdgcn_rcpf((float)half);
+          const float half_per_p = (float)half * per_p, slips = slip_p * (__builtin_amdgcn_rcpf((float)half) + per_p);
           double den[4];
 #pragma unroll
           for (int n = 0; n < 4; ++n) den[n] = fma(again.kd[n0 + n] - 1.0, P, base);

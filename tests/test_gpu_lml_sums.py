@@ -115,3 +115,21 @@ def test_ratios_shared_by_many_entries(ratios, V):
     tq[2, :40] += 8.0
     _check(td, tq, [1, 4])
     _check(td.bfloat16(), tq.bfloat16(), [1, 4])
+
+
+@pytest.mark.parametrize("V,heavy,light,spread", [(50257, 300, 7e-10, "flat"), (128256, 3000, 1e-10, "flat"), (128256, 3000, 7e-10, "normal"),
+                                                  (262136, 3000, 1e-5, "normal"), (262136, 300, 7e-10, "flat")])
+@pytest.mark.parametrize("kind", ["logits", "probs"])
+def test_sides_that_share_light_entries_only(V, heavy, light, spread, kind):
+    # either side's mass is on entries that the other has none of; the rest differ by up to e^20 or so
+    g = torch.Generator(device=DEV).manual_seed(7)
+    s = 20.0 * (torch.randn(2, V, generator=g, device=DEV) if spread == "normal" else 2.0 * torch.rand(2, V, generator=g, device=DEV) - 1.0)
+    draft, target = np.log(light) - s.clamp(min=0.0), np.log(light) + s.clamp(max=0.0)
+    at = torch.rand(2, V, generator=g, device=DEV).argsort(dim=1)
+    for mine, other, where in ((draft, target, at[:, :heavy]), (target, draft, at[:, heavy:2 * heavy])):
+        mine.scatter_(1, where, -np.log(heavy))
+        other.scatter_(1, where, float("-inf"))
+    if kind == "probs":
+        draft, target = draft.exp(), target.exp()
+    _check(draft, target, [1, 4, 64, 4096], kind)
+    _check(target, draft, [1, 4, 64, 4096], kind)
