@@ -1287,7 +1287,8 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   pl.center = 0.0;
 
   // ---- first pass: the sides' sums and largest entries.  Masses are taken relative to the largest of the first
-  // 64 entries, which serves unless that is so far below the row's largest that the sum overflows
+  // 64 entries, which serves unless it is so far below the row's largest that its mass or the sum overflows (looked for in the largest
+  // entries themselves: exp2_of makes any number of an exponent beyond 2^31)
   Masses<PROBS> mp, mq;
   mp.per = PROBS ? 1.0 : log2e_over(p.temp_draft);
   mq.per = PROBS ? 1.0 : log2e_over(p.temp_target);
@@ -1370,7 +1371,8 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
       leave();
       return;
     }
-    if (zp >= 0x1p-300 && zp < 0x1p1000 && zq >= 0x1p-300 && zq < 0x1p1000) break;
+    const bool near = PROBS || (mp.log2_of(top_p) <= 1000.0 && mq.log2_of(top_q) <= 1000.0);
+    if (near && zp >= 0x1p-300 && zp < 0x1p1000 && zq >= 0x1p-300 && zq < 0x1p1000) break;
     if (attempt == 1) {  // (uniform) a NaN among the sums: an entry of +inf
       leave();
       return;

@@ -28,6 +28,11 @@ def _check(draft, target, ks, kind="logits", rtol=2.0 ** -22, **kw):
     return ws
 
 
+def _by_cells(ws, B, V):
+    """Rows that the form behind did, in a workspace of B slots that held zeros: it writes the entries' cells there, the form by sums nothing."""
+    return ws[:24 * V * B].view(B, 24 * V)[:, :2 * V].amax(dim=1).nonzero().flatten().tolist()
+
+
 def _rows(B, V, seed):
     g = torch.Generator(device=DEV).manual_seed(seed)
     tq = -1.1 * torch.log(torch.rand(B, V, generator=g, device=DEV).argsort(dim=1) + 1.0)
@@ -133,3 +138,17 @@ def test_sides_that_share_light_entries_only(V, heavy, light, spread, kind):
         draft, target = draft.exp(), target.exp()
     _check(draft, target, [1, 4, 64, 4096], kind)
     _check(target, draft, [1, 4, 64, 4096], kind)
+
+
+@pytest.mark.parametrize("low", [-1e9, -1e10, -1e30, None])
+@pytest.mark.parametrize("temp", [0.6, 0.7, 0.8, 0.9, 1.0, 1.2])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_masked_at_their_beginning_are_like_others(low, temp, dtype):
+    # the first entries are as far below the others as the type allows (None: its lowest), on either side or both
+    low = torch.finfo(dtype).min if low is None else low
+    draft, target, _ = _rows(4, 10001, 3)
+    draft[0, :64] = low
+    target[1, :64] = low
+    draft[2, :6000], target[2, :6000] = low, low
+    ws = _check(draft.to(dtype), target.to(dtype), [1, 4], temp_draft=temp, temp_target=temp)
+    assert _by_cells(ws, 4, 10001) == []
