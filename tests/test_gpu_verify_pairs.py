@@ -23,21 +23,33 @@ def _tokens(target, S, L, K, V, g, keep=0.7, **kw):
     return tok.to(DEV)
 
 
-def _check(target, tok, S, flags=0, **kw):
-    at_once = llc.llc_verify(target, tok, want_keys=True, strong=True, flags=flags, **kw)
-    stats = llc.new_stats(DEV)
-    loop = llc.llc_verify(target, tok, want_keys=True, strong=True, flags=flags, stats=stats, **kw)
+def _both(target, tok, size=None, flags=0, **kw):
+    """The call as the library takes it, the loop over positions, and whether the first was another form: the two forms leave different
+    things in the workspace (of `size` bytes; by default one that holds whatever either needs), the loop with and without counters
+    but for a runner-up's key per row and draft."""
+    S, L1, K, V = target.shape
+    if size is None:
+        size = max(llc.llc_verify_workspace_size(S, L1 - 1, K, V), llc.llc_couple_workspace_size(S * L1 * K, K, V) + 12 * S * L1 * K * K + 512)
+    out, spaces, stats = [], [], llc.new_stats(DEV)
+    for st in (None, stats):
+        spaces.append(torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV))
+        out.append(llc.llc_verify(target, tok, want_keys=True, strong=True, flags=flags, stats=st, workspace=spaces[-1], **kw))
     torch.cuda.synchronize()
-    if stats_dict(stats)["near_ties"] == 0:
-        for name in ("Y", "n_out", "active"):
-            assert torch.equal(at_once[name], loop[name]), name
-        np.testing.assert_allclose(at_once["keyY"].cpu().numpy(), loop["keyY"].cpu().numpy(), rtol=2.0 ** -22 + 2.0 ** -23)
-    return {k: at_once[k] for k in ("Y", "n_out", "active", "keyY")}
+    return out[0], out[1], stats_dict(stats)["near_ties"], int((spaces[0] != spaces[1]).sum()) > 8 * S * L1 * K
 
 
-# (chunks of a row, one workgroup a row, two and eight groups of drafts, ragged rows, one position, an odd number of drafts)
+def _check(target, tok, at_once=True, **kw):
+    out, loop, near_ties, other_form = _both(target, tok, **kw)
+    assert other_form == at_once and near_ties == 0
+    for name in ("Y", "n_out", "active"):
+        assert torch.equal(out[name], loop[name]), name
+    np.testing.assert_allclose(out["keyY"].cpu().numpy(), loop["keyY"].cpu().numpy(), rtol=2.0 ** -22 + 2.0 ** -23)
+    return {k: out[k] for k in ("Y", "n_out", "active", "keyY")}
+
+
+# (chunks of a row, one workgroup a row, two and four groups of drafts, ragged rows, one position, an odd number of drafts; sixty-four drafts are the loop's)
 @pytest.mark.parametrize("S,L,K,V,dtype", [(1, 1, 2, 777, "f32"), (1, 4, 4, 32003, "bf16"), (3, 6, 8, 5001, "f32"), (5, 2, 9, 2051, "f32"),
-                                           (30, 3, 5, 4099, "bf16"), (2, 2, 64, 517, "f32"), (40, 4, 3, 131, "f32")])
+                                           (30, 3, 5, 4099, "bf16"), (2, 2, 64, 517, "f32"), (40, 4, 3, 131, "f32"), (1, 4, 32, 517, "f32")])
 def test_all_rows_for_all_drafts_at_once(S, L, K, V, dtype):
     g = torch.Generator().manual_seed(S * 1000 + L * 100 + K)
     target = 2.0 * torch.randn(S, L + 1, K, V, generator=g)
@@ -46,10 +58,10 @@ def test_all_rows_for_all_drafts_at_once(S, L, K, V, dtype):
     kw = dict(temp_target=0.8, seed=23, row_offset=(1 << 32) - 3, row_stride_s=7, row_stride_j=2)
     tok = _tokens(target, S, L, K, V, g, **kw)
     ref = oracle_verify(target, tok, (0, S), strong=True, **kw)
-    compare_verify(_check(target, tok, S, **kw), ref)
+    compare_verify(_check(target, tok, K <= 32, **kw), ref)
     if L > 2 and S > 2:
         assert ref["n_out"].max() > 2
-    _check(target, tok, S, flags=llc.FLAG_MIN_FIRST, **kw)
+    _check(target, tok, K <= 32, flags=llc.FLAG_MIN_FIRST, **kw)
 
 
 def test_strided_rows_log_weights_and_rows_without_mass():
@@ -62,13 +74,13 @@ def test_strided_rows_log_weights_and_rows_without_mass():
     target[3, 2, 0, 5], target[5, 1, 1, 7] = float("nan"), float("inf")
     tok = _tokens(target, S, L, K, V, g, kind="logw", seed=19)
     ref = oracle_verify(target, tok, (0, S), kind="logw", seed=19, strong=True)
-    got = _check(target, tok, S, kind="logw", seed=19)
+    got = _check(target, tok, kind="logw", seed=19)
     compare_verify(got, ref)
     assert got["Y"][2, 0].item() == -1 and got["n_out"][2].item() == 1
     # one row for all drafts, and the same buffers again for other tokens
     one = target[:, :, :1].expand(S, L + 1, K, V)
     ref = oracle_verify(one, tok, (0, S), kind="logw", seed=19, strong=True)
-    compare_verify(_check(one, tok, S, kind="logw", seed=19), ref)
+    compare_verify(_check(one, tok, kind="logw", seed=19), ref)
 
 
 def test_captured_and_replayed():
@@ -91,3 +103,12 @@ def test_captured_and_replayed():
         eager = llc.llc_verify(target, tok, seed=3, want_keys=True, strong=True)
         for name in ("Y", "n_out", "active", "keyY"):
             assert torch.equal(out[name], eager[name]), (turn, name)
+
+
+@pytest.mark.parametrize("S,L,K,V,mf", [(100, 7, 8, 9000, False), (64, 2, 16, 4000, False), (128, 4, 4, 32000, False), (32, 7, 8, 9000, False), (64, 4, 10, 20000, True)])
+def test_calls_that_are_slower_at_once_take_the_loop(S, L, K, V, mf):
+    # (where no token is accepted the loop is its first scan and two launches a position without work)
+    target = torch.randn(S, L + 1, K, V, device=DEV, dtype=torch.bfloat16)
+    tok = torch.randint(0, V, (S, L, K), device=DEV, dtype=torch.int32)
+    for size in (None, llc.llc_verify_workspace_size(S, L, K, V)):
+        assert not _both(target, tok, size, flags=llc.FLAG_MIN_FIRST if mf else 0)[3]
