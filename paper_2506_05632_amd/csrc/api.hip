@@ -69,15 +69,22 @@ void auto_shape(long long rows, long long G, int most_threads, bool lean, bool f
 // A better shape for few rows, where the time is the latency of a workgroup's phases: those of 512 threads, at most one to
 // a CU, with a tile each as far as 16 to a row go (a wavefront then shares its SIMD with one other).  For at most four drafts a pass, drawn
 // one word at a time and without normalisers: the others' phases are longer and do not pay for being more (K = 8, or with keys: 0.9 to 1.1).
-// A pool needs rows of a dozen tiles to pay.  us a call, before and now: 4 x 32 000, K = 4, bf16 17.0, 15.0; 1 x 50 257 17.3, 15.8; 16 x 24 000
+// us a call, before and now: 4 x 32 000, K = 4, bf16 17.0, 15.3; 1 x 50 257 17.3, 15.8; 16 x 24 000
 // 17.6, 15.9; drafts alone, own rows, 16 x 32 000 16.9, 13.8; 6 x 12 000 15.7, 13.3; 16 x 80 000 18.4, 16.4.
-void fine_shape(long long rows, long long G, bool with_pool, int *threads, int *chunks) {
+// Rows of few tiles are better off in one workgroup, which finishes them: a pool needs a dozen tiles to pay, drafts alone seven in a shared
+// row (with 3 and 4 tiles 1.02 to 1.05 times the time, with 5 and 6 0.99 to 1.02, with 7 0.94), five in own rows (K = 1: 1.02, 0.99 with 5), of which four
+// drafts a pass pay from three on (0.94).  And where a chunk has many tiles, twice the wavefronts a SIMD count for more than its phases: no more than six in
+// own rows (0.93 to 1.0; with 9 and more 1.02 to 1.06), in shared ones 4 where a row gets eight chunks and 5 where it gets sixteen (0.94 to 1.0; 30 x 151 000,
+// K = 4, 22.8, 25.0).
+void fine_shape(long long rows, long long G, bool with_pool, bool own, int kt, int *threads, int *chunks) {
   constexpr int kThreads = 512, kCus = 256, kMost = 16;
   const long long tiles = (G + kThreads - 1) / kThreads;
   long long c = rows > 0 ? kCus / rows : 0;
   if (c > kMost) c = kMost;
   if (c > tiles) c = tiles;
-  if (c < 3 || c < (tiles < 8 ? tiles : 8) || (with_pool && tiles < 12)) return;
+  const int least_tiles = with_pool ? 12 : !own ? 7 : kt == 4 ? 3 : 5;
+  if (c < 3 || c < (tiles < 8 ? tiles : 8) || tiles < least_tiles) return;
+  if (own ? tiles > 6 * c : 6 * tiles > (c + 16) * c) return;
   *threads = kThreads;
   *chunks = (int)c;
 }
@@ -241,7 +248,7 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   int want = j.v_chunks;
   bool fine = want == 0;
   if (fine && lean && pl.kt <= 4 && !j.min_first && !masked && !(j.need_lse && j.kind != LLC_PROBS))
-    fine_shape(rows, G, !j.no_pool, &pl.threads, &want);
+    fine_shape(rows, G, !j.no_pool, !shared, pl.kt, &pl.threads, &want);
   const bool lse = j.need_lse && j.kind != LLC_PROBS, f32 = j.dtype == LLC_F32;
   if (fine && want == 0 && !masked && (!j.min_first || (shared && lse)))
     filled_shape(rows, G, f32, pl.kt, !shared, lse, &pl.threads, &want);

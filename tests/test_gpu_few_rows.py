@@ -47,3 +47,24 @@ def test_a_workspace_that_holds_fewer_chunks_gets_those():
         out = llc.llc_couple(draft, target, 4, seed=3, workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
         for name in ("X", "Y", "accept", "match_k"):
             assert torch.equal(out[name], ref[name]), (size, name)
+
+
+@pytest.mark.parametrize("B,K,V,own", [(4, 1, 4097, False), (4, 4, 8192, False), (60, 3, 6145, False), (1, 2, 12288, False), (4, 1, 4097, True), (16, 2, 8192, True)])
+def test_drafts_alone_in_short_rows_are_one_workgroup_each(B, K, V, own):
+    # (it keeps its results to itself: nothing passes through the workspace)
+    draft = torch.randn(*((B, K, V) if own else (B, V)), device=DEV)
+    ws = torch.full((llc.llc_couple_workspace_size(B, K, V),), 0xA5, dtype=torch.uint8, device=DEV)
+    llc.llc_couple(draft, None, K, seed=9, flags=llc.FLAG_DRAFT_ONLY, workspace=ws)
+    assert (ws == 0xA5).all()
+
+
+@pytest.mark.parametrize("with_pool", [False, True])
+def test_long_rows_are_cut_into_chunks_of_large_workgroups(with_pool):
+    # 30 rows of 100 003 entries: chunks of four tiles of 1024 threads (of 512 threads they would be seven tiles, 14 336 entries)
+    B, V, chunk, n = 30, 100003, 4 * 4096, 7
+    draft, target = torch.randn(B, V, device=DEV), torch.randn(B, V, device=DEV)
+    ws = torch.zeros(llc.llc_couple_workspace_size(B, 1, V), dtype=torch.uint8, device=DEV)
+    llc.llc_couple(draft, target if with_pool else None, 1, seed=9, flags=0 if with_pool else llc.FLAG_DRAFT_ONLY, workspace=ws)
+    keys = (B * n * 8 + 255) // 256 * 256
+    winners = ws[keys:keys + B * n * 4].view(torch.int32).view(B, n)
+    assert (winners // chunk == torch.arange(n, device=DEV)).all()
