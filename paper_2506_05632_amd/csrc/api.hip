@@ -253,8 +253,9 @@ int plan_scan(const ScanJob &j, ScanPlan *out) {
   if (fine && want == 0 && !masked && (!j.min_first || (shared && lse)))
     filled_shape(rows, G, f32, pl.kt, !shared, lse, &pl.threads, &want);
   // (own rows with normalisers that fit four wavefronts to a SIMD: two workgroups of 512 threads to a CU where there are as many; us a
-  // call with 256 threads and so, K = 4: 400 x 32 000 bf16 82, 69; 512 x 128 256 277, 225; K = 2: fp32 400 x 50 257 90, 77)
-  const bool roomy = lean || (!shared && lse && !masked && !j.min_first && rows > 256 && pl.kt <= 4 && to_a_cu(f32, pl.kt, true, true) == 4);
+  // call with 256 threads and so, K = 4: 400 x 32 000 bf16 82, 69; 512 x 128 256 277, 225; K = 2: fp32 400 x 50 257 90, 77.  From six tiles of 256
+  // threads on: rows of up to 3000 entries take 1.02 to 1.1 times the time so, of 4096 and 5000 0.95 to 1.03, of 6144 0.94 to 0.99)
+  const bool roomy = lean || (!shared && lse && !masked && !j.min_first && rows > 256 && G > 5 * kBlock && pl.kt <= 4 && to_a_cu(f32, pl.kt, true, true) == 4);
   for (;; fine = false, want = 0) {
     if (want == 0)  // (min-first: a staging area and a queue per wavefront, within 64 KB of LDS)
       auto_shape(rows, G, lean && !j.min_first ? kMaxThreads : kMaxThreads / 2, roomy, fine, &pl.threads, &want);

@@ -32,3 +32,15 @@ def test_chunks_that_fill_the_chip(B, K, V, own, dtype):
         for rows in ((0, 1), (B - 1, B)):
             ref = oracle_rows(draft, target, K, rows, kind="logits", temp_target=0.8, temp_draft=1.1, seed=5)
             compare(gpu, ref, rows=rows)
+
+
+@pytest.mark.parametrize("B,K,V", [(300, 4, 3001), (512, 2, 5120), (257, 1, 2048), (140, 8, 4099)])
+def test_short_own_rows_keep_workgroups_of_256_threads(B, K, V):
+    # a normaliser's sum is taken in an order that goes with the threads: the same bits as one chunk of 256 (of 512 threads, some of the keys'
+    # last bits are others)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    target, draft = _rows(g, (B,), V, torch.bfloat16), _rows(g, (B, K), V, torch.bfloat16)
+    kw = dict(seed=5, want_keys=True)
+    out, one = llc.llc_couple(draft, target, K, **kw), llc.llc_couple(draft, target, K, v_chunks=1, **kw)
+    for name in ("X", "Y", "accept", "match_k", "keyX", "keyY"):
+        assert torch.equal(out[name], one[name]), name
