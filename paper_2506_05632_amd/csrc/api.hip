@@ -727,14 +727,14 @@ size_t llc_verify_workspace_size(int64_t S, int64_t L, int64_t K, int64_t V) {
 // one more scan and a step, which wait for each other: some 15 us a position that any sequence reaches, and 4 for its two launches where none
 // does.  Scanning all K rows of every position for all K drafts at once instead is one launch, or two, but the generator's work and the
 // workgroups' phases K times over.  How far the sequences get is not known here, so the line lies where that is no slower even if no token is
-// accepted.  What it takes beyond the loop's first scan is, in us, 14 a thousand rows and pass over eight drafts, 3 for more than four drafts (longer phases),
-// and per million entries and draft beyond the fourth 0.3, or 0.12 drawn min-first.  Of 1860 shapes on this side of the line 8 were more than a tenth
-// slower than the loop with no token accepted, 1.17 times at most, and all but one faster with tokens that are likely, as a rule 1.5 to 3 times.  us a call, loop with
+// accepted.  What it takes beyond the loop's first scan is, in us, 14 a thousand rows and pass over eight drafts, 7 for more than four drafts (longer phases),
+// and per million entries and draft beyond the fourth 0.3, or 0.12 drawn min-first.  Of 1680 shapes on this side of the line 2 were more than a tenth
+// slower than the loop with no token accepted, 1.16 times at most, and all faster with tokens that are likely, as a rule 1.5 to 3 times.  us a call, loop with
 // no token accepted, with likely ones, and at once: 16 sequences x 5 positions x 4 drafts x 32 000 bf16 51, 99, 37; 4 x 9 x 4 x 9 000 56, 154, 24; beyond
 // the line 64 x 5 x 4 x 32 000 min-first 84, 145, 86; 128 x 5 x 4 x 32 000 90, 144, 142; 100 x 8 x 8 x 9 000 126, 210, 306; 64 x 3 x 16 x 4 000 44, 74, 169.
 static bool pairs_pay(long long S, long long L, long long K, long long V, bool min_first) {
   const double rows = (double)(S * (L + 1) * K), entries = rows * (double)V;
-  return 0.014 * rows * (double)((K + 7) / 8) + (K > 4 ? 3.0 : 0.0) + (min_first ? 0.12e-6 : 0.3e-6) * entries * (K > 4 ? (double)(K - 4) : 0.5) <=
+  return 0.014 * rows * (double)((K + 7) / 8) + (K > 4 ? 7.0 : 0.0) + (min_first ? 0.12e-6 : 0.3e-6) * entries * (K > 4 ? (double)(K - 4) : 0.5) <=
          4.0 * (double)L + 3.0;
 }
 

@@ -48,8 +48,8 @@ def _check(target, tok, at_once=True, **kw):
 
 
 # (chunks of a row, one workgroup a row, two and four groups of drafts, ragged rows, one position, an odd number of drafts; sixty-four drafts are the loop's)
-@pytest.mark.parametrize("S,L,K,V,dtype", [(1, 1, 2, 777, "f32"), (1, 4, 4, 32003, "bf16"), (3, 6, 8, 5001, "f32"), (5, 2, 9, 2051, "f32"),
-                                           (30, 3, 5, 4099, "bf16"), (2, 2, 64, 517, "f32"), (40, 4, 3, 131, "f32"), (1, 4, 32, 517, "f32")])
+@pytest.mark.parametrize("S,L,K,V,dtype", [(1, 1, 2, 777, "f32"), (1, 4, 4, 32003, "bf16"), (3, 6, 8, 5001, "f32"), (5, 3, 9, 2051, "f32"),
+                                           (30, 4, 5, 4099, "bf16"), (2, 2, 64, 517, "f32"), (40, 4, 3, 131, "f32"), (1, 4, 32, 517, "f32")])
 def test_all_rows_for_all_drafts_at_once(S, L, K, V, dtype):
     g = torch.Generator().manual_seed(S * 1000 + L * 100 + K)
     target = 2.0 * torch.randn(S, L + 1, K, V, generator=g)
@@ -105,7 +105,7 @@ def test_captured_and_replayed():
             assert torch.equal(out[name], eager[name]), (turn, name)
 
 
-@pytest.mark.parametrize("S,L,K,V,mf", [(100, 7, 8, 9000, False), (64, 2, 16, 4000, False), (128, 4, 4, 32000, False), (32, 7, 8, 9000, False), (64, 4, 10, 20000, True)])
+@pytest.mark.parametrize("S,L,K,V,mf", [(100, 7, 8, 9000, False), (64, 2, 16, 4000, False), (128, 4, 4, 32000, False), (32, 7, 8, 9000, False), (64, 4, 10, 20000, True), (1, 1, 8, 70000, False), (3, 1, 8, 128256, True)])
 def test_calls_that_are_slower_at_once_take_the_loop(S, L, K, V, mf):
     # (where no token is accepted the loop is its first scan and two launches a position without work)
     target = torch.randn(S, L + 1, K, V, device=DEV, dtype=torch.bfloat16)
