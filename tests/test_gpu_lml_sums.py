@@ -46,8 +46,10 @@ def test_any_number_of_list_sizes(V, ks):
     # (by sums: an ordinary row's cells leave some 1e-8 open, of which the tenth part is missed at most; by sorting masses are
     # rounded to fp32)
     draft, target, _ = _rows(3, V, V)
-    _check(draft, target, ks, rtol=5e-9, temp_draft=0.7, temp_target=0.9)
-    _check(draft.bfloat16(), target.bfloat16(), ks, rtol=5e-9 if V >= 8192 else 2.0 ** -22)
+    ws = _check(draft, target, ks, rtol=5e-9, temp_draft=0.7, temp_target=0.9)
+    assert _by_cells(ws, 3, V) == []
+    ws = _check(draft.bfloat16(), target.bfloat16(), ks, rtol=5e-9 if V >= 8192 else 2.0 ** -22)
+    assert _by_cells(ws, 3, V) == []
 
 
 @pytest.mark.parametrize("first", [float("-inf"), float("nan"), -1e4, -1e9, -3e38, 90.0])
@@ -57,7 +59,9 @@ def test_the_first_entries_are_no_measure_of_the_others(first):
     draft[0, :64] = first
     target[1, :64] = first
     draft[2, :5000], target[2, :64] = first, first
-    _check(draft + 1000.0, target, [1, 4])
+    ws = _check(draft + 1000.0, target, [1, 4])
+    # (90: all of the draft's mass is on entries that the target has next to none of)
+    assert _by_cells(ws, 4, 20000) == ([0] if first == 90.0 else [])
 
 
 def test_rows_that_are_left_to_the_other_forms():
@@ -73,6 +77,7 @@ def test_rows_that_are_left_to_the_other_forms():
     for name in ("bound", "relaxed", "tv"):
         np.testing.assert_allclose(gpu[name].cpu().numpy(), ref[name], rtol=2.0 ** -22, atol=1e-30, err_msg=name)
     assert (gpu["bound"][3] == 0.0).all()
+    assert _by_cells(ws, 6, 9001) == [0, 1, 3, 4]               # (a row of one entry has one cell, for which nothing is open)
     draft[2] = float("-inf")                                    # no mass on a side
     gpu = llc.llc_lml_bound(draft[2:3], target[2:3], [1, 16])
     assert (gpu["bound"] == 0.0).all() and (gpu["relaxed"] == 0.0).all()
@@ -105,6 +110,7 @@ def test_cells_are_shared_out_again(V, kind):
     for draft, target in ((wide, flat), (flat, wide)):
         ws = _check(draft, target, [1, 8], kind)
         assert _left_to_sorting(ws, 4, V) == []
+        assert len(_by_cells(ws, 4, V)) <= 1
 
 
 @pytest.mark.parametrize("ratios", [1, 5, 40, 130, 300])
