@@ -95,21 +95,23 @@ int to_a_cu(bool f32, int kt, bool own, bool lse) { return own && lse && f32 && 
 // A better shape for (row, draft group) pairs of which workgroups as large as a CU takes would leave many CUs half idle: as many chunks
 // of 256 threads as the chip holds at a time.  us a call, before and now: own rows with keys, 270 to 341 pairs, K = 4, bf16 50 257
 // entries 110 to 113, 88; 128 256 251 to 263, 175 to 187; fp32 32 000 78 to 81, 70 to 73; 128 256 276 to 287, 232 to 257; 140 x 128 256 bf16 157,
-// 127, fp32 172, 145.  A chunk pays its own warm-up and exact step, and the call a finalize launch, so rows have to be long enough: 48 tiles for
-// four drafts a pass without keys (300 x 32 000 fp32 38, 40; 50 257 64, 57; 128 256 162, 142), 120 for two (50 257 35, 38; 128 256 96, 90), for a
-// shared proposal (K = 8 with keys 300 x 50 257 69, 79; 128 256 128, 119; 152 064 145, 130; min-first without keys 257 x 128 256 63, 66)
-// and for pairs that get 512 threads and a CU anyway (170 x 32 000 bf16 with keys 58, 59; 200 x 128 256 160, 139).
+// 127, fp32 172, 145.  A chunk pays its own warm-up and exact step, and the call a finalize launch, so rows have to be long enough.  The lines lie where both
+// shapes were timed on either side (time so cut to time without, at tiles of 1024 entries): fp32 own rows, four drafts a pass and keys, two chunks 12: 0.99 to 1.01, 20: 0.92
+// to 0.95; own rows with keys or four drafts a pass, three chunks 28: 1.01 to 1.1, 36: 0.98 to 1.08, 46: 0.89 to 1.03, 50 and more below 1; two without keys 70: 0.99 to 1.02, 90: 0.96 to 1.0;
+// a shared proposal with keys 70: 0.97 to 1.05, 90: 0.93 to 0.99, without 90: 1.02, 118: 0.97 (257 x 128 256 min-first without keys 63, 66); pairs that get 512 threads and a CU
+// anyway 28: 0.98 to 1.04, 46: 0.91 to 1.05, 55: 0.94 to 1.02, 75: 0.93 to 0.98.
 void filled_shape(long long rows, long long G, bool f32, int kt, bool own, bool lse, int *threads, int *chunks) {
   constexpr int kCus = 256;
   if (rows <= kCus / 2 || (own && kt > 4)) return;
   const int slots = to_a_cu(f32, kt, own, lse);
   const long long c = kCus * slots / rows;
-  int least_tiles = 120, least = 3;
+  int least_tiles = own || lse ? 100 : 120, least = 3;
   if (rows <= kCus) {
     if (!(own && lse)) return;
+    least_tiles = 52;
     least = 4;
   } else if (slots == 3) {
-    least_tiles = 30;
+    least_tiles = 16;
     least = 2;
   } else if (own && (lse || kt == 4)) {
     least_tiles = 48;

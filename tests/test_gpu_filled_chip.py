@@ -11,11 +11,12 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# (rows, drafts, entries, own rows: with normalisers from 48 tiles of 1024 entries on, or 30, or 120; then without; shared proposals)
+# (rows, drafts, entries, own rows: with normalisers from 48 tiles of 1024 entries on, or 16, or 52; then without; shared proposals)
 @pytest.mark.parametrize("B,K,V,own", [(257, 4, 48128, True), (257, 4, 48129, True), (341, 3, 49001, True), (342, 4, 30003, True), (384, 4, 30003, True),
                                        (385, 2, 9001, True), (512, 1, 9001, True), (513, 2, 9001, True), (128, 4, 122003, True), (129, 4, 122003, True),
                                        (192, 4, 121857, True), (256, 2, 121856, True), (260, 8, 30721, True), (258, 2, 121857, True),
-                                       (257, 8, 121857, False), (341, 6, 121857, False), (342, 4, 121857, False)])
+                                       (257, 8, 121857, False), (341, 6, 121857, False), (342, 4, 121857, False), (342, 4, 16384, True),
+                                       (340, 3, 16381, True), (140, 4, 53248, True), (200, 2, 53245, True), (258, 2, 102400, True), (300, 4, 102397, False)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_chunks_that_fill_the_chip(B, K, V, own, dtype):
     g = torch.Generator(device=DEV).manual_seed(B + K + V)
