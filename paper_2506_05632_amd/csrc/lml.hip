@@ -1098,8 +1098,9 @@ constexpr double kSumErrorLeast = 0.5, kSumErrorEach = 0x1p-17;
 constexpr double kShareAgain = 0x1p-18;  // what sharing the cells out again can mend
 constexpr float kLaneStep = 0x1p40f;  // (a distance is a multiple of 2^-36)
 constexpr double kU2Units = 0x1p35;   // of a side's mass in a cell's sum of p u (1 - u), which is no more than a quarter of the cell's, so that ...
+constexpr float kU2Slip = 0x1.6a09e6p-18f;  // 1 / sqrt(kU2Units)
 constexpr float kU2Most = 0x1.fp-2f;  // ... it has 32 bits in a cell with less than this (and 2^18 entries): one with more is not known
-constexpr uint32_t kDitherStep = 0x9E3779B9u;  // (2^32 over the golden ratio: its multiples are spread evenly)
+constexpr uint32_t kDitherStep = 0x9E3779B9u, kGroupStep = kDitherStep * kCellThreads;  // (2^32 over the golden ratio: its multiples are spread evenly)
 constexpr float kWide = 0.5f;         // a cell this wide in ln r leaves its entries' whole terms open
 
 // 2^y for y <= 0 or so (what is below -1074 comes out as 0, NaN too) to about an ulp: y = n + f, |f| <= 1/2, and 2^f = 1 + f P(f)
@@ -1287,8 +1288,8 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
   pl.center = 0.0;
 
   // ---- first pass: the sides' sums and largest entries.  Masses are taken relative to the largest of the first
-  // 64 entries, which serves unless it is so far below the row's largest that its mass or the sum overflows (looked for in the largest
-  // entries themselves: exp2_of makes any number of an exponent beyond 2^31)
+  // 64 entries, which serves unless it is so far below the row's largest that the largest's mass or the sum overflows.  (exp2_of makes any number of an
+  // exponent beyond 2^31: a sum is taken if, relative to the largest, it is no less than the largest itself)
   Masses<PROBS> mp, mq;
   mp.per = PROBS ? 1.0 : log2e_over(p.temp_draft);
   mq.per = PROBS ? 1.0 : log2e_over(p.temp_target);
@@ -1371,8 +1372,15 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
       leave();
       return;
     }
-    const bool near = PROBS || (mp.log2_of(top_p) <= 1000.0 && mq.log2_of(top_q) <= 1000.0);
-    if (near && zp >= 0x1p-300 && zp < 0x1p1000 && zq >= 0x1p-300 && zq < 0x1p1000) break;
+    if (!PROBS) {
+      const double off_p = (double)top_p * mp.per, off_q = (double)top_q * mq.per;
+      zp *= exp2_of(mp.off - off_p);
+      zq *= exp2_of(mq.off - off_q);
+      mp.off = off_p;
+      mq.off = off_q;
+    }
+    constexpr double kLeast = PROBS ? 0x1p-300 : 0.5;
+    if (zp >= kLeast && zp < 0x1p1000 && zq >= kLeast && zq < 0x1p1000) break;
     if (attempt == 1) {  // (uniform) a NaN among the sums: an entry of +inf
       leave();
       return;
@@ -1385,11 +1393,8 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
     zq *= mq.per;
     pl.center = uniform(pl.log_ratio(top_p, top_q));
   } else {
-    const double off_p = (double)top_p * mp.per, off_q = (double)top_q * mq.per;
-    zp *= exp2_of(mp.off - off_p);
-    zq *= exp2_of(mq.off - off_q);
-    mp.off = uniform(off_p);
-    mq.off = uniform(off_q);
+    mp.off = uniform(mp.off);
+    mq.off = uniform(mq.off);
   }
   if (tid < 4) s_sizes[tid] = p.kd[tid];
   if (tid == 0) { s_total[0] = zp; s_total[1] = zq; }  // (registers are scarce in the second pass)
@@ -1602,7 +1607,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
     const float lane_step = (float)(tid & (copies - 1)) * (1.0f / kLaneStep);  // (nothing to a distance, a cell where a place has several)
     const bool first_round = round == 0, four_sizes = p.n_k > 2, want_relaxed = first_round && p.relaxed != nullptr;
     float4 next_p = four<E>(prow, tid * 4, V, none), next_q = four<E>(qrow, tid * 4, V, none);
-    uint32_t dither = (uint32_t)tid * kDitherStep;
+    float up = (float)((uint32_t)tid * kDitherStep >> 8) * 0x1p-24f;
     Steps stage(V);
 #pragma unroll 1
     for (int i = tid * 4; i < V; i += kCellThreads * 4) {
@@ -1614,8 +1619,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
       }
       // (what an entry's share of the third sum is rounded up or down by, so that sums are right on average: a number from 0 to 1 that belongs
       // to its place in the row, and for its neighbour what is left to 1)
-      dither += (uint32_t)kCellThreads * kDitherStep;
-      const float up = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, dither, 9));  // from 1 to 2
+      up = __builtin_amdgcn_fractf(up + (float)(kGroupStep >> 8) * 0x1p-24f);
       double ep[4], eq[4];
       float d[4];
       int b[4];
@@ -1651,7 +1655,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
           const float u = __builtin_amdgcn_fractf(t);
           atomicAdd(&s_p[cell], whole_mass(ep[j], step_p));
           atomicAdd(&s_q[cell], whole_mass(eq[j], step_q));
-          atomicAdd(&s_u2[cell], saturated(fmaf((float)ep[j] * to_u2, fmaf(-u, u, u), (j & 1) != 0 ? 2.0f - up : up - 1.0f)));
+          atomicAdd(&s_u2[cell], saturated(fmaf((float)ep[j] * to_u2, fmaf(-u, u, u), (j & 1) != 0 ? 1.0f - up : up)));
         } else {
           // ratio 0, or near it: before all others (an entry without a cell that has the larger ratio has no
           // p-mass to speak of)
@@ -1719,7 +1723,7 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
 
     // ---- the cells' terms, list sizes four at a time
     // what rounding may have done to the masses before and behind a cell (four deviations of such a sum), and in all
-    const float slip = 2.0f * sqrtf((float)V), slip_p = slip * (float)unit_p, slip_q = slip * (float)unit_q;
+    const float root = sqrtf((float)V), slip_u2 = (float)(1.0 / kU2Units) * root, slip = 2.0f * root, slip_p = slip * (float)unit_p, slip_q = slip * (float)unit_q;
     const double lost_p = 0.5 * unit_p * (double)V, lost_q = 0.5 * unit_q * (double)V;
     const double may_be_open = fmin(fmax((double)V * kSumErrorEach, kSumErrorLeast), 1.0) * kRowError;
     bool open = false;
@@ -1764,17 +1768,17 @@ __global__ void __launch_bounds__(kCellThreads, 4) lml_sum_kernel(const LmlParam
             const float within = (float)s_u2[c] * (float)(1.0 / kU2Units) * per_p;  // the mean of u (1 - u): u's variance is this below mean (1 - mean)
             // what rounding may have done to it: an entry's has a variance of no more than a quarter, nor more than what it adds.  Two deviations as if the
             // cell had all of the row's entries, which is four or more of the sum over the cells unless one of them has nearly all
-            const float slip_var = fp < kU2Most ? fminf((float)(1.0 / kU2Units) * __builtin_amdgcn_sqrtf(fminf((float)V, (float)kU2Units * fp)) * per_p, 0.25f) : 0.25f;
+            const float slip_var = fp < kU2Most ? fminf(fminf(slip_u2 * per_p, kU2Slip * __builtin_amdgcn_sqrtf(per_p)), 0.25f) : 0.25f;
             float var, mean = m;
 #pragma unroll
             for (int it = 0; it < 2; ++it) {  // the logarithm of the mean ratio is half a variance above the mean place
               var = fmaxf(fmaf(-mean, mean, mean) - within, 0.0f);
-              mean = fminf(fmaxf(m - 0.5f * w * var, 0.0f), 1.0f);
+              mean = __builtin_amdgcn_fmed3f(fmaf(-0.5f * w, var, m), 0.0f, 1.0f);
             }
             var = fmaxf(fmaf(-mean, mean, mean) - within, 0.0f);
             const float var_open = fmaf(0.02f * w, w, var + slip_var);  // (and a third power more)
             v = var * w * w;
-            v_open = fmaf(0.25f * fminf(w, 1.0f), var_open, slip_var) * w * w;
+            v_open = fmaf(0.25f * w, var_open, slip_var) * w * w;
             half_g = 2.0f * var * w;
             half_g_open = w * fmaxf(var_open, __builtin_amdgcn_sqrtf(var_open * (1.0f / 3.0f)) - 2.0f * var);
           }
