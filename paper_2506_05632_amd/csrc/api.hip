@@ -69,7 +69,7 @@ void auto_shape(long long rows, long long G, int most_threads, bool lean, bool f
 // A better shape for few rows, where the time is the latency of a workgroup's phases: those of 512 threads, at most one to
 // a CU, with a tile each as far as 16 to a row go (a wavefront then shares its SIMD with one other).  For at most four drafts a pass, drawn
 // one word at a time and without normalisers: the others' phases are longer and do not pay for being more (K = 8, or with keys: 0.9 to 1.1).
-// us a call, before and now: 4 x 32 000, K = 4, bf16 17.0, 15.3; 1 x 50 257 17.3, 15.8; 16 x 24 000
+// us a call, before and now: 4 x 32 000, K = 4, bf16 17.0, 15.5; 1 x 50 257 17.3, 15.8; 16 x 24 000
 // 17.6, 15.9; drafts alone, own rows, 16 x 32 000 16.9, 13.8; 6 x 12 000 15.7, 13.3; 16 x 80 000 18.4, 16.4.
 // Rows of few tiles are better off in one workgroup, which finishes them: a pool needs a dozen tiles to pay, drafts alone seven in a shared
 // row (with 3 and 4 tiles 1.02 to 1.05 times the time, with 5 and 6 0.99 to 1.02, with 7 0.94), five in own rows (K = 1: 1.02, 0.99 with 5), of which four

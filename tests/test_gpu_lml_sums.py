@@ -1,6 +1,7 @@
 """GPU parity of llc_lml_bound's form by cells' sums where it can go wrong (needs an MI355X): references that do not serve, heavy
 entries that share threads, cells shared out again, any number of list sizes, rows that it has to leave to the other forms.
-Bound on the error: cells leave at most 0.75 x 2^-23 of a result open, the other forms 2^-22; tv and the relaxed sums are 64-bit sums."""
+Bound on the error: cells leave at most 0.75 x 2^-23 of a result open, in rows of 131 072 entries or more 0.75 x 2^-22, the other forms 2^-22; tv and the
+relaxed sums are 64-bit sums."""
 import numpy as np
 import pytest
 import torch
